@@ -317,11 +317,24 @@ __global__ __launch_bounds__(256) void batched_build_kernel(BatchDev B)
     if (tid == 0 && fail_sh) *B.fail = 1;
 }
 
-__device__ inline double lane_value(double v, int src_lane)   // src_lane: a constant
+template <int CTRL>
+__device__ inline double dpp_from(double v)   // the value of the lane that CTRL selects
 {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src_lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src_lane);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
     return __hiloint2double(hi, lo);
+}
+
+// upper half of a <-> lower half of b (HALF = 32), or the odd 16-lane rows of a <-> the even ones of b
+template <int HALF>
+__device__ inline void lane_swap(double &a, double &b)
+{
+    const auto lo = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false)
+                               : __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false)
+                               : __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(hi[0], lo[0]);
+    b = __hiloint2double(hi[1], lo[1]);
 }
 
 __device__ inline double rcp64(double x)   // 1 / x for a positive finite x, to about one unit in the last place
@@ -335,37 +348,76 @@ __device__ inline double rcp64(double x)   // 1 / x for a positive finite x, to 
 // iters Sinkhorn iterations per pair (iters == 0: only the query part), then the
 // pair's distance and marginal residual.
 //
-// One wavefront per pair, no workgroup-wide step and no LDS anywhere.  Lane l keeps in registers row l
-// and column l of the pair's kernel tile (zero beyond n x m) and the entries of index l of
-// the scaling vectors u = [u^ (n); u~ (m)], v = [v^ (m); v~ (n)] (point part; deletion part,
-// Sec. 6).  Inside the loop a vector is held as x * 2^E with one integer E for the whole
-// vector, chosen after every update so that the largest entry lies in [1, 2): the max-shift of
-// App. "Implementational details" with the shift restricted to powers of two, which costs an
-// exponent extraction instead of an exp and a log per entry and half-iteration.  Logs are
-// formed once, when the state is stored.  In a half-iteration every lane multiplies its row
-// (or column) with the point part of the input vector, whose entries it reads from the other
-// lanes' registers one by one (lane reads, no LDS, no barrier):
+// One wavefront per pair, no workgroup-wide step and no LDS anywhere.  The pair's 64 x 64 kernel tile
+// (zero beyond n x m) is dealt to the lanes in 8 x 8 blocks, held as doubles: lane (r, c) = 8 r + c owns
+// rows 8 r .. 8 r + 7 and columns 8 c .. 8 c + 7, ONE copy that serves both products.  A product is 64
+// multiply-adds on registers and a sum over the eight lanes that share the rows (columns), done by
+// recursive halving, 4 + 2 + 1 exchanges: afterwards every lane holds ONE row (column) of the result,
+// row 8 r + c (column 8 c + r), scales it, and the next product's eight inputs come back by recursive
+// doubling.  Which of a block's rows a register holds depends on the lane (row 8 r + (sigma(k) ^ c) in
+// register k, sigma the masks of the three lane permutations), so the halving needs no selects; along
+// the columns two of the three exchanges are lane swaps, which select by themselves.
+// What bounds it is one wavefront's instruction stream: about 170 vector instructions per
+// half-iteration, 64 of them the product itself (the version before it, a row and a column per lane with
+// the vector passed round by lane reads, needed 330).  50 iterations of 4096 pairs with deletion rows:
+// 188 us for the call instead of 481; of 16 pairs: 79 instead of 134.
+//
+// The entries of u = [u^ (n); u~ (m)] and v = [v^ (m); v~ (n)] (point part; deletion part, Sec. 6) live
+// where the products leave them: u^_i and v~_i in the lane of row i, v^_j and u~_j in the lane of column j.
+// A vector is held as x * 2^E with one integer E for the whole vector, the largest entry kept within
+// 2^-40 .. 2^40: the max-shift of App. "Implementational details" with the shift restricted to powers
+// of two and applied when it is due, which costs two comparisons per half-iteration instead of an exp
+// and a log per entry.  Logs are formed once, when the state is stored.
 //   (K_BP v)_i     = sum_j K_ij v^_j + k_{i,eps} v~_i          (K_BP v)_{n+j}     = k_{eps,j} v^_j + sum v~
 //   (K_BP^T u)_j   = sum_i K_ij u^_i + k_{eps,j} u~_j          (K_BP^T u)_{m+i}   = k_{i,eps} u^_i + sum u~
-__global__ __launch_bounds__(64) void batched_run_kernel(BatchDev B, int iters, float *row_marg, float *col_marg)
+template <bool BP>
+__global__ __launch_bounds__(64, 2) void batched_run_kernel(BatchDev B, int iters, float *row_marg, float *col_marg)
 {
     const double LN2 = 0.69314718055994530942;
     const int p = blockIdx.x, lane = threadIdx.x;
     const long long x0 = B.x_off[p], y0 = B.y_off[p];
     const int n = (int)(B.x_off[p + 1] - x0), m = (int)(B.y_off[p + 1] - y0);
-    const bool bp = B.bp != 0;
-    const int len_u = bp ? n + m : n, len_v = bp ? n + m : m;
-    const float *Kt = B.Kt + (long long)p * BMAX * BMAX;
-    float Kr[BMAX], Kc[BMAX];
+    const int len_u = BP ? n + m : n, len_v = BP ? n + m : m;
+    const int lr = lane >> 3, lc = lane & 7;
+    const int row = lane, col = 8 * lc + lr;   // this lane's entry of a result over rows / over columns
+    // the lane permutations of the row sums: xor 7 (half mirror), xor 2, xor 1
+    constexpr int SIG[8] = {0, 1, 2, 3, 7, 6, 5, 4};
+    double K[8][8];
+    {
+        const float *Kt = B.Kt + (long long)p * BMAX * BMAX;
+        float4 raw[8][2];
 #pragma unroll
-    for (int j = 0; j < BMAX; ++j) {
-        Kr[j] = (lane < n && j < m) ? Kt[lane * BMAX + j] : 0.f;
-        Kc[j] = (j < n && lane < m) ? Kt[j * BMAX + lane] : 0.f;
+        for (int a = 0; a < 8; ++a) {
+            const int i = 8 * lr + (SIG[a] ^ lc);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)   // the tile is stored 64 x 64 whatever n and m: always readable
+                raw[a][q] = *(const float4 *)(Kt + i * BMAX + 8 * lc + 4 * q);
+        }
+        // columns 2 g and 2 g + 1 trade places in the odd rows of lanes
+        const bool odd = lr & 1;
+        const int j_even = 8 * lc + (odd ? 1 : 0), j_odd = 8 * lc + (odd ? 0 : 1);
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+            const bool in_row = 8 * lr + (SIG[a] ^ lc) < n;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                float f0 = odd ? raw[a][q].y : raw[a][q].x, f1 = odd ? raw[a][q].x : raw[a][q].y;
+                float f2 = odd ? raw[a][q].w : raw[a][q].z, f3 = odd ? raw[a][q].z : raw[a][q].w;
+                f0 = in_row && j_even + 4 * q < m ? f0 : 0.f;
+                f1 = in_row && j_odd + 4 * q < m ? f1 : 0.f;
+                f2 = in_row && j_even + 4 * q + 2 < m ? f2 : 0.f;
+                f3 = in_row && j_odd + 4 * q + 2 < m ? f3 : 0.f;
+                K[a][4 * q] = (double)f0;
+                K[a][4 * q + 1] = (double)f1;
+                K[a][4 * q + 2] = (double)f2;
+                K[a][4 * q + 3] = (double)f3;
+            }
+        }
     }
-    const double kpe = (bp && lane < n) ? B.kpe[x0 + lane] : 0.0;
-    const double keq = (bp && lane < m) ? B.keq[y0 + lane] : 0.0;
-    const bool has_up = lane < n, has_ud = bp && lane < m;   // this lane's entries of u (point, deletion part)
-    const bool has_vp = lane < m, has_vd = bp && lane < n;   // ... and of v
+    const bool has_up = row < n, has_ud = BP && col < m;   // this lane's entries of u (point, deletion part)
+    const bool has_vp = col < m, has_vd = BP && row < n;   // ... and of v
+    const double kpe = has_vd ? B.kpe[x0 + row] : 0.0;
+    const double keq = has_ud ? B.keq[y0 + col] : 0.0;
     double *gu = B.log_u + x0 + y0, *gv = B.log_v + x0 + y0;
     const double a_each = 1.0 / (double)len_u, b_each = 1.0 / (double)len_v;   // uniform marginals
     unsigned long long nonpos = 0, empty_u = 0, empty_v = 0;
@@ -373,7 +425,7 @@ __global__ __launch_bounds__(64) void batched_run_kernel(BatchDev B, int iters, 
     // exactly zero means the point shares no bucket with any point of the other set (or only
     // vanished entries).  Such a point gets scaling 0 (log = -infinity), carries no mass and is
     // counted apart from the non-positive sums (App. "Limitations": ignored, not a failure).
-    const bool unsupported_is_zero = !bp && B.l == 0;
+    const bool unsupported_is_zero = !BP && B.l == 0;
 
     // stored logs -> x * 2^E
     auto load_vec = [&](double lp, bool hp, double ld, bool hd, double &xp, double &xd) -> int {
@@ -384,31 +436,71 @@ __global__ __launch_bounds__(64) void batched_run_kernel(BatchDev B, int iters, 
         xd = hd ? exp(ld - Ef * LN2) : 0.0;
         return (int)Ef;
     };
-    // largest entry into [1, 2); returns the exponent taken out (NaN entries are ignored by fmax)
+    // Once the largest entry has left 2^-40 .. 2^40: back into [1, 2); returns the exponent taken out
+    // (NaN entries are ignored by the comparisons and by fmax)
     auto renorm = [&](double &xp, double &xd) -> int {
-        const double mx = wave_max(fmax(xp, xd));
+        const double own = fmax(xp, xd);
+        if (!__any(own > 0x1p40) && __any(own > 0x1p-40)) return 0;
+        const double mx = wave_max(own);
         if (!(mx > 0.0) || !(mx < INFINITY)) return 0;
         const int e = ilogb(mx);
         xp = ldexp(xp, -e);
         xd = ldexp(xd, -e);
         return e;
     };
-    // One product with K_BP (Kreg = rows) or its transpose (Kreg = columns) for the input held in
-    // (xp, xd): k_p / k_d is the deletion kernel value that enters this lane's point / deletion output.
-    // len_in: length of the input's point part (the tile is zero beyond it; whole sixteens are skipped).
-    auto product = [&](const float (&Kreg)[BMAX], int len_in, double xp, double xd, double k_p, double k_d,
-                       double &s_p, double &s_d) {
-        const double tail = bp ? wave_sum(xd) : 0.0;
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    // s_row = this lane's row of K times the vector whose entries (one per lane, by column) are x
+    auto times_rows = [&](double x) -> double {
+        double in[8], acc[8];
+        in[0] = x;
+        in[1] = dpp_from<0x128>(in[0]);   // row_ror:8
 #pragma unroll
-        for (int j0 = 0; j0 < BMAX; j0 += 16) {
-            if (j0 < len_in) {   // the same in every lane
-#pragma unroll
-                for (int j = j0; j < j0 + 16; ++j) acc[j & 3] = fma((double)Kreg[j], lane_value(xp, j), acc[j & 3]);
-            }
+        for (int g = 0; g < 2; ++g) {
+            in[g + 2] = in[g];
+            lane_swap<16>(in[g], in[g + 2]);
         }
-        s_p = (acc[0] + acc[1]) + (acc[2] + acc[3]) + k_p * xd;
-        s_d = k_d * xp + tail;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            in[g + 4] = in[g];
+            lane_swap<32>(in[g], in[g + 4]);
+        }
+#pragma unroll
+        for (int a = 0; a < 8; ++a) acc[a] = K[a][0] * in[0];
+#pragma unroll
+        for (int b = 1; b < 8; ++b)
+#pragma unroll
+            for (int a = 0; a < 8; ++a) acc[a] = fma(K[a][b], in[b], acc[a]);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a] += dpp_from<0x141>(acc[a + 4]);   // row_half_mirror
+#pragma unroll
+        for (int a = 0; a < 2; ++a) acc[a] += dpp_from<0x4E>(acc[a + 2]);    // xor 2
+        return acc[0] + dpp_from<0xB1>(acc[1]);                              // xor 1
+    };
+    // s_col = this lane's column of K times the vector whose entries (one per lane, by row) are x
+    auto times_cols = [&](double x) -> double {
+        double in[8], acc[8];
+        in[0] = x;
+        in[1] = dpp_from<0xB1>(in[0]);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) in[a + 2] = dpp_from<0x4E>(in[a]);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) in[a + 4] = dpp_from<0x141>(in[a]);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) acc[b] = K[0][b] * in[0];
+#pragma unroll
+        for (int a = 1; a < 8; ++a)
+#pragma unroll
+            for (int b = 0; b < 8; ++b) acc[b] = fma(K[a][b], in[a], acc[b]);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            lane_swap<32>(acc[b], acc[b + 4]);
+            acc[b] += acc[b + 4];
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            lane_swap<16>(acc[b], acc[b + 2]);
+            acc[b] += acc[b + 2];
+        }
+        return acc[0] + dpp_from<0x128>(acc[1]);
     };
     auto scale = [&](double marg, double s, bool exists, unsigned long long &empty) -> double {
         if (!exists) return 0.0;
@@ -420,28 +512,41 @@ __global__ __launch_bounds__(64) void batched_run_kernel(BatchDev B, int iters, 
         ++nonpos;
         return NAN;
     };
+    // sums of K_BP v: of this lane's row, and of its column's deletion row; and the same of K_BP^T u
+    auto rows_of = [&](double vp, double vd, double &s_p, double &s_d) {
+        const double tail = BP ? wave_sum(vd) : 0.0;
+        s_p = times_rows(vp);
+        if (BP) s_p = fma(kpe, vd, s_p);
+        s_d = fma(keq, vp, tail);
+    };
+    auto cols_of = [&](double up, double ud, double &s_p, double &s_d) {
+        const double tail = BP ? wave_sum(ud) : 0.0;
+        s_p = times_cols(up);
+        if (BP) s_p = fma(keq, ud, s_p);
+        s_d = fma(kpe, up, tail);
+    };
 
     double xu_p = 0.0, xu_d = 0.0, xv_p, xv_d, s_p, s_d;
     int Eu = 0;
-    int Ev = load_vec(has_vp ? gv[lane] : 0.0, has_vp, has_vd ? gv[m + lane] : 0.0, has_vd, xv_p, xv_d);
-    if (iters == 0) Eu = load_vec(has_up ? gu[lane] : 0.0, has_up, has_ud ? gu[n + lane] : 0.0, has_ud, xu_p, xu_d);
+    int Ev = load_vec(has_vp ? gv[col] : 0.0, has_vp, has_vd ? gv[m + row] : 0.0, has_vd, xv_p, xv_d);
+    if (iters == 0) Eu = load_vec(has_up ? gu[row] : 0.0, has_up, has_ud ? gu[n + col] : 0.0, has_ud, xu_p, xu_d);
     for (int it = 0; it < iters; ++it) {
-        product(Kr, m, xv_p, xv_d, kpe, keq, s_p, s_d);        // u = a ./ (K_BP v), eq. 2
+        rows_of(xv_p, xv_d, s_p, s_d);        // u = a ./ (K_BP v), eq. 2
         xu_p = scale(a_each, s_p, has_up, empty_u);
-        xu_d = scale(a_each, s_d, has_ud, empty_u);
+        if (BP) xu_d = scale(a_each, s_d, has_ud, empty_u);
         Eu = -Ev + renorm(xu_p, xu_d);
-        product(Kc, n, xu_p, xu_d, keq, kpe, s_p, s_d);        // v = b ./ (K_BP^T u)
+        cols_of(xu_p, xu_d, s_p, s_d);        // v = b ./ (K_BP^T u)
         xv_p = scale(b_each, s_p, has_vp, empty_v);
-        xv_d = scale(b_each, s_d, has_vd, empty_v);
+        if (BP) xv_d = scale(b_each, s_d, has_vd, empty_v);
         Ev = -Eu + renorm(xv_p, xv_d);
     }
     const double lu_p = log(xu_p) + (double)Eu * LN2, lu_d = log(xu_d) + (double)Eu * LN2;
     const double lv_p = log(xv_p) + (double)Ev * LN2, lv_d = log(xv_d) + (double)Ev * LN2;
     if (iters > 0) {
-        if (has_up) gu[lane] = lu_p;
-        if (has_ud) gu[n + lane] = lu_d;
-        if (has_vp) gv[lane] = lv_p;
-        if (has_vd) gv[m + lane] = lv_d;
+        if (has_up) gu[row] = lu_p;
+        if (has_ud) gu[n + col] = lu_d;
+        if (has_vp) gv[col] = lv_p;
+        if (has_vd) gv[m + row] = lv_d;
         nonpos = (unsigned long long)wave_sum((double)nonpos);
         empty_u = (unsigned long long)wave_sum((double)empty_u);
         empty_v = (unsigned long long)wave_sum((double)empty_v);
@@ -452,31 +557,31 @@ __global__ __launch_bounds__(64) void batched_run_kernel(BatchDev B, int iters, 
 
     // marginals r = u .* (K_BP v), c = v .* (K_BP^T u); distance and residual
     double dsum = 0.0, esum = 0.0;
-    product(Kr, m, xv_p, xv_d, kpe, keq, s_p, s_d);
+    rows_of(xv_p, xv_d, s_p, s_d);
     if (has_up) {
         const double r = ldexp(xu_p * s_p, Eu + Ev);
         if (r != 0.0) dsum += r * lu_p;   // a point without mass (log u = -infinity) adds nothing
         esum += fabs(r - a_each);
-        if (row_marg) row_marg[x0 + y0 + lane] = (float)r;
+        if (row_marg) row_marg[x0 + y0 + row] = (float)r;
     }
     if (has_ud) {
         const double r = ldexp(xu_d * s_d, Eu + Ev);
         dsum += r * lu_d;
         esum += fabs(r - a_each);
-        if (row_marg) row_marg[x0 + y0 + n + lane] = (float)r;
+        if (row_marg) row_marg[x0 + y0 + n + col] = (float)r;
     }
-    product(Kc, n, xu_p, xu_d, keq, kpe, s_p, s_d);
+    cols_of(xu_p, xu_d, s_p, s_d);
     if (has_vp) {
         const double c = ldexp(xv_p * s_p, Eu + Ev);
         if (c != 0.0) dsum += c * lv_p;
         esum += fabs(c - b_each);
-        if (col_marg) col_marg[x0 + y0 + lane] = (float)c;
+        if (col_marg) col_marg[x0 + y0 + col] = (float)c;
     }
     if (has_vd) {
         const double c = ldexp(xv_d * s_d, Eu + Ev);
         dsum += c * lv_d;
         esum += fabs(c - b_each);
-        if (col_marg) col_marg[x0 + y0 + m + lane] = (float)c;
+        if (col_marg) col_marg[x0 + y0 + m + row] = (float)c;
     }
     const double D = wave_sum(dsum);
     const double E = wave_sum(esum);
@@ -528,13 +633,20 @@ using namespace lcn;
 namespace lcn {
 bool is_batched_handle(const void *h) { return h && *(const uint32_t *)h == BATCH_MAGIC; }
 
+static hipError_t launch_batched_run(const BatchHandle &h, int iters, float *row_dev, float *col_dev)
+{
+    if (h.dev.bp)
+        hipLaunchKernelGGL(batched_run_kernel<true>, dim3(h.dev.P), dim3(64), 0, h.stream, h.dev, iters, row_dev, col_dev);
+    else
+        hipLaunchKernelGGL(batched_run_kernel<false>, dim3(h.dev.P), dim3(64), 0, h.stream, h.dev, iters, row_dev, col_dev);
+    return hipGetLastError();
+}
+
 lcn_status batched_run(void *hh, int iters)
 {
     BatchHandle &h = *(BatchHandle *)hh;
     BHIPCHK(hipEventRecord(h.ev0, h.stream));
-    hipLaunchKernelGGL(batched_run_kernel, dim3(h.dev.P), dim3(64), 0, h.stream, h.dev, iters, (float *)nullptr,
-                       (float *)nullptr);
-    BHIPCHK(hipGetLastError());
+    BHIPCHK(launch_batched_run(h, iters, nullptr, nullptr));
     BHIPCHK(hipEventRecord(h.ev1, h.stream));
     unsigned long long c[3] = {0, 0, 0};
     BHIPCHK(hipMemcpyAsync(c, h.dev.counters, sizeof(c), hipMemcpyDeviceToHost, h.stream));
@@ -547,8 +659,7 @@ lcn_status batched_run(void *hh, int iters)
 lcn_status batched_query(void *hh, double *dist_host, double *resid_host, float *row_dev, float *col_dev)
 {
     BatchHandle &h = *(BatchHandle *)hh;
-    hipLaunchKernelGGL(batched_run_kernel, dim3(h.dev.P), dim3(64), 0, h.stream, h.dev, 0, row_dev, col_dev);
-    BHIPCHK(hipGetLastError());
+    BHIPCHK(launch_batched_run(h, 0, row_dev, col_dev));
     if (dist_host)
         BHIPCHK(hipMemcpyAsync(dist_host, h.dev.dist, sizeof(double) * h.dev.P, hipMemcpyDeviceToHost, h.stream));
     if (resid_host)

@@ -236,3 +236,29 @@ def test_batched_edge_shapes(d, l, b, mode, bp):
         worst["resid"] = max(worst["resid"], abs(resid[p] - resid_o))
     print("C4 edge", d, l, b, mode, bp, worst, flush=True)
     assert worst["log"] <= 1e-4 and worst["cost"] <= 1e-4 and worst["resid"] <= 1e-5, worst
+
+
+@pytest.mark.parametrize("mode,bp,lam", [("lcn", True, 4.0), ("dense", True, 0.12), ("dense", False, 0.12), ("sparse", True, 0.5)])
+def test_batched_iteration_on_block_edges(mode, bp, lam):
+    """The iteration deals a pair's kernel to the lanes in 8 x 8 blocks: sizes on both sides of a block,
+    of a lane row and of the half-wavefront.  The small lambdas take the scalings far out of
+    2^-40 .. 2^40, where the common exponent is taken out again."""
+    sizes = [(8, 9), (7, 64), (33, 31), (16, 8), (24, 25), (1, 9), (64, 57), (15, 41)]
+    d = 9
+    B = _edge_batch(sizes, d, 2, 2, seed=11)
+    B.lam[:] = lam
+    # kernel entries are single precision: above e^-87 they are normal numbers and keep their 24 bits
+    far = np.linalg.norm(B.X[:, None, :].astype(np.float64) - B.Y[None, :, :], axis=2).max()
+    assert mode == "lcn" or far / lam < 87.0
+    h, dist, resid, st = _run_gpu(B, mode, bp)
+    for p, (n, m) in enumerate(sizes):
+        Bl, so, dist_o, resid_o = _oracle_pair(B, p, mode, bp)
+        assert so.nonpositive == 0
+        z0 = int(B.x_off[p] + B.y_off[p])
+        lu = st["log_u"][z0:z0 + (n + m if bp else n)]
+        lv = st["log_v"][z0:z0 + (n + m if bp else m)]
+        # the pair's kernel is stored in single precision: 2^-24 per entry and half-iteration at most adds up
+        # over the 30 iterations (and is contracted by them), far below the parity bound
+        np.testing.assert_allclose(lu, so.log_u, rtol=0, atol=1e-4)
+        np.testing.assert_allclose(lv, so.log_v, rtol=0, atol=1e-4)
+        assert abs(dist[p] - dist_o) <= 1e-4 * abs(dist_o) and abs(resid[p] - resid_o) <= 1e-5
