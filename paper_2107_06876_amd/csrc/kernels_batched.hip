@@ -34,6 +34,9 @@ constexpr uint32_t BATCH_MAGIC = 0x4C434E42u;  // "LCNB"
 
 struct BatchDev {
     int P, d, cost, mode, l, b, R, T_l, T_b, bp;
+    int max_points;               // n + m of the largest pair
+    unsigned row4;                // first centroid row of every k-means run, in fours, six bits each (see build_rows)
+    int mt;                       // tiles of 16 rows they fill
     unsigned long long seed_l, seed_b;
     double ridge;
     const float *X, *Y;           // caller's points (fp32 copies in the workspace)
@@ -58,263 +61,85 @@ __device__ inline unsigned long long splitmix64_dev(unsigned long long &state)
     return z ^ (z >> 31);
 }
 
-__device__ inline double pair_cost(const float *x, const float *y, int d, int cost)
+__device__ inline double lane_value(double v, int src_lane)   // src_lane: the same in every lane
 {
-    if (cost == LCN_COST_COSINE) {
-        double xy = 0.0, xx = 0.0, yy = 0.0;
-        for (int k = 0; k < d; ++k) {
-            xy += (double)x[k] * (double)y[k];
-            xx += (double)x[k] * (double)x[k];
-            yy += (double)y[k] * (double)y[k];
-        }
-        return 1.0 - xy / (sqrt(xx) * sqrt(yy));
-    }
-    double s = 0.0;
-    for (int k = 0; k < d; ++k) {
-        double t = (double)x[k] - (double)y[k];
-        s += t * t;
-    }
-    return cost == LCN_COST_EUCLID ? sqrt(s) : s;
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src_lane);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src_lane);
+    return __hiloint2double(hi, lo);
 }
 
-// A row-major matrix in LDS whose row length is only known at launch: M[i][j].
-template <typename T>
-struct Rows {
-    T *base;
-    int stride;
-    __device__ T *operator[](int i) const { return base + i * stride; }
-};
+typedef double double4_t __attribute__((ext_vector_type(4)));
 
-// LDS of the build kernel, sized by the batch's d, l and bucket count (not by their upper
-// limits): doubles first, then floats, then integers.
+// The centroids of all k-means runs of a pair (run 0: the landmarks if there are any, then the hash rounds)
+// share tiles of 16 rows; a run starts on a multiple of four and does not straddle tiles.
+__host__ inline void build_rows(BatchDev &D)
+{
+    int row = 0, q = 0;
+    D.row4 = 0u;
+    auto put = [&](int k) {
+        const int k4 = (k + 3) & ~3;
+        if (row % 16 + k4 > 16) row = (row + 15) & ~15;
+        D.row4 |= (unsigned)(row / 4) << 6 * q++;
+        row += k4;
+    };
+    if (D.l > 0) put(D.l);
+    for (int r = 0; r < D.R; ++r) put(D.b);
+    D.mt = (row + 15) / 16;
+}
+
+// LDS of the build kernel, sized by the batch (its d, l, buckets, rounds and largest pair), not by the
+// upper limits: doubles first, then floats, then integers.
 struct BuildLds {
-    int zs, ls, kmax;   // row length of the points / centroids, of U, and the larger of l and b
-    size_t uf, vf, am, lm, li, sums, z, cent, assign, bucket, perm, cnts, fail, bytes;
+    int zs, ls, rows;   // row length of points / centroids and of the factors; points of the largest pair
+    size_t f, am, sums, pn, rn, z, cent, assign, cnts, start, flags, bytes;
 };
 
-__host__ __device__ inline BuildLds build_lds(int d, int l, int b)
+// dt: tiles of 16 dimensions, waves: wavefronts of the workgroup
+__host__ __device__ inline BuildLds build_lds(int l, int runs, int mt, int dt, int max_points, int waves)
 {
     BuildLds L;
-    L.zs = d + 1;
-    L.ls = l > 0 ? l : 1;
-    L.kmax = l > b ? l : b;
-    if (L.kmax < 1) L.kmax = 1;
+    // rows of 16-byte pieces, an odd number of them: the operand reads of a wavefront then spread over the banks
+    L.zs = 16 * dt + 4;
+    L.ls = l + 1 + (l & 1);   // odd, for the same reason
+    L.rows = (max_points + 15) & ~15;
     size_t at = 0;
     auto take = [&](size_t bytes) {
         const size_t here = at;
         at += (bytes + 15) & ~(size_t)15;
         return here;
     };
-    L.uf = take(sizeof(double) * BMAX * L.ls);
-    L.vf = take(sizeof(double) * L.ls * BMAX);
-    L.am = take(sizeof(double) * L.ls * L.ls);
-    L.lm = take(sizeof(double) * L.ls * L.ls);
-    L.li = take(sizeof(double) * L.ls * L.ls);
-    L.sums = take(sizeof(unsigned long long) * L.kmax * d);
-    L.z = take(sizeof(float) * 2 * BMAX * L.zs);
-    L.cent = take(sizeof(float) * L.kmax * L.zs);
-    L.assign = take(sizeof(int) * 2 * BMAX);
-    L.bucket = take(sizeof(int) * BR * 2 * BMAX);
-    L.perm = take(sizeof(int) * 2 * BMAX);
-    L.cnts = take(sizeof(int) * L.kmax);
-    L.fail = take(sizeof(int));
+    const int tiles = mt * dt, parts = tiles > 0 && waves > tiles ? waves / tiles : 1;
+    // the member sums are done with when the factors are formed: they share their place
+    const size_t f_bytes = l > 0 ? sizeof(double) * L.rows * L.ls : 0, sum_bytes = sizeof(double) * parts * tiles * 256;
+    L.f = L.sums = take(f_bytes > sum_bytes ? f_bytes : sum_bytes);
+    L.am = take(sizeof(double) * l * (l + 1));
+    L.pn = take(sizeof(double) * L.rows);
+    L.rn = take(sizeof(double) * BL);
+    L.z = take(sizeof(float) * L.rows * L.zs);
+    L.cent = take(sizeof(float) * 16 * mt * L.zs);
+    L.assign = take(sizeof(int) * runs * L.rows);
+    L.cnts = take(sizeof(int) * 2 * 16 * mt);
+    L.start = take(2 * sizeof(int) * 16 * mt);
+    L.flags = take(sizeof(int) * 8);
     L.bytes = at;
     return L;
 }
 
-// Lloyd's k-means on the N points in Z (LDS) by the whole workgroup; same
-// definition as the large path: seeded distinct start, exact-rule assignment,
-// fixed-point means, empty clusters keep their centroid.
-__device__ void block_kmeans(Rows<float> Z, int N, int d, int k, int T, unsigned long long seed, Rows<float> cent,
-                             int *assign, int *perm, Rows<unsigned long long> sums, int *cnts)
+// Cost of two points from their dot product and squared norms a2, b2.  Where the norms nearly cancel (squared
+// distance below 1e-4 of their sum, a relative error of 1e-11) it is taken from the differences of the
+// points' rows (LDS, zero padded to dp dimensions) instead; coinciding points are at distance zero exactly.
+__device__ inline double cost_of_dot(double dot, double a2, double b2, const float *x, const float *y, int dp, int cost)
 {
-    const int tid = threadIdx.x;
-    if (tid == 0) {
-        for (int i = 0; i < N; ++i) perm[i] = i;
-        unsigned long long s = seed;
-        for (int t = 0; t < k; ++t) {
-            int j = t + (int)(splitmix64_dev(s) % (unsigned long long)(N - t));
-            int tmp = perm[t];
-            perm[t] = perm[j];
-            perm[j] = tmp;
+    if (cost == LCN_COST_COSINE) return 1.0 - dot / (sqrt(a2) * sqrt(b2));
+    double sq = fma(-2.0, dot, a2 + b2);
+    if (!(sq > 1e-4 * (a2 + b2))) {
+        sq = 0.0;
+        for (int k = 0; k < dp; ++k) {
+            const double t = (double)x[k] - (double)y[k];
+            sq = fma(t, t, sq);
         }
     }
-    __syncthreads();
-    for (int e = tid; e < k * d; e += blockDim.x) cent[e / d][e % d] = Z[perm[e / d]][e % d];
-    __syncthreads();
-    // kp lanes share a point, one candidate centroid each (k <= 16)
-    const int kp = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
-    const int per_pass = (int)blockDim.x / kp;
-    for (int it = 0; it < T; ++it) {
-        for (int base = 0; base < N; base += per_pass) {   // same trip count in every lane
-            const int pt = base + tid / kp;
-            int bc = tid % kp;
-            double s = INFINITY;
-            if (pt < N && bc < k) {
-                s = 0.0;
-                for (int j = 0; j < d; ++j) {
-                    double t = (double)Z[pt][j] - (double)cent[bc][j];
-                    double t2 = t * t;
-                    s = s + t2;
-                }
-            }
-            for (int o = 1; o < kp; o <<= 1) {   // smallest distance, lowest index among equals
-                const double os = __shfl_xor(s, o, 64);
-                const int oc = __shfl_xor(bc, o, 64);
-                if (os < s || (os == s && oc < bc)) {
-                    s = os;
-                    bc = oc;
-                }
-            }
-            if (pt < N && tid % kp == 0) assign[pt] = bc;
-        }
-        for (int e = tid; e < k * d; e += blockDim.x) sums[e / d][e % d] = 0ull;
-        if (tid < k) cnts[tid] = 0;
-        __syncthreads();
-        // member sums in 2^-32 fixed point (integer addition: any order gives the same sum):
-        // lane j of a 64-lane group adds dimension j of the group's share of the points
-        {
-            const int j = tid & 63, grp = tid >> 6, groups = (int)blockDim.x >> 6;
-            for (int p = grp; p < N; p += groups) {
-                const int c = assign[p];
-                if (j < d)
-                    atomicAdd(&sums[c][j], (unsigned long long)__double2ll_rn((double)Z[p][j] * 4294967296.0));
-                if (j == 0) atomicAdd(&cnts[c], 1);
-            }
-        }
-        __syncthreads();
-        for (int e = tid; e < k * d; e += blockDim.x) {
-            const int c = e / d, j = e % d;
-            const int cnt = cnts[c];
-            if (cnt > 0) cent[c][j] = (float)(((double)(long long)sums[c][j] * (1.0 / 4294967296.0)) / (double)cnt);
-        }
-        __syncthreads();
-    }
-}
-
-__global__ __launch_bounds__(256) void batched_build_kernel(BatchDev B)
-{
-    extern __shared__ __align__(16) unsigned char lds[];
-    const BuildLds L = build_lds(B.d, B.l, B.b);
-    const Rows<float> Z{(float *)(lds + L.z), L.zs};            // the pair's points, X then Y
-    const Rows<float> cent{(float *)(lds + L.cent), L.zs};
-    const Rows<double> Uf{(double *)(lds + L.uf), L.ls};        // U, then U A^{-1}
-    const Rows<double> Vf{(double *)(lds + L.vf), BMAX};
-    const Rows<double> Am{(double *)(lds + L.am), L.ls}, Lm{(double *)(lds + L.lm), L.ls}, Li{(double *)(lds + L.li), L.ls};
-    const Rows<unsigned long long> sums{(unsigned long long *)(lds + L.sums), B.d};   // k-means: member sums
-    const Rows<int> bucket{(int *)(lds + L.bucket), 2 * BMAX};
-    int *assign = (int *)(lds + L.assign), *perm = (int *)(lds + L.perm), *cnts = (int *)(lds + L.cnts);
-    int &fail_sh = *(int *)(lds + L.fail);
-
-    const int p = blockIdx.x, tid = threadIdx.x;
-    const long long x0 = B.x_off[p], y0 = B.y_off[p];
-    const int n = (int)(B.x_off[p + 1] - x0), m = (int)(B.y_off[p + 1] - y0);
-    const int N = n + m, d = B.d;
-    const double lam = (double)B.lambda[p];
-    if (tid == 0) fail_sh = 0;
-    for (int e = tid; e < N * d; e += 256) {
-        const int i = e / d, j = e % d;
-        Z[i][j] = i < n ? B.X[(x0 + i) * d + j] : B.Y[(y0 + i - n) * d + j];
-    }
-    __syncthreads();
-    const bool low_rank = B.mode == LCN_MODE_NYSTROM || B.mode == LCN_MODE_LCN;
-    const bool hashed = B.mode == LCN_MODE_SPARSE || B.mode == LCN_MODE_LCN;
-    const int l = low_rank ? B.l : 0;
-
-    if (low_rank) {
-        block_kmeans(Z, N, d, l, B.T_l, B.seed_l + (unsigned long long)p, cent, assign, perm, sums, cnts);
-        for (int e = tid; e < l * d; e += 256) B.landmarks[((long long)p * l + e / d) * d + e % d] = cent[e / d][e % d];
-        // factors in fp64
-        for (int e = tid; e < n * l; e += 256) Uf[e / l][e % l] = exp(-pair_cost(Z[e / l], cent[e % l], d, B.cost) / lam);
-        for (int e = tid; e < l * m; e += 256) Vf[e / m][e % m] = exp(-pair_cost(cent[e / m], Z[n + e % m], d, B.cost) / lam);
-        for (int e = tid; e < l * l; e += 256)
-            Am[e / l][e % l] = exp(-pair_cost(cent[e / l], cent[e % l], d, B.cost) / lam) + (e / l == e % l ? B.ridge : 0.0);
-        __syncthreads();
-        if (tid == 0) {  // Cholesky of the l x l landmark kernel
-            for (int j = 0; j < l; ++j) {
-                double s = Am[j][j];
-                for (int k = 0; k < j; ++k) s -= Lm[j][k] * Lm[j][k];
-                if (!(s > 0.0)) {
-                    fail_sh = 1;
-                    s = 1.0;
-                }
-                const double ljj = sqrt(s);
-                Lm[j][j] = ljj;
-                for (int i = j + 1; i < l; ++i) {
-                    double t = Am[i][j];
-                    for (int k = 0; k < j; ++k) t -= Lm[i][k] * Lm[j][k];
-                    Lm[i][j] = t / ljj;
-                }
-            }
-        }
-        __syncthreads();
-        if (tid < l) {  // column tid of L^{-1}
-            const int c = tid;
-            for (int i = 0; i < l; ++i) {
-                double v = 0.0;
-                if (i >= c) {
-                    double t = (i == c) ? 1.0 : 0.0;
-                    for (int k = c; k < i; ++k) t -= Lm[i][k] * Li[k][c];
-                    v = t / Lm[i][i];
-                }
-                Li[i][c] = v;
-            }
-        }
-        __syncthreads();
-        for (int e = tid; e < l * l; e += 256) {  // A^{-1} = L^{-T} L^{-1}
-            const int i = e / l, j = e % l;
-            double t = 0.0;
-            for (int k = (i > j ? i : j); k < l; ++k) t += Li[k][i] * Li[k][j];
-            Am[i][j] = t;
-        }
-        __syncthreads();
-        // U <- U A^{-1}: every thread first reads the whole row it rewrites
-        for (int i = tid; i < n; i += 256) {
-            double row[BL];
-            for (int k = 0; k < l; ++k) row[k] = Uf[i][k];
-            for (int q = 0; q < l; ++q) {
-                double t = 0.0;
-                for (int k = 0; k < l; ++k) t += row[k] * Am[k][q];
-                Uf[i][q] = t;
-            }
-        }
-        __syncthreads();
-    }
-    if (hashed) {
-        for (int r = 0; r < B.R; ++r) {
-            block_kmeans(Z, N, d, B.b, B.T_b, B.seed_b + (unsigned long long)p * B.R + r, cent, assign, perm, sums,
-                         cnts);
-            for (int i = tid; i < N; i += 256) {
-                bucket[r][i] = assign[i];
-                B.buckets[(x0 + y0) * B.R + (long long)r * N + i] = assign[i];
-            }
-            __syncthreads();
-        }
-    }
-    // K~_ij: exact where x_i and y_j share a bucket, Nystrom elsewhere (0 without a Nystrom part)
-    float *Kt = B.Kt + (long long)p * BMAX * BMAX;
-    for (int e = tid; e < n * m; e += 256) {
-        const int i = e / m, j = e % m;
-        bool near = B.mode == LCN_MODE_DENSE;
-        if (hashed)
-            for (int r = 0; r < B.R; ++r) near |= bucket[r][i] == bucket[r][n + j];
-        double v = 0.0;
-        if (near) {
-            v = exp(-pair_cost(Z[i], Z[n + j], d, B.cost) / lam);
-        } else if (low_rank) {
-            for (int k = 0; k < l; ++k) v += Uf[i][k] * Vf[k][j];
-        }
-        Kt[i * BMAX + j] = (float)v;
-    }
-    if (B.bp) {
-        for (int i = tid; i < n; i += 256) B.kpe[x0 + i] = exp(-(double)B.del_x[x0 + i] / lam);
-        for (int j = tid; j < m; j += 256) B.keq[y0 + j] = exp(-(double)B.del_y[y0 + j] / lam);
-    }
-    const int len_u = B.bp ? N : n, len_v = B.bp ? N : m;
-    for (int i = tid; i < len_u; i += 256) B.log_u[x0 + y0 + i] = 0.0;
-    for (int i = tid; i < len_v; i += 256) B.log_v[x0 + y0 + i] = 0.0;
-    __syncthreads();
-    if (tid == 0 && fail_sh) *B.fail = 1;
+    return cost == LCN_COST_EUCLID ? sqrt(sq) : sq;
 }
 
 template <int CTRL>
@@ -335,6 +160,526 @@ __device__ inline void lane_swap(double &a, double &b)
                                : __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
     a = __hiloint2double(hi[0], lo[0]);
     b = __hiloint2double(hi[1], lo[1]);
+}
+
+// the smaller of two numbers in one instruction (fmin first quiets both arguments)
+__device__ inline double min64(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// over the four lanes that share l % 16
+__device__ inline double quarter_min(double v)
+{
+    double w = v;
+    lane_swap<32>(v, w);
+    v = min64(v, w);
+    w = v;
+    lane_swap<16>(v, w);
+    return min64(v, w);
+}
+
+__device__ inline double quarter_sum(double v)
+{
+    double w = v;
+    lane_swap<32>(v, w);
+    v += w;
+    w = v;
+    lane_swap<16>(v, w);
+    return v + w;
+}
+
+__device__ inline unsigned quarter_or(unsigned v)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = a[0] | a[1];
+    const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return b[0] | b[1];
+}
+
+// Cholesky factor of the l x l matrix A (LDS), l <= LP, by one wavefront, lane i holding row i: L below the
+// diagonal in place, 1 / L_jj behind the matrix.
+template <int LP>
+__device__ inline void landmark_cholesky(double *A, int l, int *not_positive)
+{
+    const int lane = threadIdx.x & 63;
+    double a[LP];
+#pragma unroll
+    for (int k = 0; k < LP; ++k) a[k] = (lane < l && k < l) ? A[lane * l + k] : (lane == k ? 1.0 : 0.0);
+    double rdiag = 1.0;
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < LP; ++j) {
+        double dd = lane_value(a[j], j);
+        if (!(dd > 0.0)) {
+            bad = true;
+            dd = 1.0;
+        }
+        double rs = __builtin_amdgcn_rsq(dd);   // 1 / sqrt to fp64 rounding: estimate and two Newton steps
+        rs = fma(0.5 * rs, fma(-dd * rs, rs, 1.0), rs);
+        rs = fma(0.5 * rs, fma(-dd * rs, rs, 1.0), rs);
+        rdiag = lane == j ? rs : rdiag;
+        a[j] *= rs;
+#pragma unroll
+        for (int k = j + 1; k < LP; ++k) a[k] = fma(-a[j], lane_value(a[j], k), a[k]);
+    }
+    if (bad && lane == 0) *not_positive = 1;
+#pragma unroll
+    for (int k = 0; k < LP; ++k)
+        if (lane < l && k < lane) A[lane * l + k] = a[k];
+    if (lane < l) A[l * l + lane] = rdiag;
+}
+
+// One workgroup of NT threads builds a pair; everything is in LDS.  What bounds it is latency: barriers,
+// chains of dependent operations on a few dozen points, and a vector instruction every 6.8 clocks where
+// a SIMD has one wavefront only (4.5 with several).  So
+//  * all k-means runs of the pair (landmarks and every hash round) advance together, a Lloyd iteration
+//    costing three barriers however many runs there are, and stop as soon as no assignment changed
+//    (from then on an iteration reproduces its own centroids bit for bit);
+//  * an assignment is a product on the fp64 matrix instruction, |c|^2 - 2 z.c for 16 points (columns; their
+//    operands stay in registers for all iterations) against 16 centroid rows, exact to rounding: centroids
+//    within 2 delta of a point's smallest score are its candidates, and only a point with several of them
+//    (near ties) is decided by the bucket rule itself;
+//  * the member sums are a product as well, of the 0/1 membership matrix with the fixed-point values: whole
+//    numbers below 2^53, so exact in any order;
+//  * the start indices of a run are drawn by a lane each and the shuffle is resolved by ballots;
+//  * the Nystrom values are products of L^{-1} u and L^{-1} v (A = L L^T): a Cholesky by one wavefront in
+//    registers and one forward substitution per point, no inverse;
+//  * every cost comes from dot products on the matrix instruction (see cost_of_dot), and so do the Nystrom
+//    values; tiles of the kernel without a pair that shares a bucket skip the costs.
+// Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 51 us for 16 pairs
+// (243 with one k-means run after the other, the rule on vector instructions and 64-bit LDS atomics), 114 us
+// for 1024 (336) and 351 us for 4096 (1145).
+// Layout of v_mfma_f64_16x16x4_f64: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16] and receives
+// D[4 v + l / 16][l % 16], v = 0..3; which dimension a step of a dot product takes is free, so a lane reads
+// four consecutive ones (16 t + 4 (l / 16) ..) for four steps.
+template <int NT, int DT>
+__global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
+{
+    constexpr int NW = NT / 64, TPW = 8 / NW;   // wavefronts; tiles of 16 points each of them holds (at most 128 points)
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int l = B.l, d = B.d, runs = (l > 0 ? 1 : 0) + B.R;
+    const BuildLds L = build_lds(l, runs, B.mt, DT, B.max_points, NW);
+    constexpr int zs = 16 * DT + 4;
+    double *F = (double *)(lds + L.f), *Am = (double *)(lds + L.am), *sums = (double *)(lds + L.sums);
+    double *pn = (double *)(lds + L.pn), *rn = (double *)(lds + L.rn);   // squared norms of the points, of the landmarks
+    float *Z = (float *)(lds + L.z), *cent = (float *)(lds + L.cent);
+    int *assign = (int *)(lds + L.assign), *cnts = (int *)(lds + L.cnts), *start = (int *)(lds + L.start);
+    int *owner = start + 16 * B.mt;   // of every centroid row: 256 run + index in the run, -1 if none
+    // [0], [1]: some assignment changed (by parity); [2]: not positive definite; [3]: a large coordinate;
+    // [4:5]: bits of the largest squared norm of a point
+    int *flags = (int *)(lds + L.flags);
+
+    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, quarter = lane >> 4;
+    const long long x0 = B.x_off[p], y0 = B.y_off[p];
+    const int n = (int)(B.x_off[p + 1] - x0), m = (int)(B.y_off[p + 1] - y0);
+    const int N = n + m, PT = (N + 15) / 16, rows16 = 16 * B.mt;
+    const double lam = (double)B.lambda[p];
+    const bool low_rank = l > 0, hashed = B.R > 0;
+    const int first_hash = low_rank ? 1 : 0;
+    const int buckets = B.b;
+    auto k_of = [&](int q) { return q < first_hash ? l : buckets; };
+    const int T_l = B.T_l, T_b = B.T_b;
+    auto iters_of = [&](int q) { return q < first_hash ? T_l : T_b; };
+    const unsigned row4 = B.row4;
+    auto row_of = [&](int q) { return (int)(row4 >> 6 * q & 63u) * 4; };
+    const int landmark_rows = (l + 3) & ~3;
+
+    if (tid < 8) flags[tid] = 0;
+    for (int e = tid; e < 2 * rows16; e += NT) cnts[e] = 0;
+    for (int e = tid; e < rows16; e += NT) owner[e] = start[e] = -1;   // rows that hold no centroid
+    __syncthreads();
+    // the pair's points, X then Y, zero padded to whole tiles of points and dimensions
+    {
+        constexpr int LANES = 16 * DT, STEP = NT / LANES;
+        const int r0 = tid / LANES, j = tid % LANES;
+        bool large = false;
+#pragma unroll 4
+        for (int i = r0; i < 16 * PT; i += STEP) {
+            const float *src = i < n ? B.X + (x0 + i) * d : B.Y + (y0 + i - n) * d;
+            const float v = (i < N && j < d) ? src[j] : 0.f;
+            Z[i * zs + j] = v;
+            large = large || !(fabsf(v) < 8192.f);
+        }
+        if (large) flags[3] = 1;
+    }
+    // Start of a run: the first k slots of a Fisher-Yates shuffle of 0 .. N-1 driven by splitmix64.  Lane t
+    // draws j_t; slot t receives what slot j_t holds, which is its own index unless an earlier step
+    // s swapped there (the last such s counts: slot j_s received slot s's value V_s).
+    for (int q = wave; q < runs; q += NW) {
+        const bool lm = q < first_hash;
+        const int k = k_of(q);
+        unsigned long long state = (lm ? B.seed_l + (unsigned long long)p
+                                       : B.seed_b + (unsigned long long)p * B.R + (unsigned long long)(q - first_hash)) +
+                                   (unsigned long long)lane * 0x9E3779B97F4A7C15ULL;
+        const unsigned long long r = splitmix64_dev(state);
+        const int J = lane < k ? lane + (int)(r % (unsigned long long)(N - lane)) : -1;
+        int V = lane, pick = 0;
+        for (int t = 0; t < k; ++t) {
+            const int jt = __builtin_amdgcn_readlane(J, t);
+            const unsigned long long below = (1ull << t) - 1ull;
+            const unsigned long long at_t = __ballot(J == t) & below, at_j = __ballot(J == jt) & below;
+            const int vt = at_t ? __builtin_amdgcn_readlane(V, 63 - __builtin_clzll(at_t)) : t;
+            const int vj = at_j ? __builtin_amdgcn_readlane(V, 63 - __builtin_clzll(at_j)) : jt;
+            if (lane == t) {
+                V = vt;
+                pick = jt == t ? vt : vj;
+            }
+        }
+        if (lane < k) {
+            start[row_of(q) + lane] = pick;
+            owner[row_of(q) + lane] = 256 * q + lane;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < 16 * DT * rows16; e += NT) {
+        const int c = e / (16 * DT), j = e % (16 * DT), s = start[c];
+        cent[c * zs + j] = s >= 0 ? Z[s * zs + j] : 0.f;
+    }
+    // this wavefront's points as matrix operands, and their squared norms
+    double zop[TPW][4 * DT];
+    {
+        double largest = 0.0;
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+            const int pt = 16 * (wave + NW * u) + col;
+            double sq = 0.0;
+#pragma unroll
+            for (int t = 0; t < DT; ++t) {
+                float4 v = {0.f, 0.f, 0.f, 0.f};
+                if (pt < 16 * PT) v = *(const float4 *)(Z + pt * zs + 16 * t + 4 * quarter);
+                const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    zop[u][4 * t + e] = (double)f[e];
+                    sq = fma((double)f[e], (double)f[e], sq);
+                }
+            }
+            sq = quarter_sum(sq);
+            if (quarter == 0 && pt < 16 * PT) pn[pt] = sq;
+            largest = fmax(largest, sq);
+        }
+        largest = wave_max(largest);
+        if (lane == 0) atomicMax((unsigned long long *)(flags + 4), (unsigned long long)__double_as_longlong(largest));
+    }
+    __syncthreads();
+    // Bound on |score - what the bucket rule computes| for any centroid: means do not leave the hull of the
+    // points, so |c|^2 and |z|^2 are at most M = the largest squared norm (plus the centroid's rounding to
+    // single precision); the score's d + 2 products and sums and the rule's 3 d operations are each off by
+    // 2^-53 of at most 4 M.  16 (d + 8) 2^-53 M covers both sides of a comparison.
+    const double two_delta = 2.0 * 1.01 * 16.0 * (double)(d + 8) * 0x1p-53 * __longlong_as_double(*(const long long *)(flags + 4));
+    const bool large = flags[3] != 0;
+    const int tiles = B.mt * DT, parts = tiles > 0 && NW > tiles ? NW / tiles : 1;
+    const int iters = T_l > T_b ? T_l : T_b;   // 0 for what does not run
+    // The bucket rule (fp64, dimensions in order, multiply and add separately, lowest index among equals) on
+    // the candidates of the points that have several: `mine` has bit v set if centroid 4 v + quarter of run q
+    // is a candidate of point pt; returns it with the winner's bit alone, in the winner's lane.
+    auto exact_winner = [&](unsigned mine, int pt, int q, int k) -> unsigned {
+        unsigned cand = 0;
+        for (int v = 0; v < 4; ++v) cand |= (mine >> v & 1u) << (4 * v + quarter);
+        cand = quarter_or(cand) & ((1u << k) - 1u);
+        if ((cand & (cand - 1)) == 0) return mine;
+        double best = INFINITY;
+        int c = __builtin_ctz(cand);
+        for (unsigned left = cand; left; left &= left - 1) {
+            const int cc = __builtin_ctz(left);
+            double D = 0.0;
+            for (int j = 0; j < d; ++j) {
+                const double t = (double)Z[pt * zs + j] - (double)cent[(row_of(q) + cc) * zs + j];
+                const double t2 = t * t;
+                D = D + t2;
+            }
+            if (D < best) {
+                best = D;
+                c = cc;
+            }
+        }
+        return (c & 3) == quarter ? 1u << (c >> 2) : 0u;
+    };
+    unsigned valid = 0;   // bit t: row col of centroid tile t holds a centroid
+    for (int t = 0; t < B.mt; ++t) valid |= (start[16 * t + col] >= 0 ? 1u : 0u) << t;
+    unsigned held[TPW];   // by run, four bits: which of this lane's centroids had the point in the last iteration
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) held[u] = 0u;
+    for (int it = 0; it < iters && runs > 0; ++it) {
+        int *cnt = cnts + (it & 1) * rows16;
+        unsigned changed = 0;
+        for (int mt = 0; mt < B.mt; ++mt) {
+            // this tile's centroids as operands: -2 c, and one step more that adds |c|^2 (rows without a
+            // centroid: a score no minimum picks)
+            double aop[4 * DT], cn = 0.0;
+#pragma unroll
+            for (int t = 0; t < DT; ++t) {
+                const float4 v = *(const float4 *)(cent + (16 * mt + col) * zs + 16 * t + 4 * quarter);
+                const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double c = (double)f[e];
+                    aop[4 * t + e] = -2.0 * c;
+                    cn = fma(c, c, cn);
+                }
+            }
+            cn = quarter_sum(cn);
+            const double an = quarter == 0 ? (valid >> mt & 1u ? cn : 1e300) : 0.0;
+            const double bn = quarter == 0 ? 1.0 : 0.0;
+#pragma unroll
+            for (int u = 0; u < TPW; ++u) {
+                const int tile = wave + NW * u;
+                if (tile >= PT) continue;   // the same in every lane
+                double4_t acc = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};   // two chains
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(an, bn, acc, 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < 4 * DT; e += 2) {
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(aop[e], zop[u][e], acc, 0, 0, 0);
+                    acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(aop[e + 1], zop[u][e + 1], acc2, 0, 0, 0);
+                }
+                acc += acc2;
+                const int pt = 16 * tile + col;
+                for (int q = 0; q < runs; ++q) {
+                    if (row_of(q) >> 4 != mt || it >= iters_of(q)) continue;   // the same in every lane
+                    const int k = k_of(q), va = (row_of(q) & 15) >> 2, vb = va + ((k + 3) >> 2);
+                    double best = INFINITY;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        best = v >= va && v < vb ? min64(best, acc[v]) : best;
+                    const double most = quarter_min(best) + two_delta;
+                    // the lanes that hold a candidate; a column (point) in which two do is undecided
+                    unsigned mine = 0;
+                    unsigned long long seen = 0, twice = 0;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                    {
+                        const bool in = v >= va && v < vb && acc[v] <= most;
+                        const unsigned long long b = __ballot(in);
+                        mine |= in ? 1u << v : 0u;
+                        twice |= seen & b;
+                        seen |= b;
+                    }
+                    mine >>= va;
+                    unsigned long long half = seen | seen >> 32;
+                    twice |= (seen & seen >> 32) | (half & half >> 16);
+                    if ((unsigned)(twice >> 32) | (unsigned)twice) mine = exact_winner(mine, pt, q, k);
+                    const int shift = 4 * q;
+                    const unsigned differs = (held[u] ^ mine << shift) & 15u << shift;
+                    changed |= differs;
+                    held[u] ^= differs;
+                    if (mine && pt < N) {   // one lane per point
+                        const int c = 4 * __builtin_ctz(mine) + quarter;
+                        assign[q * L.rows + pt] = c;
+                        atomicAdd(&cnt[row_of(q) + c], 1);
+                    }
+                }
+            }
+        }
+        if (__any(changed != 0) && lane == 0) flags[it & 1] = 1;
+        __syncthreads();
+        if (!flags[it & 1]) break;   // the same in every thread
+        if (!large) {
+            // Member sums in 2^-32 fixed point as a matrix product: rows = centroids, columns = dimensions, one
+            // step = four points.  |z| < 2^13 makes every value a whole number below 2^45 and every sum one
+            // below 2^52: exact.  With fewer output tiles than wavefronts the points are split into parts.
+            const int steps = (N + 7) / 8 * 2, per_part = ((steps + parts - 1) / parts + 1) & ~1;   // even: two steps at a time
+            for (int u = wave; u < parts * tiles; u += NW) {
+                const int tile = u % tiles, part = u / tiles, mt = tile / DT, dt = tile % DT;
+                // the run and index of this lane's centroid row
+                const int own = owner[16 * mt + col];
+                const int *as = assign + (own >= 0 ? own >> 8 : 0) * L.rows;
+                const int mine = own >= 0 ? own & 255 : -1;
+                const float *zc = Z + 16 * dt + col;
+                double4_t acc = {0.0, 0.0, 0.0, 0.0};
+                const int s1 = per_part * (part + 1) < steps ? per_part * (part + 1) : steps;
+                for (int s = per_part * part; s < s1; s += 2) {   // points past the last one are zero rows
+                    double a[2], b[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int pt = 4 * (s + e) + quarter;
+                        a[e] = as[pt] == mine ? 1.0 : 0.0;
+                        b[e] = rint((double)zc[pt * zs] * 4294967296.0);
+                    }
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b[0], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], b[1], acc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sums[256 * u + 16 * (4 * v + quarter) + col] = acc[v];
+            }
+        } else {
+            // coordinates up to 2^31: 64-bit integers
+            unsigned long long *isum = (unsigned long long *)sums;
+            for (int e = tid; e < tiles * 256; e += NT) isum[e] = 0ull;
+            __syncthreads();
+            for (int e = tid; e < N * 16 * DT; e += NT) {
+                const int i = e / (16 * DT), j = e % (16 * DT);
+                const unsigned long long fx = (unsigned long long)__double2ll_rn((double)Z[i * zs + j] * 4294967296.0);
+                for (int q = 0; q < runs; ++q) {
+                    if (it >= iters_of(q)) continue;
+                    const int row = row_of(q) + assign[q * L.rows + i];
+                    atomicAdd(&isum[256 * ((row >> 4) * DT + (j >> 4)) + 16 * (row & 15) + (j & 15)], fx);
+                }
+            }
+        }
+        __syncthreads();
+        for (int e = tid; e < 16 * DT * rows16; e += NT) {
+            const int row = e / (16 * DT), j = e % (16 * DT);
+            const int k = cnt[row];
+            if (it < (row < landmark_rows ? T_l : T_b) && k > 0) {   // an empty cluster keeps its centroid
+                const int at = 256 * ((row >> 4) * DT + (j >> 4)) + 16 * (row & 15) + (j & 15);
+                double sum;
+                if (large) {
+                    sum = (double)(long long)((const unsigned long long *)sums)[at];
+                } else {
+                    sum = sums[at];
+                    for (int part = 1; part < parts; ++part) sum += sums[256 * tiles * part + at];
+                }
+                cent[row * zs + j] = (float)((sum * (1.0 / 4294967296.0)) / (double)k);
+            }
+        }
+        for (int e = tid; e < rows16; e += NT) cnts[((it + 1) & 1) * rows16 + e] = 0;
+        if (tid == 0) flags[(it + 1) & 1] = 0;
+        __syncthreads();
+    }
+    __syncthreads();   // a loop left early has its assignments in place, but other wavefronts may still read the flag
+
+    constexpr int dp = 16 * DT;
+    const double inv_lam = 1.0 / lam;
+    // sixteen rows of Z or cent as a matrix operand of this lane
+    auto operand = [&](const float *rows, int at, double (&o)[4 * DT]) {
+#pragma unroll
+        for (int t = 0; t < DT; ++t) {
+            const float4 v = *(const float4 *)(rows + at * zs + 16 * t + 4 * quarter);
+            o[4 * t] = (double)v.x, o[4 * t + 1] = (double)v.y, o[4 * t + 2] = (double)v.z, o[4 * t + 3] = (double)v.w;
+        }
+    };
+    auto dots = [&](const double (&a)[4 * DT], const double (&b)[4 * DT]) -> double4_t {
+        double4_t x = {0.0, 0.0, 0.0, 0.0}, y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 4 * DT; e += 2) {
+            x = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], x, 0, 0, 0);
+            y = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e + 1], b[e + 1], y, 0, 0, 0);
+        }
+        return x + y;
+    };
+    if (low_rank) {
+        for (int e = tid; e < l * d; e += NT) B.landmarks[(long long)p * l * d + e] = cent[(e / d) * zs + e % d];
+        // exp(-c / lambda) of the landmarks (rows 0 .. l - 1 of the first tile) with every point and among themselves
+        double lop[4 * DT];
+        operand(cent, col, lop);
+        {
+            double sq = 0.0;
+#pragma unroll
+            for (int e = 0; e < 4 * DT; ++e) sq = fma(lop[e], lop[e], sq);
+            sq = quarter_sum(sq);
+            if (wave == 0 && quarter == 0) rn[col] = sq;
+        }
+        __syncthreads();
+        for (int t = wave; t <= PT; t += NW) {   // tile PT: the landmarks themselves
+            const bool self = t == PT;
+            double bop[4 * DT];
+            operand(self ? cent : Z, self ? col : 16 * t + col, bop);
+            const double4_t dot = dots(lop, bop);
+            const int pt = self ? col : 16 * t + col;
+            const double b2 = self ? rn[col] : pn[pt];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = 4 * v + quarter;
+                if (k < l && pt < (self ? l : N)) {
+                    const double c = (self && k == pt) ? 0.0
+                                                       : cost_of_dot(dot[v], rn[k], b2, cent + k * zs,
+                                                                     (self ? cent : Z) + pt * zs, dp, B.cost);
+                    const double f = exp(-c * inv_lam);
+                    if (self)
+                        Am[k * l + pt] = f + (k == pt ? B.ridge : 0.0);
+                    else
+                        F[pt * L.ls + k] = f;
+                }
+            }
+        }
+        __syncthreads();
+        const double *rdiag = Am + l * l;   // 1 / L_jj
+        if (wave == 0) {
+            if (l <= 8)
+                landmark_cholesky<8>(Am, l, flags + 2);
+            else
+                landmark_cholesky<BL>(Am, l, flags + 2);
+        }
+        __syncthreads();
+        // every point's factor row f -> L^{-1} f, a thread per point
+        for (int i = tid; i < N; i += NT) {
+            double *f = F + i * L.ls;
+            double x[BL];
+#pragma unroll
+            for (int k = 0; k < BL; ++k) {
+                if (k < l) {
+                    double t = f[k];
+#pragma unroll
+                    for (int q = 0; q < k; ++q) t = fma(-Am[k * l + q], x[q], t);
+                    x[k] = t * rdiag[k];
+                    f[k] = x[k];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (hashed)
+        for (int r = 0; r < B.R; ++r)
+            for (int i = tid; i < N; i += NT)
+                B.buckets[(x0 + y0) * B.R + (long long)r * N + i] = assign[(first_hash + r) * L.rows + i];
+    // K~_ij: exact where x_i and y_j share a bucket, Nystrom elsewhere (0 without a Nystrom part); a
+    // wavefront takes 16 x 16 tiles, rows x_i, columns y_j
+    float *Kt = B.Kt + (long long)p * BMAX * BMAX;
+    const int TI = (n + 15) / 16, TJ = (m + 15) / 16;
+    for (int t = wave; t < TI * TJ; t += NW) {
+        const int ti = t / TJ, tj = t % TJ;
+        const int j = 16 * tj + col;
+        const int ar = 16 * ti + col < n ? 16 * ti + col : n - 1, br = n + (j < m ? j : m - 1);   // operand rows
+        bool near[4];
+        bool any_near = false;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * ti + 4 * v + quarter;
+            const bool in = i < n && j < m;
+            near[v] = in && B.mode == LCN_MODE_DENSE;
+#pragma unroll
+            for (int r = 0; r < BR; ++r)
+                if (r < B.R) {
+                    const int *as = assign + (first_hash + r) * L.rows;
+                    near[v] = near[v] || (in && as[i < n ? i : n - 1] == as[br]);
+                }
+            any_near = any_near || near[v];
+        }
+        double4_t nys = {0.0, 0.0, 0.0, 0.0}, dot = {0.0, 0.0, 0.0, 0.0};
+        if (low_rank) {
+            for (int k = quarter; k - quarter < l; k += 4)
+                nys = __builtin_amdgcn_mfma_f64_16x16x4f64(k < l ? F[ar * L.ls + k] : 0.0,
+                                                          k < l ? F[br * L.ls + k] : 0.0, nys, 0, 0, 0);
+        }
+        if (__any(any_near)) {
+            double xop[4 * DT], yop[4 * DT];
+            operand(Z, ar, xop);
+            operand(Z, br, yop);
+            dot = dots(xop, yop);
+        }
+        const double y2 = pn[br];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * ti + 4 * v + quarter;
+            double val = nys[v];
+            if (near[v])
+                val = exp(-cost_of_dot(dot[v], pn[i], y2, Z + i * zs, Z + br * zs, dp, B.cost) * inv_lam);
+            if (i < n && j < m) Kt[i * BMAX + j] = (float)val;
+        }
+    }
+    if (B.bp) {
+        for (int i = tid; i < n; i += NT) B.kpe[x0 + i] = exp(-(double)B.del_x[x0 + i] / lam);
+        for (int i = tid; i < m; i += NT) B.keq[y0 + i] = exp(-(double)B.del_y[y0 + i] / lam);
+    }
+    const int len_u = B.bp ? N : n, len_v = B.bp ? N : m;
+    for (int i = tid; i < len_u; i += NT) B.log_u[x0 + y0 + i] = 0.0;
+    for (int i = tid; i < len_v; i += NT) B.log_v[x0 + y0 + i] = 0.0;
+    if (tid == 0 && flags[2]) *B.fail = 1;
 }
 
 __device__ inline double rcp64(double x)   // 1 / x for a positive finite x, to about one unit in the last place
@@ -633,6 +978,33 @@ using namespace lcn;
 namespace lcn {
 bool is_batched_handle(const void *h) { return h && *(const uint32_t *)h == BATCH_MAGIC; }
 
+template <int NT, int DT>
+static hipError_t launch_batched_build_as(const BatchHandle &h)
+{
+    const BatchDev &D = h.dev;
+    const size_t bytes = build_lds(D.l, (D.l > 0 ? 1 : 0) + D.R, D.mt, DT, D.max_points, NT / 64).bytes;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&batched_build_kernel<NT, DT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((batched_build_kernel<NT, DT>), dim3(D.P), dim3(NT), bytes, h.stream, D);
+    return hipGetLastError();
+}
+
+// Eight wavefronts instead of four per pair: where a compute unit has at most two pairs and the pairs more
+// than the four tiles of points that four wavefronts hold (call with its copies, d = 32, 16 to 64 points per
+// side: 64 pairs 96 against 109 us, 512 pairs 118 against 127, 768 pairs 150 against 149, 1024 pairs 167
+// against 153; 10 to 30 points: 512 pairs 84 against 83), and for more than 32 dimensions, where four
+// wavefronts have too few registers for their points (1024 pairs, d = 64: 238 against 280).
+static hipError_t launch_batched_build(const BatchHandle &h)
+{
+    const BatchDev &D = h.dev;
+    const int dt = (D.d + 15) / 16;
+    const bool wide = D.P <= 2 * device_compute_units() && D.max_points > 64;
+    if (dt <= 1) return wide ? launch_batched_build_as<512, 1>(h) : launch_batched_build_as<256, 1>(h);
+    if (dt == 2) return wide ? launch_batched_build_as<512, 2>(h) : launch_batched_build_as<256, 2>(h);
+    return launch_batched_build_as<512, 4>(h);
+}
+
 static hipError_t launch_batched_run(const BatchHandle &h, int iters, float *row_dev, float *col_dev)
 {
     if (h.dev.bp)
@@ -720,9 +1092,11 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
                    lsh->and_width > 1))
         return LCN_ERR_INVALID_ARG;
     if ((desc->del_cost_x == nullptr) != (desc->del_cost_y == nullptr)) return LCN_ERR_INVALID_ARG;
+    int max_points = 0;
     for (int p = 0; p < P; ++p) {
         const long long n = desc->x_off[p + 1] - desc->x_off[p], m = desc->y_off[p + 1] - desc->y_off[p];
         if (n < 1 || m < 1 || n > BMAX || m > BMAX) return LCN_ERR_INVALID_ARG;
+        max_points = n + m > max_points ? (int)(n + m) : max_points;
         if (low_rank && lm->num_landmarks > n + m) return LCN_ERR_INVALID_ARG;
         if (hashed && lsh->num_buckets > n + m) return LCN_ERR_INVALID_ARG;
         if (!(desc->lambda[p] > 0.f)) return LCN_ERR_INVALID_ARG;
@@ -750,6 +1124,7 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
     BatchDev &D = h.dev;
     D.P = P;
     D.d = d;
+    D.max_points = max_points;
     D.cost = cost;
     D.mode = mode;
     D.l = low_rank ? lm->num_landmarks : 0;
@@ -760,6 +1135,7 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
     D.seed_l = low_rank ? lm->seed : 0;
     D.seed_b = hashed ? lsh->seed : 0;
     D.ridge = low_rank ? lm->ridge : 0.0;
+    build_rows(D);
     D.bp = desc->del_cost_x ? 1 : 0;
     D.X = X;
     D.Y = Y;
@@ -802,11 +1178,7 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
     BHIPCHK(hipMemcpyAsync(lam, desc->lambda, sizeof(float) * P, hipMemcpyHostToDevice, h.stream));
     BHIPCHK(hipMemsetAsync(D.counters, 0, 64, h.stream));
     BHIPCHK(hipMemsetAsync(D.fail, 0, 64, h.stream));
-    const size_t lds_bytes = build_lds(D.d, D.l, D.b).bytes;
-    BHIPCHK(hipFuncSetAttribute((const void *)batched_build_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_bytes));
-    hipLaunchKernelGGL(batched_build_kernel, dim3(P), dim3(256), lds_bytes, h.stream, D);
-    BHIPCHK(hipGetLastError());
+    BHIPCHK(launch_batched_build(h));
     int fail = 0;
     BHIPCHK(hipMemcpyAsync(&fail, D.fail, sizeof(int), hipMemcpyDeviceToHost, h.stream));
     BHIPCHK(hipStreamSynchronize(h.stream));

@@ -19,6 +19,8 @@
 // that vector one iteration earlier (any reference works; logs move slowly), and
 // M travels with every quantity derived from the vector.  Products are
 // accumulated in fp64.
+#include <atomic>
+
 #include "iter_common.h"
 
 namespace lcn {
@@ -672,10 +674,18 @@ static size_t pass_lds_bytes(int lp, bool fused)
 // every row slot is dealt out once and the partial sums stay few.
 int device_compute_units()
 {
+    static std::atomic<int> known[64];   // per device, looked up once (the query takes tens of microseconds)
     int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+        (void)hipGetLastError();
+        return cus;
+    }
+    const int have = known[dev].load(std::memory_order_relaxed);
+    if (have > 0) return have;
+    int got = 0;
+    if (hipDeviceGetAttribute(&got, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && got > 0) {
+        cus = got;
+        known[dev].store(cus, std::memory_order_relaxed);
     }
     (void)hipGetLastError();
     return cus;

@@ -262,3 +262,38 @@ def test_batched_iteration_on_block_edges(mode, bp, lam):
         np.testing.assert_allclose(lu, so.log_u, rtol=0, atol=1e-4)
         np.testing.assert_allclose(lv, so.log_v, rtol=0, atol=1e-4)
         assert abs(dist[p] - dist_o) <= 1e-4 * abs(dist_o) and abs(resid[p] - resid_o) <= 1e-5
+
+
+@pytest.mark.parametrize("d,l,b,rounds,kind", [(16, 5, 3, 2, "plain"), (17, 16, 16, 4, "plain"), (33, 3, 4, 1, "ties"),
+                                               (3, 9, 7, 3, "ties"), (8, 4, 4, 1, "large")])
+def test_batched_build_decides_like_the_rule(d, l, b, rounds, kind):
+    """Buckets and landmarks bit for bit: centroids of several k-means runs over one and several tiles of
+    sixteen; points on a coarse grid, where many distances are exactly equal and the matrix product leaves
+    every decision to the rule; coordinates above 2^13, where the member sums are integers."""
+    sizes = [(16, 16), (17, 20), (64, 64), (33, 31), (40, 9)]
+    B = _edge_batch(sizes, d, l, b, seed=7)
+    if kind == "ties":
+        B.X[:] = np.round(B.X)
+        B.Y[:] = np.round(B.Y)
+    if kind == "large":
+        B.X *= 6000.0
+        B.Y *= 6000.0
+        B.lam[:] *= 6000.0
+    import paper_2107_06876_amd as lcn
+    import oracle
+    dev = "cuda:0"
+    lm = dict(num_landmarks=l, kmeans_iters=7, seed=3, ridge=0.5)
+    lsh = dict(num_buckets=b, num_rounds=rounds, kmeans_iters=9, seed=41)
+    h = lcn.lcn_build_batched(torch.from_numpy(B.X).to(dev), torch.from_numpy(B.Y).to(dev), B.x_off, B.y_off, B.lam,
+                              B.cost, lcn.MODE_LCN, None, None, landmarks=lm, lsh=lsh)
+    st = lcn.lcn_batched_get(h)
+    landmarks, buckets = st["landmarks"].cpu().numpy(), st["buckets"].cpu().numpy()
+    for p, (n, m) in enumerate(sizes):
+        Z = np.concatenate([B.X[B.x_off[p]:B.x_off[p + 1]], B.Y[B.y_off[p]:B.y_off[p + 1]]])
+        cent, _ = oracle.kmeans(Z, l, 7, 3 + p)
+        np.testing.assert_array_equal(landmarks[p], cent)
+        z0 = int(B.x_off[p] + B.y_off[p]) * rounds
+        for r in range(rounds):
+            _, asg = oracle.kmeans(Z, b, 9, 41 + p * rounds + r)
+            np.testing.assert_array_equal(buckets[z0 + r * (n + m):z0 + (r + 1) * (n + m)], asg)
+    lcn.lcn_destroy(h)
