@@ -1,5 +1,4 @@
-// Device helpers shared by the two half-iteration kernels (one row per
-// wavefront, and four rows per wavefront): cross-lane sums, the short log and
+// Device helpers of the half-iteration kernels: cross-lane sums, the short log and
 // reciprocal used by the scaling update, the factor-row register layout and the
 // in-kernel completion of the previous sweep's reduction.
 #pragma once
@@ -14,9 +13,6 @@ constexpr int MAXR = 8;
 // what the single-precision bucket-ordered copies of a scaling vector are stored times, and its inverse
 constexpr double PERM_SCALE = 18446744073709551616.0;          // 2^64
 constexpr double PERM_UNSCALE = 1.0 / 18446744073709551616.0;  // 2^-64
-#ifndef PASS_MIN_WAVES
-#define PASS_MIN_WAVES 1
-#endif
 
 // One step of a cross-lane sum of doubles through the DPP data path (no LDS):
 // adds to every lane the value of the lane that `CTRL` selects; lanes of rows
@@ -92,35 +88,36 @@ __device__ inline double fast_rcp(double x)
     return r;
 }
 
-// Factor row held by a wave.  lp = 64 T.  If T is a multiple of 4 a lane holds
-// 4 consecutive entries per 256 (one 16-byte load each), else one entry per 64.
+// Factor row of lp = 64 T entries held by a wave: per 256 entries one 16-byte load of four consecutive entries
+// per lane, then one 8-byte load if 128 or more are left, then one of 4 bytes.
 template <int T>
 struct FRow {
-    static constexpr int TT = T > 0 ? T : 1;
-    static constexpr bool VEC = (T > 0) && (T % 4 == 0);
-    float f[TT];
+    static constexpr int Q4 = T / 4 * 4;
+    float f[T];
     __device__ inline void load(const float *__restrict__ F, long long row, int lp, int lane)
     {
-        if (T == 0) return;
         F += row * lp;
-        if (VEC) {
 #pragma unroll
-            for (int q = 0; q < T / 4; ++q) {
-                const float4 v = *(const float4 *)(F + (unsigned)(256 * q + 4 * lane));
-                f[4 * q + 0] = v.x;
-                f[4 * q + 1] = v.y;
-                f[4 * q + 2] = v.z;
-                f[4 * q + 3] = v.w;
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < TT; ++t) f[t] = F[(unsigned)(64 * t + lane)];
+        for (int q = 0; q < T / 4; ++q) {
+            const float4 v = *(const float4 *)(F + (unsigned)(256 * q + 4 * lane));
+            f[4 * q + 0] = v.x;
+            f[4 * q + 1] = v.y;
+            f[4 * q + 2] = v.z;
+            f[4 * q + 3] = v.w;
         }
+        if constexpr (T % 4 >= 2) {
+            const float2 v = *(const float2 *)(F + (unsigned)(64 * Q4 + 2 * lane));
+            f[Q4] = v.x;
+            f[Q4 + 1] = v.y;
+        }
+        if constexpr (T % 2 == 1) f[T - 1] = F[(unsigned)(64 * (T - 1) + lane)];
     }
     // index into the length-lp vectors of register slot e
     __device__ static inline int kidx(int e, int lane)
     {
-        return VEC ? 256 * (e / 4) + 4 * lane + (e % 4) : 64 * e + lane;
+        if (e < Q4) return 256 * (e / 4) + 4 * lane + (e % 4);
+        if (T % 4 >= 2 && e < Q4 + 2) return 64 * Q4 + 2 * lane + (e - Q4);
+        return 64 * (T - 1) + lane;
     }
 };
 
@@ -253,5 +250,55 @@ __device__ inline void fused_fetch(const FuseArgs &Fz, const double *acc, int lp
         }
     }
 }
+
+// End of a sweep: the sums over the workgroup's wavefronts (upper half of the waves hands its values to the
+// lower half first) as one partial per workgroup.  zsh: [PASS_WAVES / 2][lp + 3].
+template <int T>
+__device__ inline void group_partials(const double (&zacc)[T], double q0, double q1, double maxlog, int lp, double *zsh,
+                                      double *partial)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int stride = lp + 3;
+    constexpr int HALF = PASS_WAVES / 2;
+    double *mine = zsh + (wave % HALF) * stride;
+    if (wave >= HALF) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) mine[FRow<T>::kidx(t, lane)] = zacc[t];
+        if (lane == 0) {
+            mine[lp] = q0;
+            mine[lp + 1] = q1;
+            mine[lp + 2] = maxlog;
+        }
+    }
+    __syncthreads();
+    if (wave < HALF) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) mine[FRow<T>::kidx(t, lane)] += zacc[t];
+        if (lane == 0) {
+            mine[lp] += q0;
+            mine[lp + 1] += q1;
+            mine[lp + 2] = fmax(mine[lp + 2], maxlog);
+        }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < stride; k += PASS_THREADS) {
+        double s = k == lp + 2 ? -INFINITY : 0.0;
+#pragma unroll
+        for (int w = 0; w < HALF; ++w) s = k == lp + 2 ? fmax(s, zsh[w * stride + k]) : s + zsh[w * stride + k];
+        partial[(long long)blockIdx.x * stride + k] = s;
+    }
+}
+
+inline size_t pass_lds_bytes(int lp, bool fused)
+{
+    size_t doubles = (size_t)(PASS_WAVES / 2) * (lp + 3);
+    if (fused) doubles += (size_t)lp + 2 + 16 * 64;
+    return sizeof(double) * doubles;
+}
+
+// sweeps without a sparse part (kernels_nystrom.hip), and how many workgroups (partial sums) one has
+hipError_t launch_nystrom_pass(const PassSide &S, const Handle &h, int mode, const FuseArgs *fuse, bool fused_in,
+                               double *partial, unsigned long long *cnt, hipStream_t s);
+int nystrom_sweep_groups(const Handle &h, long long rows);
 
 }  // namespace lcn

@@ -33,11 +33,14 @@ namespace lcn {
 // wait for nothing, so the wait ends).  This saves a dependent kernel launch
 // per sweep without any device-wide fence.
 template <int T, int RR, int MODE, bool FUSED>
-__global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(PassSide S, int R, int lp, double *partial,
-                                                            unsigned long long *counters, int empty_slot,
-                                                            FuseArgs Fz)
+__global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, int lp, double *partial,
+                                                            unsigned long long *counters, FuseArgs Fz)
 {
-    constexpr int TT = T > 0 ? T : 1;
+    // Entries of a segment requested with the row, in wavefronts: two where few rounds and short factor rows leave
+    // requests to spare (segments of 40 to 300 entries: 18.5 against 19.6 us per sweep at 40 000 rows, one round;
+    // 12.8 against 13.3 at 10 000 rows, two rounds; three or four gain nothing more), one otherwise (two
+    // rounds of rows of 512 entries: 95 against 98 us)
+    constexpr int W = RR <= 2 && T <= 4 ? 2 : 1;
     extern __shared__ double zsh[];  // [PASS_WAVES / 2][lp + 3], then [lp + 2] and [16][64] if FUSED
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -56,9 +59,9 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
     double m_in = 0.0, e_out = 1.0;
     double maxlog = -INFINITY;
 
-    double yreg[TT], zacc[TT];
+    double yreg[T], zacc[T];
 #pragma unroll
-    for (int t = 0; t < TT; ++t) {
+    for (int t = 0; t < T; ++t) {
         yreg[t] = 0.0;
         zacc[t] = 0.0;
     }
@@ -66,11 +69,11 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
         m_in = MODE != PASS_INIT ? S.acc_in[lp] : 0.0;
         e_out = MODE == PASS_UPDATE ? exp(-m_in - m_self) : (MODE == PASS_QUERY ? exp(m_in + m_self) : 1.0);
 #pragma unroll
-        for (int t = 0; t < TT; ++t)
-            yreg[t] = (T > 0 && MODE != PASS_INIT) ? S.acc_in[FRow<T>::kidx(t, lane)] : 0.0;
+        for (int t = 0; t < T; ++t)
+            yreg[t] = MODE != PASS_INIT ? S.acc_in[FRow<T>::kidx(t, lane)] : 0.0;
     }
     double q0 = 0.0, q1 = 0.0;
-    unsigned long long nonpos = 0, empty = 0, range = 0;
+    unsigned long long nonpos = 0, range = 0;
 
     // Three-stage software pipeline over the rows a wave owns: metadata is read
     // two rows ahead (scalar loads), the factor row and the first 64 entries of
@@ -78,8 +81,8 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
     // those loads are in flight.
     struct RowData {
         FRow<T> f;
-        float tv[RR];
-        float vv[RR];
+        float tv[RR][W];
+        float vv[RR][W];
     };
     // The bucket-ordered copies of the scalings are single precision in this kernel (the buffers are
     // sized for doubles; the logarithmic kernels keep doubles there): they are gathered once per
@@ -94,7 +97,7 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
     // Loads are issued for whole wavefront-wide chunks without predication: lanes
     // beyond a segment's length read the next stored values (masked when used; the
     // arrays end with 64 entries of slack) and the zero slot behind the gathered vector.
-    const unsigned zero_slot = (unsigned)((R > 0 ? R : 1) * S.rows_in);
+    const unsigned zero_slot = (unsigned)(R * S.rows_in);
     auto issue = [&](RowData &D, const RowMeta<RR> &M, long long r) {
         D.f.load(S.F, r, lp, lane);
         if (MODE != PASS_INIT) {
@@ -102,8 +105,11 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
             unsigned off = lane;
 #pragma unroll
             for (int q = 0; q < RR; ++q) {
-                D.tv[q] = vals[off];
-                D.vv[q] = perm_in[lane < M.len[q] ? (unsigned)M.vstart[q] + lane : zero_slot];
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    D.tv[q][w] = vals[off + 64 * w];
+                    D.vv[q][w] = perm_in[lane + 64 * w < M.len[q] ? (unsigned)M.vstart[q] + lane + 64 * w : zero_slot];
+                }
                 off += (unsigned)M.len[q];
             }
         }
@@ -127,10 +133,8 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
         __syncthreads();
         m_in = ysh[lp];
         e_out = ysh[lp + 1];
-        if (T > 0) {
 #pragma unroll
-            for (int t = 0; t < TT; ++t) yreg[t] = ysh[FRow<T>::kidx(t, lane)];
-        }
+        for (int t = 0; t < T; ++t) yreg[t] = ysh[FRow<T>::kidx(t, lane)];
     }
     // one row: `C` holds the row's data, `N` receives the next row's
     auto step = [&](RowData &C, RowData &N) {
@@ -147,17 +151,20 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
         } else {
             double acc = 0.0;
 #pragma unroll
-            for (int q = 0; q < RR; ++q) acc = fma((double)(lane < mc.len[q] ? C.tv[q] : 0.f), (double)C.vv[q], acc);
+            for (int q = 0; q < RR; ++q)
+#pragma unroll
+                for (int w = 0; w < W; ++w)
+                    acc = fma((double)(lane + 64 * w < mc.len[q] ? C.tv[q][w] : 0.f), (double)C.vv[q][w], acc);
             {   // what is left of segments longer than a wavefront
                 const float *__restrict__ vals = S.vals + mc.base;
                 int off = 0;
 #pragma unroll
                 for (int q = 0; q < RR; ++q) {
-                    if (mc.len[q] > 64) {
+                    if (mc.len[q] > 64 * W) {
                         // 256 entries per trip, all eight loads requested before the first is used
                         const float *tp = vals + off;
                         const float *vp = perm_in + mc.vstart[q];
-                        for (int e0 = 64; e0 < mc.len[q]; e0 += 256) {
+                        for (int e0 = 64 * W; e0 < mc.len[q]; e0 += 256) {
                             float tt[4];
                             float pv[4];
 #pragma unroll
@@ -176,10 +183,8 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
                 }
             }
             acc *= PERM_UNSCALE;
-            if (T > 0) {
 #pragma unroll
-                for (int t = 0; t < TT; ++t) acc = fma((double)C.f.f[t], yreg[t], acc);
-            }
+            for (int t = 0; t < T; ++t) acc = fma((double)C.f.f[t], yreg[t], acc);
             const double s = wave_sum(acc);
             const double marg = (double)mc.marg;
             if (MODE == PASS_UPDATE) {
@@ -189,10 +194,6 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
                     const double lg = mc.log_marg - fast_log(s) - m_in;
                     lo = (float)lg;
                     maxlog = fmax(maxlog, lg);
-                } else if (T == 0 && s == 0.0) {  // no kernel entry (or only zero ones): the point carries no mass
-                    out = 0.0;
-                    lo = -INFINITY;
-                    ++empty;
                 } else {
                     out = NAN;
                     lo = NAN;
@@ -210,12 +211,10 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
         if (MODE != PASS_QUERY) {
             if (lane == 0) S.lin_out[row] = out;
             const float outf = (float)(out * PERM_SCALE);
-            if (R > 0 && outf == INFINITY) ++range;   // without hash rounds nothing reads the copies
+            if (outf == INFINITY) ++range;
             if (lane < R) perm_out[(long long)lane * S.rows + mc.pos] = outf;
-            if (T > 0) {
 #pragma unroll
-                for (int t = 0; t < TT; ++t) zacc[t] = fma((double)C.f.f[t], out, zacc[t]);
-            }
+            for (int t = 0; t < T; ++t) zacc[t] = fma((double)C.f.f[t], out, zacc[t]);
         }
         mc = mn;
         mn = mn2;
@@ -238,43 +237,9 @@ __global__ __launch_bounds__(PASS_THREADS, PASS_MIN_WAVES) void pass_kernel(Pass
         }
     }
 
-    // workgroup reduction of the per-wave accumulators (upper half of the waves
-    // hands its values to the lower half first), then one partial per workgroup
-    constexpr int HALF = PASS_WAVES / 2;
-    double *mine = zsh + (wave % HALF) * stride;
-    if (wave >= HALF) {
-        if (T > 0) {
-#pragma unroll
-            for (int t = 0; t < TT; ++t) mine[FRow<T>::kidx(t, lane)] = zacc[t];
-        }
-        if (lane == 0) {
-            mine[lp] = q0;
-            mine[lp + 1] = q1;
-            mine[lp + 2] = maxlog;
-        }
-    }
-    __syncthreads();
-    if (wave < HALF) {
-        if (T > 0) {
-#pragma unroll
-            for (int t = 0; t < TT; ++t) mine[FRow<T>::kidx(t, lane)] += zacc[t];
-        }
-        if (lane == 0) {
-            mine[lp] += q0;
-            mine[lp + 1] += q1;
-            mine[lp + 2] = fmax(mine[lp + 2], maxlog);
-        }
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < stride; k += PASS_THREADS) {
-        double s = k == lp + 2 ? -INFINITY : 0.0;
-#pragma unroll
-        for (int w = 0; w < HALF; ++w) s = k == lp + 2 ? fmax(s, zsh[w * stride + k]) : s + zsh[w * stride + k];
-        partial[(long long)blockIdx.x * stride + k] = s;
-    }
-    if (lane == 0 && (nonpos | empty | range)) {
+    group_partials<T>(zacc, q0, q1, maxlog, lp, zsh, partial);
+    if (lane == 0 && (nonpos | range)) {
         if (nonpos) atomicAdd(&counters[0], nonpos);
-        if (empty) atomicAdd(&counters[empty_slot], empty);
         if (range) atomicAdd(&counters[6], range);
     }
 }
@@ -662,13 +627,6 @@ __global__ __launch_bounds__(1024) void max_log_kernel(const float *__restrict__
     if (threadIdx.x == 0) *out = sh[0] > -INFINITY ? (double)sh[0] : 0.0;
 }
 
-static size_t pass_lds_bytes(int lp, bool fused)
-{
-    size_t doubles = (size_t)(PASS_WAVES / 2) * (lp + 3);
-    if (fused) doubles += (size_t)lp + 2 + 16 * 64;
-    return sizeof(double) * doubles;
-}
-
 // Workgroups of a sweep: as many as are resident at once (compute units x
 // workgroups per compute unit that the kernel's register use allows), so that
 // every row slot is dealt out once and the partial sums stay few.
@@ -703,6 +661,22 @@ static int resident_blocks()
     return cus * per_cu;
 }
 
+// The kernel's loads are unrolled over exactly the hash rounds there are (up to four): a round that does not
+// exist would still cost two wavefront-wide loads per row (unrolled over four whatever their number, a sweep took
+// 23.6 us instead of 19.6 with one round of 51 entries per row, 14.6 instead of 13.1 with two of 46, 16.7
+// instead of 15.9 with three of 15, 109 instead of 105 at 200 000 rows with three).
+template <int T>
+static int resident_blocks_of_rounds(int R)
+{
+    switch (R) {
+        case 1: return resident_blocks<T, 1>();
+        case 2: return resident_blocks<T, 2>();
+        case 3: return resident_blocks<T, 3>();
+        case 4: return resident_blocks<T, 4>();
+        default: return resident_blocks<T, 8>();
+    }
+}
+
 int pass_grid(const Handle &h)
 {
     long long rows = h.n > h.m ? h.n : h.m;
@@ -711,63 +685,61 @@ int pass_grid(const Handle &h)
     if (cap <= 0) {
         if (h.log_domain) {
             cap = 512;
+        } else if (h.R == 0) {
+            cap = device_compute_units();
         } else {
-            const bool r8 = h.R > 4;
             switch (h.lp / 64) {
-                case 0: cap = r8 ? resident_blocks<0, 8>() : resident_blocks<0, 4>(); break;
-                case 1: cap = r8 ? resident_blocks<1, 8>() : resident_blocks<1, 4>(); break;
-                case 2: cap = r8 ? resident_blocks<2, 8>() : resident_blocks<2, 4>(); break;
-                case 3: cap = r8 ? resident_blocks<3, 8>() : resident_blocks<3, 4>(); break;
-                case 4: cap = r8 ? resident_blocks<4, 8>() : resident_blocks<4, 4>(); break;
-                case 5: cap = r8 ? resident_blocks<5, 8>() : resident_blocks<5, 4>(); break;
-                case 6: cap = r8 ? resident_blocks<6, 8>() : resident_blocks<6, 4>(); break;
-                case 7: cap = r8 ? resident_blocks<7, 8>() : resident_blocks<7, 4>(); break;
-                default: cap = r8 ? resident_blocks<8, 8>() : resident_blocks<8, 4>(); break;
+                case 1: cap = resident_blocks_of_rounds<1>(h.R); break;
+                case 2: cap = resident_blocks_of_rounds<2>(h.R); break;
+                case 3: cap = resident_blocks_of_rounds<3>(h.R); break;
+                case 4: cap = resident_blocks_of_rounds<4>(h.R); break;
+                case 5: cap = resident_blocks_of_rounds<5>(h.R); break;
+                case 6: cap = resident_blocks_of_rounds<6>(h.R); break;
+                case 7: cap = resident_blocks_of_rounds<7>(h.R); break;
+                default: cap = resident_blocks_of_rounds<8>(h.R); break;
             }
         }
     }
     return (int)(g < cap ? g : cap);
 }
 
-template <int T, int RR>
-static hipError_t launch_pass_tr(const PassSide &S, const Handle &h, int side, int mode, const FuseArgs *fuse,
-                                 bool fused_in, bool reduce_after, double *partial, unsigned long long *cnt,
-                                 hipStream_t s)
+// workgroups of a sweep over `rows` rows (= partial sums it leaves)
+static int sweep_groups(const Handle &h, long long rows)
 {
-    long long g = (S.rows + PASS_WAVES - 1) / PASS_WAVES;
-    int grid = (int)(g < h.grid ? g : h.grid);
-    const int stride = h.lp + 3;
-    double *qout = h.query_out + 2 * side;
-    int empty_slot = 1 + side;
-    FuseArgs none{};
-    if (mode == PASS_INIT)
-        hipLaunchKernelGGL(max_log_kernel, dim3(1), dim3(1024), 0, s, S.log_out, S.rows, S.shift_self);
+    if (!h.log_domain && h.R == 0) return nystrom_sweep_groups(h, rows);
+    const long long g = (rows + PASS_WAVES - 1) / PASS_WAVES;
+    return (int)(g < h.grid ? g : h.grid);
+}
+
+template <int T, int RR>
+static hipError_t launch_pass_tr(const PassSide &S, const Handle &h, int mode, const FuseArgs *fuse, bool fused_in,
+                                 double *partial, unsigned long long *cnt, hipStream_t s)
+{
+    const FuseArgs F = fuse ? *fuse : FuseArgs{};
+    const dim3 grid(sweep_groups(h, S.rows)), block(PASS_THREADS);
+    const size_t lds = pass_lds_bytes(h.lp, fused_in);
     if (mode == PASS_UPDATE && fused_in)
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_UPDATE, true>), dim3(grid), dim3(PASS_THREADS),
-                           pass_lds_bytes(h.lp, true), s, S, h.R, h.lp, partial, cnt, empty_slot, *fuse);
+        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_UPDATE, true>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else if (mode == PASS_UPDATE)
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_UPDATE, false>), dim3(grid), dim3(PASS_THREADS),
-                           pass_lds_bytes(h.lp, false), s, S, h.R, h.lp, partial, cnt, empty_slot,
-                           fuse ? *fuse : none);
+        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_UPDATE, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else if (mode == PASS_QUERY)
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_QUERY, false>), dim3(grid), dim3(PASS_THREADS),
-                           pass_lds_bytes(h.lp, false), s, S, h.R, h.lp, partial, cnt, empty_slot, none);
+        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_QUERY, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_INIT, false>), dim3(grid), dim3(PASS_THREADS),
-                           pass_lds_bytes(h.lp, false), s, S, h.R, h.lp, partial, cnt, empty_slot, none);
-    if (reduce_after)
-        hipLaunchKernelGGL(reduce_partials_kernel, dim3((stride + 63) / 64), dim3(1024), 0, s, partial, grid, stride,
-                           h.lp, S.acc_out, qout, S.shift_self, mode);
+        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_INIT, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     return hipGetLastError();
 }
 
 template <int T>
-static hipError_t launch_pass_t(const PassSide &S, const Handle &h, int side, int mode, const FuseArgs *fuse,
-                                bool fused_in, bool reduce_after, double *partial, unsigned long long *cnt,
-                                hipStream_t s)
+static hipError_t launch_pass_t(const PassSide &S, const Handle &h, int mode, const FuseArgs *fuse, bool fused_in,
+                                double *partial, unsigned long long *cnt, hipStream_t s)
 {
-    if (h.R <= 4) return launch_pass_tr<T, 4>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-    return launch_pass_tr<T, 8>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
+    switch (h.R) {
+        case 1: return launch_pass_tr<T, 1>(S, h, mode, fuse, fused_in, partial, cnt, s);
+        case 2: return launch_pass_tr<T, 2>(S, h, mode, fuse, fused_in, partial, cnt, s);
+        case 3: return launch_pass_tr<T, 3>(S, h, mode, fuse, fused_in, partial, cnt, s);
+        case 4: return launch_pass_tr<T, 4>(S, h, mode, fuse, fused_in, partial, cnt, s);
+        default: return launch_pass_tr<T, 8>(S, h, mode, fuse, fused_in, partial, cnt, s);
+    }
 }
 
 // side 0: rows of X (updates u, consumes y = W v, produces z = U^T u); side 1: rows of Y.
@@ -853,30 +825,34 @@ static hipError_t launch_logpass(const PassSide &S, const Handle &h, int side, i
     return hipGetLastError();
 }
 
-// workgroups of a sweep over `rows` rows (= partial sums it leaves)
-static int sweep_groups(const Handle &h, long long rows)
-{
-    const long long g = (rows + PASS_WAVES - 1) / PASS_WAVES;
-    return (int)(g < h.grid ? g : h.grid);
-}
-
 static hipError_t dispatch_pass(const PassSide &S, const Handle &h, int side, int mode, const FuseArgs *fuse,
                                 bool fused_in, bool reduce_after, double *partial, hipStream_t s,
                                 unsigned long long *cnt = nullptr)
 {
     if (!cnt) cnt = h.counters;
-    switch (h.lp / 64) {
-        case 0: return launch_pass_t<0>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 1: return launch_pass_t<1>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 2: return launch_pass_t<2>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 3: return launch_pass_t<3>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 4: return launch_pass_t<4>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 5: return launch_pass_t<5>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 6: return launch_pass_t<6>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 7: return launch_pass_t<7>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        case 8: return launch_pass_t<8>(S, h, side, mode, fuse, fused_in, reduce_after, partial, cnt, s);
-        default: return hipErrorInvalidValue;
+    if (mode == PASS_INIT)
+        hipLaunchKernelGGL(max_log_kernel, dim3(1), dim3(1024), 0, s, S.log_out, S.rows, S.shift_self);
+    hipError_t e = hipErrorInvalidValue;
+    if (h.R == 0) {
+        e = launch_nystrom_pass(S, h, mode, fuse, fused_in, partial, cnt, s);
+    } else {
+        switch (h.lp / 64) {
+            case 1: e = launch_pass_t<1>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            case 2: e = launch_pass_t<2>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            case 3: e = launch_pass_t<3>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            case 4: e = launch_pass_t<4>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            case 5: e = launch_pass_t<5>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            case 6: e = launch_pass_t<6>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            case 7: e = launch_pass_t<7>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            case 8: e = launch_pass_t<8>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
+            default: break;
+        }
     }
+    if (e != hipSuccess || !reduce_after) return e;
+    const int stride = h.lp + 3;
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((stride + 63) / 64), dim3(1024), 0, s, partial,
+                       sweep_groups(h, S.rows), stride, h.lp, S.acc_out, h.query_out + 2 * side, S.shift_self, mode);
+    return hipGetLastError();
 }
 
 hipError_t launch_pass(const Handle &h, int side, int mode, int acc_in, int acc_out, float *marg_out, hipStream_t s)

@@ -746,9 +746,9 @@ struct Builder {
         h.undecided_last = (long long)undecided2[0] + undecided2[1];
         h.ntiles = (int)totals[1];
 
-        // 64 entries of slack: a sweep reads whole wavefront-wide chunks and masks the excess
-        h.vals_x = bump.take<float>((size_t)h.nnz_stored + 64);
-        h.vals_y = bump.take<float>((size_t)h.nnz_stored + 64);
+        // slack: a sweep reads whole wavefront-wide chunks, up to two per segment, and masks the excess
+        h.vals_x = bump.take<float>((size_t)h.nnz_stored + 128);
+        h.vals_y = bump.take<float>((size_t)h.nnz_stored + 128);
         h.ws_used = bump.used;
         if (bytes_needed) *bytes_needed = bump.used + 256;
         if (bump.used > h.ws_bytes) return LCN_ERR_ALLOC;
@@ -830,8 +830,8 @@ lcn_status lcn_workspace_bytes(int64_t n, int64_t m, int32_t d, int32_t mode, co
         else
             nnz = 0;
     }
-    bump.take<float>((size_t)nnz + 64);
-    bump.take<float>((size_t)nnz + 64);
+    bump.take<float>((size_t)nnz + 128);
+    bump.take<float>((size_t)nnz + 128);
     *bytes = bump.used + 256;
     return LCN_OK;
 }

@@ -653,3 +653,28 @@ def test_bucket_shapes(case):
         p = workloads.config3(n=2500, d=40, landmarks=64, buckets=3, rounds=2, iters=20, name="C3 reduced")
     out = compare(p, "lcn")
     print("bucket shapes", case, out, flush=True)
+
+
+@pytest.mark.parametrize("n,m,landmarks", [(3, 70, 3), (511, 513, 64), (4099, 64, 65), (1000, 5001, 200), (700, 650, 300),
+                                           (600, 900, 512)])
+def test_nystrom_sweeps_by_groups_of_rows(n, m, landmarks):
+    """The sweep without a sparse part takes four or eight rows per wavefront: sizes on both sides of whole
+    groups, factor rows of one to eight times 64 entries (loads of 4, 8 and 16 bytes per lane), sides too
+    small for the hand-over of the totals."""
+    from parity import compare
+    p = workloads.config3(n=max(n, m), d=24, landmarks=min(landmarks, n + m), buckets=8, rounds=1, iters=12, name="C3 cut")
+    p.X, p.Y = p.X[:n], p.Y[:m]
+    p.a = np.full(n, 1.0 / n, dtype=np.float32)
+    p.b = np.full(m, 1.0 / m, dtype=np.float32)
+    p.cost, p.lam = workloads.COST_SQEUCLID, 1.0   # smooth enough for every sum to stay positive
+    p.ridge = 1e-6
+    print("nystrom groups", n, m, landmarks, compare(p, "nystrom"), flush=True)
+
+
+@pytest.mark.parametrize("rounds,buckets", [(1, 1), (1, 3), (2, 5), (3, 4), (4, 6), (5, 7)])
+def test_sweeps_unrolled_over_the_rounds(rounds, buckets):
+    """The sweep's loads are unrolled over the rounds there are; segments below 64, between 64 and 128, and
+    far beyond (one bucket: 700 entries)."""
+    from parity import compare
+    p = workloads.config3(n=700, d=20, landmarks=70, buckets=buckets, rounds=rounds, iters=10, name="C3 cut")
+    print("rounds", rounds, buckets, compare(p, "lcn"), flush=True)
