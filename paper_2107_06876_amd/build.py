@@ -18,6 +18,7 @@ SOURCES = {
     "kernels_mfma.hip": [],
     "kernels_iter.hip": [],
     "kernels_nystrom.hip": [],
+    "kernels_dense.hip": [],
     "kernels_batched.hip": ["-ffp-contract=off"],  # bucket rule again
     "lcn_api.hip": [],
     "calibrate.hip": [],

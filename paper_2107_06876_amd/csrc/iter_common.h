@@ -80,6 +80,21 @@ __device__ inline double fast_log(double x)
     return (double)__logf((float)mant) + (double)e * 0.69314718055994530942;
 }
 
+// One term of a log-sum-exp with a running maximum.
+__device__ inline void lse_step(double t, double &mx, double &sm)
+{
+    if (t > -INFINITY) {
+        const double d = t - mx;
+        const double e = (double)__expf(-fabsf((float)d));
+        if (d > 0.0) {
+            sm = fma(sm, e, 1.0);
+            mx = t;
+        } else {
+            sm += e;
+        }
+    }
+}
+
 __device__ inline double fast_rcp(double x)
 {
     double r = __builtin_amdgcn_rcp(x);

@@ -1,0 +1,312 @@
+// One whole iteration of dense Sinkhorn from one read of the kernel matrix.
+//
+// A half-iteration by itself is bound by reading the n x m matrix (rows of K for u, rows of its transpose for v).
+// With the new u_i at hand while row i is still in registers, the row's share of the sums over columns
+// costs one multiply-add per entry: with shift_i = log a_i - log u_i (previous u), E_ij = exp(k_ij +
+// log v_j - shift_i) and t_i = sum_j E_ij,
+//     log u_i = log a_i - shift_i - log t_i,
+//     sum_i exp(k_ij + log u_i) v_j = sum_i E_ij a_i / t_i =: s_j,     log v_j = log b_j + log v_j - log s_j,
+// so there is no second exponential either.  What bounds it is the one read of the matrix.
+//
+// A workgroup (one per compute unit, 1024 threads) takes RG rows at a time, each thread C columns of them, the next
+// RG rows' loads in flight meanwhile; log v_j and the column sums stay in registers for the whole launch.
+// RG * C is about 24: two sets of values and two per column fill the 128 registers a thread has (30 spills).  The
+// prefetch is unconditional (past the end the last row again): behind a condition the compiler waits for all loads.
+// The column sums of the workgroups (single precision over the few dozen rows one of them has) are added in double
+// precision by dense_columns_kernel, which finishes v.
+// 10 000 x 10 000 (400 MB), 100 iterations: 160 us per iteration with two reads, 80 us so (5.0 TB/s).
+#include "iter_common.h"
+
+namespace lcn {
+
+constexpr int DI_THREADS = 1024;
+constexpr int DI_WAVES = DI_THREADS / 64;
+// A row's sum above the first bounds what its smallest terms lose in single precision (terms below 1e-38) after the
+// division by the sum.  A row outside the range gets its log-sum-exp with running maxima and stays out of the
+// workgroup's column sums, and dense_columns_kernel takes every column from the transpose.  That is the first
+// iteration from new scalings at most, or one in which a scaling moves by four orders of magnitude.
+constexpr double DI_ROW_MIN = 1e-4, DI_MAX = 1e30;
+constexpr double DI_COLUMN_MIN = 1e-20;   // the same for a column's sum, which is of order one here
+
+// Workgroup barrier that waits for LDS only: the loads of the next rows stay in flight.
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Log-sum-exp of k[e] + p[e] over `len` entries by one wavefront's share (from `first`, every `step`), with a
+// running maximum per lane; merged over the wavefront.
+__device__ inline void wave_lse(const float *__restrict__ k, const double *__restrict__ p, int first, int step, int len,
+                                double &M, double &sum)
+{
+    double mx = -INFINITY, sm = 0.0;
+#pragma unroll 1
+    for (int e = first; e < len; e += step) lse_step((double)k[e] + p[e], mx, sm);
+    M = wave_max(mx);
+    sum = wave_sum(mx > -INFINITY ? sm * exp(mx - M) : 0.0);
+}
+
+// Rows of C pieces of 1024 columns, the last piece not empty.
+template <int C, int RG>
+__global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, float *__restrict__ column_part,
+                                                                unsigned long long *counters)
+{
+    __shared__ double sums[2][RG][DI_WAVES];
+    __shared__ double wide[DI_WAVES][2];
+    const unsigned tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = (int)S.rows, cols = (int)S.rows_in;
+    const int step = gridDim.x * RG;
+    const unsigned last_piece = cols - DI_THREADS * (C - 1);   // 1 .. 1024 columns
+    const bool in_last = tid < last_piece;
+    // a lane past the end reads the last column and weighs it with zero
+    const unsigned tid_last = in_last ? tid : last_piece - 1;
+    unsigned long long empty = 0;
+    bool missing = false, any_bad = false;
+
+    auto load_values = [&](int r0, float (&k)[RG][C]) {
+#pragma unroll
+        for (int i = 0; i < RG; ++i) {   // rows past the end repeat the last row and count for nothing
+            const float *__restrict__ kr = S.vals + (long long)(r0 + i < rows ? r0 + i : rows - 1) * cols;
+#pragma unroll
+            for (int c = 0; c < C; ++c) k[i][c] = (kr + DI_THREADS * c)[c == C - 1 ? tid_last : tid];
+        }
+    };
+    // lane i < RG of every wavefront: what row i of the group needs
+    auto load_record = [&](int r0, double &log_marg, double &log_u, float &marg) {
+        int row = r0 + (lane < RG ? lane : RG - 1);
+        row = row < rows ? row : rows - 1;
+        const int *rec = S.meta + (long long)row * S.meta_stride;
+        marg = __int_as_float(rec[2]);
+        log_marg = __hiloint2double(rec[5], rec[4]);
+        log_u = S.lin_out[row];
+    };
+    float ka[RG][C], kb[RG][C], pf[C], acc[C];
+    const int first = blockIdx.x * RG;
+    double base;
+    {
+        double log_marg, log_u;
+        float marg;
+        load_record(first, log_marg, log_u, marg);
+        base = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(log_marg - log_u), 0),
+                                __builtin_amdgcn_readlane(__double2loint(log_marg - log_u), 0));
+    }
+    load_values(first, ka);
+    // one fp64 reference for the workgroup's shifts and for log v, their differences in single precision
+    if (!(base > -INFINITY && base < INFINITY)) base = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const double p = (S.perm_in + DI_THREADS * c)[c == C - 1 ? tid_last : tid];
+        pf[c] = c == C - 1 && !in_last ? -INFINITY : (float)(p - base);
+        acc[c] = 0.f;
+    }
+
+    auto group = [&](int r0, int buf, float (&k)[RG][C], float (&kn)[RG][C]) {
+        double log_marg, log_u;
+        float marg;
+        load_record(r0, log_marg, log_u, marg);
+        load_values(r0 + step, kn);
+        const double shift = log_marg - log_u;
+        // a shift that cannot be used: terms of zero
+        const float off_l = shift > -INFINITY && shift < INFINITY ? (float)(shift - base) : INFINITY;
+#pragma unroll
+        for (int i = 0; i < RG; ++i) {
+            const float off = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(off_l), i));
+            float s = 0.f;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                k[i][c] = __expf(k[i][c] + (pf[c] - off));
+                s += k[i][c];
+            }
+            const double tot = wave_sum((double)s);
+            if (lane == 0) sums[buf][i][wave] = tot;
+        }
+        lds_barrier();   // the buffer is written again two groups on, behind the next group's barrier
+        double tot = 0.0;   // lane i < RG: row i's sum
+#pragma unroll
+        for (int w = 0; w < DI_WAVES; ++w) tot += sums[buf][lane < RG ? lane : RG - 1][w];
+        const bool good = tot > DI_ROW_MIN && tot < DI_MAX && shift > -INFINITY && shift < INFINITY;
+        any_bad = any_bad || __ballot(!good && lane < RG) != 0;   // the same in every wavefront
+        // the column sums are taken times the number of columns: of order one
+        const float f_l = r0 + lane < rows && good ? (float)((double)marg * (double)cols * fast_rcp(tot)) : 0.f;
+#pragma unroll
+        for (int i = 0; i < RG; ++i) {
+            const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f_l), i));
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] = fmaf(k[i][c], f, acc[c]);
+        }
+        if (wave == 0 && lane < RG && r0 + lane < rows) {
+            const int row = r0 + lane;
+            const double lg = log_marg - (shift + fast_log(tot));
+            S.log_out[row] = good ? (float)lg : __builtin_nanf("");   // marked for the second look below
+            if (good) {
+                S.lin_out[row] = lg;
+                S.perm_out[row] = lg;   // one bucket: its order is the points' own
+            }
+        }
+    };
+    for (int r0 = first; r0 < rows; r0 += 2 * step) {
+        group(r0, 0, ka, kb);
+        group(r0 + step, 1, kb, ka);   // possibly past the end: the last row, without effect
+    }
+    float *part = column_part + (long long)blockIdx.x * cols;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if (c < C - 1 || in_last) (part + DI_THREADS * c)[tid] = acc[c];
+    if (any_bad) {   // the marked rows' log-sum-exp with running maxima
+        __syncthreads();
+        for (int r0 = first; r0 < rows; r0 += step)
+            for (int row = r0; row < r0 + RG && row < rows; ++row) {
+                if (S.log_out[row] == S.log_out[row]) continue;   // the same in every thread
+                double M, sm;
+                wave_lse(S.vals + (long long)row * cols, S.perm_in, (int)tid, DI_THREADS, cols, M, sm);
+                if (lane == 0) {
+                    wide[wave][0] = M;
+                    wide[wave][1] = sm;
+                }
+                __syncthreads();   // and every thread has seen the mark
+                if (tid == 0) {
+                    M = -INFINITY;
+                    for (int w = 0; w < DI_WAVES; ++w) M = fmax(M, wide[w][0]);
+                    sm = 0.0;
+                    for (int w = 0; w < DI_WAVES; ++w)
+                        if (wide[w][0] > -INFINITY) sm += wide[w][1] * exp(wide[w][0] - M);
+                    const int *rec = S.meta + (long long)row * S.meta_stride;
+                    double lg;
+                    if (sm > 0.0) {
+                        lg = __hiloint2double(rec[5], rec[4]) - (M + log(sm));
+                        // the row is missing from the column sums: without mass it would add nothing
+                        if (__int_as_float(rec[2]) != 0.f) missing = true;
+                    } else {  // no kernel entry reaches this point: it carries no mass
+                        lg = -INFINITY;
+                        ++empty;
+                    }
+                    S.log_out[row] = (float)lg;
+                    S.lin_out[row] = lg;
+                    S.perm_out[row] = lg;
+                }
+                __syncthreads();
+            }
+    }
+    if (tid == 0) {
+        if (empty) atomicAdd(&counters[1], empty);
+        column_part[(long long)gridDim.x * cols + blockIdx.x] = missing ? 1.f : 0.f;
+    }
+}
+
+// v from the workgroups' column sums, 64 columns per workgroup; a column whose sum left the range (a first
+// iteration, a scaling that was infinite) takes its log-sum-exp from its row of the transpose.
+__global__ __launch_bounds__(DI_THREADS) void dense_columns_kernel(PassSide S, const float *__restrict__ column_part,
+                                                                   int groups, unsigned long long *counters)
+{
+    __shared__ double sums[DI_WAVES][64];
+    __shared__ double wide[64];
+    __shared__ unsigned long long bad_sh;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long j0 = (long long)blockIdx.x * 64;
+    const long long j = j0 + lane < S.rows ? j0 + lane : S.rows - 1;
+    // a workgroup left a row out of its sums: every column is taken from the transpose
+    bool missing = false;
+    for (int g = lane; g < groups; g += 64) missing = missing || column_part[(long long)groups * S.rows + g] != 0.f;
+    missing = __ballot(missing) != 0;
+    double s = 0.0;
+#pragma unroll 8
+    for (int g = wave; g < groups; g += DI_WAVES) s += (double)column_part[(long long)g * S.rows + j];
+    sums[wave][lane] = s;
+    __syncthreads();
+    double lse = 0.0, log_marg = 0.0;
+    if (wave == 0) {
+        s = 0.0;
+#pragma unroll
+        for (int w = 0; w < DI_WAVES; ++w) s += sums[w][lane];
+        const int *rec = S.meta + j * S.meta_stride;
+        log_marg = __hiloint2double(rec[5], rec[4]);
+        const double prev = S.lin_out[j];
+        const bool good = !missing && s > DI_COLUMN_MIN && s < DI_MAX && prev > -INFINITY && prev < INFINITY;
+        lse = fast_log(s) - log((double)S.rows) - prev;
+        const unsigned long long bad = __ballot(!good && j0 + lane < S.rows);
+        if (lane == 0) bad_sh = bad;
+    }
+    __syncthreads();
+    const unsigned long long bad = bad_sh;
+    if (bad) {   // the same in every thread
+        for (int i = wave; i < 64; i += DI_WAVES) {
+            if (!(bad >> i & 1)) continue;
+            double M, sm;
+            wave_lse(S.vals + (j0 + i) * S.rows_in, S.perm_in, lane, 64, (int)S.rows_in, M, sm);
+            if (lane == 0) wide[i] = sm > 0.0 ? M + log(sm) : -INFINITY;
+        }
+        __syncthreads();
+        if (wave == 0 && (bad >> lane & 1)) lse = wide[lane];
+    }
+    if (wave == 0) {
+        unsigned long long empty = 0;
+        if (j0 + lane < S.rows) {
+            double lg;
+            if (lse > -INFINITY) {
+                lg = log_marg - lse;
+            } else {  // no kernel entry reaches this point: it carries no mass
+                lg = -INFINITY;
+                ++empty;
+            }
+            S.log_out[j] = (float)lg;
+            S.lin_out[j] = lg;
+            S.perm_out[j] = lg;
+        }
+        empty = (unsigned long long)wave_sum((double)empty);
+        if (lane == 0 && empty) atomicAdd(&counters[2], empty);
+    }
+}
+
+static constexpr int dense_rows_of(int c) { return c <= 3 ? 8 : c >= 12 ? 1 : 24 / c; }
+
+// Where the matrix is small the two launches and the trip through the column sums cost more than the second read
+// of it (us per iteration, half-iterations by themselves against this: 1000 x 1000 12.7 / 14.1, 1500 x 1500
+// 13.9 / 15.4, 3000 x 1000 15.9 / 14.2, 2000 x 2000 16.4 / 16.2, 4000 x 4000 30 / 26, 8000 x 8200 114 / 50,
+// 10 000 x 10 000 161 / 80, 12 000 x 14 000 250 / 130); beyond 18 pieces a thread's registers are full.
+int dense_iteration_groups(long long n, long long m, int cus)
+{
+    const bool worth = m <= DENSE_ITERATION_MAX_COLUMNS && n * m >= DENSE_ITERATION_MIN_PAIRS;
+    return worth ? cus : 0;
+}
+
+hipError_t launch_dense_iteration(const PassSide &X, const PassSide &Y, const Handle &h, hipStream_t s)
+{
+    const int c = (int)((h.m + DI_THREADS - 1) / DI_THREADS);
+    const dim3 grid(h.column_groups), block(DI_THREADS);
+#define LCN_DENSE_ROWS(C)                                                                                             \
+    case C:                                                                                                          \
+        hipLaunchKernelGGL((dense_rows_kernel<C, dense_rows_of(C)>), grid, block, 0, s, X, h.column_part, h.counters); \
+        break
+    switch (c) {
+        LCN_DENSE_ROWS(1);
+        LCN_DENSE_ROWS(2);
+        LCN_DENSE_ROWS(3);
+        LCN_DENSE_ROWS(4);
+        LCN_DENSE_ROWS(5);
+        LCN_DENSE_ROWS(6);
+        LCN_DENSE_ROWS(7);
+        LCN_DENSE_ROWS(8);
+        LCN_DENSE_ROWS(9);
+        LCN_DENSE_ROWS(10);
+        LCN_DENSE_ROWS(11);
+        LCN_DENSE_ROWS(12);
+        LCN_DENSE_ROWS(13);
+        LCN_DENSE_ROWS(14);
+        LCN_DENSE_ROWS(15);
+        LCN_DENSE_ROWS(16);
+        LCN_DENSE_ROWS(17);
+        LCN_DENSE_ROWS(18);
+        default: return hipErrorInvalidValue;
+    }
+#undef LCN_DENSE_ROWS
+    hipLaunchKernelGGL(dense_columns_kernel, dim3((unsigned)((h.m + 63) / 64)), block, 0, s, Y, h.column_part,
+                       h.column_groups, h.counters);
+    return hipGetLastError();
+}
+
+}  // namespace lcn

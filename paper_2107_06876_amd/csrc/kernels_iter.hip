@@ -250,20 +250,6 @@ __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, i
 // is a log-sum-exp (App. "Implementational details") with a running maximum per
 // lane, so that scalings may drift arbitrarily far (a sparse kernel need not
 // have support, App. "Limitations") without over- or underflow.
-__device__ inline void lse_step(double t, double &mx, double &sm)
-{
-    if (t > -INFINITY) {
-        const double d = t - mx;
-        const double e = (double)__expf(-fabsf((float)d));
-        if (d > 0.0) {
-            sm = fma(sm, e, 1.0);
-            mx = t;
-        } else {
-            sm += e;
-        }
-    }
-}
-
 template <int RR, int MODE>
 __global__ __launch_bounds__(PASS_THREADS) void logpass_kernel(PassSide S, int R, double *partial,
                                                                unsigned long long *counters, int empty_slot)
@@ -893,12 +879,18 @@ hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s)
         first = 1;   // the loop below starts with the sweep over Y, now with its exponent known
     }
     h.last_launches = 2 * iters + (first ? 2 : 0);   // half-iteration launches of this run, the repeated ones included
+    const bool fresh = h.fresh != 0;
     if (iters > 0) h.fresh = 0;
     for (int t = first; t < 2 * iters; ++t) {
         const int side = t & 1;
         const PassSide S = make_side(h, side, side == 0 ? 0 : 1, side == 0 ? 1 : 0, nullptr);
         hipError_t e;
-        if (h.log_domain) {
+        if (h.column_part && side == 0 && !(fresh && t == 0)) {
+            // dense: both halves of the iteration from one read of the kernel matrix.  Not for scalings that have
+            // not been iterated: their shifts are far off and every row and column would be walked again.
+            e = launch_dense_iteration(S, make_side(h, 1, 1, 0, nullptr), h, s);
+            ++t;
+        } else if (h.log_domain) {
             e = launch_logpass(S, h, side, PASS_UPDATE, s);
         } else if (!fused) {
             e = dispatch_pass(S, h, side, PASS_UPDATE, nullptr, false, true, h.partial, s);

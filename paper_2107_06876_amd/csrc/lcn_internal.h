@@ -153,6 +153,11 @@ hipError_t launch_csr_values(const Handle &h, const float *rec, const float *rec
 // ---- iteration (kernels_iter.hip) ------------------------------------------
 hipError_t launch_pass(const Handle &h, int side, int mode, int acc_in, int acc_out, float *marg_out, hipStream_t s);
 hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s);
+// A whole dense iteration from one read of the kernel matrix (kernels_dense.hip): workgroups whose column sums
+// it leaves, 0 where the two half-iterations by themselves are to be used.
+constexpr long long DENSE_ITERATION_MIN_PAIRS = 3000000, DENSE_ITERATION_MAX_COLUMNS = 18 * 1024;
+int dense_iteration_groups(long long n, long long m, int cus);
+hipError_t launch_dense_iteration(const PassSide &X, const PassSide &Y, const Handle &h, hipStream_t s);
 int device_compute_units();
 int pass_grid(const Handle &h);
 
@@ -202,6 +207,8 @@ struct Handle {
     double *shift;             // [2]: exponent taken out of u and of v
     double *partial;           // [grid][lp + 3] per-workgroup partial sums of a sweep
     double *partial2;          // second buffer: consecutive sweeps alternate when the reduction is fused
+    float *column_part;        // [column_groups][m] column sums of a dense iteration (null: not used)
+    int column_groups;
     int fused_reduce;          // sweeps add up their predecessor's partial sums themselves
     int fresh;                 // the scalings have not been iterated since they were set: their exponents are stale
     unsigned long long wait_ticks;  // bound of a sweep's wait for its totals, in ticks of the 100 MHz clock (default 0.2 s)

@@ -678,3 +678,24 @@ def test_sweeps_unrolled_over_the_rounds(rounds, buckets):
     from parity import compare
     p = workloads.config3(n=700, d=20, landmarks=70, buckets=buckets, rounds=rounds, iters=10, name="C3 cut")
     print("rounds", rounds, buckets, compare(p, "lcn"), flush=True)
+
+
+@pytest.mark.parametrize("n,m,lam,zeros", [(3100, 1024, 0.3, False), (2999, 1025, 0.02, False), (3001, 1001, 0.3, True),
+                                           (1500, 2049, 0.01, True), (260, 12289, 0.3, False), (165, 18432, 0.05, False),
+                                           (165, 18433, 0.3, False)])
+def test_dense_iterations_from_one_read(n, m, lam, zeros):
+    """Both halves of a dense iteration from one read of the kernel matrix: rows of whole and barely begun pieces
+    of 1024 columns up to the 18 there may be (and one column more: the half-iterations by themselves), fewer
+    rows than workgroups, lambda small enough for scalings to jump out of the range of the sums taken with the
+    previous ones, points without mass."""
+    from parity import compare
+    p = workloads.config3(n=max(n, m), d=8, landmarks=8, buckets=8, rounds=1, iters=5, name="C3 cut")
+    p.X, p.Y = p.X[:n], p.Y[:m]
+    p.a = np.full(n, 1.0 / n, dtype=np.float32)
+    p.b = np.full(m, 1.0 / m, dtype=np.float32)
+    if zeros:
+        p.a[::7], p.b[::5] = 0.0, 0.0
+        p.a /= p.a.sum()
+        p.b /= p.b.sum()
+    p.cost, p.lam = workloads.COST_SQEUCLID, lam
+    print("dense iterations", n, m, lam, compare(p, "dense"), flush=True)
