@@ -14,7 +14,7 @@
 // prefetch is unconditional (past the end the last row again): behind a condition the compiler waits for all loads.
 // The column sums of the workgroups (single precision over the few dozen rows one of them has) are added in double
 // precision by dense_columns_kernel, which finishes v.
-// 10 000 x 10 000 (400 MB), 100 iterations: 160 us per iteration with two reads, 80 us so (5.0 TB/s).
+// 10 000 x 10 000 (400 MB), 100 iterations: 160 us per iteration with two reads, 83 us so (4.8 TB/s).
 #include "iter_common.h"
 
 namespace lcn {
@@ -34,6 +34,25 @@ __device__ inline void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// log of a positive finite double to 2e-11: 2 atanh((m - 1) / (m + 1)) for the mantissa in [sqrt(1/2), sqrt(2)).
+__device__ inline double short_log(double x)
+{
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    if (m < 0.70710678118654752440) {
+        m += m;
+        --e;
+    }
+    const double z = (m - 1.0) * fast_rcp(m + 1.0), q = z * z;
+    double p = 2.0 / 11;
+    p = fma(p, q, 2.0 / 9);
+    p = fma(p, q, 2.0 / 7);
+    p = fma(p, q, 2.0 / 5);
+    p = fma(p, q, 2.0 / 3);
+    p = fma(p, q, 2.0);
+    return fma((double)e, 0.69314718055994530942, p * z);
 }
 
 // Log-sum-exp of k[e] + p[e] over `len` entries by one wavefront's share (from `first`, every `step`), with a
@@ -86,17 +105,24 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
     };
     float ka[RG][C], kb[RG][C], pf[C], acc[C];
     const int first = blockIdx.x * RG;
-    double base;
+    // One fp64 reference for the workgroup's shifts and for log v, their differences in single precision: a log v
+    // itself, as what a column's difference loses is not seen by the rows.  `typical`: the shift of a row with mass.
+    double base, typical;
+    auto first_finite = [&](double x) {   // 0 if no lane has one
+        const unsigned long long usable = __ballot(x > -INFINITY && x < INFINITY);
+        const int from = usable ? __ffsll(usable) - 1 : 0;
+        const double v = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), from),
+                                          __builtin_amdgcn_readlane(__double2loint(x), from));
+        return usable ? v : 0.0;
+    };
     {
         double log_marg, log_u;
         float marg;
         load_record(first, log_marg, log_u, marg);
-        base = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(log_marg - log_u), 0),
-                                __builtin_amdgcn_readlane(__double2loint(log_marg - log_u), 0));
+        typical = first_finite(log_marg - log_u);
+        base = first_finite(S.perm_in[lane < cols ? lane : cols - 1]);
     }
     load_values(first, ka);
-    // one fp64 reference for the workgroup's shifts and for log v, their differences in single precision
-    if (!(base > -INFINITY && base < INFINITY)) base = 0.0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const double p = (S.perm_in + DI_THREADS * c)[c == C - 1 ? tid_last : tid];
@@ -104,14 +130,20 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
         acc[c] = 0.f;
     }
 
+    // Near the fixed point the factors of all rows with equal marginals round alike; what one lost, relative to it,
+    // is handed to the lane's next row, or the common part would add up over the iterations (u up, v down: 8e-7
+    // after 50, eight times the rest of the error).  For the same reason the logarithms are double precision ones.
+    double carry = 0.0;
     auto group = [&](int r0, int buf, float (&k)[RG][C], float (&kn)[RG][C]) {
         double log_marg, log_u;
         float marg;
         load_record(r0, log_marg, log_u, marg);
         load_values(r0 + step, kn);
-        const double shift = log_marg - log_u;
+        // a row without mass only has to show that its sum is not empty: any shift does
+        const double wanted = marg == 0.f ? typical : log_marg - log_u;
         // a shift that cannot be used: terms of zero
-        const float off_l = shift > -INFINITY && shift < INFINITY ? (float)(shift - base) : INFINITY;
+        const float off_l = wanted > -INFINITY && wanted < INFINITY ? (float)(wanted - base) : INFINITY;
+        const double shift = base + (double)off_l;   // as the terms have it: its rounding is no error of the row
 #pragma unroll
         for (int i = 0; i < RG; ++i) {
             const float off = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(off_l), i));
@@ -128,10 +160,16 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
         double tot = 0.0;   // lane i < RG: row i's sum
 #pragma unroll
         for (int w = 0; w < DI_WAVES; ++w) tot += sums[buf][lane < RG ? lane : RG - 1][w];
-        const bool good = tot > DI_ROW_MIN && tot < DI_MAX && shift > -INFINITY && shift < INFINITY;
+        const bool good = (tot > DI_ROW_MIN || (marg == 0.f && tot > 0.0)) && tot < DI_MAX && shift > -INFINITY &&
+                          shift < INFINITY;
         any_bad = any_bad || __ballot(!good && lane < RG) != 0;   // the same in every wavefront
         // the column sums are taken times the number of columns: of order one
-        const float f_l = r0 + lane < rows && good ? (float)((double)marg * (double)cols * fast_rcp(tot)) : 0.f;
+        float f_l = 0.f;
+        if (r0 + lane < rows && good && marg != 0.f) {
+            const double f = (double)marg * (double)cols * fast_rcp(tot) * (1.0 + carry);
+            f_l = (float)f;
+            carry = (f - (double)f_l) * (double)__builtin_amdgcn_rcpf(f_l);
+        }
 #pragma unroll
         for (int i = 0; i < RG; ++i) {
             const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f_l), i));
@@ -140,7 +178,7 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
         }
         if (wave == 0 && lane < RG && r0 + lane < rows) {
             const int row = r0 + lane;
-            const double lg = log_marg - (shift + fast_log(tot));
+            const double lg = log_marg - (shift + short_log(tot));
             S.log_out[row] = good ? (float)lg : __builtin_nanf("");   // marked for the second look below
             if (good) {
                 S.lin_out[row] = lg;
@@ -155,7 +193,11 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
     float *part = column_part + (long long)blockIdx.x * cols;
 #pragma unroll
     for (int c = 0; c < C; ++c)
-        if (c < C - 1 || in_last) (part + DI_THREADS * c)[tid] = acc[c];
+        if (c < C - 1 || in_last) {
+            // what log v - base lost in single precision is a factor of the whole sum
+            const double lost = (S.perm_in + DI_THREADS * c)[tid] - base - (double)pf[c];
+            (part + DI_THREADS * c)[tid] = fabs(lost) < 1.0 ? (float)fma((double)acc[c], lost, (double)acc[c]) : acc[c];
+        }
     if (any_bad) {   // the marked rows' log-sum-exp with running maxima
         __syncthreads();
         for (int r0 = first; r0 < rows; r0 += step)
@@ -198,13 +240,15 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
 }
 
 // v from the workgroups' column sums, 64 columns per workgroup; a column whose sum left the range (a first
-// iteration, a scaling that was infinite) takes its log-sum-exp from its row of the transpose.
+// iteration, a scaling that was infinite) takes its log-sum-exp from its row of the transpose.  A column without
+// mass has no such sum either, but ends with a scaling of zero whatever it is: its row is read until one entry shows
+// that it is not empty, mostly the first 64.
 __global__ __launch_bounds__(DI_THREADS) void dense_columns_kernel(PassSide S, const float *__restrict__ column_part,
                                                                    int groups, unsigned long long *counters)
 {
     __shared__ double sums[DI_WAVES][64];
     __shared__ double wide[64];
-    __shared__ unsigned long long bad_sh;
+    __shared__ unsigned long long bad_sh, massless_sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long long j0 = (long long)blockIdx.x * 64;
@@ -227,15 +271,28 @@ __global__ __launch_bounds__(DI_THREADS) void dense_columns_kernel(PassSide S, c
         log_marg = __hiloint2double(rec[5], rec[4]);
         const double prev = S.lin_out[j];
         const bool good = !missing && s > DI_COLUMN_MIN && s < DI_MAX && prev > -INFINITY && prev < INFINITY;
-        lse = fast_log(s) - log((double)S.rows) - prev;
+        lse = log(s / (double)S.rows) - prev;
         const unsigned long long bad = __ballot(!good && j0 + lane < S.rows);
-        if (lane == 0) bad_sh = bad;
+        const unsigned long long massless = __ballot(log_marg == -INFINITY);
+        if (lane == 0) {
+            bad_sh = bad;
+            massless_sh = massless;
+        }
     }
     __syncthreads();
     const unsigned long long bad = bad_sh;
     if (bad) {   // the same in every thread
         for (int i = wave; i < 64; i += DI_WAVES) {
             if (!(bad >> i & 1)) continue;
+            if (massless_sh >> i & 1) {
+                bool some = false;
+                for (long long e0 = 0; e0 < S.rows_in && !some; e0 += 64) {
+                    const long long e = e0 + lane < S.rows_in ? e0 + lane : S.rows_in - 1;
+                    some = __ballot((double)S.vals[(j0 + i) * S.rows_in + e] + S.perm_in[e] > -INFINITY) != 0;
+                }
+                if (lane == 0) wide[i] = some ? 0.0 : -INFINITY;
+                continue;
+            }
             double M, sm;
             wave_lse(S.vals + (j0 + i) * S.rows_in, S.perm_in, lane, 64, (int)S.rows_in, M, sm);
             if (lane == 0) wide[i] = sm > 0.0 ? M + log(sm) : -INFINITY;
@@ -266,8 +323,8 @@ static constexpr int dense_rows_of(int c) { return c <= 3 ? 8 : c >= 12 ? 1 : 24
 
 // Where the matrix is small the two launches and the trip through the column sums cost more than the second read
 // of it (us per iteration, half-iterations by themselves against this: 1000 x 1000 12.7 / 14.1, 1500 x 1500
-// 13.9 / 15.4, 3000 x 1000 15.9 / 14.2, 2000 x 2000 16.4 / 16.2, 4000 x 4000 30 / 26, 8000 x 8200 114 / 50,
-// 10 000 x 10 000 161 / 80, 12 000 x 14 000 250 / 130); beyond 18 pieces a thread's registers are full.
+// 13.9 / 15.4, 3000 x 1000 15.9 / 14.2, 2000 x 2000 16.4 / 16.2, 4000 x 4000 30 / 26, 8000 x 8200 115 / 57,
+// 10 000 x 10 000 161 / 83, 12 000 x 14 000 250 / 130); beyond 18 pieces a thread's registers are full.
 int dense_iteration_groups(long long n, long long m, int cus)
 {
     const bool worth = m <= DENSE_ITERATION_MAX_COLUMNS && n * m >= DENSE_ITERATION_MIN_PAIRS;
