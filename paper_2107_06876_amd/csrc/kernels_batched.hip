@@ -269,7 +269,7 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     int *assign = (int *)(lds + L.assign), *cnts = (int *)(lds + L.cnts), *start = (int *)(lds + L.start);
     int *owner = start + 16 * B.mt;   // of every centroid row: 256 run + index in the run, -1 if none
     // [0], [1]: some assignment changed (by parity); [2]: not positive definite; [3]: a large coordinate;
-    // [4:5]: bits of the largest squared norm of a point
+    // [4:5]: bits of the largest squared norm of a point; [6]: a coordinate the rule alone decides on
     int *flags = (int *)(lds + L.flags);
 
     const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
@@ -297,15 +297,17 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     {
         constexpr int LANES = 16 * DT, STEP = NT / LANES;
         const int r0 = tid / LANES, j = tid % LANES;
-        bool large = false;
+        bool large = false, beyond = false;
 #pragma unroll 4
         for (int i = r0; i < 16 * PT; i += STEP) {
             const float *src = i < n ? B.X + (x0 + i) * d : B.Y + (y0 + i - n) * d;
             const float v = (i < N && j < d) ? src[j] : 0.f;
             Z[i * zs + j] = v;
             large = large || !(fabsf(v) < 8192.f);
+            beyond = beyond || !(fabsf(v) < 16777216.f);
         }
         if (large) flags[3] = 1;
+        if (beyond) flags[6] = 1;
     }
     // Start of a run: the first k slots of a Fisher-Yates shuffle of 0 .. N-1 driven by splitmix64.  Lane t
     // draws j_t; slot t receives what slot j_t holds, which is its own index unless an earlier step
@@ -371,31 +373,37 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     // points, so |c|^2 and |z|^2 are at most M = the largest squared norm (plus the centroid's rounding to
     // single precision); the score's d + 2 products and sums and the rule's 3 d operations are each off by
     // 2^-53 of at most 4 M.  16 (d + 8) 2^-53 M covers both sides of a comparison.
-    const double two_delta = 2.0 * 1.01 * 16.0 * (double)(d + 8) * 0x1p-53 * __longlong_as_double(*(const long long *)(flags + 4));
+    // With a coordinate that is not finite, or so large (2^24) that the 64-bit sum of 128 of them may wrap and leave
+    // the hull, there is no such bound: every centroid is a candidate and the rule decides by itself.
+    const double two_delta = flags[6] ? INFINITY
+                                      : 2.0 * 1.01 * 16.0 * (double)(d + 8) * 0x1p-53 *
+                                            __longlong_as_double(*(const long long *)(flags + 4));
     const bool large = flags[3] != 0;
     const int tiles = B.mt * DT, parts = tiles > 0 && NW > tiles ? NW / tiles : 1;
     const int iters = T_l > T_b ? T_l : T_b;   // 0 for what does not run
     // The bucket rule (fp64, dimensions in order, multiply and add separately, lowest index among equals) on
     // the candidates of the points that have several: `mine` has bit v set if centroid 4 v + quarter of run q
-    // is a candidate of point pt; returns it with the winner's bit alone, in the winner's lane.
+    // is a candidate of point pt (bits of rows that hold no centroid count for nothing); returns the winner's bit
+    // alone, in the winner's lane.
     auto exact_winner = [&](unsigned mine, int pt, int q, int k) -> unsigned {
         unsigned cand = 0;
         for (int v = 0; v < 4; ++v) cand |= (mine >> v & 1u) << (4 * v + quarter);
         cand = quarter_or(cand) & ((1u << k) - 1u);
-        if ((cand & (cand - 1)) == 0) return mine;
-        double best = INFINITY;
         int c = __builtin_ctz(cand);
-        for (unsigned left = cand; left; left &= left - 1) {
-            const int cc = __builtin_ctz(left);
-            double D = 0.0;
-            for (int j = 0; j < d; ++j) {
-                const double t = (double)Z[pt * zs + j] - (double)cent[(row_of(q) + cc) * zs + j];
-                const double t2 = t * t;
-                D = D + t2;
-            }
-            if (D < best) {
-                best = D;
-                c = cc;
+        if (cand & (cand - 1)) {
+            double best = 0.0;
+            for (unsigned left = cand; left; left &= left - 1) {
+                const int cc = __builtin_ctz(left);
+                double D = 0.0;
+                for (int j = 0; j < d; ++j) {
+                    const double t = (double)Z[pt * zs + j] - (double)cent[(row_of(q) + cc) * zs + j];
+                    const double t2 = t * t;
+                    D = D + t2;
+                }
+                if (left == cand || D < best) {   // a first distance that is not a number keeps the point
+                    best = D;
+                    c = cc;
+                }
             }
         }
         return (c & 3) == quarter ? 1u << (c >> 2) : 0u;
@@ -453,7 +461,8 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                     {
-                        const bool in = v >= va && v < vb && acc[v] <= most;
+                        // (not "at most": a score that is not a number is one the rule has to decide)
+                        const bool in = v >= va && v < vb && !(acc[v] > most);
                         const unsigned long long b = __ballot(in);
                         mine |= in ? 1u << v : 0u;
                         twice |= seen & b;

@@ -297,3 +297,73 @@ def test_batched_build_decides_like_the_rule(d, l, b, rounds, kind):
             _, asg = oracle.kmeans(Z, b, 9, 41 + p * rounds + r)
             np.testing.assert_array_equal(buckets[z0 + r * (n + m):z0 + (r + 1) * (n + m)], asg)
     lcn.lcn_destroy(h)
+
+
+def _build_only(B, mode, lm, lsh):
+    import paper_2107_06876_amd as lcn
+    modes = {"dense": lcn.MODE_DENSE, "sparse": lcn.MODE_SPARSE, "nystrom": lcn.MODE_NYSTROM, "lcn": lcn.MODE_LCN}
+    return lcn.lcn_build_batched(torch.from_numpy(B.X).cuda(), torch.from_numpy(B.Y).cuda(), B.x_off, B.y_off, B.lam,
+                                 B.cost, modes[mode], None, None, landmarks=lm if mode in ("lcn", "nystrom") else None,
+                                 lsh=lsh if mode in ("lcn", "sparse") else None)
+
+
+@pytest.mark.parametrize("mode", ["sparse", "lcn"])
+@pytest.mark.parametrize("what", [np.nan, np.inf])
+def test_batched_points_that_are_not_finite(mode, what):
+    """No distance of such a point is a finite number: it is in bucket 0 of every round, as the rule has it (the
+    lowest index among equals; a first distance that is not a number is never beaten), the pair fails where its
+    kernel has such entries, and the other pairs do not change by a bit."""
+    import paper_2107_06876_amd as lcn
+    sizes = [(20, 30), (33, 31), (16, 16), (64, 60)]
+    d, l, b, rounds = 18, 5, 4, 2
+    lm = dict(num_landmarks=l, kmeans_iters=6, seed=3, ridge=0.5)
+    lsh = dict(num_buckets=b, num_rounds=rounds, kmeans_iters=6, seed=41)
+    out = []
+    for spoilt in (False, True):
+        B = _edge_batch(sizes, d, l, b, seed=7)
+        if spoilt:
+            B.X[B.x_off[1] + 4, 3] = what
+            B.Y[B.y_off[1] + 30, 17] = what
+        h = _build_only(B, mode, lm, lsh)
+        status = lcn.sinkhorn_run(h, 5, check=False)
+        st = {k: v.cpu().numpy() for k, v in lcn.lcn_batched_get(h).items()}
+        out.append((status, st))
+        lcn.lcn_destroy(h)
+    (_, clean), (status, st) = out
+    if np.isnan(what):
+        assert status == lcn.binding.ERR_NONPOSITIVE
+    for p, (n, m) in enumerate(sizes):
+        z0, N = int(B.x_off[p] + B.y_off[p]), n + m
+        buckets = st["buckets"][z0 * rounds:(z0 + N) * rounds].reshape(rounds, N)
+        if p == 1:
+            assert buckets.min() >= 0 and buckets.max() < b
+            assert (buckets[:, 4] == 0).all() and (buckets[:, n + 30] == 0).all()
+            continue
+        np.testing.assert_array_equal(buckets, clean["buckets"][z0 * rounds:(z0 + N) * rounds].reshape(rounds, N))
+        np.testing.assert_array_equal(st["kernel"][p][:n, :m], clean["kernel"][p][:n, :m])
+        np.testing.assert_array_equal(st["log_u"][z0:z0 + n], clean["log_u"][z0:z0 + n])
+        np.testing.assert_array_equal(st["log_v"][z0:z0 + m], clean["log_v"][z0:z0 + m])
+        if mode == "lcn":
+            np.testing.assert_array_equal(st["landmarks"][p], clean["landmarks"][p])
+
+
+@pytest.mark.parametrize("scale", [3e7, 1e8])
+def test_batched_build_on_far_points(scale):
+    """Coordinates above 2^24, where the 64-bit sum of 128 of them might wrap: the rule decides on every centroid."""
+    import paper_2107_06876_amd as lcn
+    sizes = [(16, 16), (17, 20), (40, 9)]
+    B = _edge_batch(sizes, 8, 3, 4, seed=7)
+    B.X *= scale / 4
+    B.Y *= scale / 4
+    B.lam[:] *= scale
+    h = _build_only(B, "lcn", dict(num_landmarks=3, kmeans_iters=7, seed=3, ridge=0.5),
+                    dict(num_buckets=4, num_rounds=2, kmeans_iters=9, seed=41))
+    st = {k: v.cpu().numpy() for k, v in lcn.lcn_batched_get(h).items()}
+    for p, (n, m) in enumerate(sizes):
+        Z = np.concatenate([B.X[B.x_off[p]:B.x_off[p + 1]], B.Y[B.y_off[p]:B.y_off[p + 1]]])
+        assert np.abs(Z.astype(np.float64).sum(axis=0)).max() * 2.0 ** 32 < 2.0 ** 63   # no sum wraps
+        np.testing.assert_array_equal(st["landmarks"][p], oracle.kmeans(Z, 3, 7, 3 + p)[0])
+        z0 = int(B.x_off[p] + B.y_off[p]) * 2
+        for r in range(2):
+            np.testing.assert_array_equal(st["buckets"][z0 + r * (n + m):z0 + (r + 1) * (n + m)],
+                                          oracle.kmeans(Z, 4, 9, 41 + p * 2 + r)[1])
