@@ -162,7 +162,9 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
         for (int w = 0; w < DI_WAVES; ++w) tot += sums[buf][lane < RG ? lane : RG - 1][w];
         const bool good = (tot > DI_ROW_MIN || (marg == 0.f && tot > 0.0)) && tot < DI_MAX && shift > -INFINITY &&
                           shift < INFINITY;
-        any_bad = any_bad || __ballot(!good && lane < RG) != 0;   // the same in every wavefront
+        // The same in every wavefront: the rows of this workgroup are written by it alone, behind the barrier.  Rows
+        // past the end do not count: their stand-in, the last row, is another workgroup's to write meanwhile.
+        any_bad = any_bad || __ballot(!good && lane < RG && r0 + lane < rows) != 0;
         // the column sums are taken times the number of columns: of order one
         float f_l = 0.f;
         if (r0 + lane < rows && good && marg != 0.f) {

@@ -699,3 +699,33 @@ def test_dense_iterations_from_one_read(n, m, lam, zeros):
         p.b /= p.b.sum()
     p.cost, p.lam = workloads.COST_SQEUCLID, lam
     print("dense iterations", n, m, lam, compare(p, "dense"), flush=True)
+
+
+@pytest.mark.parametrize("n,m", [(1701, 1801), (2050, 1500)])
+def test_dense_iterations_with_a_last_row_nothing_reaches(n, m):
+    """The last row's point is too far from everything: its sum is empty in every iteration and is looked at a second time, by
+    the workgroup that owns the row only, though every workgroup's groups past the end repeat it.  With n = 1701 all of
+    them have such a group.  The other points are those of the problem without it."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    rng = np.random.default_rng(4)
+    X = rng.standard_normal((n, 6)).astype(np.float32)
+    Y = (rng.standard_normal((m, 6)) + 0.3).astype(np.float32)
+    X[-1, 2] = 1e25   # log kernel below every single-precision number
+    a, b = np.full(n, 1.0 / n, dtype=np.float32), np.full(m, 1.0 / m, dtype=np.float32)
+    iters, lam = 6, 2.5
+    h = lcn.lcn_build(*(torch.from_numpy(t).cuda() for t in (X, Y, a, b)), lam, lcn.COST_SQEUCLID, lcn.MODE_DENSE)
+    assert lcn.sinkhorn_run(h, iters, check=False) == lcn.binding.WARN_NO_SUPPORT
+    assert lcn.lcn_last_error_counts(h) == (0, iters, 0)
+    u, v = (t.cpu().numpy() for t in lcn.lcn_get_scalings(h))
+    lcn.lcn_destroy(h)
+    Xd, Yd = X[:-1].astype(np.float64), Y.astype(np.float64)
+    K = np.exp(-((Xd * Xd).sum(1)[:, None] + (Yd * Yd).sum(1)[None, :] - 2.0 * Xd @ Yd.T) / lam)
+    vd = np.ones(m)
+    for _ in range(iters):
+        ud = a[0].astype(np.float64) / (K @ vd)
+        vd = b[0].astype(np.float64) / (K.T @ ud)
+    assert u[-1] == -np.inf
+    # stored logs round to 2^-24 of values up to 16; kernel exponents of up to 40 round to 2^-24 of themselves
+    np.testing.assert_allclose(u[:-1], np.log(ud), rtol=0, atol=2e-5)
+    np.testing.assert_allclose(v, np.log(vd), rtol=0, atol=2e-5)
