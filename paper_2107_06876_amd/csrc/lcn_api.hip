@@ -755,7 +755,7 @@ struct Builder {
         // room of its own behind everything else: a workspace that ends here is still taken
         h.column_groups = h.mode == LCN_MODE_DENSE ? dense_iteration_groups(h.n, h.m, h.cus) : 0;
         if (h.column_groups) {
-            h.column_part = bump.take<float>((size_t)h.column_groups * (size_t)(h.m + 1));
+            h.column_part = bump.take<float>(dense_iteration_floats(h.column_groups, h.m));
             if (h.column_part) h.ws_used = bump.used;
         }
         return LCN_OK;
@@ -838,7 +838,7 @@ lcn_status lcn_workspace_bytes(int64_t n, int64_t m, int32_t d, int32_t mode, co
     }
     bump.take<float>((size_t)nnz + 128);
     bump.take<float>((size_t)nnz + 128);
-    if (mode == LCN_MODE_DENSE) bump.take<float>((size_t)dense_iteration_groups(n, m, device_compute_units()) * (size_t)(m + 1));
+    if (mode == LCN_MODE_DENSE) bump.take<float>(dense_iteration_floats(dense_iteration_groups(n, m, device_compute_units()), m));
     *bytes = bump.used + 256;
     return LCN_OK;
 }

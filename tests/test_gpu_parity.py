@@ -729,3 +729,42 @@ def test_dense_iterations_with_a_last_row_nothing_reaches(n, m):
     # stored logs round to 2^-24 of values up to 16; kernel exponents of up to 40 round to 2^-24 of themselves
     np.testing.assert_allclose(u[:-1], np.log(ud), rtol=0, atol=2e-5)
     np.testing.assert_allclose(v, np.log(vd), rtol=0, atol=2e-5)
+
+
+@pytest.mark.parametrize("n,m,zeros", [(2000, 2000, False), (10000, 10000, False), (8000, 3000, False), (6000, 6000, True)])
+def test_dense_scalings_do_not_drift(n, m, zeros):
+    """Two groups of coinciding points per side: every row's factor and every column's terms round alike in every
+    iteration, so a rounding that is not made good again moves log u and log v in opposite directions for good.
+    Also with a mass below the smallest normal number, whose factor has no reciprocal, and points without any."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    rng = np.random.default_rng(12)
+    c = rng.standard_normal((2, 8))
+    px, py = c.astype(np.float32), (0.7 * c + 0.1).astype(np.float32)
+    a, b = np.full(n, 1.0 / n, dtype=np.float32), np.full(m, 1.0 / m, dtype=np.float32)
+    if zeros:
+        a[::7], b[::5], a[3] = 0.0, 0.0, 1e-43
+    lam = 0.3 * float(((px[:, None] - py[None, :]).astype(np.float64) ** 2).sum(-1).mean())
+    lam = float(np.float32(lam))
+    gx, gy = np.arange(n) % 2, np.arange(m) % 2
+    h = lcn.lcn_build(*(torch.from_numpy(t).cuda() for t in (px[gx], py[gy], a, b)), lam, lcn.COST_SQEUCLID, lcn.MODE_DENSE)
+    K = np.exp(-((px[:, None].astype(np.float64) - py[None, :]) ** 2).sum(-1) / lam)
+    v = np.ones(m)
+    worst = {}
+    for iters in (2, 298):
+        assert lcn.sinkhorn_run(h, iters) == 0
+        for _ in range(iters):   # every sum over points depends on the point's group only
+            u = a.astype(np.float64) / (K @ np.bincount(gy, v, 2))[gx]
+            v = b.astype(np.float64) / (K.T @ np.bincount(gx, u, 2))[gy]
+        lu, lv = (t.cpu().numpy().astype(np.float64) for t in lcn.lcn_get_scalings(h))
+        np.testing.assert_array_equal(np.isfinite(lu), u > 0)
+        np.testing.assert_array_equal(np.isfinite(lv), v > 0)
+        worst[iters] = (lu[u > 0] - np.log(u[u > 0])).mean(), (lv[v > 0] - np.log(v[v > 0])).mean()
+        if zeros:   # the tiny mass: its scaling is as good as any (log u about -90, rounded to 2^-24 of itself)
+            assert abs(lu[3] - np.log(u[3])) < 2e-5
+    lcn.lcn_destroy(h)
+    print("drift", n, m, worst, flush=True)
+    for early, late in zip(worst[2], worst[298]):
+        # values of 8 to 16 are stored in steps of 9.5e-7, and where all are equal they all round the same way; half a
+        # step more for the iteration itself (1.7e-6 to 2.7e-6 with a factor's rounding handed to the next row only)
+        assert abs(late - early) <= 1.5e-6, worst
