@@ -10,8 +10,10 @@
 //
 // A workgroup (one per compute unit, 1024 threads) takes RG rows at a time, each thread C columns of them, the next
 // RG rows' loads in flight meanwhile; log v_j and the column sums stay in registers for the whole launch.
-// RG * C is about 24: two sets of values and two per column fill the 128 registers a thread has (30 spills).  The
-// prefetch is unconditional (past the end the last row again): behind a condition the compiler waits for all loads.
+// RG * C is at most 24 (8 and 16 for one and two pieces, 12 .. 18 with a row at a time): two sets of values and two
+// per column fill the 128 registers a thread has (30 spills).  The prefetch is unconditional (past the end the last
+// row again): behind a condition the compiler waits for all loads.  A group past the end is not worked on: with two
+// groups at a time whatever their number, 4000 x 4000 (three) took 27.4 us per iteration instead of 23.1.
 // The column sums of the workgroups, in single precision over n / (number of workgroups) rows, are added in double
 // precision by dense_columns_kernel, which finishes v.
 // 10 000 x 10 000 (400 MB), 100 iterations: 160 us per iteration with two reads, 82 us so (4.9 TB/s).
@@ -192,10 +194,13 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
             }
         }
     };
-    for (int r0 = first; r0 < rows; r0 += 2 * step) {
-        group(r0, 0, ka, kb);
-        group(r0 + step, 1, kb, ka);   // possibly past the end: the last row, without effect
-    }
+    if (first < rows)
+        for (int r0 = first;;) {
+            group(r0, 0, ka, kb);
+            if ((r0 += step) >= rows) break;
+            group(r0, 1, kb, ka);
+            if ((r0 += step) >= rows) break;
+        }
     float *part = column_part + (long long)blockIdx.x * cols, *lost_out = column_part + (long long)gridDim.x * cols;
     double have = 0.0;   // what this thread's column sums hold of the mass
 #pragma unroll
@@ -358,10 +363,11 @@ __global__ __launch_bounds__(DI_THREADS) void dense_columns_kernel(PassSide S, c
 
 static constexpr int dense_rows_of(int c) { return c <= 3 ? 8 : c >= 12 ? 1 : 24 / c; }
 
-// Where the matrix is small the two launches and the trip through the column sums cost more than the second read
-// of it (us per iteration, half-iterations by themselves against this: 1000 x 1000 12.7 / 14.1, 1500 x 1500
-// 13.9 / 15.4, 3000 x 1000 15.9 / 14.2, 2000 x 2000 16.4 / 16.2, 4000 x 4000 30 / 26, 8000 x 8200 115 / 57,
-// 10 000 x 10 000 161 / 83, 12 000 x 14 000 250 / 130); beyond 18 pieces a thread's registers are full.
+// Where the matrix is small the two launches and the trip through the column sums cost what the second read of it
+// does (us per iteration, half-iterations by themselves against this: 2000 x 2000 15.1 / 12.3, 1500 x 2049
+// 14.5 / 12.9, 3000 x 1024 14.8 / 13.3, 1000 x 3073 15.2 / 13.1, 46 000 x 70 102 / 72, 3500 x 3501 24.6 / 22.0, 4000 x 4000
+// 29 / 23, 300 x 18 000 47 / 24, 10 000 x 10 000 159 / 81, 200 000 x 64 424 / 285); beyond 18 pieces a thread's
+// registers are full.
 int dense_iteration_groups(long long n, long long m, int cus)
 {
     const bool worth = m <= DENSE_ITERATION_MAX_COLUMNS && n * m >= DENSE_ITERATION_MIN_PAIRS;
