@@ -125,9 +125,11 @@ __host__ __device__ inline BuildLds build_lds(int l, int runs, int mt, int dt, i
     return L;
 }
 
-// Cost of two points from their dot product and squared norms a2, b2.  Where the norms nearly cancel (squared
-// distance below 1e-4 of their sum, a relative error of 1e-11) it is taken from the differences of the
-// points' rows (LDS, zero padded to dp dimensions) instead; coinciding points are at distance zero exactly.
+// Cost of two points from their dot product and squared norms a2, b2, for an entry of the kernel.  Where the norms
+// nearly cancel (squared distance below 1e-4 of their sum) it is taken from the differences of the points' rows (LDS,
+// zero padded to dp dimensions) instead; coinciding points are at distance zero exactly.  The cost's relative error is
+// about 1e-12 then and below 1.5e-10 in any case, the entry's (an exponent above -104) below 1.6e-8, a quarter of its
+// rounding to single precision.
 __device__ inline double cost_of_dot(double dot, double a2, double b2, const float *x, const float *y, int dp, int cost)
 {
     if (cost == LCN_COST_COSINE) return 1.0 - dot / (sqrt(a2) * sqrt(b2));
@@ -247,8 +249,8 @@ __device__ inline void landmark_cholesky(double *A, int l, int *not_positive)
 //  * the start indices of a run are drawn by a lane each and the shuffle is resolved by ballots;
 //  * the Nystrom values are products of L^{-1} u and L^{-1} v (A = L L^T): a Cholesky by one wavefront in
 //    registers and one forward substitution per point, no inverse;
-//  * every cost comes from dot products on the matrix instruction (see cost_of_dot), and so do the Nystrom
-//    values; tiles of the kernel without a pair that shares a bucket skip the costs.
+//  * the costs of the pairs that share a bucket come from dot products on the matrix instruction (see
+//    cost_of_dot), and so do the Nystrom values; tiles of the kernel without such a pair skip the costs.
 // Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 51 us for 16 pairs
 // (243 with one k-means run after the other, the rule on vector instructions and 64-bit LDS atomics), 114 us
 // for 1024 (336) and 351 us for 4096 (1145).
@@ -573,32 +575,60 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     };
     if (low_rank) {
         for (int e = tid; e < l * d; e += NT) B.landmarks[(long long)p * l * d + e] = cent[(e / d) * zs + e % d];
-        // exp(-c / lambda) of the landmarks (rows 0 .. l - 1 of the first tile) with every point and among themselves
+        // exp(-c / lambda) of the landmarks (rows 0 .. l - 1 of the first tile) with every point and among themselves.
+        // Squared distances from the differences, not from dot products: what A^{-1} does to an error of these costs is
+        // its condition number (two dimensions, sixteen landmarks, points 70 from the origin: K~ off by up to 5e-4
+        // of itself from dot products, below its rounding to single precision from differences).
+        const bool cosine = B.cost == LCN_COST_COSINE;
         double lop[4 * DT];
-        operand(cent, col, lop);
-        {
+        if (cosine) {
+            operand(cent, col, lop);
             double sq = 0.0;
 #pragma unroll
             for (int e = 0; e < 4 * DT; ++e) sq = fma(lop[e], lop[e], sq);
             sq = quarter_sum(sq);
             if (wave == 0 && quarter == 0) rn[col] = sq;
+            __syncthreads();   // the same in every thread
         }
-        __syncthreads();
         for (int t = wave; t <= PT; t += NW) {   // tile PT: the landmarks themselves
             const bool self = t == PT;
-            double bop[4 * DT];
-            operand(self ? cent : Z, self ? col : 16 * t + col, bop);
-            const double4_t dot = dots(lop, bop);
             const int pt = self ? col : 16 * t + col;
-            const double b2 = self ? rn[col] : pn[pt];
+            const float *other = self ? cent : Z;
+            double c[4] = {0.0, 0.0, 0.0, 0.0};   // of landmark 4 v + quarter and point pt
+            if (cosine) {
+                double bop[4 * DT];
+                operand(other, pt, bop);
+                const double4_t dot = dots(lop, bop);
+                const double b2 = self ? rn[col] : pn[pt];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[v] = 1.0 - dot[v] / (sqrt(rn[4 * v + quarter]) * sqrt(b2));
+            } else {
+#pragma unroll 4
+                for (int k = 0; k < dp; k += 4) {
+                    const float4 z = *(const float4 *)(other + pt * zs + k);
+                    const double zd[4] = {(double)z.x, (double)z.y, (double)z.z, (double)z.w};
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (4 * v < l) {   // the same in every lane
+                            const float4 f = *(const float4 *)(cent + (4 * v + quarter) * zs + k);
+                            const double fd[4] = {(double)f.x, (double)f.y, (double)f.z, (double)f.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const double diff = zd[e] - fd[e];
+                                c[v] = fma(diff, diff, c[v]);
+                            }
+                        }
+                }
+                if (B.cost == LCN_COST_EUCLID) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) c[v] = sqrt(c[v]);
+                }
+            }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int k = 4 * v + quarter;
                 if (k < l && pt < (self ? l : N)) {
-                    const double c = (self && k == pt) ? 0.0
-                                                       : cost_of_dot(dot[v], rn[k], b2, cent + k * zs,
-                                                                     (self ? cent : Z) + pt * zs, dp, B.cost);
-                    const double f = exp(-c * inv_lam);
+                    const double f = exp(-(self && k == pt ? 0.0 : c[v]) * inv_lam);
                     if (self)
                         Am[k * l + pt] = f + (k == pt ? B.ridge : 0.0);
                     else

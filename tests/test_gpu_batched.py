@@ -367,3 +367,47 @@ def test_batched_build_on_far_points(scale):
         for r in range(2):
             np.testing.assert_array_equal(st["buckets"][z0 + r * (n + m):z0 + (r + 1) * (n + m)],
                                           oracle.kmeans(Z, 4, 9, 41 + p * 2 + r)[1])
+
+
+def _nystrom_extended(Z, n, L, lam, ridge, euclid):
+    """U A^{-1} V of a pair in extended precision, and the condition number of A."""
+    Z, L, lam = Z.astype(np.longdouble), L.astype(np.longdouble), np.longdouble(lam)
+
+    def kernel(a, b):
+        sq = ((a[:, None] - b[None]) ** 2).sum(-1)
+        return np.exp(-(np.sqrt(sq) if euclid else sq) / lam)
+    F, A = kernel(Z, L), kernel(L, L) + np.longdouble(ridge) * np.eye(len(L), dtype=np.longdouble)
+    C, W = np.zeros_like(A), np.zeros_like(F)
+    for j in range(len(L)):
+        C[j, j] = np.sqrt(A[j, j] - (C[j, :j] ** 2).sum())
+        for i in range(j + 1, len(L)):
+            C[i, j] = (A[i, j] - (C[i, :j] * C[j, :j]).sum()) / C[j, j]
+        W[:, j] = (F[:, j] - W[:, :j] @ C[j, :j]) / C[j, j]
+    return W[:n] @ W[n:].T, np.linalg.cond(A.astype(np.float64))
+
+
+@pytest.mark.parametrize("cost", [workloads.COST_SQEUCLID, workloads.COST_EUCLID])
+@pytest.mark.parametrize("d,l", [(2, 16), (3, 7), (17, 9)])
+def test_batched_landmark_costs_away_from_the_origin(cost, d, l):
+    """Points whose norms are large against their distances: a cost from dot products would lose the digits that the
+    norms have in common, and the inverse of the landmarks' matrix multiplies that by its condition number."""
+    import paper_2107_06876_amd as lcn
+    sizes = [(40, 50)] * 16
+    B = _edge_batch(sizes, d, l, 2, seed=9)
+    B.X[:, 0] += 50.0 * d ** 0.5
+    B.Y[:, 0] += 50.0 * d ** 0.5
+    B.cost = cost
+    B.lam[:] = d
+    h = _build_only(B, "nystrom", dict(num_landmarks=l, kmeans_iters=1, seed=3, ridge=1e-10), None)
+    st = {k: v.cpu().numpy() for k, v in lcn.lcn_batched_get(h).items()}
+    lcn.lcn_destroy(h)
+    worst = 0.0
+    for p, (n, m) in enumerate(sizes):
+        Z = np.concatenate([B.X[B.x_off[p]:B.x_off[p + 1]], B.Y[B.y_off[p]:B.y_off[p + 1]]])
+        want, cond = _nystrom_extended(Z, n, st["landmarks"][p], B.lam[p], 1e-10, cost == workloads.COST_EUCLID)
+        # the rounding of the stored entry, and l double precision roundings in each of the two factors, which
+        # A^{-1} multiplies by its condition number at most
+        bound = 2.0 ** -24 * np.abs(want) + 2 * l * 2.0 ** -53 * cond
+        worst = max(worst, float((np.abs(st["kernel"][p][:n, :m] - want) / bound).max()))
+    print("landmark costs", cost, d, l, "largest error over its bound", worst, flush=True)
+    assert worst <= 1.0
