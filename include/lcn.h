@@ -34,7 +34,9 @@
  *     that INVALID_ARG comes after the build has used the workspace (no handle
  *     is returned and the caller's inputs are never written).
  *   - Same inputs and seeds give bit-identical landmarks, buckets, block
- *     structure, factors and scalings.
+ *     structure, factors and scalings.  (A dense build whose workspace has
+ *     fewer bytes than its *bytes_needed, but enough to succeed, sums in
+ *     another order: its scalings agree to single precision only.)
  *   - A handle must not be used from two threads at once.
  */
 #ifndef LCN_H
@@ -151,7 +153,9 @@ lcn_status lcn_workspace_bytes(int64_t n, int64_t m, int32_t d, int32_t mode, co
  *   cost       lcn_cost; k-means always uses the Euclidean rule on the vectors as given
  *   mode       lcn_mode; landmarks is required for NYSTROM/LCN, lsh for SPARSE/LCN
  *   workspace  device, 256-byte aligned; everything the handle needs lives in it
- *   bytes_needed  host, nullable; set on LCN_OK and on LCN_ERR_ALLOC
+ *   bytes_needed  host, nullable; set on LCN_OK and on LCN_ERR_ALLOC.  A dense
+ *              build may succeed with less (up to 4 (m + 1) bytes per compute unit):
+ *              it then reads its kernel twice per iteration
  *   out        host; receives the handle (NULL on error)
  * The scalings start at v = 1 (eq. 2).  Points must satisfy |x| < 2^10 and
  * n + m <= 2^20 when k-means is used (its means are summed in 2^-32 fixed

@@ -750,14 +750,16 @@ struct Builder {
         h.vals_x = bump.take<float>((size_t)h.nnz_stored + 128);
         h.vals_y = bump.take<float>((size_t)h.nnz_stored + 128);
         h.ws_used = bump.used;
-        if (bytes_needed) *bytes_needed = bump.used + 256;
-        if (bump.used > h.ws_bytes) return LCN_ERR_ALLOC;
-        // room of its own behind everything else: a workspace that ends here is still taken
+        const size_t least = bump.used;
+        // Last, room for the column sums of a dense iteration.  It belongs to what a build needs, so that whoever asks
+        // gets the same iteration; a workspace that ends before it is still taken, with the two half-iterations.
         h.column_groups = h.mode == LCN_MODE_DENSE ? dense_iteration_groups(h.n, h.m, h.cus) : 0;
         if (h.column_groups) {
             h.column_part = bump.take<float>(dense_iteration_floats(h.column_groups, h.m));
             if (h.column_part) h.ws_used = bump.used;
         }
+        if (bytes_needed) *bytes_needed = bump.used + 256;
+        if (least > h.ws_bytes) return LCN_ERR_ALLOC;
         return LCN_OK;
     }
 

@@ -768,3 +768,55 @@ def test_dense_scalings_do_not_drift(n, m, zeros):
         # values of 8 to 16 are stored in steps of 9.5e-7, and where all are equal they all round the same way; half a
         # step more for the iteration itself (1.7e-6 to 2.7e-6 with a factor's rounding handed to the next row only)
         assert abs(late - early) <= 1.5e-6, worst
+
+
+def test_dense_workspace_decides_the_iteration_only_below_what_is_needed():
+    """A dense build in a workspace of exactly what it asks for takes both halves of an iteration from one read, like one
+    in a larger workspace, bit for bit.  One that ends before the room for that is still taken and reads the
+    kernel twice: the same scalings to single precision.  Below that it is refused."""
+    import ctypes
+    import torch
+    import paper_2107_06876_amd as lcn
+    from paper_2107_06876_amd import binding
+    n, m, d, lam, iters = 2100, 1900, 8, 0.5, 7
+    rng = np.random.default_rng(3)
+    X, Y = (torch.from_numpy(rng.standard_normal((k, d)).astype(np.float32)).cuda() for k in (n, m))
+    a, b = (torch.full((k,), 1.0 / k, device="cuda") for k in (n, m))
+    lib = binding.load_library()
+
+    def build(nbytes):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        raw, need = ctypes.c_void_p(), ctypes.c_size_t(0)
+        st = lib.lcn_build(X.data_ptr(), n, Y.data_ptr(), m, d, binding.F32, a.data_ptr(), b.data_ptr(), lam,
+                           lcn.COST_SQEUCLID, lcn.MODE_DENSE, None, None, ws.data_ptr(), ws.numel(),
+                           ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), ctypes.byref(need), ctypes.byref(raw))
+        return st, need.value, binding.LcnHandle(raw, ws, (n, m, d, 0, 0)) if st == lcn.binding.OK else None
+
+    def scalings(h):
+        assert lcn.sinkhorn_run(h, iters) == 0
+        used = lcn.lcn_get_info(h).workspace_used
+        u, v = (t.cpu().numpy().astype(np.float64) for t in lcn.lcn_get_scalings(h))
+        lcn.lcn_destroy(h)
+        return u, v, used
+
+    enough = lcn.lcn_workspace_bytes(n, m, d, lcn.MODE_DENSE)
+    st, need, h = build(enough)
+    assert st == lcn.binding.OK and need <= enough
+    u0, v0, used = scalings(h)
+    assert used <= need
+    st, again, h = build(need)
+    assert (st, again) == (lcn.binding.OK, need)
+    u1, v1, used = scalings(h)
+    np.testing.assert_array_equal(u1, u0)
+    np.testing.assert_array_equal(v1, v0)
+    column_sums = 4 * (m + 1) * (torch.cuda.get_device_properties(0).multi_processor_count + 1)
+    less = need - 256 - (column_sums + 255) // 256 * 256
+    st, again, h = build(less)
+    assert (st, again) == (lcn.binding.OK, need)
+    u2, v2, used = scalings(h)
+    assert used <= less
+    # logs up to 16 in steps of 9.5e-7; both iterations are within 3e-6 of double precision
+    np.testing.assert_allclose(u2, u0, rtol=0, atol=8e-6)
+    np.testing.assert_allclose(v2, v0, rtol=0, atol=8e-6)
+    st, again, h = build(less - 256)
+    assert (st, again, h) == (lcn.binding.ERR_ALLOC, need, None)
