@@ -370,44 +370,49 @@ def test_batched_build_on_far_points(scale):
 
 
 def _nystrom_extended(Z, n, L, lam, ridge, euclid):
-    """U A^{-1} V of a pair in extended precision, and the condition number of A."""
+    """U A^{-1} V of a pair in extended precision, and what double precision may change in it, to first order: an
+    exponent from d differences is off by d + 2 roundings of itself and the exponential by two more; the solve by
+    2 l roundings of the (unit) diagonal."""
     Z, L, lam = Z.astype(np.longdouble), L.astype(np.longdouble), np.longdouble(lam)
 
-    def kernel(a, b):
+    def exponents(a, b):
         sq = ((a[:, None] - b[None]) ** 2).sum(-1)
-        return np.exp(-(np.sqrt(sq) if euclid else sq) / lam)
-    F, A = kernel(Z, L), kernel(L, L) + np.longdouble(ridge) * np.eye(len(L), dtype=np.longdouble)
-    C, W = np.zeros_like(A), np.zeros_like(F)
-    for j in range(len(L)):
+        return (np.sqrt(sq) if euclid else sq) / lam
+    (d, l), eF, eA = (Z.shape[1], len(L)), exponents(Z, L), exponents(L, L)
+    F, A = np.exp(-eF), np.exp(-eA) + np.longdouble(ridge) * np.eye(l, dtype=np.longdouble)
+    C, W, S = np.zeros_like(A), np.zeros_like(F), np.zeros_like(F)
+    for j in range(l):
         C[j, j] = np.sqrt(A[j, j] - (C[j, :j] ** 2).sum())
-        for i in range(j + 1, len(L)):
+        for i in range(j + 1, l):
             C[i, j] = (A[i, j] - (C[i, :j] * C[j, :j]).sum()) / C[j, j]
         W[:, j] = (F[:, j] - W[:, :j] @ C[j, :j]) / C[j, j]
-    return W[:n] @ W[n:].T, np.linalg.cond(A.astype(np.float64))
+    for j in reversed(range(l)):
+        S[:, j] = (W[:, j] - S[:, j + 1:] @ C[j + 1:, j]) / C[j, j]
+    S = np.abs(S)   # |F A^{-1}|
+    dF, dA = ((d + 2) * eF + 2) * F, ((d + 2) * eA + 2) * A + 2 * l
+    return W[:n] @ W[n:].T, 2.0 ** -53 * (dF[:n] @ S[n:].T + S[:n] @ dF[n:].T + S[:n] @ dA @ S[n:].T)
 
 
-@pytest.mark.parametrize("cost", [workloads.COST_SQEUCLID, workloads.COST_EUCLID])
-@pytest.mark.parametrize("d,l", [(2, 16), (3, 7), (17, 9)])
-def test_batched_landmark_costs_away_from_the_origin(cost, d, l):
+@pytest.mark.parametrize("cost,d,l,lam", [(workloads.COST_SQEUCLID, 2, 16, 2.0), (workloads.COST_SQEUCLID, 2, 16, 1.0),
+                                          (workloads.COST_SQEUCLID, 5, 12, 0.6), (workloads.COST_EUCLID, 17, 9, 4.0)])
+def test_batched_landmark_costs_away_from_the_origin(cost, d, l, lam):
     """Points whose norms are large against their distances: a cost from dot products would lose the digits that the
-    norms have in common, and the inverse of the landmarks' matrix multiplies that by its condition number."""
+    norms have in common, and the inverse of the landmarks' matrix multiplies what is lost."""
     import paper_2107_06876_amd as lcn
-    sizes = [(40, 50)] * 16
+    sizes = [(40, 50)] * 48
     B = _edge_batch(sizes, d, l, 2, seed=9)
-    B.X[:, 0] += 50.0 * d ** 0.5
-    B.Y[:, 0] += 50.0 * d ** 0.5
+    B.X[:, 0] += 70.0 * d ** 0.5
+    B.Y[:, 0] += 70.0 * d ** 0.5
     B.cost = cost
-    B.lam[:] = d
+    B.lam[:] = lam
     h = _build_only(B, "nystrom", dict(num_landmarks=l, kmeans_iters=1, seed=3, ridge=1e-10), None)
     st = {k: v.cpu().numpy() for k, v in lcn.lcn_batched_get(h).items()}
     lcn.lcn_destroy(h)
     worst = 0.0
     for p, (n, m) in enumerate(sizes):
         Z = np.concatenate([B.X[B.x_off[p]:B.x_off[p + 1]], B.Y[B.y_off[p]:B.y_off[p + 1]]])
-        want, cond = _nystrom_extended(Z, n, st["landmarks"][p], B.lam[p], 1e-10, cost == workloads.COST_EUCLID)
-        # the rounding of the stored entry, and l double precision roundings in each of the two factors, which
-        # A^{-1} multiplies by its condition number at most
-        bound = 2.0 ** -24 * np.abs(want) + 2 * l * 2.0 ** -53 * cond
+        want, bound = _nystrom_extended(Z, n, st["landmarks"][p], B.lam[p], 1e-10, cost == workloads.COST_EUCLID)
+        bound += 2.0 ** -24 * (np.abs(want) + bound)   # the entry is stored in single precision
         worst = max(worst, float((np.abs(st["kernel"][p][:n, :m] - want) / bound).max()))
-    print("landmark costs", cost, d, l, "largest error over its bound", worst, flush=True)
+    print("landmark costs", cost, d, l, lam, "largest error over its bound", worst, flush=True)
     assert worst <= 1.0
