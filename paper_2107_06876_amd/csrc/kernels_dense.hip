@@ -11,12 +11,12 @@
 // A workgroup (one per compute unit, 1024 threads) takes RG rows at a time, each thread C columns of them, the next
 // RG rows' loads in flight meanwhile; log v_j and the column sums stay in registers for the whole launch.
 // RG * C is at most 24 (8 and 16 for one and two pieces, 12 .. 18 with a row at a time): two sets of values and two
-// per column fill the 128 registers a thread has (30 spills).  The prefetch is unconditional (past the end the last
+// per column fill the 128 registers a thread has (30 spills; eighteen pieces spill two outside the loop).  The prefetch is unconditional (past the end the last
 // row again): behind a condition the compiler waits for all loads.  A group past the end is not worked on: with two
 // groups at a time whatever their number, 4000 x 4000 (three) took 27.4 us per iteration instead of 23.1.
 // The column sums of the workgroups, in single precision over n / (number of workgroups) rows, are added in double
 // precision by dense_columns_kernel, which finishes v.
-// 10 000 x 10 000 (400 MB), 100 iterations: 160 us per iteration with two reads, 82 us so (4.9 TB/s).
+// 10 000 x 10 000 (400 MB): 160 us per iteration with two reads, 80 us so (5.0 TB/s).
 // Root mean square error of log u, log v against 64 bits (two reads): 10 000 x 10 000 after 100 iterations 5.5e-7, 1.8e-7
 // (5.7e-7, 1.3e-7), 4000 x 9000 4.8e-7, 5.4e-7 (1.4e-6, 1.3e-6), 200 000 x 64 after 50 3.1e-7, 1.8e-7 (4.8e-6, 5.0e-6).
 #include "iter_common.h"
@@ -78,6 +78,9 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
 {
     __shared__ double sums[2][RG][DI_WAVES];
     __shared__ double wide[DI_WAVES][2];
+    // what log v_j - base loses in single precision, each thread's own: kept here for the end, where a second trip to
+    // memory for log v would cost 2 us
+    __shared__ float lost_sh[C][DI_THREADS];
     const unsigned tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -132,6 +135,8 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
         const double p = (S.perm_in + DI_THREADS * c)[c == C - 1 ? tid_last : tid];
         pf[c] = c == C - 1 && !in_last ? -INFINITY : (float)(p - base);
         acc[c] = 0.f;
+        const double lost = p - base - (double)pf[c];
+        lost_sh[c][tid] = fabs(lost) < 1.0 ? (float)lost : 0.f;
     }
 
     // Near the fixed point the factors of all rows with equal marginals round alike, iteration after iteration, and
@@ -207,11 +212,10 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
     for (int c = 0; c < C; ++c)
         if (c < C - 1 || in_last) {
             // what log v - base lost in single precision, the same in every workgroup, is a factor of the whole sum
-            double lost = (S.perm_in + DI_THREADS * c)[tid] - base - (double)pf[c];
-            if (!(fabs(lost) < 1.0)) lost = 0.0;
-            have += fma((double)acc[c], lost, (double)acc[c]);
+            const float lost = lost_sh[c][tid];
+            have += fma((double)acc[c], (double)lost, (double)acc[c]);
             (part + DI_THREADS * c)[tid] = acc[c];
-            if (blockIdx.x == 0) (lost_out + DI_THREADS * c)[tid] = (float)lost;
+            if (blockIdx.x == 0) (lost_out + DI_THREADS * c)[tid] = lost;
         }
     if (any_bad) {   // the marked rows' log-sum-exp with running maxima
         __syncthreads();
@@ -364,9 +368,9 @@ __global__ __launch_bounds__(DI_THREADS) void dense_columns_kernel(PassSide S, c
 static constexpr int dense_rows_of(int c) { return c <= 3 ? 8 : c >= 12 ? 1 : 24 / c; }
 
 // Where the matrix is small the two launches and the trip through the column sums cost what the second read of it
-// does (us per iteration, half-iterations by themselves against this: 2000 x 2000 15.1 / 12.3, 1500 x 2049
-// 14.5 / 12.9, 3000 x 1024 14.8 / 13.3, 1000 x 3073 15.2 / 13.1, 46 000 x 70 102 / 72, 3500 x 3501 24.6 / 22.0, 4000 x 4000
-// 29 / 23, 300 x 18 000 47 / 24, 10 000 x 10 000 159 / 81, 200 000 x 64 424 / 285); beyond 18 pieces a thread's
+// does (us per iteration, half-iterations by themselves against this: 2000 x 2000 15.1 / 12.4, 1500 x 2049
+// 14.5 / 12.9, 3000 x 1024 14.8 / 13.3, 1000 x 3073 15.2 / 13.1, 46 000 x 70 102 / 72, 3500 x 3501 24.6 / 21.7, 4000 x 4000
+// 29 / 22.8, 300 x 18 000 47 / 22, 10 000 x 10 000 159 / 80, 200 000 x 64 424 / 286); beyond 18 pieces a thread's
 // registers are full.
 int dense_iteration_groups(long long n, long long m, int cus)
 {
