@@ -416,3 +416,38 @@ def test_batched_landmark_costs_away_from_the_origin(cost, d, l, lam):
         worst = max(worst, float((np.abs(st["kernel"][p][:n, :m] - want) / bound).max()))
     print("landmark costs", cost, d, l, lam, "largest error over its bound", worst, flush=True)
     assert worst <= 1.0
+
+
+@pytest.mark.parametrize("d,l,b,rounds,kind,many", [(8, 5, 3, 2, "plain", True), (16, 16, 16, 4, "ties", True),
+                                                    (12, 9, 7, 3, "large", True), (24, 9, 7, 3, "ties", True),
+                                                    (32, 16, 16, 4, "plain", True), (20, 4, 4, 1, "large", True),
+                                                    (17, 3, 16, 2, "large", True), (9, 7, 5, 3, "ties", False),
+                                                    (31, 16, 9, 2, "plain", False), (50, 6, 6, 2, "ties", False)])
+def test_batched_build_by_four_wavefronts(d, l, b, rounds, kind, many):
+    """As above where four wavefronts build a pair: more than two pairs per compute unit (so that each holds two tiles of
+    points; for up to 16 dimensions, up to 32, and one to five tiles of centroids, whose sums are split into parts or
+    not), or pairs of at most 64 points; and eight wavefronts for more than 32 dimensions."""
+    import paper_2107_06876_amd as lcn
+    base = [(16, 16), (17, 20), (64, 64), (33, 31), (40, 9)] if many else [(16, 16), (17, 20), (33, 31), (40, 9)]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    sizes = base * ((2 * cus) // len(base) + 1) if many else base
+    B = _edge_batch(sizes, d, l, b, seed=7)
+    if kind == "ties":
+        B.X[:] = np.round(B.X)
+        B.Y[:] = np.round(B.Y)
+    if kind == "large":
+        B.X *= 6000.0
+        B.Y *= 6000.0
+        B.lam[:] *= 6000.0
+    h = _build_only(B, "lcn", dict(num_landmarks=l, kmeans_iters=7, seed=3, ridge=0.5),
+                    dict(num_buckets=b, num_rounds=rounds, kmeans_iters=9, seed=41))
+    st = {k: v.cpu().numpy() for k, v in lcn.lcn_batched_get(h).items()}
+    lcn.lcn_destroy(h)
+    for p in sorted({*range(len(base)), *range(len(sizes) - len(base), len(sizes))}):
+        n, m = sizes[p]
+        Z = np.concatenate([B.X[B.x_off[p]:B.x_off[p + 1]], B.Y[B.y_off[p]:B.y_off[p + 1]]])
+        np.testing.assert_array_equal(st["landmarks"][p], oracle.kmeans(Z, l, 7, 3 + p)[0])
+        z0 = int(B.x_off[p] + B.y_off[p]) * rounds
+        for r in range(rounds):
+            np.testing.assert_array_equal(st["buckets"][z0 + r * (n + m):z0 + (r + 1) * (n + m)],
+                                          oracle.kmeans(Z, b, 9, 41 + p * rounds + r)[1])

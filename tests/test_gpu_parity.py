@@ -820,3 +820,23 @@ def test_dense_workspace_decides_the_iteration_only_below_what_is_needed():
     np.testing.assert_allclose(v2, v0, rtol=0, atol=8e-6)
     st, again, h = build(less - 256)
     assert (st, again, h) == (lcn.binding.ERR_ALLOC, need, None)
+
+
+@pytest.mark.parametrize("n,m,lam,zeros", [(1003, 3073, 0.3, True), (1700, 4096, 0.05, False), (1030, 4097, 0.3, True),
+                                           (1500, 5121, 0.05, True), (515, 6145, 0.3, False), (1601, 8192, 0.02, True),
+                                           (801, 8193, 0.3, False), (400, 11264, 0.05, True), (230, 13313, 0.3, True),
+                                           (257, 15360, 0.3, False), (300, 16384, 0.05, True), (259, 17409, 0.3, True)])
+def test_dense_iterations_from_one_read_at_every_width(n, m, lam, zeros):
+    """The widths in between, where a workgroup takes six, four, three, two or one row at a time: numbers of rows with a last
+    group that is partly empty, with one group, two and three per workgroup, points without mass in any place of a group."""
+    from parity import compare
+    p = workloads.config3(n=max(n, m), d=8, landmarks=8, buckets=8, rounds=1, iters=5, name="C3 cut")
+    p.X, p.Y = p.X[:n], p.Y[:m]
+    p.a = np.full(n, 1.0 / n, dtype=np.float32)
+    p.b = np.full(m, 1.0 / m, dtype=np.float32)
+    if zeros:
+        p.a[::7], p.b[::5] = 0.0, 0.0
+        p.a /= p.a.sum()
+        p.b /= p.b.sum()
+    p.cost, p.lam = workloads.COST_SQEUCLID, lam
+    print("dense iterations", n, m, lam, compare(p, "dense"), flush=True)
