@@ -6,7 +6,7 @@
 // fp64, exact kernel values on pairs that share a bucket (Secs. 3-4).  At these
 // sizes (at most 64 points per side) the approximated kernel K~ = U A^{-1} V +
 // (K^sp - K^sp_Nys) is written out as a dense 64 x 64 fp32 tile, which is what
-// the iteration then keeps in LDS.
+// the iteration then keeps in registers.
 //
 // Iteration: Sinkhorn on the bipartite-matching matrix of Sec. 6,
 //   K_BP = [[K~, diag(k_p,eps)], [diag(k_eps,q), 1]],

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, i
     unsigned long long nonpos = 0, range = 0;
 
     // Three-stage software pipeline over the rows a wave owns: metadata is read
-    // two rows ahead (scalar loads), the factor row and the first 64 entries of
+    // two rows ahead (scalar loads), the factor row and the first 64 W entries of
     // every round's segment one row ahead, and the current row is reduced while
     // those loads are in flight.
     struct RowData {
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, i
     float *__restrict__ perm_out = reinterpret_cast<float *>(S.perm_out);
     // Loads are issued for whole wavefront-wide chunks without predication: lanes
     // beyond a segment's length read the next stored values (masked when used; the
-    // arrays end with 64 entries of slack) and the zero slot behind the gathered vector.
+    // arrays end with 64 W, that is 128, entries of slack) and the zero slot behind the gathered vector.
     const unsigned zero_slot = (unsigned)(R * S.rows_in);
     auto issue = [&](RowData &D, const RowMeta<RR> &M, long long r) {
         D.f.load(S.F, r, lp, lane);
