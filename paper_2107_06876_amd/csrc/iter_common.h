@@ -14,6 +14,33 @@ constexpr int MAXR = 8;
 constexpr double PERM_SCALE = 18446744073709551616.0;          // 2^64
 constexpr double PERM_UNSCALE = 1.0 / 18446744073709551616.0;  // 2^-64
 
+__device__ inline double lane_value(double v, int src_lane)   // src_lane: the same in every lane
+{
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src_lane);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src_lane);
+    return __hiloint2double(hi, lo);
+}
+
+template <int CTRL>
+__device__ inline double dpp_from(double v)   // the value of the lane that CTRL selects
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
+// upper half of a <-> lower half of b (HALF = 32), or the odd 16-lane rows of a <-> the even ones of b
+template <int HALF>
+__device__ inline void lane_swap(double &a, double &b)
+{
+    const auto lo = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false)
+                               : __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false)
+                               : __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(hi[0], lo[0]);
+    b = __hiloint2double(hi[1], lo[1]);
+}
+
 // One step of a cross-lane sum of doubles through the DPP data path (no LDS):
 // adds to every lane the value of the lane that `CTRL` selects; lanes of rows
 // outside ROW_MASK add zero.  With a full row mask every lane receives a value,
@@ -42,9 +69,7 @@ __device__ inline double wave_sum(double v)
     v = dpp_add<0x140, 0xF>(v);  // row_mirror: every lane of a 16-lane row holds the row's sum
     v = dpp_add<0x142, 0xA>(v);  // row_bcast15 into rows 1 and 3
     v = dpp_add<0x143, 0xC>(v);  // row_bcast31 into rows 2 and 3: lane 63 holds the total
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-    return __hiloint2double(hi, lo);
+    return lane_value(v, 63);
 }
 
 template <int CTRL, int ROW_MASK>
@@ -66,9 +91,7 @@ __device__ inline double wave_max(double v)
     v = dpp_max<0x140, 0xF>(v);
     v = dpp_max<0x142, 0xA>(v);
     v = dpp_max<0x143, 0xC>(v);
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-    return __hiloint2double(hi, lo);
+    return lane_value(v, 63);
 }
 
 // natural log of a positive finite double: exponent taken out exactly, the
@@ -95,7 +118,7 @@ __device__ inline void lse_step(double t, double &mx, double &sm)
     }
 }
 
-__device__ inline double fast_rcp(double x)
+__device__ inline double fast_rcp(double x)   // 1 / x for a positive finite x, to about one unit in the last place
 {
     double r = __builtin_amdgcn_rcp(x);
     r = fma(fma(-x, r, 1.0), r, r);

@@ -61,13 +61,6 @@ __device__ inline unsigned long long splitmix64_dev(unsigned long long &state)
     return z ^ (z >> 31);
 }
 
-__device__ inline double lane_value(double v, int src_lane)   // src_lane: the same in every lane
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src_lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src_lane);
-    return __hiloint2double(hi, lo);
-}
-
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // The centroids of all k-means runs of a pair (run 0: the landmarks if there are any, then the hash rounds)
@@ -142,26 +135,6 @@ __device__ inline double cost_of_dot(double dot, double a2, double b2, const flo
         }
     }
     return cost == LCN_COST_EUCLID ? sqrt(sq) : sq;
-}
-
-template <int CTRL>
-__device__ inline double dpp_from(double v)   // the value of the lane that CTRL selects
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-
-// upper half of a <-> lower half of b (HALF = 32), or the odd 16-lane rows of a <-> the even ones of b
-template <int HALF>
-__device__ inline void lane_swap(double &a, double &b)
-{
-    const auto lo = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false)
-                               : __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-    const auto hi = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false)
-                               : __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-    a = __hiloint2double(hi[0], lo[0]);
-    b = __hiloint2double(hi[1], lo[1]);
 }
 
 // the smaller of two numbers in one instruction (fmin first quiets both arguments)
@@ -721,14 +694,6 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     if (tid == 0 && flags[2]) *B.fail = 1;
 }
 
-__device__ inline double rcp64(double x)   // 1 / x for a positive finite x, to about one unit in the last place
-{
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return r;
-}
-
 // iters Sinkhorn iterations per pair (iters == 0: only the query part), then the
 // pair's distance and marginal residual.
 //
@@ -888,7 +853,7 @@ __global__ __launch_bounds__(64, 2) void batched_run_kernel(BatchDev B, int iter
     };
     auto scale = [&](double marg, double s, bool exists, unsigned long long &empty) -> double {
         if (!exists) return 0.0;
-        if (s > 0.0) return marg * rcp64(s);
+        if (s > 0.0) return marg * fast_rcp(s);
         if (unsupported_is_zero && s == 0.0) {
             ++empty;
             return 0.0;

@@ -118,8 +118,7 @@ __global__ __launch_bounds__(DI_THREADS) void dense_rows_kernel(PassSide S, floa
     auto first_finite = [&](double x) {   // 0 if no lane has one
         const unsigned long long usable = __ballot(x > -INFINITY && x < INFINITY);
         const int from = usable ? __ffsll(usable) - 1 : 0;
-        const double v = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), from),
-                                          __builtin_amdgcn_readlane(__double2loint(x), from));
+        const double v = lane_value(x, from);
         return usable ? v : 0.0;
     };
     {

@@ -8,6 +8,7 @@
 // the GEMMs of the inverse) run on the fp64 matrix instruction, 64 x 64 output
 // tiles per workgroup, operands staged through LDS with the next chunks' global
 // loads in flight; costs are formed from the dot product and fp64 squared norms.
+#include "iter_common.h"   // reads of another lane
 #include "lcn_internal.h"
 
 namespace lcn {
@@ -443,13 +444,6 @@ constexpr int CB = 16;           // block size of the inverse
 constexpr int CLD = NB + 1;      // row stride of the LDS copies
 constexpr size_t CHOL_LDS = sizeof(double) * (2 * NB * CLD + 3 * CB * CB + NB);
 
-__device__ inline double lane_read64(double v, int lane)
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
-}
-
 // 1 / sqrt(x) to fp64 rounding for positive normal x: hardware estimate and two Newton steps
 __device__ inline double rsqrt64(double x)
 {
@@ -499,7 +493,7 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(double *Lm, int l, int j
             for (int k = 0; k < PB; ++k) a[k] = As[c0 + r][c0 + k];
 #pragma unroll
             for (int c = 0; c < PB; ++c) {
-                double dd = lane_read64(a[c], c);
+                double dd = lane_value(a[c], c);
                 if (!(dd > 0.0)) {
                     fail = true;
                     dd = 1.0;
@@ -508,7 +502,7 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(double *Lm, int l, int j
                 if (tid == 0) rs_sh[c0 + c] = rs;
                 a[c] *= rs;
 #pragma unroll
-                for (int k = c + 1; k < PB; ++k) a[k] = fma(-a[c], lane_read64(a[c], k), a[k]);
+                for (int k = c + 1; k < PB; ++k) a[k] = fma(-a[c], lane_value(a[c], k), a[k]);
             }
             if (tid < PB) {
 #pragma unroll

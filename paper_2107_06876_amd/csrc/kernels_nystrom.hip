@@ -16,24 +16,13 @@
 
 namespace lcn {
 
-template <int CTRL>
-__device__ inline double dpp_value(double v)   // the value of the lane that CTRL selects
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-
 // One step of the cross-lane sum of two values: lanes in the upper half (HALF = 32) or in the odd 16-lane
 // rows (HALF = 16) end up with b's sum over the pair of lanes, the others with a's.
 template <int HALF>
 __device__ inline double halve(double a, double b)
 {
-    const auto lo = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false)
-                               : __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-    const auto hi = HALF == 32 ? __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false)
-                               : __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    lane_swap<HALF>(a, b);
+    return a + b;
 }
 
 // Sums of NV (4 or 8) values over the 64 lanes; lane l receives the sum of value l / (64 / NV).
@@ -50,20 +39,13 @@ __device__ inline double reduce_values(double (&v)[NV])
         const double e = halve<16>(a, c), f = halve<16>(b, d);
         const bool odd = threadIdx.x & 8;
         const double keep = odd ? f : e, give = odd ? e : f;
-        s = keep + dpp_value<0x128>(give);   // row_ror:8
+        s = keep + dpp_from<0x128>(give);   // row_ror:8
     }
-    s += dpp_value<0xB1>(s);    // quad_perm [1,0,3,2]
-    s += dpp_value<0x4E>(s);    // quad_perm [2,3,0,1]
-    s += dpp_value<0x141>(s);   // row_half_mirror
-    if constexpr (NV == 4) s += dpp_value<0x140>(s);   // row_mirror
+    s += dpp_from<0xB1>(s);    // quad_perm [1,0,3,2]
+    s += dpp_from<0x4E>(s);    // quad_perm [2,3,0,1]
+    s += dpp_from<0x141>(s);   // row_half_mirror
+    if constexpr (NV == 4) s += dpp_from<0x140>(s);   // row_mirror
     return s;
-}
-
-__device__ inline double lane_read(double v, int lane)   // lane: the same in every lane
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
 }
 
 template <int T, int MODE, bool FUSED, int RG>
@@ -171,7 +153,7 @@ __global__ __launch_bounds__(PASS_THREADS) void nystrom_pass_kernel(PassSide S, 
             if (exists && sub == 0) S.lin_out[mine] = out;
 #pragma unroll
             for (int t = 0; t < RG; ++t) {
-                const double o = lane_read(out, t * GL);
+                const double o = lane_value(out, t * GL);
 #pragma unroll
                 for (int k = 0; k < T; ++k) zacc[k] = fma((double)f[t].f[k], o, zacc[k]);
             }
