@@ -224,9 +224,9 @@ __device__ inline void landmark_cholesky(double *A, int l, int *not_positive)
 //    registers and one forward substitution per point, no inverse;
 //  * the costs of the pairs that share a bucket come from dot products on the matrix instruction (see
 //    cost_of_dot), and so do the Nystrom values; tiles of the kernel without such a pair skip the costs.
-// Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 51 us for 16 pairs
-// (243 with one k-means run after the other, the rule on vector instructions and 64-bit LDS atomics), 114 us
-// for 1024 (336) and 351 us for 4096 (1145).
+// Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 44 us for 16 pairs
+// (243 with one k-means run after the other, the rule on vector instructions and 64-bit LDS atomics), 117 us
+// for 1024 (336) and 364 us for 4096 (1145).
 // Layout of v_mfma_f64_16x16x4_f64: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16] and receives
 // D[4 v + l / 16][l % 16], v = 0..3; which dimension a step of a dot product takes is free, so a lane reads
 // four consecutive ones (16 t + 4 (l / 16) ..) for four steps.

@@ -11,14 +11,16 @@
 // A workgroup (one per compute unit, 1024 threads) takes RG rows at a time, each thread C columns of them, the next
 // RG rows' loads in flight meanwhile; log v_j and the column sums stay in registers for the whole launch.
 // RG * C is at most 24 (8 and 16 for one and two pieces, 12 .. 18 with a row at a time): two sets of values and two
-// per column fill the 128 registers a thread has (30 spills; eighteen pieces spill two outside the loop).  The prefetch is unconditional (past the end the last
-// row again): behind a condition the compiler waits for all loads.  A group past the end is not worked on: with two
-// groups at a time whatever their number, 4000 x 4000 (three) took 27.4 us per iteration instead of 23.1.
+// per column fill the 128 registers a thread has (30 spills; eighteen pieces spill one outside the loop).  The prefetch
+// is unconditional (past the end the last row again): behind a condition the compiler waits for all loads.  A group
+// past the end is not worked on: with two groups at a time whatever their number, 4000 x 4000 (three) took 27.4 us per
+// iteration instead of 23.1.
 // The column sums of the workgroups, in single precision over n / (number of workgroups) rows, are added in double
 // precision by dense_columns_kernel, which finishes v.
 // 10 000 x 10 000 (400 MB): 160 us per iteration with two reads, 80 us so (5.0 TB/s).
-// Root mean square error of log u, log v against 64 bits (two reads): 10 000 x 10 000 after 100 iterations 5.5e-7, 1.8e-7
-// (5.7e-7, 1.3e-7), 4000 x 9000 4.8e-7, 5.4e-7 (1.4e-6, 1.3e-6), 200 000 x 64 after 50 3.1e-7, 1.8e-7 (4.8e-6, 5.0e-6).
+// Root mean square error of log u, log v against 64 bits (two reads): 10 000 x 10 000 after 400 iterations 2.7e-7, 0.7e-7
+// (1.4e-6, 1.4e-6), 4000 x 9000 after 1000 4.8e-7, 4.7e-7, left by the first iteration (1.9e-6, 1.8e-6), 200 000 x 64 after
+// 50 3.1e-7, 1.8e-7 (4.8e-6, 5.0e-6).
 #include "iter_common.h"
 
 namespace lcn {
