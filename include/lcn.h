@@ -189,7 +189,10 @@ typedef struct {
  * buckets <= 16, rounds <= 4, problem p round r uses seed + p*rounds + r.
  * The handle works with sinkhorn_run, transport_cost (writes num_problems
  * doubles), lcn_last_run_timing and lcn_destroy; results per problem come from
- * lcn_batched_results / lcn_batched_get.  Errors as lcn_build. */
+ * lcn_batched_results / lcn_batched_get.  Errors as lcn_build, but the points'
+ * coordinates are not checked: a point with one that is not finite is in bucket
+ * 0 of every round, its problem's run ends in LCN_ERR_NONPOSITIVE where kernel
+ * entries are not numbers, and the other problems are not affected. */
 lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lcn_batch_desc *desc, int32_t cost,
                              int32_t mode, const lcn_landmark_params *landmarks, const lcn_lsh_params *lsh,
                              void *workspace, size_t workspace_bytes, void *hip_stream, size_t *bytes_needed,
