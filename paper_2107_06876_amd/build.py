@@ -16,6 +16,9 @@ SOURCES = {
     "kernels_structure.hip": ["-ffp-contract=off"],   # bucket rule: separate multiply and add
     "kernels_factors.hip": [],
     "kernels_mfma.hip": [],
+    "kernels_sweep_mid.hip": [],
+    "kernels_sweep_short.hip": [],
+    "kernels_sweep_long.hip": [],
     "kernels_iter.hip": [],
     "kernels_nystrom.hip": [],
     "kernels_dense.hip": [],
@@ -62,7 +65,7 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + res.stdout)
         return res.stdout
 
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         for out in ex.map(run, jobs):
             if verbose and out.strip():
                 print(out)

@@ -82,6 +82,24 @@ __device__ inline double dpp_max(double v)
     return fmax(v, __hiloint2double(phi, plo));
 }
 
+// Sum over a row of 16 lanes; every lane of the row gets the result.
+__device__ inline double row_sum(double v)
+{
+    v = dpp_add<0xB1, 0xF>(v);
+    v = dpp_add<0x4E, 0xF>(v);
+    v = dpp_add<0x141, 0xF>(v);
+    return dpp_add<0x140, 0xF>(v);
+}
+
+// Sum over a half-wavefront; every lane of the half gets the result.
+__device__ inline double half_sum(double v)
+{
+    v = row_sum(v);
+    double w = v;
+    lane_swap<16>(v, w);
+    return v + w;
+}
+
 // Maximum over the 64 lanes of a wavefront; every lane gets the result.
 __device__ inline double wave_max(double v)
 {
@@ -92,6 +110,24 @@ __device__ inline double wave_max(double v)
     v = dpp_max<0x142, 0xA>(v);
     v = dpp_max<0x143, 0xC>(v);
     return lane_value(v, 63);
+}
+
+// Maximum over a row of 16 lanes; every lane of the row gets the result.
+__device__ inline double row_max(double v)
+{
+    v = dpp_max<0xB1, 0xF>(v);
+    v = dpp_max<0x4E, 0xF>(v);
+    v = dpp_max<0x141, 0xF>(v);
+    return dpp_max<0x140, 0xF>(v);
+}
+
+// Maximum over a half-wavefront; every lane of the half gets the result.
+__device__ inline double half_max(double v)
+{
+    v = row_max(v);
+    double w = v;
+    lane_swap<16>(v, w);
+    return fmax(v, w);
 }
 
 // natural log of a positive finite double: exponent taken out exactly, the
@@ -124,6 +160,38 @@ __device__ inline double fast_rcp(double x)   // 1 / x for a positive finite x, 
     r = fma(fma(-x, r, 1.0), r, r);
     r = fma(fma(-x, r, 1.0), r, r);
     return r;
+}
+
+// One step of the cross-lane sum of two values: lanes in the upper half (HALF = 32) or in the odd 16-lane
+// rows (HALF = 16) end up with b's sum over the pair of lanes, the others with a's.
+template <int HALF>
+__device__ inline double halve(double a, double b)
+{
+    lane_swap<HALF>(a, b);
+    return a + b;
+}
+
+// Sums of NV (4 or 8) values over the 64 lanes; lane l receives the sum of value l / (64 / NV).
+template <int NV>
+__device__ inline double reduce_values(double (&v)[NV])
+{
+    double s;
+    if constexpr (NV == 4) {
+        const double a = halve<32>(v[0], v[2]), b = halve<32>(v[1], v[3]);
+        s = halve<16>(a, b);
+    } else {
+        const double a = halve<32>(v[0], v[4]), b = halve<32>(v[1], v[5]), c = halve<32>(v[2], v[6]),
+                     d = halve<32>(v[3], v[7]);
+        const double e = halve<16>(a, c), f = halve<16>(b, d);
+        const bool odd = threadIdx.x & 8;
+        const double keep = odd ? f : e, give = odd ? e : f;
+        s = keep + dpp_from<0x128>(give);   // row_ror:8
+    }
+    s += dpp_from<0xB1>(s);    // quad_perm [1,0,3,2]
+    s += dpp_from<0x4E>(s);    // quad_perm [2,3,0,1]
+    s += dpp_from<0x141>(s);   // row_half_mirror
+    if constexpr (NV == 4) s += dpp_from<0x140>(s);   // row_mirror
+    return s;
 }
 
 // Factor row of lp = 64 T entries held by a wave: per 256 entries one 16-byte load of four consecutive entries
@@ -159,6 +227,56 @@ struct FRow {
     }
 };
 
+// The rounds' segments of a row's record, read from the packed metadata (wave-uniform: scalar registers).
+template <int RR>
+struct RecordWalk {
+    unsigned shift[RR];  // entry e of round r stands at place e + shift[r] of the gathered vector
+    int end[RR];         // ... and is below end[r]; rounds that do not exist are empty
+};
+
+// Where entry e of the record gathers from; `zero_slot` past its end.
+template <int RR, class Walk>
+__device__ inline unsigned gather_place(const Walk &M, int e, unsigned zero_slot)
+{
+    // (readfirstlane: uniform already; a plain select of two members would become a load through a selected
+    // address and keep the record in scratch memory)
+    unsigned sh = __builtin_amdgcn_readfirstlane(M.shift[0]);
+#pragma unroll
+    for (int r = 1; r < RR; ++r) {
+        const unsigned other = __builtin_amdgcn_readfirstlane(M.shift[r]);
+        sh = e >= M.end[r - 1] ? other : sh;
+    }
+    return e < M.end[RR - 1] ? (unsigned)e + sh : zero_slot;
+}
+
+// Up to so many hash rounds RR is the number of rounds; above it rounds RR > R are read as far as they go (a record
+// of R rounds holds at least 6 + 2 R + 6 words) and taken as empty.
+constexpr int EXACT_ROUNDS = 4;
+
+// the records are written once at build time: reading them through the constant
+// address space lets the compiler use scalar loads although the kernel also stores
+typedef const __attribute__((address_space(4))) int *const_int_ptr;
+
+__device__ inline long long record_base(const PassSide &S, long long row)
+{
+    const_int_ptr rec = (const_int_ptr)(S.meta + row * S.meta_stride);
+    return ((long long)rec[1] << 32) | (unsigned)rec[0];
+}
+
+// (an empty record for a row past the last one)
+template <int RR>
+__device__ inline void load_walk(RecordWalk<RR> &W, const PassSide &S, int R, long long row)
+{
+    const bool exists = row < S.rows;
+    const_int_ptr rec = (const_int_ptr)(S.meta + (exists ? row : S.rows - 1) * S.meta_stride);
+#pragma unroll
+    for (int r = 0; r < RR; ++r) {
+        W.shift[r] = (unsigned)rec[6 + 2 * r];
+        const int end = rec[7 + 2 * r];
+        W.end[r] = !exists ? 0 : RR <= EXACT_ROUNDS || r < R ? end : W.end[r > 0 ? r - 1 : 0];
+    }
+}
+
 // Per-row metadata, read from the packed record (see meta_kernel): wave-uniform,
 // so it lives in scalar registers.
 template <int RR>
@@ -166,8 +284,7 @@ struct RowMeta {
     long long base;
     float marg;
     double log_marg;
-    int vstart[RR];
-    int len[RR];
+    RecordWalk<RR> walk;
     int pos;     // lane r < R: position of the row in round r's bucket order
     double lin;  // query mode: the row's current scaling
 };
@@ -175,18 +292,11 @@ struct RowMeta {
 template <int RR, int MODE>
 __device__ inline void load_meta(RowMeta<RR> &M, const PassSide &S, int R, long long row, int lane)
 {
-    // the records are written once at build time: reading them through the constant
-    // address space lets the compiler use scalar loads although the kernel also stores
-    typedef const __attribute__((address_space(4))) int *const_int_ptr;
     const_int_ptr rec = (const_int_ptr)(S.meta + row * S.meta_stride);
     M.base = ((long long)rec[1] << 32) | (unsigned)rec[0];
     M.marg = __int_as_float(rec[2]);
     M.log_marg = __hiloint2double(rec[5], rec[4]);
-#pragma unroll
-    for (int r = 0; r < RR; ++r) {
-        M.vstart[r] = r < R ? rec[6 + 2 * r] : 0;
-        M.len[r] = r < R ? rec[7 + 2 * r] : 0;
-    }
+    load_walk<RR>(M.walk, S, R, row);
     M.pos = (MODE != PASS_QUERY && lane < R) ? rec[6 + 2 * R + lane] : 0;
     M.lin = MODE == PASS_QUERY ? S.lin_out[row] : 0.0;
 }
@@ -203,8 +313,10 @@ constexpr unsigned long long ACC_PENDING = 0x7FF8A5A55A5AC3C3ull;
 struct FuseArgs {
     const double *prev_partial;  // [prev_groups][lp + 3] partial sums the previous sweep left
     int prev_groups;
+    int direct;                  // every workgroup takes the totals for itself
     double *acc;                 // where the totals go: this sweep's input accumulator (lp + 2 entries)
-    double *shift_other;         // exponent of the other side's vector (the previous sweep's own)
+    const double *shift_other;   // exponent of the other side's vector (the previous sweep's own)
+    double *shift_next;          // the exponent of the other side's next vector
     const double *shift_self;    // exponent of this side's vector
     double *mark_pending;        // accumulator the NEXT sweep reduces into (nullable): filled with ACC_PENDING
     unsigned long long *timeouts;
@@ -219,49 +331,129 @@ __device__ inline void mark_pending(const FuseArgs &Fz, int lp)
         for (int k = threadIdx.x; k <= lp + 1; k += 64) ((unsigned long long *)Fz.mark_pending)[k] = ACC_PENDING;
 }
 
-// The sum of the per-workgroup partials in the fixed order of
-// reduce_partials_kernel (bitwise the same result), by workgroup `b` for its 64
-// entries, published with device-scope stores.  Nothing here waits, so a
-// reducing workgroup always gets through.
-__device__ inline void reduce_publish(const FuseArgs &Fz, int b, int lp, double *red)
+// The total of a column of the partial sums is taken in one fixed order everywhere, whoever takes it: row g belongs
+// to running sum g % 64; the four of them with the same g % 16 are added up in turn, then four such sums 4 q .. 4 q + 3
+// in turn, and the four results as (0 + 2) + (1 + 3).  The last column's total is a maximum.
+constexpr int REDUCE_COLUMNS = 16;
+__device__ inline double join_sums(bool is_max, double a, double b) { return is_max ? fmax(a, b) : a + b; }
+
+// By one workgroup of 1024 threads for 16 columns: lane l of wavefront w has row 4 w + l / 16 and every 64th after it,
+// 256 rows being four loads per lane.  Column 16 b + l % 16 is returned in lanes 0 .. 15 of wavefront 0.  red: [64][16]
+// doubles of LDS.  (64 columns per workgroup, 16 loads per lane: a compute unit then has to bring in 131 KB by itself,
+// and the totals of 259 columns were there 3.3 us after the start of the sweep instead of 2.5.)
+__device__ inline double reduce_columns(const double *__restrict__ partial, int groups, int stride, int b, int max_column,
+                                        double *red)
 {
-    double *acc = Fz.acc;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nw = blockDim.x >> 6;
-    const int stride = lp + 3;
-    const int k = b * 64 + lane;
-    const bool is_max = k == lp + 2;
-    // 16 running sums as in reduce_partials_kernel (sum a takes partials a, a + 16, ...),
-    // shared out among the wavefronts this workgroup has
-    for (int a = wave; a < 16; a += nw) {
-        double s = is_max ? -INFINITY : 0.0;
-        if (k < stride) {
-#pragma unroll 16
-            for (int g = a; g < Fz.prev_groups; g += 16) {
-                const double v = Fz.prev_partial[(long long)g * stride + k];
-                s = is_max ? fmax(s, v) : s + v;
-            }
-        }
-        red[a * 64 + lane] = s;
+    const int col = lane & 15, sub = lane >> 4, k = REDUCE_COLUMNS * b + col;
+    const bool is_max = k == max_column;
+    const double none = is_max ? -INFINITY : 0.0;
+    double s = none;
+    if (k < stride) {
+#pragma unroll 4
+        for (int g = 4 * wave + sub; g < groups; g += 64) s = join_sums(is_max, s, partial[(long long)g * stride + k]);
     }
+    red[(4 * wave + sub) * 16 + col] = s;
     __syncthreads();
-    if (wave == 0 && k < stride) {
-        double s = is_max ? -INFINITY : 0.0;
+    s = none;
+    if (wave == 0) {
 #pragma unroll
-        for (int w = 0; w < 16; ++w) s = is_max ? fmax(s, red[w * 64 + lane]) : s + red[w * 64 + lane];
-        if (k < lp) {
-            __hip_atomic_store(acc + k, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (is_max) {
-            // the exponent the previous sweep's vector was stored with, and the factor
-            // exp(-m_in - m_self) this sweep applies to its results
-            const double m_in = *Fz.shift_other;
-            __hip_atomic_store(acc + lp, m_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(acc + lp + 1, exp(-m_in - *Fz.shift_self), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            *Fz.shift_other = (s > -INFINITY && s < INFINITY) ? s : 0.0;
+        for (int w = 4 * sub; w < 4 * sub + 4; ++w) {
+            double r = red[w * 16 + col];
+#pragma unroll
+            for (int q = 1; q < 4; ++q) r = join_sums(is_max, r, red[(w + 16 * q) * 16 + col]);
+            s = w == 4 * sub ? r : join_sums(is_max, s, r);
+        }
+        double o = s;
+        lane_swap<32>(s, o);
+        s = join_sums(is_max, s, o);
+        o = s;
+        lane_swap<16>(s, o);
+        s = join_sums(is_max, s, o);
+    }
+    return s;
+}
+
+// The totals of the previous sweep's partial sums (bitwise those of reduce_partials_kernel), 16 columns per
+// workgroup, published with device-scope stores by the first workgroups of the grid (in turns if it has fewer
+// than there are columns for).  Nothing here waits, so a reducing workgroup always gets through.
+// (With the partial sums requested first and added up only after the workgroup's rows had been requested a sweep
+// is slower, 15.8 against 13.7 us at 20 000 rows of 256 entries: loads return in order, so everybody's totals then
+// wait for those rows.)
+__device__ inline void reduce_publish(const FuseArgs &Fz, int lp, double *red)
+{
+    const int stride = lp + 3, blocks = (stride + REDUCE_COLUMNS - 1) / REDUCE_COLUMNS;
+    for (int b = blockIdx.x; b < blocks; b += gridDim.x) {
+        // what the last column needs besides is requested with the sums: the exponent the previous sweep's vector
+        // was stored with, and this side's
+        const double m_in = *Fz.shift_other, m_self = *Fz.shift_self;
+        if (b != (int)blockIdx.x) __syncthreads();   // the previous turn has read the sums
+        const double s = reduce_columns(Fz.prev_partial, Fz.prev_groups, stride, b, lp + 2, red);
+        const int k = REDUCE_COLUMNS * b + threadIdx.x;
+        if (threadIdx.x < REDUCE_COLUMNS && k < stride) {
+            if (k < lp) {
+                __hip_atomic_store(Fz.acc + k, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else if (k == lp + 2) {
+                // ... and the factor exp(-m_in - m_self) this sweep applies to its results
+                __hip_atomic_store(Fz.acc + lp, m_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(Fz.acc + lp + 1, exp(-m_in - m_self), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                *Fz.shift_next = (s > -INFINITY && s < INFINITY) ? s : 0.0;
+            }
         }
     }
 }
+
+// Up to 64 factor columns and 64 partial sums: every workgroup takes the totals for itself (at most 34 KB from the
+// cache) and nothing has to be handed over: a store, a trip through memory and the wait for it less per sweep (1024
+// rows: 5.8 us instead of 6.5).  With 256 partial sums, 137 KB, it is the slower way (50 000 rows: 8.9 against 8.5).
+// Wavefront w has the rows g % 16 == w, a lane a column; all loads are requested at once, before the workgroup's own
+// rows are.  The exponents exist twice (shift_other is read by every workgroup, shift_next written by one).
+constexpr int DIRECT_GROUPS = 64;
+struct DirectTotals {
+    double v[4], top, m_in, m_self;
+    __device__ inline void request(const FuseArgs &Fz, int lp)
+    {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, stride = lp + 3, last = Fz.prev_groups - 1;
+        m_in = *Fz.shift_other;
+        m_self = *Fz.shift_self;
+        const double *__restrict__ at = Fz.prev_partial + lane;
+        // (a row past the last one repeats it and is not added)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = at[(wave + 16 * u < last ? wave + 16 * u : last) * stride];
+        // (the first wavefront: a row per lane)
+        top = wave == 0 ? Fz.prev_partial[(lane < last ? lane : last) * stride + lp + 2] : -INFINITY;
+    }
+    // the total of column `lane` (lp = 64); red: [16][64] doubles of LDS
+    __device__ inline double finish(const FuseArgs &Fz, int lp, double *red, double &m_in_out, double &e_out)
+    {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        double r = wave < Fz.prev_groups ? v[0] : 0.0;
+#pragma unroll
+        for (int q = 1; q < 4; ++q) r += wave + 16 * q < Fz.prev_groups ? v[q] : 0.0;
+        red[wave * 64 + lane] = r;
+        m_in_out = m_in;
+        e_out = exp(-m_in - m_self);   // the factor this sweep applies to its results
+        __syncthreads();
+        double p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            p[q] = red[4 * q * 64 + lane];
+#pragma unroll
+            for (int j = 1; j < 4; ++j) p[q] += red[(4 * q + j) * 64 + lane];
+        }
+        const double s = (p[0] + p[2]) + (p[1] + p[3]);
+        if (blockIdx.x == 0 && wave == 0) {   // for queries and derivatives after the run, and for the next sweep
+            Fz.acc[lane] = s;
+            if (lane == 0) {
+                Fz.acc[lp] = m_in;
+                Fz.acc[lp + 1] = e_out;
+            }
+            const double m = wave_max(top);
+            if (lane == 0) *Fz.shift_next = (m > -INFINITY && m < INFINITY) ? m : 0.0;
+        }
+        return s;
+    }
+};
 
 // Reads the totals (lp + 2 doubles) into `ysh`, re-reading until the reducing
 // workgroups of this launch have replaced every pending entry (bounded wait).
@@ -286,6 +478,25 @@ __device__ inline void fused_fetch(const FuseArgs &Fz, const double *acc, int lp
             if (lane == 0) atomicAdd(Fz.timeouts, 1ull);
             give_up = true;
         }
+    }
+}
+
+// The totals into every wavefront's registers, by whichever of the two ways (the workgroup's row requests stand
+// between the request of the partial sums and this).
+template <int T>
+__device__ inline void take_totals(const FuseArgs &Fz, const double *acc_in, int lp, double *ysh, DirectTotals &totals,
+                                   double (&yreg)[T], double &m_in, double &e_out)
+{
+    const int lane = threadIdx.x & 63;
+    if (T == 1 && Fz.direct) {
+        yreg[0] = totals.finish(Fz, lp, ysh + lp + 2, m_in, e_out);
+    } else {
+        if (threadIdx.x < 64) fused_fetch(Fz, acc_in, lp, ysh);
+        __syncthreads();
+        m_in = ysh[lp];
+        e_out = ysh[lp + 1];
+#pragma unroll
+        for (int t = 0; t < T; ++t) yreg[t] = ysh[FRow<T>::kidx(t, lane)];
     }
 }
 
@@ -330,9 +541,18 @@ __device__ inline void group_partials(const double (&zacc)[T], double q0, double
 inline size_t pass_lds_bytes(int lp, bool fused)
 {
     size_t doubles = (size_t)(PASS_WAVES / 2) * (lp + 3);
-    if (fused) doubles += (size_t)lp + 2 + 16 * 64;
+    if (fused) doubles += (size_t)lp + 2 + 64 * REDUCE_COLUMNS;
     return sizeof(double) * doubles;
 }
+
+// sweeps with a sparse part by the length of the factor rows: up to 128 entries, up to 256, more
+hipError_t launch_short_sweep(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
+                              double *partial, unsigned long long *cnt, hipStream_t s);
+hipError_t launch_mid_sweep(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
+                            double *partial, unsigned long long *cnt, hipStream_t s);
+hipError_t launch_long_sweep(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
+                             double *partial, unsigned long long *cnt, hipStream_t s);
+int rows_at_a_time(const Handle &h, long long rows);
 
 // sweeps without a sparse part (kernels_nystrom.hip), and how many workgroups (partial sums) one has
 hipError_t launch_nystrom_pass(const PassSide &S, const Handle &h, int mode, const FuseArgs *fuse, bool fused_in,

@@ -1,248 +1,10 @@
-// The Sinkhorn half-iteration (Sec. 2 eq. 2 on the decomposed kernel of Sec. 4):
-// for every row i of one side
-//     s_i   = F_i . acc_in  +  (row record of sparse values) . (gathered scalings)
-//     out_i = marg_i / s_i
-// and, in the same sweep, acc_out = F^T out for the other side's next sweep.
-// For the rows of X: F = U, acc_in = y = W v, acc_out = z = U^T u.
-// For the rows of Y: F = W^T, acc_in = z, acc_out = y.
-// Each stored value (factor entry or sparse value) is read exactly once per
-// sweep.  One wavefront owns a row: consecutive lanes read consecutive
-// addresses of the factor row and of the row's record of sparse values; the
-// next row's factor entries and metadata are requested before the current
-// row is reduced, so that a wave always has loads in flight.
-//
-// Log-domain stabilisation (App. "Implementational details"): the state is the
-// natural log of each scaling (fp32, what is reported).  Because the Nystrom
-// part and the correction have signed entries the kernel cannot itself be held
-// as logs, so the largest exponent is taken out per vector instead: the working
-// copy of a scaling vector is exp(log x - M) in fp64, with M the largest log of
-// that vector one iteration earlier (any reference works; logs move slowly), and
-// M travels with every quantity derived from the vector.  Products are
-// accumulated in fp64.
+// The half-iteration's host side, the sweeps of kernels held as logs (sparse, dense) and the reduction of the
+// partial sums; the sweeps with factors are in sweep.h and kernels_sweep_long.hip.
 #include <atomic>
 
 #include "iter_common.h"
 
 namespace lcn {
-
-// FUSED (update sweeps after the first of a run): the previous sweep's partial
-// sums have not been added up yet.  The first ceil((lp + 3) / 64) workgroups of
-// this launch do that before their own rows and publish the totals; every
-// workgroup requests its first rows, then waits for the totals (bounded wait;
-// the reducing workgroups have the lowest indices, are dispatched first and
-// wait for nothing, so the wait ends).  This saves a dependent kernel launch
-// per sweep without any device-wide fence.
-template <int T, int RR, int MODE, bool FUSED>
-__global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, int lp, double *partial,
-                                                            unsigned long long *counters, FuseArgs Fz)
-{
-    // Entries of a segment requested with the row, in wavefronts: two where few rounds and short factor rows leave
-    // requests to spare (segments of 40 to 300 entries: 18.5 against 19.6 us per sweep at 40 000 rows, one round;
-    // 12.8 against 13.3 at 10 000 rows, two rounds; three or four gain nothing more), one otherwise (two
-    // rounds of rows of 512 entries: 95 against 98 us)
-    constexpr int W = RR <= 2 && T <= 4 ? 2 : 1;
-    extern __shared__ double zsh[];  // [PASS_WAVES / 2][lp + 3], then [lp + 2] and [16][64] if FUSED
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long nwaves = (long long)gridDim.x * PASS_WAVES;
-    // Rows are dealt out from the last workgroup down: the reducing workgroups of a fused
-    // sweep (the first few) start late, so they get the row slots that may hold one row less.
-    // The dealing is the same with and without fusion, so both give the same bits.
-    const long long gw = (long long)(gridDim.x - 1 - blockIdx.x) * PASS_WAVES + wave;
-    const int stride = lp + 3;
-    // exponents taken out of this side's vector (m_self) and of the input vectors (m_in)
-    // (a query reads the exponent its vector was stored with, kept beside the accumulator it produced)
-    if (MODE == PASS_UPDATE) mark_pending(Fz, lp);
-    if (FUSED && (int)blockIdx.x < (stride + 63) / 64)
-        reduce_publish(Fz, blockIdx.x, lp, zsh + (size_t)(PASS_WAVES / 2) * stride + lp + 2);
-    const double m_self = MODE == PASS_QUERY ? S.acc_out[lp] : *S.shift_self;
-    double m_in = 0.0, e_out = 1.0;
-    double maxlog = -INFINITY;
-
-    double yreg[T], zacc[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        yreg[t] = 0.0;
-        zacc[t] = 0.0;
-    }
-    if (!FUSED) {
-        m_in = MODE != PASS_INIT ? S.acc_in[lp] : 0.0;
-        e_out = MODE == PASS_UPDATE ? exp(-m_in - m_self) : (MODE == PASS_QUERY ? exp(m_in + m_self) : 1.0);
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-            yreg[t] = MODE != PASS_INIT ? S.acc_in[FRow<T>::kidx(t, lane)] : 0.0;
-    }
-    double q0 = 0.0, q1 = 0.0;
-    unsigned long long nonpos = 0, range = 0;
-
-    // Three-stage software pipeline over the rows a wave owns: metadata is read
-    // two rows ahead (scalar loads), the factor row and the first 64 W entries of
-    // every round's segment one row ahead, and the current row is reduced while
-    // those loads are in flight.
-    struct RowData {
-        FRow<T> f;
-        float tv[RR][W];
-        float vv[RR][W];
-    };
-    // The bucket-ordered copies of the scalings are single precision in this kernel (the buffers are
-    // sized for doubles; the logarithmic kernels keep doubles there): they are gathered once per
-    // stored value, and at half the size they stay in the per-die cache beside the streamed rows.
-    // The exponent taken out keeps the largest entry near one, and the copies are stored times
-    // PERM_SCALE = 2^64 (exact): single precision then holds entries from 2^-190 (e^-131) below the
-    // vector's largest up to 2^63 (e^43) above it.  A sum's sparse part is scaled back before the
-    // factor part is added.  An entry that grows past that within one iteration overflows its copy:
-    // counted, and the run is reported as failed (LCN_ERR_RANGE).
-    const float *__restrict__ perm_in = reinterpret_cast<const float *>(S.perm_in);
-    float *__restrict__ perm_out = reinterpret_cast<float *>(S.perm_out);
-    // Loads are issued for whole wavefront-wide chunks without predication: lanes
-    // beyond a segment's length read the next stored values (masked when used; the
-    // arrays end with 64 W, that is 128, entries of slack) and the zero slot behind the gathered vector.
-    const unsigned zero_slot = (unsigned)(R * S.rows_in);
-    auto issue = [&](RowData &D, const RowMeta<RR> &M, long long r) {
-        D.f.load(S.F, r, lp, lane);
-        if (MODE != PASS_INIT) {
-            const float *__restrict__ vals = S.vals + M.base;
-            unsigned off = lane;
-#pragma unroll
-            for (int q = 0; q < RR; ++q) {
-#pragma unroll
-                for (int w = 0; w < W; ++w) {
-                    D.tv[q][w] = vals[off + 64 * w];
-                    D.vv[q][w] = perm_in[lane + 64 * w < M.len[q] ? (unsigned)M.vstart[q] + lane + 64 * w : zero_slot];
-                }
-                off += (unsigned)M.len[q];
-            }
-        }
-    };
-    RowData cur{}, nxt{};
-    RowMeta<RR> mc{}, mn{}, mn2{};
-    const int Rm = MODE == PASS_INIT ? 0 : R;
-    long long row = gw, next = gw + nwaves, next2 = gw + 2 * nwaves;
-    if (row < S.rows) {
-        load_meta<RR, MODE>(mc, S, Rm, row, lane);
-        if (MODE == PASS_INIT && lane < R) mc.pos = S.meta[row * S.meta_stride + 6 + 2 * R + lane];
-        issue(cur, mc, row);
-    }
-    if (next < S.rows) {
-        load_meta<RR, MODE>(mn, S, Rm, next, lane);
-        if (MODE == PASS_INIT && lane < R) mn.pos = S.meta[next * S.meta_stride + 6 + 2 * R + lane];
-    }
-    if (FUSED) {
-        double *ysh = zsh + (size_t)(PASS_WAVES / 2) * stride;
-        if (wave == 0) fused_fetch(Fz, S.acc_in, lp, ysh);
-        __syncthreads();
-        m_in = ysh[lp];
-        e_out = ysh[lp + 1];
-#pragma unroll
-        for (int t = 0; t < T; ++t) yreg[t] = ysh[FRow<T>::kidx(t, lane)];
-    }
-    // one row: `C` holds the row's data, `N` receives the next row's
-    auto step = [&](RowData &C, RowData &N) {
-        if (next < S.rows) issue(N, mn, next);
-        if (next2 < S.rows) {
-            load_meta<RR, MODE>(mn2, S, Rm, next2, lane);
-            if (MODE == PASS_INIT && lane < R) mn2.pos = S.meta[next2 * S.meta_stride + 6 + 2 * R + lane];
-        }
-        double out;
-        if (MODE == PASS_INIT) {
-            const double lo = (double)S.log_out[row];
-            out = exp(lo - m_self);
-            if (lo > maxlog && lo < INFINITY) maxlog = lo;
-        } else {
-            double acc = 0.0;
-#pragma unroll
-            for (int q = 0; q < RR; ++q)
-#pragma unroll
-                for (int w = 0; w < W; ++w)
-                    acc = fma((double)(lane + 64 * w < mc.len[q] ? C.tv[q][w] : 0.f), (double)C.vv[q][w], acc);
-            {   // what is left of segments longer than a wavefront
-                const float *__restrict__ vals = S.vals + mc.base;
-                int off = 0;
-#pragma unroll
-                for (int q = 0; q < RR; ++q) {
-                    if (mc.len[q] > 64 * W) {
-                        // 256 entries per trip, all eight loads requested before the first is used
-                        const float *tp = vals + off;
-                        const float *vp = perm_in + mc.vstart[q];
-                        for (int e0 = 64 * W; e0 < mc.len[q]; e0 += 256) {
-                            float tt[4];
-                            float pv[4];
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                const int e = e0 + 64 * k + lane;
-                                const bool ok = e < mc.len[q];
-                                tt[k] = tp[ok ? e : 0];
-                                pv[k] = vp[ok ? e : 0];
-                                if (!ok) tt[k] = 0.f;
-                            }
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) acc = fma((double)tt[k], (double)pv[k], acc);
-                        }
-                    }
-                    off += mc.len[q];
-                }
-            }
-            acc *= PERM_UNSCALE;
-#pragma unroll
-            for (int t = 0; t < T; ++t) acc = fma((double)C.f.f[t], yreg[t], acc);
-            const double s = wave_sum(acc);
-            const double marg = (double)mc.marg;
-            if (MODE == PASS_UPDATE) {
-                float lo;
-                if (s > 0.0) {
-                    out = marg * fast_rcp(s) * e_out;
-                    const double lg = mc.log_marg - fast_log(s) - m_in;
-                    lo = (float)lg;
-                    maxlog = fmax(maxlog, lg);
-                } else {
-                    out = NAN;
-                    lo = NAN;
-                    ++nonpos;
-                }
-                if (lane == 0) S.log_out[row] = lo;
-            } else {  // PASS_QUERY
-                out = mc.lin;
-                const double ri = out * s * e_out;
-                if (lane == 0 && S.marg_out) S.marg_out[row] = (float)ri;
-                if (out > 0.0) q0 += ri * (log(out) + m_self);
-                q1 += fabs(ri - marg);
-            }
-        }
-        if (MODE != PASS_QUERY) {
-            if (lane == 0) S.lin_out[row] = out;
-            const float outf = (float)(out * PERM_SCALE);
-            if (outf == INFINITY) ++range;
-            if (lane < R) perm_out[(long long)lane * S.rows + mc.pos] = outf;
-#pragma unroll
-            for (int t = 0; t < T; ++t) zacc[t] = fma((double)C.f.f[t], out, zacc[t]);
-        }
-        mc = mn;
-        mn = mn2;
-        row = next;
-        next = next2;
-        next2 += nwaves;
-    };
-    if (T < 6) {
-        // the two data buffers swap roles from row to row (no register copies)
-        while (row < S.rows) {
-            step(cur, nxt);
-            if (row >= S.rows) break;
-            step(nxt, cur);
-        }
-    } else {
-        // long factor rows: one copy of the loop body keeps the kernel within its registers
-        while (row < S.rows) {
-            step(cur, nxt);
-            cur = nxt;
-        }
-    }
-
-    group_partials<T>(zacc, q0, q1, maxlog, lp, zsh, partial);
-    if (lane == 0 && (nonpos | range)) {
-        if (nonpos) atomicAdd(&counters[0], nonpos);
-        if (range) atomicAdd(&counters[6], range);
-    }
-}
 
 // The half-iteration for kernels without signed parts (sparse K^sp, and the
 // dense kernel as its one-bucket case), entirely in logs: the stored values
@@ -250,133 +12,149 @@ __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, i
 // is a log-sum-exp (App. "Implementational details") with a running maximum per
 // lane, so that scalings may drift arbitrarily far (a sparse kernel need not
 // have support, App. "Limitations") without over- or underflow.
-template <int RR, int MODE>
-__global__ __launch_bounds__(PASS_THREADS) void logpass_kernel(PassSide S, int R, double *partial,
-                                                               unsigned long long *counters, int empty_slot)
+//
+// G lanes work on a row (16 or 32), a workgroup on 256 / G rows, and an update has a workgroup for
+// every 256 / G rows there are: nothing is carried from row to row, so it is the chip that refills its compute units.
+// The record is walked flat (see pass_kernel), G U entries at a time, all loads of a trip requested together.
+// What bounds it: rows of some twenty entries, the launch and three trips to memory one after the other (record,
+// values and scalings, stores); rows of some hundred entries, the values and the gathered scalings (8 bytes each).
+template <int RR, int G, int U, int MODE>
+__global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double *partial, unsigned long long *counters,
+                                                      int empty_slot)
 {
-    __shared__ double qsh[PASS_WAVES][2];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long nwaves = (long long)gridDim.x * PASS_WAVES;
+    constexpr int RPB = 256 / G;
+    __shared__ double qsh[4][2];
+    __shared__ int empty_rows;
+    const int sub = threadIdx.x % G;
     double q0 = 0.0, q1 = 0.0;
-    unsigned long long empty = 0;
-
-    RowMeta<RR> mc{}, mn{};
-    long long row = (long long)blockIdx.x * PASS_WAVES + wave;
-    if (row < S.rows) load_meta<RR, MODE>(mc, S, R, row, lane);
-    while (row < S.rows) {
-        const long long next = row + nwaves;
+    if (MODE == PASS_UPDATE) {
+        if (threadIdx.x == 0) empty_rows = 0;
+        __syncthreads();
+    }
+    // (an update and the initial copies run through this once)
+    for (long long r0 = (long long)blockIdx.x * RPB; r0 < S.rows; r0 += (long long)gridDim.x * RPB) {
+        long long row = r0 + threadIdx.x / G;
+        const bool exists = row < S.rows;
+        if (!exists) row = S.rows - 1;   // worked on again, not written
         double lg;
         if (MODE == PASS_INIT) {
-            if (next < S.rows) load_meta<RR, MODE>(mn, S, R, next, lane);
             lg = (double)S.log_out[row];
         } else {
-            const float *__restrict__ vals = S.vals + mc.base;
-            // f(log kernel value, log scaling) for every stored entry of the row; a lane past the end
-            // of a piece passes a scaling of -infinity
-            auto walk = [&](auto &&f) {
-                float k0[RR];
-                double p0[RR];
-                int segoff[RR];
-                int total_len = 0;
+            // what takes an entry's number to its place in the gathered vector: place[0], and from the end of
+            // every round on place[r] more
+            long long base;
+            float marg;
+            double log_marg;
+            int end[RR];
+            unsigned place[RR];
+            {
+                const int *rec = S.meta + row * S.meta_stride;
+                base = ((long long)rec[1] << 32) | (unsigned)rec[0];
+                marg = __int_as_float(rec[2]);
+                log_marg = __hiloint2double(rec[5], rec[4]);
+                unsigned before = 0u;
 #pragma unroll
                 for (int r = 0; r < RR; ++r) {
-                    segoff[r] = total_len;
-                    total_len += mc.len[r];
-                    const bool in = lane < mc.len[r];
-                    k0[r] = in ? vals[segoff[r] + lane] : 0.f;
-                    p0[r] = in ? S.perm_in[mc.vstart[r] + lane] : -INFINITY;
+                    const unsigned shift = (unsigned)rec[6 + 2 * r];
+                    place[r] = shift - before;
+                    before = shift;
+                    const int e = rec[7 + 2 * r];
+                    end[r] = RR <= EXACT_ROUNDS || r < R ? e : end[r > 0 ? r - 1 : 0];
                 }
+            }
+            const double prev = S.lin_out[row];   // what the row's current scaling was computed from
+            const float *__restrict__ vals = S.vals + base;
+            const int total = end[RR - 1];
+            // f(log kernel value, log scaling, whether there is such an entry)
+            auto walk = [&](auto &&f) {
+                for (int e0 = 0; e0 < total; e0 += G * U) {
+                    float k[U];
+                    double p[U];
 #pragma unroll
-                for (int r = 0; r < RR; ++r) f(k0[r], p0[r]);
+                    for (int u = 0; u < U; ++u) {
+                        int e = e0 + G * u + sub;
+                        e = e < total ? e : total - 1;   // past the end: the last entry again, not counted
+                        unsigned at = (unsigned)e + place[0];
 #pragma unroll
-                for (int r = 0; r < RR; ++r) {
-                    if (mc.len[r] > 64) {
-                        const float *tp = vals + segoff[r];
-                        const double *vp = S.perm_in + mc.vstart[r];
-                        // four wavefront-wide pieces per trip, all eight loads requested before the first use
-                        for (int e0 = 64 + lane; e0 < mc.len[r]; e0 += 256) {
-                            float kv[4];
-                            double pv[4];
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const int e = e0 + 64 * q;
-                                const bool in = e < mc.len[r];
-                                kv[q] = in ? tp[e] : 0.f;
-                                pv[q] = in ? vp[e] : -INFINITY;
-                            }
-#pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                if (e0 - lane + 64 * q < mc.len[r])   // the same in every lane: whole pieces are skipped
-                                    f(kv[q], pv[q]);
-                        }
+                        for (int r = 1; r < RR; ++r) at += e >= end[r - 1] ? place[r] : 0u;
+                        k[u] = vals[(unsigned)e];
+                        p[u] = S.perm_in[at];
                     }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) f(k[u], p[u], e0 + G * u + sub < total);
                 }
             };
-            // The row's log-sum-exp.  First with the row's previous value as the shift (what its current
-            // scaling was computed from: near the answer, so the terms are of order one): one subtraction,
+            auto sum_lanes = [&](double v) { return G == 32 ? half_sum(v) : row_sum(v); };
+            // The row's log-sum-exp.  First with the row's previous value as the shift (near the answer, so the
+            // terms are of order one): one subtraction,
             // one single-precision exp and one addition per entry.  If that shift is unusable (no previous
             // value, or the sum leaves single precision's range) the row is walked again with a running
             // maximum per lane, which cannot over- or underflow.
-            const double prev = MODE == PASS_QUERY ? mc.lin : S.lin_out[row];
-            const double shift = mc.log_marg - prev;
-            if (next < S.rows) load_meta<RR, MODE>(mn, S, R, next, lane);
-            double lse;
+            const double shift = log_marg - prev;
+            double lse = 0.0;
             bool done = false;
-            if (shift > -INFINITY && shift < INFINITY) {
+            if (shift > -INFINITY && shift < INFINITY) {   // the same in every lane of the row
                 float accf = 0.f;
-                walk([&](float k, double pl) { accf += __expf(k + (float)(pl - shift)); });
-                const double tot = wave_sum((double)accf);
+                walk([&](float k, double pl, bool in) {
+                    const float t = __expf(k + (float)(pl - shift));
+                    accf += in ? t : 0.f;
+                });
+                const double tot = sum_lanes((double)accf);
                 if (tot > 1e-30 && tot < 1e30) {
                     lse = shift + fast_log(tot);
                     done = true;
                 }
             }
-            if (!done) {   // the same in every lane
+            if (!done) {
                 double mx = -INFINITY, sm = 0.0;
-                walk([&](float k, double pl) { lse_step((double)k + pl, mx, sm); });
-                const double M = wave_max(mx);
+                walk([&](float k, double pl, bool in) { lse_step(in ? (double)k + pl : -INFINITY, mx, sm); });
+                const double M = G == 32 ? half_max(mx) : row_max(mx);
                 const double part = mx > -INFINITY ? sm * exp(mx - M) : 0.0;
-                const double ssum = wave_sum(part);
+                const double ssum = sum_lanes(part);
                 lse = ssum > 0.0 ? M + log(ssum) : -INFINITY;
             }
             if (MODE == PASS_UPDATE) {
                 if (lse > -INFINITY) {
-                    lg = mc.log_marg - lse;
+                    lg = log_marg - lse;
                 } else {  // no kernel entry reaches this point: it carries no mass
                     lg = -INFINITY;
-                    ++empty;
+                    if (exists && sub == 0) atomicAdd(&empty_rows, 1);
                 }
-                if (lane == 0) S.log_out[row] = (float)lg;
+                if (exists && sub == 0) S.log_out[row] = (float)lg;
             } else {  // PASS_QUERY
-                lg = mc.lin;
+                lg = prev;
                 const double ri = (lg > -INFINITY && lse > -INFINITY) ? exp(lg + lse) : 0.0;
-                if (lane == 0 && S.marg_out) S.marg_out[row] = (float)ri;
-                if (ri != 0.0) q0 += ri * lg;
-                q1 += fabs(ri - (double)mc.marg);
+                if (exists && sub == 0) {
+                    if (S.marg_out) S.marg_out[row] = (float)ri;
+                    if (ri != 0.0) q0 += ri * lg;
+                    q1 += fabs(ri - (double)marg);
+                }
             }
         }
-        if (MODE != PASS_QUERY) {
-            if (lane == 0) S.lin_out[row] = lg;
-            if (lane < R) S.perm_out[(long long)lane * S.rows + mc.pos] = lg;
+        if (MODE != PASS_QUERY && exists) {
+            if (sub == 0) S.lin_out[row] = lg;
+            if (sub < R) S.perm_out[(long long)sub * S.rows + S.meta[row * S.meta_stride + 6 + 2 * R + sub]] = lg;
         }
-        mc = mn;
-        row = next;
     }
     if (MODE == PASS_QUERY) {
-        if (lane == 0) {
-            qsh[wave][0] = q0;
-            qsh[wave][1] = q1;
+        q0 = wave_sum(q0);
+        q1 = wave_sum(q1);
+        if ((threadIdx.x & 63) == 0) {
+            qsh[threadIdx.x >> 6][0] = q0;
+            qsh[threadIdx.x >> 6][1] = q1;
         }
         __syncthreads();
         if (threadIdx.x < 3) {
             double s = threadIdx.x == 2 ? -INFINITY : 0.0;
             if (threadIdx.x < 2)
-                for (int w = 0; w < PASS_WAVES; ++w) s += qsh[w][threadIdx.x];
+                for (int w = 0; w < 4; ++w) s += qsh[w][threadIdx.x];
             partial[(long long)blockIdx.x * 3 + threadIdx.x] = s;
         }
     }
-    if (lane == 0 && empty) atomicAdd(&counters[empty_slot], empty);
+    if (MODE == PASS_UPDATE) {
+        __syncthreads();
+        if (threadIdx.x == 0 && empty_rows) atomicAdd(&counters[empty_slot], (unsigned long long)empty_rows);
+    }
 }
 
 // The dense kernel (one bucket, one round): every row multiplies the same vector, so a workgroup
@@ -403,8 +181,8 @@ __global__ __launch_bounds__(64 * DENSE_WAVES) void logpass_dense_kernel(PassSid
 #pragma unroll
         for (int i = 0; i < DENSE_ROWS; ++i)   // rows past the end repeat the last row and are dropped below
             load_meta<1, MODE>(mt[i], S, 1, r0 + i < S.rows ? r0 + i : S.rows - 1, lane);
-        const int len = mt[0].len[0];
-        const double *__restrict__ vp = S.perm_in + mt[0].vstart[0];
+        const int len = mt[0].walk.end[0];
+        const double *__restrict__ vp = S.perm_in + mt[0].walk.shift[0];
         // two wavefront-wide pieces per trip; the next trip's loads are requested before this trip's
         // values are used
         auto fetch = [&](int e0, double (&p)[2], float (&k)[DENSE_ROWS][2]) {
@@ -557,8 +335,7 @@ __global__ __launch_bounds__(64 * DENSE_WAVES) void logpass_dense_kernel(PassSid
 }
 
 // Adds the per-workgroup partial sums of a sweep in a fixed order (so the
-// result does not depend on timing).  One workgroup per 64 entries; wave w adds
-// the partials of workgroups w, w + 16, ..., then the 16 wave sums are added.
+// result does not depend on timing), 16 columns per workgroup.
 // Entry lp + 2 is a maximum (the largest log scaling of the sweep), which
 // becomes this side's exponent for the next sweep; entry lp of the output
 // accumulator records the exponent that this sweep's vector was stored with.
@@ -566,24 +343,10 @@ __global__ __launch_bounds__(1024) void reduce_partials_kernel(const double *__r
                                                                int stride, int lp, double *acc_out,
                                                                double *query_out, double *shift_self, int mode)
 {
-    __shared__ double sh[16][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int k = blockIdx.x * 64 + lane;
-    const bool is_max = k == lp + 2;
-    double s = is_max ? -INFINITY : 0.0;
-    if (k < stride) {
-#pragma unroll 16
-        for (int g = wave; g < groups; g += 16) {
-            const double v = partial[(long long)g * stride + k];
-            s = is_max ? fmax(s, v) : s + v;
-        }
-    }
-    sh[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0 && k < stride) {
-        s = is_max ? -INFINITY : 0.0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) s = is_max ? fmax(s, sh[w][lane]) : s + sh[w][lane];
+    __shared__ double red[64 * REDUCE_COLUMNS];
+    const double s = reduce_columns(partial, groups, stride, blockIdx.x, lp + 2, red);
+    const int k = REDUCE_COLUMNS * blockIdx.x + threadIdx.x;
+    if (threadIdx.x < REDUCE_COLUMNS && k < stride) {
         if (k < lp) {
             if (mode != PASS_QUERY) acc_out[k] = s;
         } else if (k < lp + 2) {
@@ -635,34 +398,6 @@ int device_compute_units()
     return cus;
 }
 
-template <int T, int RR>
-static int resident_blocks()
-{
-    int cus = device_compute_units(), per_cu = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pass_kernel<T, RR, PASS_UPDATE, true>, PASS_THREADS,
-                                                     pass_lds_bytes(64 * T, true)) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    (void)hipGetLastError();
-    return cus * per_cu;
-}
-
-// The kernel's loads are unrolled over exactly the hash rounds there are (up to four): a round that does not
-// exist would still cost two wavefront-wide loads per row (unrolled over four whatever their number, a sweep took
-// 23.6 us instead of 19.6 with one round of 51 entries per row, 14.6 instead of 13.1 with two of 46, 16.7
-// instead of 15.9 with three of 15, 109 instead of 105 at 200 000 rows with three).
-template <int T>
-static int resident_blocks_of_rounds(int R)
-{
-    switch (R) {
-        case 1: return resident_blocks<T, 1>();
-        case 2: return resident_blocks<T, 2>();
-        case 3: return resident_blocks<T, 3>();
-        case 4: return resident_blocks<T, 4>();
-        default: return resident_blocks<T, 8>();
-    }
-}
-
 int pass_grid(const Handle &h)
 {
     long long rows = h.n > h.m ? h.n : h.m;
@@ -671,61 +406,33 @@ int pass_grid(const Handle &h)
     if (cap <= 0) {
         if (h.log_domain) {
             cap = 512;
-        } else if (h.R == 0) {
-            cap = device_compute_units();
         } else {
-            switch (h.lp / 64) {
-                case 1: cap = resident_blocks_of_rounds<1>(h.R); break;
-                case 2: cap = resident_blocks_of_rounds<2>(h.R); break;
-                case 3: cap = resident_blocks_of_rounds<3>(h.R); break;
-                case 4: cap = resident_blocks_of_rounds<4>(h.R); break;
-                case 5: cap = resident_blocks_of_rounds<5>(h.R); break;
-                case 6: cap = resident_blocks_of_rounds<6>(h.R); break;
-                case 7: cap = resident_blocks_of_rounds<7>(h.R); break;
-                default: cap = resident_blocks_of_rounds<8>(h.R); break;
-            }
+            cap = device_compute_units();
         }
     }
     return (int)(g < cap ? g : cap);
+}
+
+// Rows a wavefront takes at a time in a sweep with a sparse part: as many as give every wavefront of the chip one
+// group (up to five), else three or five, whichever comes to fewer rows per wavefront.  1024 rows: one 5.6 us, two
+// 5.9, three 6.2; 10 000 rows of 128 entries: two 13.6, three 11.6, five 13.6; 20 000 rows of 256: two 15.1, three
+// 13.8, five 13.3 (eight spill).
+int rows_at_a_time(const Handle &h, long long rows)
+{
+    if (h.lp > 256) return 1;
+    const long long waves = (long long)PASS_WAVES * (h.cus > 0 ? h.cus : 256), each = (rows + waves - 1) / waves;
+    if (each <= 3) return (int)each;
+    if (each <= 5) return 5;
+    const long long three = (rows + 3 * waves - 1) / (3 * waves) * 3, five = (rows + 5 * waves - 1) / (5 * waves) * 5;
+    return three < five ? 3 : 5;
 }
 
 // workgroups of a sweep over `rows` rows (= partial sums it leaves)
 static int sweep_groups(const Handle &h, long long rows)
 {
     if (!h.log_domain && h.R == 0) return nystrom_sweep_groups(h, rows);
-    const long long g = (rows + PASS_WAVES - 1) / PASS_WAVES;
+    const long long per = (long long)PASS_WAVES * rows_at_a_time(h, rows), g = (rows + per - 1) / per;
     return (int)(g < h.grid ? g : h.grid);
-}
-
-template <int T, int RR>
-static hipError_t launch_pass_tr(const PassSide &S, const Handle &h, int mode, const FuseArgs *fuse, bool fused_in,
-                                 double *partial, unsigned long long *cnt, hipStream_t s)
-{
-    const FuseArgs F = fuse ? *fuse : FuseArgs{};
-    const dim3 grid(sweep_groups(h, S.rows)), block(PASS_THREADS);
-    const size_t lds = pass_lds_bytes(h.lp, fused_in);
-    if (mode == PASS_UPDATE && fused_in)
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_UPDATE, true>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
-    else if (mode == PASS_UPDATE)
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_UPDATE, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
-    else if (mode == PASS_QUERY)
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_QUERY, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
-    else
-        hipLaunchKernelGGL((pass_kernel<T, RR, PASS_INIT, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
-    return hipGetLastError();
-}
-
-template <int T>
-static hipError_t launch_pass_t(const PassSide &S, const Handle &h, int mode, const FuseArgs *fuse, bool fused_in,
-                                double *partial, unsigned long long *cnt, hipStream_t s)
-{
-    switch (h.R) {
-        case 1: return launch_pass_tr<T, 1>(S, h, mode, fuse, fused_in, partial, cnt, s);
-        case 2: return launch_pass_tr<T, 2>(S, h, mode, fuse, fused_in, partial, cnt, s);
-        case 3: return launch_pass_tr<T, 3>(S, h, mode, fuse, fused_in, partial, cnt, s);
-        case 4: return launch_pass_tr<T, 4>(S, h, mode, fuse, fused_in, partial, cnt, s);
-        default: return launch_pass_tr<T, 8>(S, h, mode, fuse, fused_in, partial, cnt, s);
-    }
 }
 
 // side 0: rows of X (updates u, consumes y = W v, produces z = U^T u); side 1: rows of Y.
@@ -758,14 +465,51 @@ static PassSide make_side(const Handle &h, int side, int acc_in, int acc_out, fl
     S.acc_out = acc_out >= 0 ? h.acc[acc_out] : nullptr;
     S.marg_out = marg_out;
     S.meta_stride = h.sort.meta_stride;
-    S.shift_self = h.shift + side;
+    S.shift_self = h.shift + 2 * side + h.shift_slot[side];
     return S;
+}
+
+template <int RR, int G, int U>
+static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
+{
+    // a query leaves 3 partial sums per workgroup and there is room for h.grid of them
+    const int lanes = mode == PASS_UPDATE ? G : mode == PASS_QUERY ? 32 : 16;
+    const long long all = (S.rows + 256 / lanes - 1) / (256 / lanes);
+    const int grid = (int)(mode == PASS_QUERY && all > h.grid ? h.grid : all);
+    if (mode == PASS_UPDATE)
+        hipLaunchKernelGGL((logpass_kernel<RR, G, U, PASS_UPDATE>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
+    else if (mode == PASS_QUERY)
+        hipLaunchKernelGGL((logpass_kernel<RR, 32, 4, PASS_QUERY>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
+    else
+        hipLaunchKernelGGL((logpass_kernel<1, 16, 1, PASS_INIT>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
+    return grid;
+}
+
+// Lanes per row by the length of the records: 10 000 rows of 20 stored values 3.6 us per sweep with sixteen lanes
+// and two entries each at a time (a wavefront with four: 6.1; a wavefront per row and a 1024-thread workgroup working
+// through its rows, loads unrolled over four rounds: 6.4); 20 000 rows of 510 values in three rounds 14.8 us with 32
+// lanes and four entries each, 16.3 with sixteen and two, 15.5 with 64 and four (19.6 before).
+template <int RR>
+static int launch_logpass_length(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
+{
+    return h.nnz_stored <= 48 * S.rows ? launch_logpass_rows<RR, 16, 2>(S, h, mode, empty_slot, s)
+                                       : launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);
+}
+
+// returns the workgroups launched
+static int launch_logpass_rounds(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
+{
+    switch (h.R) {
+        case 1: return launch_logpass_length<1>(S, h, mode, empty_slot, s);
+        case 2: return launch_logpass_length<2>(S, h, mode, empty_slot, s);
+        case 3: return launch_logpass_length<3>(S, h, mode, empty_slot, s);
+        case 4: return launch_logpass_length<4>(S, h, mode, empty_slot, s);
+        default: return launch_logpass_length<8>(S, h, mode, empty_slot, s);
+    }
 }
 
 static hipError_t launch_logpass(const PassSide &S, const Handle &h, int side, int mode, hipStream_t s)
 {
-    long long g = (S.rows + PASS_WAVES - 1) / PASS_WAVES;
-    const int grid = (int)(g < h.grid ? g : h.grid);
     const int empty_slot = 1 + side;
     if (h.mode == LCN_MODE_DENSE && mode != PASS_INIT) {
         const long long gd = (S.rows + DENSE_ROWS - 1) / DENSE_ROWS;
@@ -784,27 +528,7 @@ static hipError_t launch_logpass(const PassSide &S, const Handle &h, int side, i
                                h.query_out + 2 * side, S.shift_self, mode);
         return hipGetLastError();
     }
-    if (h.R <= 4) {
-        if (mode == PASS_UPDATE)
-            hipLaunchKernelGGL((logpass_kernel<4, PASS_UPDATE>), dim3(grid), dim3(PASS_THREADS), 0, s, S, h.R,
-                               h.partial, h.counters, empty_slot);
-        else if (mode == PASS_QUERY)
-            hipLaunchKernelGGL((logpass_kernel<4, PASS_QUERY>), dim3(grid), dim3(PASS_THREADS), 0, s, S, h.R,
-                               h.partial, h.counters, empty_slot);
-        else
-            hipLaunchKernelGGL((logpass_kernel<4, PASS_INIT>), dim3(grid), dim3(PASS_THREADS), 0, s, S, h.R,
-                               h.partial, h.counters, empty_slot);
-    } else {
-        if (mode == PASS_UPDATE)
-            hipLaunchKernelGGL((logpass_kernel<8, PASS_UPDATE>), dim3(grid), dim3(PASS_THREADS), 0, s, S, h.R,
-                               h.partial, h.counters, empty_slot);
-        else if (mode == PASS_QUERY)
-            hipLaunchKernelGGL((logpass_kernel<8, PASS_QUERY>), dim3(grid), dim3(PASS_THREADS), 0, s, S, h.R,
-                               h.partial, h.counters, empty_slot);
-        else
-            hipLaunchKernelGGL((logpass_kernel<8, PASS_INIT>), dim3(grid), dim3(PASS_THREADS), 0, s, S, h.R,
-                               h.partial, h.counters, empty_slot);
-    }
+    const int grid = launch_logpass_rounds(S, h, mode, empty_slot, s);
     if (mode == PASS_QUERY)
         hipLaunchKernelGGL(reduce_partials_kernel, dim3(1), dim3(1024), 0, s, h.partial, grid, 3, 0, S.acc_out,
                            h.query_out + 2 * side, S.shift_self, mode);
@@ -822,21 +546,18 @@ static hipError_t dispatch_pass(const PassSide &S, const Handle &h, int side, in
     if (h.R == 0) {
         e = launch_nystrom_pass(S, h, mode, fuse, fused_in, partial, cnt, s);
     } else {
-        switch (h.lp / 64) {
-            case 1: e = launch_pass_t<1>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            case 2: e = launch_pass_t<2>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            case 3: e = launch_pass_t<3>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            case 4: e = launch_pass_t<4>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            case 5: e = launch_pass_t<5>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            case 6: e = launch_pass_t<6>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            case 7: e = launch_pass_t<7>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            case 8: e = launch_pass_t<8>(S, h, mode, fuse, fused_in, partial, cnt, s); break;
-            default: break;
-        }
+        const FuseArgs F = fuse ? *fuse : FuseArgs{};
+        const int groups = sweep_groups(h, S.rows);
+        if (h.lp <= 128)
+            e = launch_short_sweep(S, h, mode, F, fused_in, groups, partial, cnt, s);
+        else if (h.lp <= 256)
+            e = launch_mid_sweep(S, h, mode, F, fused_in, groups, partial, cnt, s);
+        else
+            e = launch_long_sweep(S, h, mode, F, fused_in, groups, partial, cnt, s);
     }
     if (e != hipSuccess || !reduce_after) return e;
     const int stride = h.lp + 3;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((stride + 63) / 64), dim3(1024), 0, s, partial,
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((stride + REDUCE_COLUMNS - 1) / REDUCE_COLUMNS), dim3(1024), 0, s, partial,
                        sweep_groups(h, S.rows), stride, h.lp, S.acc_out, h.query_out + 2 * side, S.shift_self, mode);
     return hipGetLastError();
 }
@@ -863,11 +584,10 @@ hipError_t launch_pass(const Handle &h, int side, int mode, int acc_in, int acc_
 // iteration earlier, and logs move little per iteration.
 hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s)
 {
-    // a sweep's first ceil((lp + 3) / 64) workgroups add up its predecessor's partial sums: a side with
-    // fewer workgroups than that (a handful of rows) cannot, and every sweep gets its reduction launch
-    const int reducers = (h.lp + 3 + 63) / 64;
-    const bool fused = h.fused_reduce && !h.log_domain && sweep_groups(h, h.n) >= reducers &&
-                       sweep_groups(h, h.m) >= reducers;
+    const bool fused = h.fused_reduce && !h.log_domain;
+    auto direct_into = [&](int side) {   // how the sweep over `side` takes the totals of the other side's
+        return h.lp == 64 && sweep_groups(h, side == 0 ? h.m : h.n) <= DIRECT_GROUPS;
+    };
     int first = 0;
     if (h.fresh && h.double_first && !h.log_domain && iters > 0) {
         unsigned long long *discard = h.counters + 8;
@@ -900,17 +620,20 @@ hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s)
             if (t == first) {
                 // not fused itself, but its successor reduces into this sweep's output accumulator
                 FuseArgs F{};
-                F.mark_pending = last ? nullptr : h.acc[side == 0 ? 1 : 0];
+                F.mark_pending = last || direct_into(1 - side) ? nullptr : h.acc[side == 0 ? 1 : 0];
                 e = dispatch_pass(S, h, side, PASS_UPDATE, &F, false, last, mine, s);
             } else {
                 const long long rows_prev = side == 0 ? h.m : h.n;
                 FuseArgs F;
                 F.prev_partial = (t & 1) ? h.partial : h.partial2;
                 F.prev_groups = sweep_groups(h, rows_prev);
+                F.direct = direct_into(side);
                 F.acc = h.acc[side == 0 ? 0 : 1];
-                F.shift_other = h.shift + (1 - side);
-                F.shift_self = h.shift + side;
-                F.mark_pending = last ? nullptr : h.acc[side == 0 ? 1 : 0];
+                F.shift_other = h.shift + 2 * (1 - side) + h.shift_slot[1 - side];
+                F.shift_self = S.shift_self;
+                h.shift_slot[1 - side] ^= 1;
+                F.shift_next = h.shift + 2 * (1 - side) + h.shift_slot[1 - side];
+                F.mark_pending = last || direct_into(1 - side) ? nullptr : h.acc[side == 0 ? 1 : 0];
                 F.timeouts = h.counters + 5;
                 F.wait_ticks = h.wait_ticks;
                 e = dispatch_pass(S, h, side, PASS_UPDATE, &F, true, last, mine, s);

@@ -16,38 +16,6 @@
 
 namespace lcn {
 
-// One step of the cross-lane sum of two values: lanes in the upper half (HALF = 32) or in the odd 16-lane
-// rows (HALF = 16) end up with b's sum over the pair of lanes, the others with a's.
-template <int HALF>
-__device__ inline double halve(double a, double b)
-{
-    lane_swap<HALF>(a, b);
-    return a + b;
-}
-
-// Sums of NV (4 or 8) values over the 64 lanes; lane l receives the sum of value l / (64 / NV).
-template <int NV>
-__device__ inline double reduce_values(double (&v)[NV])
-{
-    double s;
-    if constexpr (NV == 4) {
-        const double a = halve<32>(v[0], v[2]), b = halve<32>(v[1], v[3]);
-        s = halve<16>(a, b);
-    } else {
-        const double a = halve<32>(v[0], v[4]), b = halve<32>(v[1], v[5]), c = halve<32>(v[2], v[6]),
-                     d = halve<32>(v[3], v[7]);
-        const double e = halve<16>(a, c), f = halve<16>(b, d);
-        const bool odd = threadIdx.x & 8;
-        const double keep = odd ? f : e, give = odd ? e : f;
-        s = keep + dpp_from<0x128>(give);   // row_ror:8
-    }
-    s += dpp_from<0xB1>(s);    // quad_perm [1,0,3,2]
-    s += dpp_from<0x4E>(s);    // quad_perm [2,3,0,1]
-    s += dpp_from<0x141>(s);   // row_half_mirror
-    if constexpr (NV == 4) s += dpp_from<0x140>(s);   // row_mirror
-    return s;
-}
-
 template <int T, int MODE, bool FUSED, int RG>
 __global__ __launch_bounds__(PASS_THREADS) void nystrom_pass_kernel(PassSide S, int lp, double *partial,
                                                                     unsigned long long *counters, FuseArgs Fz)
@@ -63,7 +31,11 @@ __global__ __launch_bounds__(PASS_THREADS) void nystrom_pass_kernel(PassSide S, 
     const int stride = lp + 3;
     double *ysh = zsh + (size_t)(PASS_WAVES / 2) * stride;
     if (MODE == PASS_UPDATE) mark_pending(Fz, lp);
-    if (FUSED && (int)blockIdx.x < (stride + 63) / 64) reduce_publish(Fz, blockIdx.x, lp, ysh + lp + 2);
+    DirectTotals totals;
+    if (FUSED && T == 1 && Fz.direct)
+        totals.request(Fz, lp);
+    else if (FUSED)
+        reduce_publish(Fz, lp, ysh + lp + 2);
     const double m_self = MODE == PASS_QUERY ? S.acc_out[lp] : *S.shift_self;
     double m_in = 0.0, e_out = 1.0;
     double maxlog = -INFINITY, q0 = 0.0, q1 = 0.0;
@@ -87,21 +59,19 @@ __global__ __launch_bounds__(PASS_THREADS) void nystrom_pass_kernel(PassSide S, 
         log_marg = MODE == PASS_INIT ? (double)S.log_out[mine] : __hiloint2double(rec[5], rec[4]);
         lin = MODE == PASS_QUERY ? S.lin_out[mine] : 0.0;
     };
-    if (g < groups) request();
+    // (unconditional, so that the loads in flight can be counted: a wavefront without rows requests the last group)
+    const bool busy = g < groups;
+    if (!busy) g = groups - 1;
+    request();
     if (FUSED) {
-        if (wave == 0) fused_fetch(Fz, S.acc_in, lp, ysh);
-        __syncthreads();
-        m_in = ysh[lp];
-        e_out = ysh[lp + 1];
-#pragma unroll
-        for (int t = 0; t < T; ++t) yreg[t] = ysh[FRow<T>::kidx(t, lane)];
+        take_totals<T>(Fz, S.acc_in, lp, ysh, totals, yreg, m_in, e_out);
     } else if (MODE != PASS_INIT) {
         m_in = S.acc_in[lp];
         e_out = MODE == PASS_UPDATE ? exp(-m_in - m_self) : exp(m_in + m_self);
 #pragma unroll
         for (int t = 0; t < T; ++t) yreg[t] = S.acc_in[FRow<T>::kidx(t, lane)];
     }
-    if (g < groups) for (;;) {
+    if (busy) for (;;) {
         const long long mine = (long long)g * RG + my;
         const bool exists = my < RG && mine < S.rows;
         double out;

@@ -1304,7 +1304,8 @@ hipError_t launch_bucket_sort(const SortBuffers &B, hipStream_t s)
 // Packed per-row metadata read by the sweeps, one record per row:
 //   [0:1] start of the row's record of sparse values (int64)
 //   [2]   marginal (float)          [4:5] its natural log (double)
-//   [6 + 2r], [7 + 2r]  round r: start in the other side's bucket-ordered vector, length
+//   [6 + 2r], [7 + 2r]  round r: what takes an entry's number in the record to its place in the other side's
+//                       bucket-ordered vector (modulo 2^32), and the number of the first entry past the round
 //   [6 + 2R + r]        round r: position of the row in its own side's bucket order
 int meta_stride_for(int R) { return (6 + 3 * R + 3) / 4 * 4; }
 
@@ -1325,10 +1326,12 @@ __global__ void meta_kernel(SortBuffers B, const float *a, const float *b)
     rec[4] = __double2loint(lm);
     rec[5] = __double2hiint(lm);
     const int *pos = B.pos + (side ? (long long)B.R * B.n : 0);
+    int at = 0;
     for (int r = 0; r < B.R; ++r) {
         const Seg sg = (side ? B.seg_y : B.seg_x)[(long long)r * cnt + i];
-        rec[6 + 2 * r] = sg.vstart;
-        rec[7 + 2 * r] = sg.len;
+        rec[6 + 2 * r] = (int)((unsigned)sg.vstart - (unsigned)at);
+        at += sg.len;
+        rec[7 + 2 * r] = at;
         rec[6 + 2 * B.R + r] = pos[(long long)r * cnt + i];
     }
 }

@@ -183,7 +183,7 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
     h.perm_u = bump.take<double>((size_t)(h.R > 0 ? h.R : 1) * h.n + 8);
     h.perm_v = bump.take<double>((size_t)(h.R > 0 ? h.R : 1) * h.m + 8);
     for (int i = 0; i < 2; ++i) h.acc[i] = bump.take<double>(lp1 + 2);
-    h.shift = bump.take<double>(2);
+    h.shift = bump.take<double>(4);
     h.grid = bump.dry ? 1024 : pass_grid(h);
     h.partial = bump.take<double>((size_t)(bump.dry ? 1024 : h.grid) * (h.lp + 3));
     h.partial2 = bump.take<double>((size_t)(bump.dry ? 1024 : h.grid) * (h.lp + 3));
@@ -746,9 +746,9 @@ struct Builder {
         h.undecided_last = (long long)undecided2[0] + undecided2[1];
         h.ntiles = (int)totals[1];
 
-        // slack: a sweep reads whole wavefront-wide chunks, up to two per segment, and masks the excess
-        h.vals_x = bump.take<float>((size_t)h.nnz_stored + 128);
-        h.vals_y = bump.take<float>((size_t)h.nnz_stored + 128);
+        // slack: a sweep reads whole wavefront-wide chunks, up to four at a time, and masks the excess
+        h.vals_x = bump.take<float>((size_t)h.nnz_stored + VALUE_SLACK);
+        h.vals_y = bump.take<float>((size_t)h.nnz_stored + VALUE_SLACK);
         h.ws_used = bump.used;
         const size_t least = bump.used;
         // Last, room for the column sums of a dense iteration.  It belongs to what a build needs, so that whoever asks
@@ -838,8 +838,8 @@ lcn_status lcn_workspace_bytes(int64_t n, int64_t m, int32_t d, int32_t mode, co
         else
             nnz = 0;
     }
-    bump.take<float>((size_t)nnz + 128);
-    bump.take<float>((size_t)nnz + 128);
+    bump.take<float>((size_t)nnz + VALUE_SLACK);
+    bump.take<float>((size_t)nnz + VALUE_SLACK);
     if (mode == LCN_MODE_DENSE) bump.take<float>(dense_iteration_floats(dense_iteration_groups(n, m, device_compute_units()), m));
     *bytes = bump.used + 256;
     return LCN_OK;

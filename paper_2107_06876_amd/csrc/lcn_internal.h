@@ -47,6 +47,8 @@ struct BackwardArgs {
     float *rec_sp = nullptr, *rec_nys = nullptr;      // outputs, layout of the row records of X
 };
 
+constexpr int VALUE_SLACK = 256;   // floats behind the stored values that a sweep may read
+
 struct Handle;
 
 // ---- structure build (kernels_structure.hip) -------------------------------
@@ -205,7 +207,8 @@ struct Handle {
     double *lin_u, *lin_v;
     double *perm_u, *perm_v;   // [R][n], [R][m]
     double *acc[2];            // lp + 2 each (last slot: scratch of the fused reduction): [0] y = W v, [1] z = U^T u, each followed by its exponent
-    double *shift;             // [2]: exponent taken out of u and of v
+    double *shift;             // [2][2]: exponent taken out of u and of v, each in the slot that shift_slot says
+    int shift_slot[2];         // (a sweep writes the other side's next exponent beside the one it reads)
     double *partial;           // [grid][lp + 3] per-workgroup partial sums of a sweep
     double *partial2;          // second buffer: consecutive sweeps alternate when the reduction is fused
     float *column_part;        // column sums of a dense iteration and their corrections, (column_groups + 1)(m + 1) floats (null: not used)
