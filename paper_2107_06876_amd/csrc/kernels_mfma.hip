@@ -40,21 +40,10 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
-// bf16 of a finite float, round to nearest even: |x - bf16(x)| <= 2^-8 |x|
-__device__ inline unsigned bf16_bits(float x)
-{
-    const unsigned u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
 constexpr int FP = 128;  // points per workgroup
 constexpr int FC = 128;  // centroids per pass
 
 static inline int steps_of(int d) { return (d + 15) / 16; }
-
-// With more than 256 centroids a thread of the exact list kernel walks several chains of d
-// dependent additions; then it pays to separate the points that have just two candidates.
-bool filter_uses_pairs(int k) { return k > 256; }
 
 size_t split_plane_bytes(long long rows, int d)
 {
@@ -64,26 +53,33 @@ size_t split_plane_bytes(long long rows, int d)
 // Splits the rows of `src` (rows x d, fp32) into `planes` bf16 planes in operand
 // order: out[plane][group][step][lane] (16 bytes each); rows and dimensions
 // beyond the matrix are zero.  One workgroup per group of 32 rows.
-// NORMS (the centroids): also the squared norm of every row as fp32 into cn, and the
-// largest of them into cmax_bits (the bit pattern of a non-negative float orders like an
-// unsigned integer; cmax_bits is zero on entry).
-template <bool NORMS>
+// START (the centroids at the start of a k-means run): also the squared norm of every row as fp32 into cn;
+// with `pick` the rows are those of the points it names, which are written to `rows_out` as well; `zeros` (two
+// words) are cleared.
+template <bool START>
 __global__ __launch_bounds__(256) void split_planes_kernel(const float *__restrict__ src, long long rows, int d, int S,
                                                            int planes, bf16x8 *__restrict__ out, long long plane_stride,
-                                                           float *__restrict__ cn, unsigned *cmax_bits)
+                                                           float *__restrict__ cn, const long long *__restrict__ pick,
+                                                           float *rows_out, int *zeros)
 {
     __shared__ double red[4][32];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const long long group = blockIdx.x;
     const long long row = group * 32 + (lane & 31);
+    const long long from = START && pick && row < rows ? pick[row] : row;
+    if (START && group == 0 && threadIdx.x < 2) zeros[threadIdx.x] = 0;
     double sq = 0.0;
     for (int s = w; s < S; s += 4) {
         const int k0 = 16 * s + 8 * (lane >> 5);
         u16x8 p1, p2;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float x = (row < rows && k0 + e < d) ? src[row * d + k0 + e] : 0.f;
-            if (NORMS) sq = fma((double)x, (double)x, sq);
+            const bool in = row < rows && k0 + e < d;
+            const float x = in ? src[from * d + k0 + e] : 0.f;
+            if (START) {
+                sq = fma((double)x, (double)x, sq);
+                if (pick && in) rows_out[row * d + k0 + e] = x;
+            }
             const unsigned h = bf16_bits(x);
             p1[e] = (unsigned short)h;
             p2[e] = (unsigned short)bf16_bits(x - __uint_as_float(h << 16));  // the difference is exact in fp32
@@ -92,15 +88,12 @@ __global__ __launch_bounds__(256) void split_planes_kernel(const float *__restri
         out[at] = __builtin_bit_cast(bf16x8, p1);
         if (planes > 1) out[plane_stride + at] = __builtin_bit_cast(bf16x8, p2);
     }
-    if (NORMS) {
+    if (START) {
         sq += __shfl_xor(sq, 32, 64);   // the two halves of a row's 16 dimensions per step
         if (lane < 32) red[w][lane] = sq;
         __syncthreads();
-        if (w == 0 && lane < 32 && row < rows) {
-            const float f = (float)(red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane]);
-            cn[row] = f;
-            atomicMax(cmax_bits, __float_as_uint(f * 1.0000002f));
-        }
+        if (w == 0 && lane < 32 && row < rows)
+            cn[row] = (float)(red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane]);
     }
 }
 
@@ -110,8 +103,35 @@ hipError_t launch_split_planes(const float *src, long long rows, int d, int plan
     const int S = steps_of(d);
     hipLaunchKernelGGL(split_planes_kernel<false>, dim3((unsigned)groups), dim3(256), 0, s, src, rows, d, S, planes,
                        (bf16x8 *)out, (long long)(split_plane_bytes(rows, d) / 16), (float *)nullptr,
-                       (unsigned *)nullptr);
+                       (const long long *)nullptr, (float *)nullptr, (int *)nullptr);
     return hipGetLastError();
+}
+
+CentroidPlanes centroid_planes(void *Ct, int k, int d, float *cn)
+{
+    return CentroidPlanes{(unsigned short *)Ct, (long long)(split_plane_bytes(k, d) / 2), steps_of(d), cn};
+}
+
+// The start of a k-means run for the filter: centroids from the points that `pick` names (null: cent is given),
+// their two bf16 planes and squared norms, and the two counters of undecided points at zero, in one launch.
+hipError_t launch_kmeans_start(const float *Z, const long long *pick, float *cent, int k, int d, void *Ct, float *cn,
+                               int *nflagged, hipStream_t s)
+{
+    hipLaunchKernelGGL(split_planes_kernel<true>, dim3((unsigned)((k + 31) / 32)), dim3(256), 0, s, pick ? Z : cent,
+                       (long long)k, d, steps_of(d), 2, (bf16x8 *)Ct, (long long)(split_plane_bytes(k, d) / 16), cn, pick,
+                       cent, nflagged);
+    return hipGetLastError();
+}
+
+// The largest squared norm of a centroid (rounded up), by a workgroup of 256 threads; sh: four words of LDS.
+__device__ inline float largest_norm(const float *__restrict__ cn, int k, float *sh)
+{
+    float m = 0.f;
+    for (int c = threadIdx.x; c < k; c += 256) m = fmaxf(m, cn[c]);
+    for (int o = 1; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+    __syncthreads();
+    return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])) * 1.0000002f;
 }
 
 // What the filter makes of a point's three smallest scores.
@@ -120,17 +140,15 @@ hipError_t launch_split_planes(const float *src, long long rows, int d, int plan
 //   second beyond that      -> bidx is the winner;
 //   only third beyond that  -> the winner is bidx or sidx (decided by the exact rule on those two);
 //   otherwise               -> the exact rule over all centroids.
-template <bool TOP3>
 __device__ inline void filter_decide(long long p, float best, float second, float third, int bidx, int sidx,
-                                     const double *__restrict__ zn, const unsigned *__restrict__ cmax_bits,
+                                     const double *__restrict__ zn, float cmax,
                                      float err_coef, int32_t *__restrict__ out, int *__restrict__ flagged,
                                      int *__restrict__ pairs, int *nflagged)
 {
     out[p] = bidx;
-    const float cmax = __uint_as_float(*cmax_bits);
     const float delta = err_coef * ((float)zn[p] * 1.0000002f + cmax);
     if (!(second - best > 2.f * delta)) {
-        if (TOP3 && third - best > 2.f * delta) {
+        if (third - best > 2.f * delta) {
             const int slot = atomicAdd(nflagged + 1, 1);
             pairs[3 * (long long)slot] = (int)p;
             pairs[3 * (long long)slot + 1] = bidx;
@@ -143,21 +161,20 @@ __device__ inline void filter_decide(long long p, float best, float second, floa
 }
 
 // ZP: planes of the points (2: fp32 input, 1: input exactly representable in bf16).
-// TOP3: also track the third smallest score and the second's centroid, so that a point
-// with exactly two candidates goes to the exact rule on those two; pays off when the
-// exact rule over all centroids is long (many centroids).
-template <int ZP, bool TOP3>
+// The three smallest scores are tracked, with the centroids of the first two: a point with exactly two candidates goes
+// to the exact rule on those two, which is short.
+template <int ZP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void assign_filter_kernel(const bf16x8 *__restrict__ Zt, long long zplane, long long N,
                                                             int S, const bf16x8 *__restrict__ Ct, long long cplane,
                                                             int k, const float *__restrict__ cn,
-                                                            const double *__restrict__ zn,
-                                                            const unsigned *__restrict__ cmax_bits, float err_coef,
+                                                            const double *__restrict__ zn, float err_coef,
                                                             int32_t *__restrict__ out, int *__restrict__ flagged,
                                                             int *__restrict__ pairs, int *nflagged)
 {
     // [buffer][step of the stage][centroid group][plane][lane]: 32 KB
     __shared__ bf16x8 Cs[2][2][4][2][64];
     __shared__ float cn_s[FC];  // squared norms of the pass's centroids (+inf beyond the last one)
+    __shared__ float cmax_s[4];
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -179,12 +196,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     // (best, second, s), the new third that of (second, third, s); plain selects, no branch)
     auto offer = [&](float s, int c) {
         const bool lt1 = s < best;
-        if (TOP3) {
-            const bool lt2 = s < second;
-            const int keep = lt2 ? c : sidx;
-            third = __builtin_amdgcn_fmed3f(second, third, s);
-            sidx = lt1 ? bidx : keep;
-        }
+        const bool lt2 = s < second;
+        const int keep = lt2 ? c : sidx;
+        third = __builtin_amdgcn_fmed3f(second, third, s);
+        sidx = lt1 ? bidx : keep;
         second = __builtin_amdgcn_fmed3f(best, second, s);
         bidx = lt1 ? c : bidx;
         best = __builtin_amdgcn_fmed3f(-INFINITY, best, s);
@@ -282,9 +297,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
         offer(os, osi);
         offer(ot, 0);  // cannot rank above third: two scores of the other half are not larger
     }
+    const float cmax = largest_norm(cn, k, cmax_s);
     const long long p = P * 32 + col;
     if (active && half == 0 && p < N)
-        filter_decide<TOP3>(p, best, second, third, bidx, sidx, zn, cmax_bits, err_coef, out, flagged, pairs, nflagged);
+        filter_decide(p, best, second, third, bidx, sidx, zn, cmax, err_coef, out, flagged, pairs, nflagged);
 }
 
 // The filter for points given as bf16 (one plane) against many centroids: the 128 points of a
@@ -300,12 +316,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 // points, over the centroids its wavefront saw; half-wavefronts and wavefronts are merged at the end.
 constexpr int FR_MERGE_BYTES = 4 * FP * 5 * 4;
 
-template <bool TOP3>
 __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
     const bf16x8 *__restrict__ Zt, long long N, int S, const bf16x8 *__restrict__ Ct, long long cplane, int k,
-    const float *__restrict__ cn, const double *__restrict__ zn, const unsigned *__restrict__ cmax_bits, float err_coef,
+    const float *__restrict__ cn, const double *__restrict__ zn, float err_coef,
     int32_t *__restrict__ out, int *__restrict__ flagged, int *__restrict__ pairs, int *nflagged)
 {
+    __shared__ float cmax_s[4];
     extern __shared__ __align__(16) unsigned char fr_lds[];
     bf16x8 *Zs = reinterpret_cast<bf16x8 *>(fr_lds);   // [4 point groups][S][64]
     const int tid = threadIdx.x;
@@ -429,12 +445,10 @@ __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
                 const float sc = fmaf(-2.f, acc[g][v], cnv[v]);
                 const int code = 16 * pass + v;
                 const bool lt1 = sc < b;
-                if (TOP3) {
-                    const bool lt2 = sc < s2;
-                    const int keep = lt2 ? code : si;
-                    t3 = __builtin_amdgcn_fmed3f(s2, t3, sc);
-                    si = lt1 ? bi : keep;
-                }
+                const bool lt2 = sc < s2;
+                const int keep = lt2 ? code : si;
+                t3 = __builtin_amdgcn_fmed3f(s2, t3, sc);
+                si = lt1 ? bi : keep;
                 s2 = __builtin_amdgcn_fmed3f(b, s2, sc);
                 bi = lt1 ? code : bi;
                 b = __builtin_amdgcn_fmed3f(-INFINITY, b, sc);
@@ -453,10 +467,8 @@ __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
     // above third: two scores of its own set are not larger), then the four wavefronts' through LDS
     auto offer = [&](float &b, float &s2, float &t3, int &bi, int &si, float sc, int c) {
         const bool lt1 = sc < b, lt2 = sc < s2;
-        if (TOP3) {
-            t3 = fminf(t3, fmaxf(sc, s2));
-            si = lt1 ? bi : (lt2 ? c : si);
-        }
+        t3 = fminf(t3, fmaxf(sc, s2));
+        si = lt1 ? bi : (lt2 ? c : si);
         s2 = fminf(s2, fmaxf(sc, b));
         bi = lt1 ? c : bi;
         b = fminf(b, sc);
@@ -482,6 +494,7 @@ __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
         }
     }
     __syncthreads();
+    const float cmax = largest_norm(cn, k, cmax_s);
     if (tid < FP) {
         const long long p = G0 * 32 + tid;
         if (p < N) {
@@ -493,7 +506,7 @@ __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
                 offer(b, s2, t3, bi, si, mf[(1 * 4 + ww) * FP + tid], mi[(1 * 4 + ww) * FP + tid]);
                 offer(b, s2, t3, bi, si, mf[(2 * 4 + ww) * FP + tid], 0);
             }
-            filter_decide<TOP3>(p, b, s2, t3, bi, si, zn, cmax_bits, err_coef, out, flagged, pairs, nflagged);
+            filter_decide(p, b, s2, t3, bi, si, zn, cmax, err_coef, out, flagged, pairs, nflagged);
         }
     }
 }
@@ -501,34 +514,29 @@ __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
 // More than 64 KB of dynamic LDS has to be allowed per kernel and device before the first such launch.
 // Done once per device and kernel (and again only for a larger size), under a lock: the k-means runs
 // of a build launch from several host threads.
-static hipError_t allow_dynamic_lds(const void *kernel, int which, size_t bytes)
+static hipError_t allow_dynamic_lds(const void *kernel, size_t bytes)
 {
     static std::mutex mu;
-    static size_t allowed[64][2] = {};
+    static size_t allowed[64] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     std::lock_guard<std::mutex> lock(mu);
-    if (allowed[dev][which] >= bytes) return hipSuccess;
+    if (allowed[dev] >= bytes) return hipSuccess;
     e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e == hipSuccess) allowed[dev][which] = bytes;
+    if (e == hipSuccess) allowed[dev] = bytes;
     return e;
 }
 
-// Zt: the points' planes (launch_split_planes, `zplanes` of them); Ct: room for two planes of k centroids.
+// Zt: the points' planes (launch_split_planes, `zplanes` of them); Ct, cn: the centroids' two planes and squared
+// norms as the start of the run and the centroid updates leave them.  nflagged[0..1] are zero on entry.
 // flagged: points for the exact rule over all centroids (count nflagged[0]); pairs: (point, centroid, centroid)
 // triples for the exact rule on two centroids (count nflagged[1]).
-hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, const float *cent, int k, void *Ct,
-                                const double *zn, float *cn, unsigned *cmax_bits, int32_t *out, int *flagged,
-                                int *pairs, int *nflagged, hipStream_t s)
+hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, int k, const void *Ct, const double *zn,
+                                const float *cn, int32_t *out, int *flagged, int *pairs, int *nflagged, hipStream_t s)
 {
-    // cmax_bits and nflagged[0..1] are zero on entry: cleared by the caller before the first
-    // call and by the centroid update after every call
     const int S = steps_of(d);
-    // the centroids' two bf16 planes, their squared norms and the largest norm in one launch
-    hipLaunchKernelGGL(split_planes_kernel<true>, dim3((unsigned)((k + 31) / 32)), dim3(256), 0, s, cent, (long long)k, d,
-                       S, 2, (bf16x8 *)Ct, (long long)(split_plane_bytes(k, d) / 16), cn, cmax_bits);
     // Bound on |computed score - exact score| / (||z||^2 + max ||c||^2):
     //  * dropped products: z.c - (z1.c1 + z1.c2 + z2.c1) = z2.c2 + r_z.c + z.r_c - ..., each at most
     //    2^-16 sum |z_k||c_k| (plus terms of order 2^-24), and sum |z_k||c_k| <= (||z||^2 + ||c||^2) / 2;
@@ -544,43 +552,23 @@ hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d,
     const long long zplane = (long long)(split_plane_bytes(N, d) / 16);
     const long long cplane = (long long)(split_plane_bytes(k, d) / 16);
     const unsigned grid = (unsigned)((N + FP - 1) / FP);
-    const bool top3 = filter_uses_pairs(k);
     // points given as bf16, several passes over the centroids, and two workgroups' points fit the LDS
     // of a compute unit: the kernel that keeps the points on chip
     if (zplanes == 1 && k > FC && S <= 19) {
         const size_t lds = (size_t)4 * S * 1024 > (size_t)FR_MERGE_BYTES ? (size_t)4 * S * 1024 : (size_t)FR_MERGE_BYTES;
         const unsigned rgrid = (unsigned)(((N + 31) / 32 + 3) / 4);
-#define LCN_RESIDENT_LAUNCH(T3_)                                                                                       \
-    do {                                                                                                               \
-        hipError_t e_ = allow_dynamic_lds(reinterpret_cast<const void *>(&assign_filter_resident_kernel<T3_>),         \
-                                          T3_ ? 1 : 0, lds);                                                           \
-        if (e_ != hipSuccess) return e_;                                                                               \
-        hipLaunchKernelGGL((assign_filter_resident_kernel<T3_>), dim3(rgrid), dim3(256), lds, s, (const bf16x8 *)Zt,   \
-                           N, S, (const bf16x8 *)Ct, cplane, k, cn, zn, cmax_bits, err_safe, out, flagged, pairs,      \
-                           nflagged);                                                                                  \
-    } while (0)
-        if (top3)
-            LCN_RESIDENT_LAUNCH(true);
-        else
-            LCN_RESIDENT_LAUNCH(false);
-#undef LCN_RESIDENT_LAUNCH
+        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&assign_filter_resident_kernel), lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(assign_filter_resident_kernel, dim3(rgrid), dim3(256), lds, s, (const bf16x8 *)Zt, N, S,
+                           (const bf16x8 *)Ct, cplane, k, cn, zn, err_safe, out, flagged, pairs, nflagged);
         return hipGetLastError();
     }
-#define LCN_FILTER_LAUNCH(ZP_, T3_)                                                                                   \
-    hipLaunchKernelGGL((assign_filter_kernel<ZP_, T3_>), dim3(grid), dim3(256), 0, s, (const bf16x8 *)Zt, zplane, N,  \
-                       S, (const bf16x8 *)Ct, cplane, k, cn, zn, cmax_bits, err_safe, out, flagged, pairs, nflagged)
-    if (zplanes > 1) {
-        if (top3)
-            LCN_FILTER_LAUNCH(2, true);
-        else
-            LCN_FILTER_LAUNCH(2, false);
-    } else {
-        if (top3)
-            LCN_FILTER_LAUNCH(1, true);
-        else
-            LCN_FILTER_LAUNCH(1, false);
-    }
-#undef LCN_FILTER_LAUNCH
+    if (zplanes > 1)
+        hipLaunchKernelGGL(assign_filter_kernel<2>, dim3(grid), dim3(256), 0, s, (const bf16x8 *)Zt, zplane, N, S,
+                           (const bf16x8 *)Ct, cplane, k, cn, zn, err_safe, out, flagged, pairs, nflagged);
+    else
+        hipLaunchKernelGGL(assign_filter_kernel<1>, dim3(grid), dim3(256), 0, s, (const bf16x8 *)Zt, zplane, N, S,
+                           (const bf16x8 *)Ct, cplane, k, cn, zn, err_safe, out, flagged, pairs, nflagged);
     return hipGetLastError();
 }
 

@@ -317,8 +317,7 @@ constexpr int LDT = TILE + 4;
 
 template <int KIND>
 __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ Z, long long N, int d,
-                                                     const float *__restrict__ C, int k, int32_t *__restrict__ out,
-                                                     const int *__restrict__ list, const int *__restrict__ list_count)
+                                                     const float *__restrict__ C, int k, int32_t *__restrict__ out)
 {
     __shared__ float Ps[KCH][LDT];
     __shared__ float Cs[KCH][LDT];
@@ -329,10 +328,7 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ Z
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
     const long long p0 = (long long)blockIdx.x * TILE;
-    // with a list, only the listed points are decided (those the MFMA filter could not)
-    const long long cnt = list ? (long long)*list_count : N;
-    if (p0 >= cnt) return;
-    if (tid < TILE) pidx[tid] = p0 + tid < cnt ? (list ? (long long)list[p0 + tid] : p0 + tid) : -1;
+    if (tid < TILE) pidx[tid] = p0 + tid < N ? p0 + tid : -1;
     __syncthreads();
 
     double bestv[4];
@@ -464,45 +460,80 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ Z
     }
 }
 
-// Exact rule for a (short) list of points: one workgroup per listed point, one
-// thread per centroid (strided), each adding the dimensions left to right.
-__global__ __launch_bounds__(256) void assign_list_kernel(const float *__restrict__ Z, int d,
-                                                          const float *__restrict__ C, int k,
-                                                          int32_t *__restrict__ out, const int *__restrict__ list,
-                                                          const int *__restrict__ list_count)
+// Exact rule on what the filter left undecided, in one launch.
+//
+// Points with more than two candidates (the list): one workgroup per point, one thread per centroid (strided), each
+// adding the dimensions left to right.  The centroids come through LDS, 32 dimensions of 256 of them at a time in
+// whole lines, the next 32 already requested (a thread that reads its centroid's row by itself asks for 64 lines per
+// load: 17 us for a few hundred points of 300 dimensions).
+//
+// Points with two candidates: sixteen per workgroup at a time.  The order of the additions is the rule, but the squares
+// are independent of each other: the workgroup forms them for 64 dimensions of 32 (point, centroid) pairs with whole
+// lines of the two rows, and a lane per pair adds them up from LDS, the next 64 dimensions already requested.  (A thread
+// that reads both rows by itself waits ten times for memory: 17 us at 38 768 points of 300 dimensions.)
+constexpr int UP = 32, UD = 64;   // pairs of a point and a centroid, dimensions
+constexpr int UL = 32, UC = 256;  // dimensions and centroids at a time for a listed point
+
+__global__ __launch_bounds__(256) void assign_undecided_kernel(const float *__restrict__ Z, int d,
+                                                               const float *__restrict__ C, int k,
+                                                               int32_t *__restrict__ out, const int *__restrict__ list,
+                                                               const int *__restrict__ pairs,
+                                                               const int *__restrict__ count)
 {
-    extern __shared__ float zrow[];  // d floats
     __shared__ double bv_sh[256];
     __shared__ int bi_sh[256];
-    const int cnt = *list_count;
+    __shared__ float zs[2][UL];
+    __shared__ union {
+        float cent[UL][UC + 1];
+        double sq[UP][UD + 1];
+    } sh;
+    auto &sq = sh.sq;
+    const int cnt = count[0];
+    const long long npairs = count[1];
     for (int it = blockIdx.x; it < cnt; it += gridDim.x) {
         const long long p = list[it];
-        __syncthreads();
-        for (int j = threadIdx.x; j < d; j += 256) zrow[j] = Z[p * d + j];
-        __syncthreads();
         double bv = 0.0;
         int bi = -1;
-        for (int c = threadIdx.x; c < k; c += 256) {
-            const float *cr = C + (long long)c * d;
+        const int dim = threadIdx.x & (UL - 1), r0 = threadIdx.x / UL;
+        for (int c0 = 0; c0 < k; c0 += UC) {
+            const int c = c0 + (int)threadIdx.x;
             double s = 0.0;
-            int j = 0;
-            for (; j + 32 <= d; j += 32) {  // the order of the additions is the rule; 32 loads are requested at once
-                float cv[32];
+            float cv[UL], zv;
+            auto fetch = [&](int j0) {   // past the last dimension or centroid: the last one again, not added
+                const int j = j0 + dim < d ? j0 + dim : d - 1;
 #pragma unroll
-                for (int e = 0; e < 32; ++e) cv[e] = cr[j + e];
+                for (int u = 0; u < UL; ++u) {
+                    const int r = c0 + r0 + 8 * u < k ? c0 + r0 + 8 * u : k - 1;
+                    cv[u] = C[(long long)r * d + j];
+                }
+                zv = Z[p * d + j];
+            };
+            fetch(0);
+            for (int j0 = 0; j0 < d; j0 += UL) {
+                const int buf = (j0 / UL) & 1;
+                __syncthreads();   // the dimensions before have been added
 #pragma unroll
-                for (int e = 0; e < 32; ++e) {
-                    double t = (double)zrow[j + e] - (double)cv[e];
-                    double t2 = t * t;
-                    s = s + t2;
+                for (int u = 0; u < UL; ++u) sh.cent[dim][r0 + 8 * u] = cv[u];
+                if (threadIdx.x < UL) zs[buf][dim] = zv;
+                __syncthreads();
+                fetch(j0 + UL);
+                const int m = d - j0 < UL ? d - j0 : UL;
+                if (m == UL) {
+#pragma unroll
+                    for (int e = 0; e < UL; ++e) {
+                        const double t = (double)zs[buf][e] - (double)sh.cent[e][threadIdx.x];
+                        const double t2 = t * t;
+                        s = s + t2;
+                    }
+                } else {
+                    for (int e = 0; e < m; ++e) {
+                        const double t = (double)zs[buf][e] - (double)sh.cent[e][threadIdx.x];
+                        const double t2 = t * t;
+                        s = s + t2;
+                    }
                 }
             }
-            for (; j < d; ++j) {
-                double t = (double)zrow[j] - (double)cr[j];
-                double t2 = t * t;
-                s = s + t2;
-            }
-            if (bi < 0 || s < bv) {  // ascending c: strict < keeps the lowest index
+            if (c < k && (bi < 0 || s < bv)) {  // ascending c: strict < keeps the lowest index
                 bv = s;
                 bi = c;
             }
@@ -525,71 +556,72 @@ __global__ __launch_bounds__(256) void assign_list_kernel(const float *__restric
         }
         if (threadIdx.x == 0) out[p] = bi_sh[0];
     }
-}
-
-// Exact rule on two candidate centroids: a thread adds the dimensions of one
-// (point, centroid) pair left to right; neighbouring threads hold the two
-// candidates of a point and the smaller sum wins (the lower index if equal).
-__global__ __launch_bounds__(256) void assign_pairs_kernel(const float *__restrict__ Z, int d,
-                                                           const float *__restrict__ C, int32_t *__restrict__ out,
-                                                           const int *__restrict__ pairs,
-                                                           const int *__restrict__ pair_count)
-{
-    const long long cnt = *pair_count;
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    // every trip is taken by whole pairs of lanes, so the exchange below always has its partner
-    for (long long t0 = (long long)blockIdx.x * blockDim.x; t0 < 2 * cnt; t0 += stride) {
-        const long long t = t0 + threadIdx.x;
-        const bool live = t < 2 * cnt;
-        const long long slot = live ? t >> 1 : 0;
-        const long long p = pairs[3 * slot];
-        const int c = pairs[3 * slot + 1 + (int)(t & 1)];
-        const float *zr = Z + p * d;
-        const float *cr = C + (long long)c * d;
+    // the workgroups without a listed point first
+    for (long long s0 = (long long)(gridDim.x - 1 - blockIdx.x) * UP; s0 < 2 * npairs; s0 += (long long)gridDim.x * UP) {
+        const int lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        // wavefront w forms the squares of slots 8 w .. 8 w + 7, lane j dimension j (past the last slot: the last again)
+        const float *zr[UP / 4], *cr[UP / 4];
+#pragma unroll
+        for (int u = 0; u < UP / 4; ++u) {
+            long long t = s0 + (UP / 4) * wave + u;
+            t = t < 2 * npairs ? t : 2 * npairs - 1;
+            zr[u] = Z + (long long)pairs[3 * (t >> 1)] * d;
+            cr[u] = C + (long long)pairs[3 * (t >> 1) + 1 + (int)(t & 1)] * d;
+        }
+        float zv[UP / 4], cv[UP / 4];
+        auto fetch = [&](int j0) {
+            const int j = j0 + lane < d ? j0 + lane : d - 1;
+#pragma unroll
+            for (int u = 0; u < UP / 4; ++u) {
+                zv[u] = zr[u][j];
+                cv[u] = cr[u][j];
+            }
+        };
         double s = 0.0;
-        int j = 0;
-        for (; j + 32 <= d; j += 32) {  // the order of the additions is the rule; 64 loads are requested at once
-            float zv[32], cv[32];
+        fetch(0);
+        for (int j0 = 0; j0 < d; j0 += UD) {
+            __syncthreads();   // the sums of the dimensions before have been taken
 #pragma unroll
-            for (int e = 0; e < 32; ++e) {
-                zv[e] = zr[j + e];
-                cv[e] = cr[j + e];
+            for (int u = 0; u < UP / 4; ++u) {
+                const double t = (double)zv[u] - (double)cv[u];
+                sq[(UP / 4) * wave + u][lane] = t * t;
             }
-#pragma unroll
-            for (int e = 0; e < 32; ++e) {
-                double u = (double)zv[e] - (double)cv[e];
-                double u2 = u * u;
-                s = s + u2;
+            __syncthreads();
+            fetch(j0 + UD);
+            if (threadIdx.x < UP) {
+                const int m = d - j0 < UD ? d - j0 : UD;
+                if (m == UD) {
+#pragma unroll 16
+                    for (int e = 0; e < UD; ++e) s = s + sq[threadIdx.x][e];
+                } else {
+                    for (int e = 0; e < m; ++e) s = s + sq[threadIdx.x][e];
+                }
             }
         }
-        for (; j < d; ++j) {
-            double u = (double)zr[j] - (double)cr[j];
-            double u2 = u * u;
-            s = s + u2;
+        if (threadIdx.x < UP) {   // neighbouring lanes hold a point's two candidates: the lower index if equal
+            long long t = s0 + threadIdx.x;
+            const bool live = t < 2 * npairs;
+            t = live ? t : 2 * npairs - 1;
+            const int c = pairs[3 * (t >> 1) + 1 + (int)(t & 1)];
+            const double so = __shfl_xor(s, 1, 64);
+            const int co = __shfl_xor(c, 1, 64);
+            if (live && (t & 1) == 0) out[pairs[3 * (t >> 1)]] = (so < s || (so == s && co < c)) ? co : c;
         }
-        const double so = __shfl_xor(s, 1, 64);
-        const int co = __shfl_xor(c, 1, 64);
-        if (live && (t & 1) == 0) out[p] = (so < s || (so == s && co < c)) ? co : c;
     }
 }
 
-hipError_t launch_assign_pairs(const float *Z, int d, const float *cent, int32_t *out, const int *pairs,
-                               const int *pair_count, hipStream_t s)
+hipError_t launch_assign_undecided(const float *Z, int d, const float *cent, int k, int32_t *out, const int *list,
+                                   const int *pairs, const int *count, hipStream_t s)
 {
-    hipLaunchKernelGGL(assign_pairs_kernel, dim3(512), dim3(256), 0, s, Z, d, cent, out, pairs, pair_count);
+    hipLaunchKernelGGL(assign_undecided_kernel, dim3(1024), dim3(256), 0, s, Z, d, cent, k, out, list, pairs, count);
     return hipGetLastError();
 }
 
-hipError_t launch_assign_kmeans(const float *Z, long long N, int d, const float *cent, int k, int32_t *out,
-                                const int *list, const int *list_count, hipStream_t s)
+hipError_t launch_assign_kmeans(const float *Z, long long N, int d, const float *cent, int k, int32_t *out, hipStream_t s)
 {
-    if (list) {
-        hipLaunchKernelGGL(assign_list_kernel, dim3(2048), dim3(256), sizeof(float) * (size_t)d, s, Z, d, cent, k, out,
-                           list, list_count);
-        return hipGetLastError();
-    }
     int grid = (int)((N + TILE - 1) / TILE);
-    hipLaunchKernelGGL(assign_kernel<0>, dim3(grid), dim3(256), 0, s, Z, N, d, cent, k, out, list, list_count);
+    hipLaunchKernelGGL(assign_kernel<0>, dim3(grid), dim3(256), 0, s, Z, N, d, cent, k, out);
     return hipGetLastError();
 }
 
@@ -597,8 +629,7 @@ hipError_t launch_assign_crosspolytope(const float *Z, long long N, int d, const
                                        hipStream_t s)
 {
     int grid = (int)((N + TILE - 1) / TILE);
-    hipLaunchKernelGGL(assign_kernel<1>, dim3(grid), dim3(256), 0, s, Z, N, d, Rm, b / 2, out, (const int *)nullptr,
-                       (const int *)nullptr);
+    hipLaunchKernelGGL(assign_kernel<1>, dim3(grid), dim3(256), 0, s, Z, N, d, Rm, b / 2, out);
     return hipGetLastError();
 }
 
@@ -729,21 +760,50 @@ hipError_t launch_combine_hash(int32_t *acc, const int32_t *h, int b, int first,
 // -------------------------------------------------------- k-means update --
 //
 // Member sums in 2^-32 fixed point: integer addition is associative, so the
-// sums are the same in any order (and the counting sort below may place the
-// members of a cluster in any order).  Per Lloyd update:
+// sums are the same in any order.  Two ways to them:
+//
+// kmeans_by_members (few clusters times points): a workgroup takes ONE cluster and a range of at most 8192 points, reads
+// that range's assignments, keeps the indices of its members in LDS and adds up their rows.  One range: the new
+// centroid follows in the same launch; several: a second launch adds up the ranges' sums.  Every workgroup of a range
+// reads the same assignments (from the cache, 4 k N bytes in all).
+//
+// Otherwise a counting sort of the points by cluster first:
 //   count   -- members per cluster (histogram in LDS, one device atomic per
 //              workgroup and cluster present);
 //   scatter -- point indices grouped by cluster (each workgroup redoes the
 //              small scan of the counts, reserves its ranges with one atomic per
 //              cluster present and ranks its points in LDS);
-//   sum     -- one workgroup per (cluster, slice of 64 dimensions): its 16
-//              wavefronts share out the members, every member is one coalesced
-//              256-byte read, and the mean is written straight to the centroid.
-// The point matrix is read once, by rows; nothing but the centroids is written.
-// The count and cursor arrays exist twice and alternate between updates: the sum
+//   partial, mean -- see there (rows of more than 512 dimensions: sum).
+// The count and cursor arrays exist twice and alternate between updates: the last
 // kernel clears the pair the next update will use.
+//
+// Whoever writes a centroid also writes its bf16 planes and squared norm for the next assignment step.
 
 constexpr int KM_POINTS = 2048;  // points per workgroup of count and scatter
+
+__device__ inline void write_centroid(float *cent, const CentroidPlanes &P, int c, int d, int j, float v)
+{
+    cent[(long long)c * d + j] = v;
+    if (P.first) {   // operand order: groups of 32 rows, steps of 16 dimensions, lane = row % 32 + 32 (j % 16 / 8)
+        const long long at = (((long long)(c >> 5) * P.steps + (j >> 4)) * 64 + (c & 31) + 32 * (j >> 3 & 1)) * 8 + (j & 7);
+        const unsigned h = bf16_bits(v);
+        P.first[at] = (unsigned short)h;
+        P.first[P.plane + at] = (unsigned short)bf16_bits(v - __uint_as_float(h << 16));   // the difference is exact
+    }
+}
+
+// The centroid's squared norm from every thread's share of it; sh: a double per wavefront of the workgroup.
+__device__ inline void write_norm(const CentroidPlanes &P, int c, double sq, double *sh)
+{
+    for (int o = 1; o < 64; o <<= 1) sq += __shfl_xor(sq, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0 && P.first) {
+        double s = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += sh[w];
+        P.cn[c] = (float)s;
+    }
+}
 
 __global__ __launch_bounds__(256) void kmeans_count_kernel(const int32_t *__restrict__ assign, long long N, int k,
                                                            int *__restrict__ counts)
@@ -815,7 +875,7 @@ __global__ __launch_bounds__(64 * WPB) void kmeans_sum_kernel(const float *__res
                                                           const int *__restrict__ counts, const int *__restrict__ offs,
                                                           const int *__restrict__ order, float *__restrict__ cent,
                                                           int *__restrict__ counts_next, int *__restrict__ cursor_next,
-                                                          unsigned *reset_a, int *reset_b)
+                                                          int *reset)
 {
     constexpr int RPL = 64 / SW;   // members per wave-wide load
     __shared__ long long red[WPB][SW];
@@ -826,12 +886,9 @@ __global__ __launch_bounds__(64 * WPB) void kmeans_sum_kernel(const float *__res
     if (slice == 0 && threadIdx.x == 0) {  // scratch of the next assignment and update steps starts from zero
         counts_next[c] = 0;
         cursor_next[c] = 0;
-        if (c == 0) {
-            if (reset_a) *reset_a = 0u;
-            if (reset_b) {
-                reset_b[0] = 0;
-                reset_b[1] = 0;
-            }
+        if (c == 0 && reset) {
+            reset[0] = 0;
+            reset[1] = 0;
         }
     }
     const int cnt = counts[c];
@@ -889,13 +946,25 @@ __global__ __launch_bounds__(64 * WPB) void kmeans_sum_kernel(const float *__res
 // The fixed-point value of an entry: z 2^32 + 1.5 2^52 rounds to an integer (to nearest even, as rint
 // does) whose low mantissa bits are that integer in two's complement, so the bit patterns are added
 // as they are and the constants' share is taken off per member (all modulo 2^64).
+constexpr int KM_RANGE = 8192;   // points a workgroup looks through for its cluster's members
+// Clusters times points up to which every cluster's workgroups look through the assignments themselves: 268 MB of reads
+// from the cache, about what counting and scattering take.
+constexpr long long KM_MEMBERS_WORK = 1ll << 26;
+
+static int kmeans_ranges(long long N) { return (int)((N + KM_RANGE - 1) / KM_RANGE); }
+
+bool kmeans_by_members(long long N, int k, int d) { return d <= 512 && (long long)k * N <= KM_MEMBERS_WORK; }
+
 int kmeans_sum_chunk(long long N) { return N <= 65536 ? 16 : N <= 131072 ? 32 : N <= 262144 ? 64 : 128; }
 
 size_t kmeans_partial_elems(long long N, int kmax, int d)
 {
     if (d > 512) return 1;   // wider rows take the sliced kernel, which needs none
     const int M = kmeans_sum_chunk(N);
-    return (size_t)((N + M - 1) / M + kmax) * (size_t)d;
+    // (any number of clusters up to kmax, by whichever way that number takes)
+    const long long k = KM_MEMBERS_WORK / N < kmax ? KM_MEMBERS_WORK / N : kmax;
+    const size_t sorted = (size_t)((N + M - 1) / M + kmax), members = (size_t)k * (size_t)kmeans_ranges(N);
+    return (members > sorted ? members : sorted) * (size_t)d;
 }
 
 constexpr unsigned long long FIX_MAGIC_BITS = 0x4338000000000000ull;   // 1.5 * 2^52
@@ -983,22 +1052,20 @@ __global__ __launch_bounds__(512) void kmeans_mean_kernel(const unsigned long lo
                                                           const int *__restrict__ counts,
                                                           const int *__restrict__ offs, float *__restrict__ cent,
                                                           int *__restrict__ counts_next,
-                                                          int *__restrict__ cursor_next, unsigned *reset_a,
-                                                          int *reset_b)
+                                                          int *__restrict__ cursor_next, CentroidPlanes planes,
+                                                          int *reset)
 {
     __shared__ unsigned long long red[8][NS][64];
+    __shared__ double norm_sh[8];
     const int c = blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x == 0) {  // scratch of the next assignment and update steps starts from zero
         counts_next[c] = 0;
         cursor_next[c] = 0;
-        if (c == 0) {
-            if (reset_a) *reset_a = 0u;
-            if (reset_b) {
-                reset_b[0] = 0;
-                reset_b[1] = 0;
-            }
+        if (c == 0 && reset) {
+            reset[0] = 0;
+            reset[1] = 0;
         }
     }
     const int cnt = counts[c];
@@ -1030,32 +1097,213 @@ __global__ __launch_bounds__(512) void kmeans_mean_kernel(const unsigned long lo
 #pragma unroll
     for (int q = 0; q < NS; ++q) red[wave][q][lane] = sum[q];
     __syncthreads();
+    double sq = 0.0;
     for (int t = threadIdx.x; t < 64 * NS; t += 512) {
         const int q = t >> 6, jl = t & 63, j = 64 * q + jl;
         if (j < d) {
             unsigned long long tot = 0ull;
 #pragma unroll
             for (int w = 0; w < 8; ++w) tot += red[w][q][jl];
-            const double mean = ((double)(long long)tot * (1.0 / 4294967296.0)) / (double)cnt;
-            cent[(long long)c * d + j] = (float)mean;
+            const float mean = (float)(((double)(long long)tot * (1.0 / 4294967296.0)) / (double)cnt);
+            write_centroid(cent, planes, c, d, j, mean);
+            sq += (double)mean * (double)mean;
         }
+    }
+    write_norm(planes, c, sq, norm_sh);
+}
+
+// grid: (clusters, ranges).  Ranges are cut where the assignments are aligned to four of them; the first one also
+// takes what comes before.  ONE: a single range, the centroid is written here; otherwise the range's sums go to
+// part[cluster][range][d] and its number of members to cnts[cluster][range].
+// What bounds it is the largest cluster of a range (early assignments are lopsided), hence eight wavefronts, eight rows in
+// flight each; little LDS (indices as 16-bit distances, the sums in their place afterwards), as the k-means runs
+// of a build and its other kernels share the compute units.
+constexpr int KM_THREADS = 512, KM_WAVES = KM_THREADS / 64;
+
+template <int NS, bool ONE>
+__global__ __launch_bounds__(KM_THREADS) void kmeans_members_kernel(const float *__restrict__ Z, long long N, int d,
+                                                                    const int32_t *__restrict__ assign,
+                                                                    unsigned long long *__restrict__ part,
+                                                                    int *__restrict__ cnts, float *__restrict__ cent,
+                                                                    CentroidPlanes planes, int *reset)
+{
+    constexpr int LIST_BYTES = 2 * (KM_RANGE + 4), RED_BYTES = 8 * (KM_WAVES / 2) * NS * 64;
+    __shared__ __align__(16) unsigned char room[LIST_BYTES > RED_BYTES ? LIST_BYTES : RED_BYTES];
+    unsigned short *members = (unsigned short *)room;   // distances from the range's start
+    unsigned long long(*red)[NS][64] = (unsigned long long(*)[NS][64])room;   // [KM_WAVES / 2], once the rows are added up
+    __shared__ double norm_sh[KM_WAVES];
+    __shared__ int found;
+    const int c = blockIdx.x, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x == 0) {
+        found = 0;
+        if (ONE && c == 0 && reset) {
+            reset[0] = 0;
+            reset[1] = 0;
+        }
+    }
+    __syncthreads();
+    const int head = (int)((16 - ((uintptr_t)assign & 15)) & 15) / 4;   // until the next multiple of 16 bytes
+    const long long lo = (long long)blockIdx.y * KM_RANGE + head;       // where the range's whole groups of four begin
+    const long long start = blockIdx.y == 0 ? 0 : lo;
+    auto keep = [&](long long i) { members[atomicAdd(&found, 1)] = (unsigned short)(i - start); };
+    if (blockIdx.y == 0 && (int)threadIdx.x < head && threadIdx.x < N && assign[threadIdx.x] == c) keep(threadIdx.x);
+    {   // all loads requested before the first is looked at (a group past the end: the last whole one again, not
+        // looked at)
+        const long long whole = N - head > 3 ? (N - head) / 4 * 4 + head : head;   // end of the whole groups
+        constexpr int PER = KM_RANGE / (4 * KM_THREADS);
+        if (whole > head) {
+            int4 v[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const long long i = lo + 4 * (KM_THREADS * u + (int)threadIdx.x);
+                v[u] = *(const int4 *)(assign + (i < whole ? i : whole - 4));
+            }
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const long long i = lo + 4 * (KM_THREADS * u + (int)threadIdx.x);
+                const bool x = v[u].x == c, y = v[u].y == c, z = v[u].z == c, w = v[u].w == c;
+                if ((x || y || z || w) && i < whole) {
+                    if (x) keep(i);
+                    if (y) keep(i + 1);
+                    if (z) keep(i + 2);
+                    if (w) keep(i + 3);
+                }
+            }
+        }
+        const long long i = whole + threadIdx.x;   // up to three left over
+        if (threadIdx.x < 3 && i < N && i >= lo && i < lo + KM_RANGE && assign[i] == c) keep(i);
+    }
+    __syncthreads();
+    const int cnt = found;
+    unsigned long long sum[NS];
+    int jc[NS];
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+        sum[q] = 0ull;
+        jc[q] = 64 * q + lane < d ? 64 * q + lane : d - 1;
+    }
+    int held = 0;
+    // eight rows at a time per wavefront, all loads unconditional (see kmeans_partial_kernel for the arithmetic)
+    for (int u0 = 8 * wave; u0 < cnt; u0 += 8 * KM_WAVES) {
+        float z[8][NS];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int row = __builtin_amdgcn_readfirstlane((int)start + members[u0 + u < cnt ? u0 + u : cnt - 1]);
+            const float *__restrict__ zrow = Z + (long long)row * d;
+#pragma unroll
+            for (int q = 0; q < NS; ++q) z[u][q] = zrow[jc[q]];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (u0 + u < cnt) {   // the same in every lane
+                ++held;
+#pragma unroll
+                for (int q = 0; q < NS; ++q)
+                    sum[q] += (unsigned long long)__double_as_longlong(fma((double)z[u][q], 4294967296.0, 6755399441055744.0));
+            }
+    }
+    __syncthreads();   // the list has been read
+    if (wave >= KM_WAVES / 2)
+#pragma unroll
+        for (int q = 0; q < NS; ++q) red[wave - KM_WAVES / 2][q][lane] = sum[q] - (unsigned long long)held * FIX_MAGIC_BITS;
+    __syncthreads();
+    if (wave < KM_WAVES / 2)
+#pragma unroll
+        for (int q = 0; q < NS; ++q) red[wave][q][lane] += sum[q] - (unsigned long long)held * FIX_MAGIC_BITS;
+    __syncthreads();
+    if (ONE && cnt == 0) return;   // an empty cluster keeps its centroid (the same in every thread)
+    double sq = 0.0;
+    for (int t = threadIdx.x; t < 64 * NS; t += KM_THREADS) {
+        const int q = t >> 6, jl = t & 63, j = 64 * q + jl;
+        if (j < d) {
+            unsigned long long tot = 0ull;
+#pragma unroll
+            for (int w = 0; w < KM_WAVES / 2; ++w) tot += red[w][q][jl];
+            if (ONE) {
+                const float mean = (float)(((double)(long long)tot * (1.0 / 4294967296.0)) / (double)cnt);
+                write_centroid(cent, planes, c, d, j, mean);
+                sq += (double)mean * (double)mean;
+            } else {
+                part[((size_t)c * gridDim.y + blockIdx.y) * (size_t)d + j] = tot;
+            }
+        }
+    }
+    if (ONE)
+        write_norm(planes, c, sq, norm_sh);
+    else if (threadIdx.x == 0)
+        cnts[c * gridDim.y + blockIdx.y] = cnt;
+}
+
+// Adds up a cluster's ranges and writes its centroid; one workgroup per cluster.
+__global__ __launch_bounds__(256) void kmeans_ranges_kernel(const unsigned long long *__restrict__ part, int d, int ranges,
+                                                            const int *__restrict__ cnts, float *__restrict__ cent,
+                                                            CentroidPlanes planes, int *reset)
+{
+    __shared__ double norm_sh[4];
+    const int c = blockIdx.x;
+    if (threadIdx.x == 0 && c == 0 && reset) {
+        reset[0] = 0;
+        reset[1] = 0;
+    }
+    int cnt = 0;
+    for (int r = 0; r < ranges; ++r) cnt += cnts[c * ranges + r];
+    if (cnt == 0) return;  // an empty cluster keeps its centroid (the same in every thread)
+    double sq = 0.0;
+    for (int j = threadIdx.x; j < d; j += 256) {
+        unsigned long long tot = 0ull;
+#pragma unroll 8
+        for (int r = 0; r < ranges; ++r) tot += part[((size_t)c * ranges + r) * (size_t)d + j];
+        const float mean = (float)(((double)(long long)tot * (1.0 / 4294967296.0)) / (double)cnt);
+        write_centroid(cent, planes, c, d, j, mean);
+        sq += (double)mean * (double)mean;
+    }
+    write_norm(planes, c, sq, norm_sh);
+}
+
+template <int NS>
+static void launch_members(const float *Z, long long N, int d, const int32_t *assign, int k, int *cnts,
+                           unsigned long long *part, float *cent, const CentroidPlanes &planes, int *reset, hipStream_t s)
+{
+    const int ranges = kmeans_ranges(N);
+    if (ranges == 1) {
+        hipLaunchKernelGGL((kmeans_members_kernel<NS, true>), dim3((unsigned)k), dim3(KM_THREADS), 0, s, Z, N, d, assign, part, cnts,
+                           cent, planes, reset);
+    } else {
+        hipLaunchKernelGGL((kmeans_members_kernel<NS, false>), dim3((unsigned)k, (unsigned)ranges), dim3(KM_THREADS), 0, s, Z, N, d,
+                           assign, part, cnts, cent, planes, reset);
+        hipLaunchKernelGGL(kmeans_ranges_kernel, dim3((unsigned)k), dim3(256), 0, s, part, d, ranges, cnts, cent, planes,
+                           reset);
     }
 }
 
-// counts2 / cursor2: [2][k] each, zero on the first call of a k-means run; offs: [k]; `parity` alternates per call.
-// part: kmeans_partial_elems(N, k, d) 64-bit words of scratch (rows of up to 512 dimensions).
-// reset_a / reset_b (nullable) are cleared for the next assignment step.
 hipError_t launch_kmeans_update(const float *Z, long long N, int d, const int32_t *assign, int k, int *counts2,
                                 int *cursor2, int *order, int *offs, long long *part, int parity, float *cent,
-                                unsigned *reset_a, int *reset_b, hipStream_t s)
+                                const CentroidPlanes &planes, int *reset, hipStream_t s)
 {
+    const int ns = (d + 63) / 64;
+    if (kmeans_by_members(N, k, d)) {
+#define LCN_MEMBERS(NS_) \
+    launch_members<NS_>(Z, N, d, assign, k, order, (unsigned long long *)part, cent, planes, reset, s)
+        switch (ns) {
+            case 1: LCN_MEMBERS(1); break;
+            case 2: LCN_MEMBERS(2); break;
+            case 3: LCN_MEMBERS(3); break;
+            case 4: LCN_MEMBERS(4); break;
+            case 5: LCN_MEMBERS(5); break;
+            case 6: LCN_MEMBERS(6); break;
+            case 7: LCN_MEMBERS(7); break;
+            default: LCN_MEMBERS(8); break;
+        }
+#undef LCN_MEMBERS
+        return hipGetLastError();
+    }
     int *counts = counts2 + (size_t)(parity & 1) * k, *counts_next = counts2 + (size_t)((parity + 1) & 1) * k;
     int *cursor = cursor2 + (size_t)(parity & 1) * k, *cursor_next = cursor2 + (size_t)((parity + 1) & 1) * k;
     const unsigned blocks = (unsigned)((N + KM_POINTS - 1) / KM_POINTS);
     hipLaunchKernelGGL(kmeans_count_kernel, dim3(blocks), dim3(256), sizeof(int) * (size_t)k, s, assign, N, k, counts);
     hipLaunchKernelGGL(kmeans_scatter_kernel, dim3(blocks), dim3(256), 2 * sizeof(int) * (size_t)k, s, assign, N, k,
                        counts, cursor, order, offs);
-    const int ns = (d + 63) / 64;
     if (ns <= 8) {
         const int M = kmeans_sum_chunk(N);
         const unsigned pblocks = (unsigned)(((N + M - 1) / M + 3) / 4);
@@ -1063,8 +1311,7 @@ hipError_t launch_kmeans_update(const float *Z, long long N, int d, const int32_
     hipLaunchKernelGGL((kmeans_partial_kernel<NS_>), dim3(pblocks), dim3(256), 0, s, Z, N, d, M, assign, order,       \
                        (unsigned long long *)part);                                                                    \
     hipLaunchKernelGGL((kmeans_mean_kernel<NS_>), dim3((unsigned)k), dim3(512), 0, s,                                  \
-                       (const unsigned long long *)part, d, M, counts, offs, cent, counts_next, cursor_next, reset_a, \
-                       reset_b)
+                       (const unsigned long long *)part, d, M, counts, offs, cent, counts_next, cursor_next, planes, reset)
         switch (ns) {
             case 1: LCN_SUM_PARTIAL(1); break;
             case 2: LCN_SUM_PARTIAL(2); break;
@@ -1076,13 +1323,19 @@ hipError_t launch_kmeans_update(const float *Z, long long N, int d, const int32_
             default: LCN_SUM_PARTIAL(8); break;
         }
 #undef LCN_SUM_PARTIAL
-    } else if ((long long)k * ((d + 63) / 64) >= 512)
+        return hipGetLastError();
+    }
+    if ((long long)k * ((d + 63) / 64) >= 512)
         hipLaunchKernelGGL((kmeans_sum_kernel<64, 16>), dim3((unsigned)k, (unsigned)((d + 63) / 64)), dim3(1024), 0, s, Z,
-                           d, k, counts, offs, order, cent, counts_next, cursor_next, reset_a, reset_b);
+                           d, k, counts, offs, order, cent, counts_next, cursor_next, reset);
     else   // few clusters: narrower slices, four times the workgroups
         hipLaunchKernelGGL((kmeans_sum_kernel<16, 16>), dim3((unsigned)k, (unsigned)((d + 15) / 16)), dim3(1024), 0, s, Z,
-                           d, k, counts, offs, order, cent, counts_next, cursor_next, reset_a, reset_b);
-    return hipGetLastError();
+                           d, k, counts, offs, order, cent, counts_next, cursor_next, reset);
+    hipError_t e = hipGetLastError();
+    // a centroid's slices are written by several workgroups: the planes and norms follow in a launch of their own
+    if (e == hipSuccess && planes.first && reset)   // (the last iteration's are not used)
+        e = launch_kmeans_start(nullptr, nullptr, cent, k, d, planes.first, planes.cn, reset, s);
+    return e;
 }
 
 // ------------------------------------------------------------ bucket sort --

@@ -74,7 +74,6 @@ struct KmScratch {  // what one k-means run needs for itself
     long long *part;                        // ... and its partial sums
     int32_t *assign;
     float *cn;
-    unsigned *cmax_bits;
     int *flagged, *nflagged, *pairs;
     unsigned long long *pp_state;  // k-means++: bits of the largest squared norm
     int *horder, *hchunks, *nchild;  // hierarchical k-means: points grouped by parent, chunk list, children per parent
@@ -115,10 +114,9 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
         KmScratch &km = sc.km[q];
         km.idx = bump.take<long long>((size_t)kmax);
         km.cent = bump.take<float>((size_t)kmax * h.d);
-        // counts2 .. nflagged are cleared together at the start of a k-means run
+        // counts2 and cursor2 are cleared together at the start of a k-means run that uses them
         km.counts2 = bump.take<int>(2 * (size_t)kmax);
         km.cursor2 = bump.take<int>(2 * (size_t)kmax);
-        km.cmax_bits = bump.take<unsigned>(4);
         km.nflagged = bump.take<int>(4);
         km.order = bump.take<int>((size_t)N);
         km.offs = bump.take<int>((size_t)kmax);
@@ -310,30 +308,34 @@ lcn_status run_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s, int 
         // the assignment's buffers are free until the first Lloyd iteration
         HIPCHK(launch_kmeanspp(h.Z, N, h.d, k, (const unsigned long long *)km.idx, (double *)km.pairs,
                                (unsigned long long *)km.flagged, km.order, km.pp_state, cent, s));
-    } else if (start_dev) {
-        HIPCHK(launch_gather_rows(h.Z, h.d, start_dev, k, cent, s));
-    } else {
+    } else if (!start_dev) {
         std::vector<long long> idx = seeded_indices(seed, N, k);
         HIPCHK(hipMemcpyAsync(km.idx, idx.data(), sizeof(long long) * (size_t)k, hipMemcpyHostToDevice, s));
         HIPCHK(hipStreamSynchronize(s));  // idx is a local host vector
-        HIPCHK(launch_gather_rows(h.Z, h.d, km.idx, k, cent, s));
+        start_dev = km.idx;
     }
-    // member counts and cursors of the update, the filter's largest centroid norm and its two
-    // counters lie side by side: one clear
-    HIPCHK(hipMemsetAsync(km.counts2, 0, (size_t)((char *)(km.nflagged + 4) - (char *)km.counts2), s));
+    // (start_dev: the starts are points, still to be copied)
+    CentroidPlanes planes{};
+    if (h.exact_assign_only || T == 0) {
+        if (start_dev) HIPCHK(launch_gather_rows(h.Z, h.d, start_dev, k, cent, s));
+        HIPCHK(hipMemsetAsync(km.nflagged, 0, 2 * sizeof(int), s));
+    } else {
+        planes = centroid_planes(km.ct, k, h.d, km.cn);
+        HIPCHK(launch_kmeans_start(h.Z, start_dev, cent, k, h.d, km.ct, km.cn, km.nflagged, s));
+    }
+    if (T > 0 && !kmeans_by_members(N, k, h.d))   // member counts and cursors of the update lie side by side
+        HIPCHK(hipMemsetAsync(km.counts2, 0, (size_t)((char *)km.nflagged - (char *)km.counts2), s));
     for (int it = 0; it < T; ++it) {
         if (h.exact_assign_only) {
-            HIPCHK(launch_assign_kmeans(h.Z, N, h.d, cent, k, assign, nullptr, nullptr, s));
+            HIPCHK(launch_assign_kmeans(h.Z, N, h.d, cent, k, assign, s));
         } else {
-            HIPCHK(launch_assign_filter(sc.zt, sc.zplanes, N, h.d, cent, k, km.ct, h.zn, km.cn, km.cmax_bits, assign,
-                                        km.flagged, km.pairs, km.nflagged, s));
-            if (filter_uses_pairs(k))
-                HIPCHK(launch_assign_pairs(h.Z, h.d, cent, assign, km.pairs, km.nflagged + 1, s));
-            HIPCHK(launch_assign_kmeans(h.Z, N, h.d, cent, k, assign, km.flagged, km.nflagged, s));
+            HIPCHK(launch_assign_filter(sc.zt, sc.zplanes, N, h.d, k, km.ct, h.zn, km.cn, assign, km.flagged, km.pairs,
+                                        km.nflagged, s));
+            HIPCHK(launch_assign_undecided(h.Z, h.d, cent, k, assign, km.flagged, km.pairs, km.nflagged, s));
         }
         // the last iteration leaves the count of undecided points in place for lcn_get_info
         HIPCHK(launch_kmeans_update(h.Z, N, h.d, assign, k, km.counts2, km.cursor2, km.order, km.offs, km.part, it, cent,
-                                    km.cmax_bits, it + 1 < T ? km.nflagged : nullptr, s));
+                                    planes, it + 1 < T ? km.nflagged : nullptr, s));
     }
     return LCN_OK;
 }
@@ -397,7 +399,7 @@ lcn_status run_hier_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s,
             HIPCHK(launch_assign_children(h.Z, h.d, km.cent, parents, bl, km.nchild, km.horder, km.hchunks, nchunks,
                                           km.hcent, dst, s));
             HIPCHK(launch_kmeans_update(h.Z, N, h.d, dst, (int)k, km.counts2, km.cursor2, km.order, km.offs, km.part,
-                                        it, km.cent, nullptr, nullptr, s));
+                                        it, km.cent, CentroidPlanes{}, nullptr, s));
         }
         parents = k;
     }

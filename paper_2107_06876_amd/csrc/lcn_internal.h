@@ -74,30 +74,45 @@ hipError_t launch_combine_hash(int32_t *acc, const int32_t *h, int b, int first,
 hipError_t launch_kmeanspp(const float *Z, long long N, int d, int k, const unsigned long long *rnd, double *w,
                            unsigned long long *partial, int *picks, unsigned long long *state, float *cent,
                            hipStream_t s);
-// exact rule for all points (list == nullptr) or for the listed ones
-hipError_t launch_assign_kmeans(const float *Z, long long N, int d, const float *cent, int k, int32_t *out,
-                                const int *list, const int *list_count, hipStream_t s);
+// exact rule for all points
+hipError_t launch_assign_kmeans(const float *Z, long long N, int d, const float *cent, int k, int32_t *out, hipStream_t s);
 // bf16 planes of a row-major fp32 matrix in matrix-instruction operand order (kernels_mfma.hip)
 size_t split_plane_bytes(long long rows, int d);
 hipError_t launch_split_planes(const float *src, long long rows, int d, int planes, void *out, hipStream_t s);
+// bf16 of a finite float, round to nearest even: |x - bf16(x)| <= 2^-8 |x|
+__device__ inline unsigned bf16_bits(float x)
+{
+    const unsigned u = __float_as_uint(x);
+    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+// The centroids' two bf16 planes in operand order and their squared norms; first == nullptr: not kept.
+struct CentroidPlanes {
+    unsigned short *first;
+    long long plane;   // entries from one plane to the other
+    int steps;         // of 16 dimensions
+    float *cn;
+};
+CentroidPlanes centroid_planes(void *Ct, int k, int d, float *cn);
+hipError_t launch_kmeans_start(const float *Z, const long long *pick, float *cent, int k, int d, void *Ct, float *cn,
+                               int *nflagged, hipStream_t s);
 // MFMA filter: writes the assignment of every point and lists those it could not decide.
-// Zt: planes of the points (zplanes of them); Ct: room for two planes of k centroids.
-hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, const float *cent, int k, void *Ct,
-                                const double *zn, float *cn, unsigned *cmax_bits, int32_t *out, int *flagged,
-                                int *pairs, int *nflagged, hipStream_t s);
-bool filter_uses_pairs(int k);
-// exact rule on two candidate centroids per listed point: pairs = (point, c1, c2) triples
-hipError_t launch_assign_pairs(const float *Z, int d, const float *cent, int32_t *out, const int *pairs,
-                               const int *pair_count, hipStream_t s);
+// Zt: planes of the points (zplanes of them); Ct: two planes of k centroids.
+hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, int k, const void *Ct, const double *zn,
+                                const float *cn, int32_t *out, int *flagged, int *pairs, int *nflagged, hipStream_t s);
+// exact rule on what the filter left: list of points (count[0]) over all centroids, pairs = (point, c1, c2) triples
+// (count[1]) over two
+hipError_t launch_assign_undecided(const float *Z, int d, const float *cent, int k, int32_t *out, const int *list,
+                                   const int *pairs, const int *count, hipStream_t s);
 hipError_t launch_assign_crosspolytope(const float *Z, long long N, int d, const float *Rm, int b, int32_t *out,
                                        hipStream_t s);
-// counts2 / cursor2: [2][k] ints each, zero before the first update of a k-means run; order: [N], offs: [k] ints;
-// part: kmeans_partial_elems(N, largest k, d) 64-bit words of scratch for the partial sums;
-// `parity` alternates from update to update.  reset_a / reset_b (nullable) are cleared for the next
-// assignment step.
+// New centroids from the assignment.  counts2 / cursor2: [2][k] ints each, zero before the first update of a k-means
+// run (not used where kmeans_by_members() is true); order: [N], offs: [k] ints; part: kmeans_partial_elems(N, largest
+// k, d) 64-bit words of scratch for the partial sums; `parity` alternates from update to update; planes: the filter's
+// copy of the centroids, kept up to date; reset (nullable): two words cleared for the next assignment step.
 hipError_t launch_kmeans_update(const float *Z, long long N, int d, const int32_t *assign, int k, int *counts2,
                                 int *cursor2, int *order, int *offs, long long *part, int parity, float *cent,
-                                unsigned *reset_a, int *reset_b, hipStream_t s);
+                                const CentroidPlanes &planes, int *reset, hipStream_t s);
+bool kmeans_by_members(long long N, int k, int d);
 size_t kmeans_partial_elems(long long N, int kmax, int d);
 
 struct SortBuffers {
