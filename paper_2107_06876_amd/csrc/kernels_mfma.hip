@@ -53,14 +53,13 @@ size_t split_plane_bytes(long long rows, int d)
 // Splits the rows of `src` (rows x d, fp32) into `planes` bf16 planes in operand
 // order: out[plane][group][step][lane] (16 bytes each); rows and dimensions
 // beyond the matrix are zero.  One workgroup per group of 32 rows.
-// START (the centroids at the start of a k-means run): also the squared norm of every row as fp32 into cn;
-// with `pick` the rows are those of the points it names, which are written to `rows_out` as well; `zeros` (two
-// words) are cleared.
+// START (the centroids at the start of k-means runs, one per blockIdx.y): also the squared norm of every row as fp32
+// into cn; with `pick` the rows are those of the points it names, which are written to cent as well; the run's two
+// counters are cleared.
 template <bool START>
-__global__ __launch_bounds__(256) void split_planes_kernel(const float *__restrict__ src, long long rows, int d, int S,
-                                                           int planes, bf16x8 *__restrict__ out, long long plane_stride,
-                                                           float *__restrict__ cn, const long long *__restrict__ pick,
-                                                           float *rows_out, int *zeros)
+__device__ inline void split_group(const float *__restrict__ src, long long rows, int d, int S, int planes,
+                                   bf16x8 *__restrict__ out, long long plane_stride, float *__restrict__ cn,
+                                   const long long *__restrict__ pick, float *rows_out, int *zeros)
 {
     __shared__ double red[4][32];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -97,29 +96,47 @@ __global__ __launch_bounds__(256) void split_planes_kernel(const float *__restri
     }
 }
 
+__global__ __launch_bounds__(256) void split_planes_kernel(const float *__restrict__ src, long long rows, int d, int S,
+                                                           int planes, bf16x8 *__restrict__ out, long long plane_stride)
+{
+    split_group<false>(src, rows, d, S, planes, out, plane_stride, nullptr, nullptr, nullptr, nullptr);
+}
+
+__global__ __launch_bounds__(256) void kmeans_start_kernel(const float *__restrict__ Z, int d, int S, KmRuns R)
+{
+    const KmRun &r = R.run[blockIdx.y];
+    if ((int)blockIdx.x * 32 >= r.k) return;
+    split_group<true>(r.pick ? Z : r.cent, r.k, d, S, 2, (bf16x8 *)r.first, r.plane / 8, r.cn, r.pick, r.cent, r.nflagged);
+}
+
 hipError_t launch_split_planes(const float *src, long long rows, int d, int planes, void *out, hipStream_t s)
 {
     const long long groups = (rows + 31) / 32;
     const int S = steps_of(d);
-    hipLaunchKernelGGL(split_planes_kernel<false>, dim3((unsigned)groups), dim3(256), 0, s, src, rows, d, S, planes,
-                       (bf16x8 *)out, (long long)(split_plane_bytes(rows, d) / 16), (float *)nullptr,
-                       (const long long *)nullptr, (float *)nullptr, (int *)nullptr);
+    hipLaunchKernelGGL(split_planes_kernel, dim3((unsigned)groups), dim3(256), 0, s, src, rows, d, S, planes,
+                       (bf16x8 *)out, (long long)(split_plane_bytes(rows, d) / 16));
     return hipGetLastError();
 }
 
-CentroidPlanes centroid_planes(void *Ct, int k, int d, float *cn)
+void centroid_planes(KmRun &r, void *Ct, float *cn, int d)
 {
-    return CentroidPlanes{(unsigned short *)Ct, (long long)(split_plane_bytes(k, d) / 2), steps_of(d), cn};
+    r.first = (unsigned short *)Ct;
+    r.plane = (long long)(split_plane_bytes(r.k, d) / 2);
+    r.cn = cn;
 }
 
-// The start of a k-means run for the filter: centroids from the points that `pick` names (null: cent is given),
-// their two bf16 planes and squared norms, and the two counters of undecided points at zero, in one launch.
-hipError_t launch_kmeans_start(const float *Z, const long long *pick, float *cent, int k, int d, void *Ct, float *cn,
-                               int *nflagged, hipStream_t s)
+static int most_clusters(const KmRuns &runs)
 {
-    hipLaunchKernelGGL(split_planes_kernel<true>, dim3((unsigned)((k + 31) / 32)), dim3(256), 0, s, pick ? Z : cent,
-                       (long long)k, d, steps_of(d), 2, (bf16x8 *)Ct, (long long)(split_plane_bytes(k, d) / 16), cn, pick,
-                       cent, nflagged);
+    int k = 0;
+    for (int q = 0; q < runs.count; ++q) k = runs.run[q].k > k ? runs.run[q].k : k;
+    return k;
+}
+
+// The start of k-means runs for the filter, in one launch.
+hipError_t launch_kmeans_start(const float *Z, int d, const KmRuns &runs, hipStream_t s)
+{
+    const unsigned groups = (unsigned)((most_clusters(runs) + 31) / 32);
+    hipLaunchKernelGGL(kmeans_start_kernel, dim3(groups, (unsigned)runs.count), dim3(256), 0, s, Z, d, steps_of(d), runs);
     return hipGetLastError();
 }
 
@@ -165,12 +182,14 @@ __device__ inline void filter_decide(long long p, float best, float second, floa
 // to the exact rule on those two, which is short.
 template <int ZP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void assign_filter_kernel(const bf16x8 *__restrict__ Zt, long long zplane, long long N,
-                                                            int S, const bf16x8 *__restrict__ Ct, long long cplane,
-                                                            int k, const float *__restrict__ cn,
-                                                            const double *__restrict__ zn, float err_coef,
-                                                            int32_t *__restrict__ out, int *__restrict__ flagged,
-                                                            int *__restrict__ pairs, int *nflagged)
+                                                            int S, const double *__restrict__ zn, float err_coef,
+                                                            KmRuns R)
 {
+    const KmRun &run = R.run[blockIdx.y];
+    const bf16x8 *__restrict__ Ct = (const bf16x8 *)run.first;
+    const long long cplane = run.plane / 8;
+    const int k = run.k;
+    const float *__restrict__ cn = run.cn;
     // [buffer][step of the stage][centroid group][plane][lane]: 32 KB
     __shared__ bf16x8 Cs[2][2][4][2][64];
     __shared__ float cn_s[FC];  // squared norms of the pass's centroids (+inf beyond the last one)
@@ -300,7 +319,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     const float cmax = largest_norm(cn, k, cmax_s);
     const long long p = P * 32 + col;
     if (active && half == 0 && p < N)
-        filter_decide(p, best, second, third, bidx, sidx, zn, cmax, err_coef, out, flagged, pairs, nflagged);
+        filter_decide(p, best, second, third, bidx, sidx, zn, cmax, err_coef, run.assign, run.flagged, run.pairs, run.nflagged);
 }
 
 // The filter for points given as bf16 (one plane) against many centroids: the 128 points of a
@@ -316,11 +335,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
 // points, over the centroids its wavefront saw; half-wavefronts and wavefronts are merged at the end.
 constexpr int FR_MERGE_BYTES = 4 * FP * 5 * 4;
 
-__global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
-    const bf16x8 *__restrict__ Zt, long long N, int S, const bf16x8 *__restrict__ Ct, long long cplane, int k,
-    const float *__restrict__ cn, const double *__restrict__ zn, float err_coef,
-    int32_t *__restrict__ out, int *__restrict__ flagged, int *__restrict__ pairs, int *nflagged)
+__global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(const bf16x8 *__restrict__ Zt, long long N, int S,
+                                                                        const double *__restrict__ zn, float err_coef,
+                                                                        KmRuns R)
 {
+    const KmRun &run = R.run[blockIdx.y];
+    const bf16x8 *__restrict__ Ct = (const bf16x8 *)run.first;
+    const long long cplane = run.plane / 8;
+    const int k = run.k;
+    const float *__restrict__ cn = run.cn;
     __shared__ float cmax_s[4];
     extern __shared__ __align__(16) unsigned char fr_lds[];
     bf16x8 *Zs = reinterpret_cast<bf16x8 *>(fr_lds);   // [4 point groups][S][64]
@@ -506,7 +529,7 @@ __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(
                 offer(b, s2, t3, bi, si, mf[(1 * 4 + ww) * FP + tid], mi[(1 * 4 + ww) * FP + tid]);
                 offer(b, s2, t3, bi, si, mf[(2 * 4 + ww) * FP + tid], 0);
             }
-            filter_decide(p, b, s2, t3, bi, si, zn, cmax, err_coef, out, flagged, pairs, nflagged);
+            filter_decide(p, b, s2, t3, bi, si, zn, cmax, err_coef, run.assign, run.flagged, run.pairs, run.nflagged);
         }
     }
 }
@@ -529,12 +552,10 @@ static hipError_t allow_dynamic_lds(const void *kernel, size_t bytes)
     return e;
 }
 
-// Zt: the points' planes (launch_split_planes, `zplanes` of them); Ct, cn: the centroids' two planes and squared
-// norms as the start of the run and the centroid updates leave them.  nflagged[0..1] are zero on entry.
-// flagged: points for the exact rule over all centroids (count nflagged[0]); pairs: (point, centroid, centroid)
-// triples for the exact rule on two centroids (count nflagged[1]).
-hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, int k, const void *Ct, const double *zn,
-                                const float *cn, int32_t *out, int *flagged, int *pairs, int *nflagged, hipStream_t s)
+// Zt: the points' planes (launch_split_planes, `zplanes` of them); the centroids' planes and squared norms are as the
+// start of a run and the centroid updates leave them, and so are the two counters, at zero.
+hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, const double *zn, const KmRuns &runs,
+                                hipStream_t s)
 {
     const int S = steps_of(d);
     // Bound on |computed score - exact score| / (||z||^2 + max ||c||^2):
@@ -550,25 +571,30 @@ hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d,
                            (float)(products * S) * 9.5367431640625e-7f + 4.76837158203125e-7f;
     const float err_safe = 1.02f * err_coef;  // |z1| and |c1| may exceed |z| and |c| by a factor 1 + 2^-8
     const long long zplane = (long long)(split_plane_bytes(N, d) / 16);
-    const long long cplane = (long long)(split_plane_bytes(k, d) / 16);
     const unsigned grid = (unsigned)((N + FP - 1) / FP);
     // points given as bf16, several passes over the centroids, and two workgroups' points fit the LDS
     // of a compute unit: the kernel that keeps the points on chip
-    if (zplanes == 1 && k > FC && S <= 19) {
+    KmRuns resident{}, others{};
+    for (int q = 0; q < runs.count; ++q) {
+        KmRuns &to = zplanes == 1 && runs.run[q].k > FC && S <= 19 ? resident : others;
+        to.run[to.count++] = runs.run[q];
+    }
+    if (resident.count > 0) {
         const size_t lds = (size_t)4 * S * 1024 > (size_t)FR_MERGE_BYTES ? (size_t)4 * S * 1024 : (size_t)FR_MERGE_BYTES;
         const unsigned rgrid = (unsigned)(((N + 31) / 32 + 3) / 4);
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&assign_filter_resident_kernel), lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(assign_filter_resident_kernel, dim3(rgrid), dim3(256), lds, s, (const bf16x8 *)Zt, N, S,
-                           (const bf16x8 *)Ct, cplane, k, cn, zn, err_safe, out, flagged, pairs, nflagged);
-        return hipGetLastError();
+        hipLaunchKernelGGL(assign_filter_resident_kernel, dim3(rgrid, (unsigned)resident.count), dim3(256), lds, s,
+                           (const bf16x8 *)Zt, N, S, zn, err_safe, resident);
     }
-    if (zplanes > 1)
-        hipLaunchKernelGGL(assign_filter_kernel<2>, dim3(grid), dim3(256), 0, s, (const bf16x8 *)Zt, zplane, N, S,
-                           (const bf16x8 *)Ct, cplane, k, cn, zn, err_safe, out, flagged, pairs, nflagged);
-    else
-        hipLaunchKernelGGL(assign_filter_kernel<1>, dim3(grid), dim3(256), 0, s, (const bf16x8 *)Zt, zplane, N, S,
-                           (const bf16x8 *)Ct, cplane, k, cn, zn, err_safe, out, flagged, pairs, nflagged);
+    if (others.count > 0) {
+        if (zplanes > 1)
+            hipLaunchKernelGGL(assign_filter_kernel<2>, dim3(grid, (unsigned)others.count), dim3(256), 0, s,
+                               (const bf16x8 *)Zt, zplane, N, S, zn, err_safe, others);
+        else
+            hipLaunchKernelGGL(assign_filter_kernel<1>, dim3(grid, (unsigned)others.count), dim3(256), 0, s,
+                               (const bf16x8 *)Zt, zplane, N, S, zn, err_safe, others);
+    }
     return hipGetLastError();
 }
 

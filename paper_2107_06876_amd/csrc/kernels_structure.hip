@@ -474,12 +474,13 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ Z
 constexpr int UP = 32, UD = 64;   // pairs of a point and a centroid, dimensions
 constexpr int UL = 32, UC = 256;  // dimensions and centroids at a time for a listed point
 
-__global__ __launch_bounds__(256) void assign_undecided_kernel(const float *__restrict__ Z, int d,
-                                                               const float *__restrict__ C, int k,
-                                                               int32_t *__restrict__ out, const int *__restrict__ list,
-                                                               const int *__restrict__ pairs,
-                                                               const int *__restrict__ count)
+__global__ __launch_bounds__(256) void assign_undecided_kernel(const float *__restrict__ Z, int d, KmRuns R)
 {
+    const KmRun &run = R.run[blockIdx.y];
+    const float *__restrict__ C = run.cent;
+    const int k = run.k;
+    int32_t *__restrict__ out = run.assign;
+    const int *__restrict__ list = run.flagged, *__restrict__ pairs = run.pairs, *__restrict__ count = run.nflagged;
     __shared__ double bv_sh[256];
     __shared__ int bi_sh[256];
     __shared__ float zs[2][UL];
@@ -611,10 +612,9 @@ __global__ __launch_bounds__(256) void assign_undecided_kernel(const float *__re
     }
 }
 
-hipError_t launch_assign_undecided(const float *Z, int d, const float *cent, int k, int32_t *out, const int *list,
-                                   const int *pairs, const int *count, hipStream_t s)
+hipError_t launch_assign_undecided(const float *Z, int d, const KmRuns &runs, hipStream_t s)
 {
-    hipLaunchKernelGGL(assign_undecided_kernel, dim3(1024), dim3(256), 0, s, Z, d, cent, k, out, list, pairs, count);
+    hipLaunchKernelGGL(assign_undecided_kernel, dim3(1024, (unsigned)runs.count), dim3(256), 0, s, Z, d, runs);
     return hipGetLastError();
 }
 
@@ -781,11 +781,11 @@ hipError_t launch_combine_hash(int32_t *acc, const int32_t *h, int b, int first,
 
 constexpr int KM_POINTS = 2048;  // points per workgroup of count and scatter
 
-__device__ inline void write_centroid(float *cent, const CentroidPlanes &P, int c, int d, int j, float v)
+__device__ inline void write_centroid(const KmRun &P, int c, int d, int j, float v)
 {
-    cent[(long long)c * d + j] = v;
+    P.cent[(long long)c * d + j] = v;
     if (P.first) {   // operand order: groups of 32 rows, steps of 16 dimensions, lane = row % 32 + 32 (j % 16 / 8)
-        const long long at = (((long long)(c >> 5) * P.steps + (j >> 4)) * 64 + (c & 31) + 32 * (j >> 3 & 1)) * 8 + (j & 7);
+        const long long at = (((long long)(c >> 5) * ((d + 15) / 16) + (j >> 4)) * 64 + (c & 31) + 32 * (j >> 3 & 1)) * 8 + (j & 7);
         const unsigned h = bf16_bits(v);
         P.first[at] = (unsigned short)h;
         P.first[P.plane + at] = (unsigned short)bf16_bits(v - __uint_as_float(h << 16));   // the difference is exact
@@ -793,7 +793,7 @@ __device__ inline void write_centroid(float *cent, const CentroidPlanes &P, int 
 }
 
 // The centroid's squared norm from every thread's share of it; sh: a double per wavefront of the workgroup.
-__device__ inline void write_norm(const CentroidPlanes &P, int c, double sq, double *sh)
+__device__ inline void write_norm(const KmRun &P, int c, double sq, double *sh)
 {
     for (int o = 1; o < 64; o <<= 1) sq += __shfl_xor(sq, o, 64);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sq;
@@ -1050,11 +1050,11 @@ __global__ __launch_bounds__(256) void kmeans_partial_kernel(const float *__rest
 template <int NS>
 __global__ __launch_bounds__(512) void kmeans_mean_kernel(const unsigned long long *__restrict__ part, int d, int M,
                                                           const int *__restrict__ counts,
-                                                          const int *__restrict__ offs, float *__restrict__ cent,
                                                           int *__restrict__ counts_next,
-                                                          int *__restrict__ cursor_next, CentroidPlanes planes,
-                                                          int *reset)
+                                                          int *__restrict__ cursor_next, KmRun run)
 {
+    const int *__restrict__ offs = run.offs;
+    int *reset = run.keep_counts ? nullptr : run.nflagged;
     __shared__ unsigned long long red[8][NS][64];
     __shared__ double norm_sh[8];
     const int c = blockIdx.x;
@@ -1105,28 +1105,28 @@ __global__ __launch_bounds__(512) void kmeans_mean_kernel(const unsigned long lo
 #pragma unroll
             for (int w = 0; w < 8; ++w) tot += red[w][q][jl];
             const float mean = (float)(((double)(long long)tot * (1.0 / 4294967296.0)) / (double)cnt);
-            write_centroid(cent, planes, c, d, j, mean);
+            write_centroid(run, c, d, j, mean);
             sq += (double)mean * (double)mean;
         }
     }
-    write_norm(planes, c, sq, norm_sh);
+    write_norm(run, c, sq, norm_sh);
 }
 
 // grid: (clusters, ranges).  Ranges are cut where the assignments are aligned to four of them; the first one also
 // takes what comes before.  ONE: a single range, the centroid is written here; otherwise the range's sums go to
-// part[cluster][range][d] and its number of members to cnts[cluster][range].
+// part[cluster][range][d] and its number of members to order[cluster][range].
 // What bounds it is the largest cluster of a range (early assignments are lopsided), hence eight wavefronts, eight rows in
 // flight each; little LDS (indices as 16-bit distances, the sums in their place afterwards), as the k-means runs
 // of a build and its other kernels share the compute units.
 constexpr int KM_THREADS = 512, KM_WAVES = KM_THREADS / 64;
 
 template <int NS, bool ONE>
-__global__ __launch_bounds__(KM_THREADS) void kmeans_members_kernel(const float *__restrict__ Z, long long N, int d,
-                                                                    const int32_t *__restrict__ assign,
-                                                                    unsigned long long *__restrict__ part,
-                                                                    int *__restrict__ cnts, float *__restrict__ cent,
-                                                                    CentroidPlanes planes, int *reset)
+__global__ __launch_bounds__(KM_THREADS) void kmeans_members_kernel(const float *__restrict__ Z, long long N, int d, KmRuns R)
 {
+    const KmRun &run = R.run[blockIdx.z];
+    if ((int)blockIdx.x >= run.k) return;
+    const int32_t *__restrict__ assign = run.assign;
+    unsigned long long *__restrict__ part = run.part;
     constexpr int LIST_BYTES = 2 * (KM_RANGE + 4), RED_BYTES = 8 * (KM_WAVES / 2) * NS * 64;
     __shared__ __align__(16) unsigned char room[LIST_BYTES > RED_BYTES ? LIST_BYTES : RED_BYTES];
     unsigned short *members = (unsigned short *)room;   // distances from the range's start
@@ -1137,9 +1137,9 @@ __global__ __launch_bounds__(KM_THREADS) void kmeans_members_kernel(const float 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x == 0) {
         found = 0;
-        if (ONE && c == 0 && reset) {
-            reset[0] = 0;
-            reset[1] = 0;
+        if (ONE && c == 0 && !run.keep_counts) {
+            run.nflagged[0] = 0;
+            run.nflagged[1] = 0;
         }
     }
     __syncthreads();
@@ -1222,7 +1222,7 @@ __global__ __launch_bounds__(KM_THREADS) void kmeans_members_kernel(const float 
             for (int w = 0; w < KM_WAVES / 2; ++w) tot += red[w][q][jl];
             if (ONE) {
                 const float mean = (float)(((double)(long long)tot * (1.0 / 4294967296.0)) / (double)cnt);
-                write_centroid(cent, planes, c, d, j, mean);
+                write_centroid(run, c, d, j, mean);
                 sq += (double)mean * (double)mean;
             } else {
                 part[((size_t)c * gridDim.y + blockIdx.y) * (size_t)d + j] = tot;
@@ -1230,21 +1230,23 @@ __global__ __launch_bounds__(KM_THREADS) void kmeans_members_kernel(const float 
         }
     }
     if (ONE)
-        write_norm(planes, c, sq, norm_sh);
+        write_norm(run, c, sq, norm_sh);
     else if (threadIdx.x == 0)
-        cnts[c * gridDim.y + blockIdx.y] = cnt;
+        run.order[c * gridDim.y + blockIdx.y] = cnt;
 }
 
 // Adds up a cluster's ranges and writes its centroid; one workgroup per cluster.
-__global__ __launch_bounds__(256) void kmeans_ranges_kernel(const unsigned long long *__restrict__ part, int d, int ranges,
-                                                            const int *__restrict__ cnts, float *__restrict__ cent,
-                                                            CentroidPlanes planes, int *reset)
+__global__ __launch_bounds__(256) void kmeans_ranges_kernel(int d, int ranges, KmRuns R)
 {
+    const KmRun &run = R.run[blockIdx.y];
+    if ((int)blockIdx.x >= run.k) return;
+    const unsigned long long *__restrict__ part = run.part;
+    const int *__restrict__ cnts = run.order;
     __shared__ double norm_sh[4];
     const int c = blockIdx.x;
-    if (threadIdx.x == 0 && c == 0 && reset) {
-        reset[0] = 0;
-        reset[1] = 0;
+    if (threadIdx.x == 0 && c == 0 && !run.keep_counts) {
+        run.nflagged[0] = 0;
+        run.nflagged[1] = 0;
     }
     int cnt = 0;
     for (int r = 0; r < ranges; ++r) cnt += cnts[c * ranges + r];
@@ -1255,63 +1257,59 @@ __global__ __launch_bounds__(256) void kmeans_ranges_kernel(const unsigned long 
 #pragma unroll 8
         for (int r = 0; r < ranges; ++r) tot += part[((size_t)c * ranges + r) * (size_t)d + j];
         const float mean = (float)(((double)(long long)tot * (1.0 / 4294967296.0)) / (double)cnt);
-        write_centroid(cent, planes, c, d, j, mean);
+        write_centroid(run, c, d, j, mean);
         sq += (double)mean * (double)mean;
     }
-    write_norm(planes, c, sq, norm_sh);
+    write_norm(run, c, sq, norm_sh);
 }
 
 template <int NS>
-static void launch_members(const float *Z, long long N, int d, const int32_t *assign, int k, int *cnts,
-                           unsigned long long *part, float *cent, const CentroidPlanes &planes, int *reset, hipStream_t s)
+static void launch_members(const float *Z, long long N, int d, const KmRuns &runs, int kmax, hipStream_t s)
 {
     const int ranges = kmeans_ranges(N);
+    const dim3 grid((unsigned)kmax, (unsigned)ranges, (unsigned)runs.count);
     if (ranges == 1) {
-        hipLaunchKernelGGL((kmeans_members_kernel<NS, true>), dim3((unsigned)k), dim3(KM_THREADS), 0, s, Z, N, d, assign, part, cnts,
-                           cent, planes, reset);
+        hipLaunchKernelGGL((kmeans_members_kernel<NS, true>), grid, dim3(KM_THREADS), 0, s, Z, N, d, runs);
     } else {
-        hipLaunchKernelGGL((kmeans_members_kernel<NS, false>), dim3((unsigned)k, (unsigned)ranges), dim3(KM_THREADS), 0, s, Z, N, d,
-                           assign, part, cnts, cent, planes, reset);
-        hipLaunchKernelGGL(kmeans_ranges_kernel, dim3((unsigned)k), dim3(256), 0, s, part, d, ranges, cnts, cent, planes,
-                           reset);
+        hipLaunchKernelGGL((kmeans_members_kernel<NS, false>), grid, dim3(KM_THREADS), 0, s, Z, N, d, runs);
+        hipLaunchKernelGGL(kmeans_ranges_kernel, dim3((unsigned)kmax, (unsigned)runs.count), dim3(256), 0, s, d, ranges, runs);
     }
 }
 
-hipError_t launch_kmeans_update(const float *Z, long long N, int d, const int32_t *assign, int k, int *counts2,
-                                int *cursor2, int *order, int *offs, long long *part, int parity, float *cent,
-                                const CentroidPlanes &planes, int *reset, hipStream_t s)
+hipError_t launch_kmeans_update(const float *Z, long long N, int d, const KmRuns &runs, int parity, hipStream_t s)
 {
     const int ns = (d + 63) / 64;
+    int k = 0;
+    for (int q = 0; q < runs.count; ++q) k = runs.run[q].k > k ? runs.run[q].k : k;
     if (kmeans_by_members(N, k, d)) {
-#define LCN_MEMBERS(NS_) \
-    launch_members<NS_>(Z, N, d, assign, k, order, (unsigned long long *)part, cent, planes, reset, s)
         switch (ns) {
-            case 1: LCN_MEMBERS(1); break;
-            case 2: LCN_MEMBERS(2); break;
-            case 3: LCN_MEMBERS(3); break;
-            case 4: LCN_MEMBERS(4); break;
-            case 5: LCN_MEMBERS(5); break;
-            case 6: LCN_MEMBERS(6); break;
-            case 7: LCN_MEMBERS(7); break;
-            default: LCN_MEMBERS(8); break;
+            case 1: launch_members<1>(Z, N, d, runs, k, s); break;
+            case 2: launch_members<2>(Z, N, d, runs, k, s); break;
+            case 3: launch_members<3>(Z, N, d, runs, k, s); break;
+            case 4: launch_members<4>(Z, N, d, runs, k, s); break;
+            case 5: launch_members<5>(Z, N, d, runs, k, s); break;
+            case 6: launch_members<6>(Z, N, d, runs, k, s); break;
+            case 7: launch_members<7>(Z, N, d, runs, k, s); break;
+            default: launch_members<8>(Z, N, d, runs, k, s); break;
         }
-#undef LCN_MEMBERS
         return hipGetLastError();
     }
-    int *counts = counts2 + (size_t)(parity & 1) * k, *counts_next = counts2 + (size_t)((parity + 1) & 1) * k;
-    int *cursor = cursor2 + (size_t)(parity & 1) * k, *cursor_next = cursor2 + (size_t)((parity + 1) & 1) * k;
+    if (runs.count != 1) return hipErrorInvalidValue;
+    const KmRun &r = runs.run[0];
+    int *counts = r.counts2 + (size_t)(parity & 1) * k, *counts_next = r.counts2 + (size_t)((parity + 1) & 1) * k;
+    int *cursor = r.cursor2 + (size_t)(parity & 1) * k, *cursor_next = r.cursor2 + (size_t)((parity + 1) & 1) * k;
     const unsigned blocks = (unsigned)((N + KM_POINTS - 1) / KM_POINTS);
-    hipLaunchKernelGGL(kmeans_count_kernel, dim3(blocks), dim3(256), sizeof(int) * (size_t)k, s, assign, N, k, counts);
-    hipLaunchKernelGGL(kmeans_scatter_kernel, dim3(blocks), dim3(256), 2 * sizeof(int) * (size_t)k, s, assign, N, k,
-                       counts, cursor, order, offs);
+    hipLaunchKernelGGL(kmeans_count_kernel, dim3(blocks), dim3(256), sizeof(int) * (size_t)k, s, r.assign, N, k, counts);
+    hipLaunchKernelGGL(kmeans_scatter_kernel, dim3(blocks), dim3(256), 2 * sizeof(int) * (size_t)k, s, r.assign, N, k,
+                       counts, cursor, r.order, r.offs);
     if (ns <= 8) {
         const int M = kmeans_sum_chunk(N);
         const unsigned pblocks = (unsigned)(((N + M - 1) / M + 3) / 4);
 #define LCN_SUM_PARTIAL(NS_)                                                                                       \
-    hipLaunchKernelGGL((kmeans_partial_kernel<NS_>), dim3(pblocks), dim3(256), 0, s, Z, N, d, M, assign, order,       \
-                       (unsigned long long *)part);                                                                    \
-    hipLaunchKernelGGL((kmeans_mean_kernel<NS_>), dim3((unsigned)k), dim3(512), 0, s,                                  \
-                       (const unsigned long long *)part, d, M, counts, offs, cent, counts_next, cursor_next, planes, reset)
+    hipLaunchKernelGGL((kmeans_partial_kernel<NS_>), dim3(pblocks), dim3(256), 0, s, Z, N, d, M, r.assign, r.order,   \
+                       r.part);                                                                                        \
+    hipLaunchKernelGGL((kmeans_mean_kernel<NS_>), dim3((unsigned)k), dim3(512), 0, s, r.part, d, M, counts,            \
+                       counts_next, cursor_next, r)
         switch (ns) {
             case 1: LCN_SUM_PARTIAL(1); break;
             case 2: LCN_SUM_PARTIAL(2); break;
@@ -1325,16 +1323,20 @@ hipError_t launch_kmeans_update(const float *Z, long long N, int d, const int32_
 #undef LCN_SUM_PARTIAL
         return hipGetLastError();
     }
+    int *reset = r.keep_counts ? nullptr : r.nflagged;
     if ((long long)k * ((d + 63) / 64) >= 512)
         hipLaunchKernelGGL((kmeans_sum_kernel<64, 16>), dim3((unsigned)k, (unsigned)((d + 63) / 64)), dim3(1024), 0, s, Z,
-                           d, k, counts, offs, order, cent, counts_next, cursor_next, reset);
+                           d, k, counts, r.offs, r.order, r.cent, counts_next, cursor_next, reset);
     else   // few clusters: narrower slices, four times the workgroups
         hipLaunchKernelGGL((kmeans_sum_kernel<16, 16>), dim3((unsigned)k, (unsigned)((d + 15) / 16)), dim3(1024), 0, s, Z,
-                           d, k, counts, offs, order, cent, counts_next, cursor_next, reset);
+                           d, k, counts, r.offs, r.order, r.cent, counts_next, cursor_next, reset);
     hipError_t e = hipGetLastError();
     // a centroid's slices are written by several workgroups: the planes and norms follow in a launch of their own
-    if (e == hipSuccess && planes.first && reset)   // (the last iteration's are not used)
-        e = launch_kmeans_start(nullptr, nullptr, cent, k, d, planes.first, planes.cn, reset, s);
+    if (e == hipSuccess && r.first && reset) {   // (the last iteration's are not used)
+        KmRuns again = runs;
+        again.run[0].pick = nullptr;
+        e = launch_kmeans_start(nullptr, d, again, s);
+    }
     return e;
 }
 

@@ -64,8 +64,9 @@ std::vector<long long> seeded_indices(uint64_t seed, long long N, int k)
 
 bool uses_landmarks(int mode) { return mode == LCN_MODE_NYSTROM || mode == LCN_MODE_LCN; }
 bool uses_lsh(int mode) { return mode == LCN_MODE_SPARSE || mode == LCN_MODE_LCN; }
+constexpr long long KM_MERGE_POINTS = 1ll << 17;
 
-constexpr int KM_LANES = 4;   // k-means runs of a build that may be in flight together
+constexpr int KM_LANES = 4;   // k-means runs of a build that may be in flight together on streams of their own
 
 struct KmScratch {  // what one k-means run needs for itself
     long long *idx;
@@ -88,7 +89,7 @@ struct Scratch {  // build-only buffers
     long long *totals;
     char *zt;  // bf16 planes of the points (assignment filter)
     int zplanes;
-    KmScratch km[KM_LANES];
+    KmScratch km[KM_MAX_RUNS];   // one per lane, or one per run where all runs advance together
 };
 
 // Lays out everything except the sparse values.  With bump.dry only sizes are
@@ -110,7 +111,8 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
     // bf16 planes for the assignment filter: points (one plane if the input was bf16), centroids
     sc.zplanes = h.in_dtype == LCN_BF16 ? 1 : 2;
     sc.zt = bump.take<char>((size_t)sc.zplanes * split_plane_bytes(N, h.d));
-    for (int q = 0; q < KM_LANES; ++q) {
+    const int sets = h.merged_runs > KM_LANES ? h.merged_runs : KM_LANES;
+    for (int q = 0; q < sets; ++q) {
         KmScratch &km = sc.km[q];
         km.idx = bump.take<long long>((size_t)kmax);
         km.cent = bump.take<float>((size_t)kmax * h.d);
@@ -276,6 +278,13 @@ void fill_shape(Handle &h, long long n, long long m, int d, int mode, const lcn_
         h.b = 1;
         h.hash = -1;
     }
+    // Flat k-means runs (landmarks, one per hash round) advance together, a launch for all of them, where the points
+    // are few enough for that to be the faster way; see Builder.
+    const int hashing = h.hash == LCN_HASH_KMEANS && h.hier_levels <= 1 ? h.R : 0;
+    const int most = h.l > h.b ? h.l : h.b;
+    const bool merge = n + m <= KM_MERGE_POINTS && kmeans_by_members(n + m, most, d) && (h.l > 0 || hashing > 0) &&
+                       (h.hash != LCN_HASH_KMEANS || h.hier_levels <= 1);
+    h.merged_runs = merge ? (h.l > 0 ? 1 : 0) + hashing : 0;
 }
 
 #define HIPCHK(expr)                         \
@@ -287,57 +296,102 @@ void fill_shape(Handle &h, long long n, long long m, int d, int mode, const lcn_
         }                                    \
     } while (0)
 
-// T Lloyd iterations on Z from the start `init` names (LCN_INIT_*): centroids into cent, the last
-// iteration's assignment into assign (untouched if T == 0).
-// start_dev (nullable): the k seeded start indices, already on the device (LCN_INIT_SAMPLE only).
-// km: the run's own scratch; s: the stream it is ordered on.
-lcn_status run_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s, int k, int T, uint64_t seed, float *cent,
-                      int32_t *assign, const long long *start_dev = nullptr, int init = LCN_INIT_SAMPLE,
-                      const float *given = nullptr)
+// A k-means run with the buffers of `km`; `assign`: the last iteration's assignment.
+KmRun kmeans_run(Handle &h, KmScratch &km, int k, float *cent, int32_t *assign)
+{
+    KmRun r{};
+    r.k = k;
+    r.cent = cent;
+    r.assign = assign;
+    r.flagged = km.flagged;
+    r.pairs = km.pairs;
+    r.nflagged = km.nflagged;
+    r.part = (unsigned long long *)km.part;
+    r.order = km.order;
+    r.offs = km.offs;
+    r.counts2 = km.counts2;
+    r.cursor2 = km.cursor2;
+    if (!h.exact_assign_only) centroid_planes(r, km.ct, km.cn, h.d);
+    return r;
+}
+
+// Where the run's centroids start (LCN_INIT_*): given ones and those of k-means++ go to cent, otherwise r.pick names the
+// seeded points (start_dev: already on the device).
+lcn_status kmeans_init(Handle &h, KmScratch &km, hipStream_t s, KmRun &r, uint64_t seed, const long long *start_dev,
+                       int init = LCN_INIT_SAMPLE, const float *given = nullptr)
 {
     const long long N = h.n + h.m;
     if (init == LCN_INIT_GIVEN) {
-        HIPCHK(hipMemcpyAsync(cent, given, sizeof(float) * (size_t)k * h.d, hipMemcpyDeviceToDevice, s));
+        HIPCHK(hipMemcpyAsync(r.cent, given, sizeof(float) * (size_t)r.k * h.d, hipMemcpyDeviceToDevice, s));
     } else if (init == LCN_INIT_KMEANSPP) {
-        std::vector<unsigned long long> rnd((size_t)k);
+        std::vector<unsigned long long> rnd((size_t)r.k);
         uint64_t st = seed;
-        for (int t = 0; t < k; ++t) rnd[(size_t)t] = splitmix64(st);
-        HIPCHK(hipMemcpyAsync(km.idx, rnd.data(), sizeof(unsigned long long) * (size_t)k, hipMemcpyHostToDevice,
-                              s));
+        for (int t = 0; t < r.k; ++t) rnd[(size_t)t] = splitmix64(st);
+        HIPCHK(hipMemcpyAsync(km.idx, rnd.data(), sizeof(unsigned long long) * (size_t)r.k, hipMemcpyHostToDevice, s));
         HIPCHK(hipStreamSynchronize(s));  // rnd is a local host vector
         // the assignment's buffers are free until the first Lloyd iteration
-        HIPCHK(launch_kmeanspp(h.Z, N, h.d, k, (const unsigned long long *)km.idx, (double *)km.pairs,
-                               (unsigned long long *)km.flagged, km.order, km.pp_state, cent, s));
-    } else if (!start_dev) {
-        std::vector<long long> idx = seeded_indices(seed, N, k);
-        HIPCHK(hipMemcpyAsync(km.idx, idx.data(), sizeof(long long) * (size_t)k, hipMemcpyHostToDevice, s));
-        HIPCHK(hipStreamSynchronize(s));  // idx is a local host vector
-        start_dev = km.idx;
-    }
-    // (start_dev: the starts are points, still to be copied)
-    CentroidPlanes planes{};
-    if (h.exact_assign_only || T == 0) {
-        if (start_dev) HIPCHK(launch_gather_rows(h.Z, h.d, start_dev, k, cent, s));
-        HIPCHK(hipMemsetAsync(km.nflagged, 0, 2 * sizeof(int), s));
+        HIPCHK(launch_kmeanspp(h.Z, N, h.d, r.k, (const unsigned long long *)km.idx, (double *)km.pairs,
+                               (unsigned long long *)km.flagged, km.order, km.pp_state, r.cent, s));
+    } else if (start_dev) {
+        r.pick = start_dev;
     } else {
-        planes = centroid_planes(km.ct, k, h.d, km.cn);
-        HIPCHK(launch_kmeans_start(h.Z, start_dev, cent, k, h.d, km.ct, km.cn, km.nflagged, s));
-    }
-    if (T > 0 && !kmeans_by_members(N, k, h.d))   // member counts and cursors of the update lie side by side
-        HIPCHK(hipMemsetAsync(km.counts2, 0, (size_t)((char *)km.nflagged - (char *)km.counts2), s));
-    for (int it = 0; it < T; ++it) {
-        if (h.exact_assign_only) {
-            HIPCHK(launch_assign_kmeans(h.Z, N, h.d, cent, k, assign, s));
-        } else {
-            HIPCHK(launch_assign_filter(sc.zt, sc.zplanes, N, h.d, k, km.ct, h.zn, km.cn, assign, km.flagged, km.pairs,
-                                        km.nflagged, s));
-            HIPCHK(launch_assign_undecided(h.Z, h.d, cent, k, assign, km.flagged, km.pairs, km.nflagged, s));
-        }
-        // the last iteration leaves the count of undecided points in place for lcn_get_info
-        HIPCHK(launch_kmeans_update(h.Z, N, h.d, assign, k, km.counts2, km.cursor2, km.order, km.offs, km.part, it, cent,
-                                    planes, it + 1 < T ? km.nflagged : nullptr, s));
+        std::vector<long long> idx = seeded_indices(seed, N, r.k);
+        HIPCHK(hipMemcpyAsync(km.idx, idx.data(), sizeof(long long) * (size_t)r.k, hipMemcpyHostToDevice, s));
+        HIPCHK(hipStreamSynchronize(s));  // idx is a local host vector
+        r.pick = km.idx;
     }
     return LCN_OK;
+}
+
+// T[q] Lloyd iterations of every run, all of them together (more than one: kmeans_by_members() holds for each):
+// centroids into cent, the last iteration's assignment into assign (untouched if T[q] == 0).
+lcn_status run_kmeans(Handle &h, Scratch &sc, hipStream_t s, const KmRuns &all, const int *T)
+{
+    const long long N = h.n + h.m;
+    KmRuns start{};
+    int most = 0;
+    for (int q = 0; q < all.count; ++q) {
+        const KmRun &r = all.run[q];
+        most = T[q] > most ? T[q] : most;
+        if (r.first && T[q] > 0) {
+            start.run[start.count++] = r;
+        } else {
+            if (r.pick) HIPCHK(launch_gather_rows(h.Z, h.d, r.pick, r.k, r.cent, s));
+            HIPCHK(hipMemsetAsync(r.nflagged, 0, 2 * sizeof(int), s));
+        }
+        if (T[q] > 0 && !kmeans_by_members(N, r.k, h.d))   // member counts and cursors lie side by side
+            HIPCHK(hipMemsetAsync(r.counts2, 0, (size_t)((char *)r.nflagged - (char *)r.counts2), s));
+    }
+    if (start.count > 0) HIPCHK(launch_kmeans_start(h.Z, h.d, start, s));
+    for (int it = 0; it < most; ++it) {
+        KmRuns now{};   // those that are not done yet
+        for (int q = 0; q < all.count; ++q)
+            if (it < T[q]) {
+                now.run[now.count] = all.run[q];
+                // the last iteration leaves the count of undecided points in place for lcn_get_info
+                now.run[now.count++].keep_counts = it + 1 == T[q];
+            }
+        if (h.exact_assign_only) {
+            for (int q = 0; q < now.count; ++q)
+                HIPCHK(launch_assign_kmeans(h.Z, N, h.d, now.run[q].cent, now.run[q].k, now.run[q].assign, s));
+        } else {
+            HIPCHK(launch_assign_filter(sc.zt, sc.zplanes, N, h.d, h.zn, now, s));
+            HIPCHK(launch_assign_undecided(h.Z, h.d, now, s));
+        }
+        HIPCHK(launch_kmeans_update(h.Z, N, h.d, now, it, s));
+    }
+    return LCN_OK;
+}
+
+lcn_status run_one_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s, int k, int T, uint64_t seed, float *cent,
+                          int32_t *assign, const long long *start_dev = nullptr, int init = LCN_INIT_SAMPLE,
+                          const float *given = nullptr)
+{
+    KmRuns runs{};
+    runs.count = 1;
+    runs.run[0] = kmeans_run(h, km, k, cent, assign);
+    const lcn_status st = kmeans_init(h, km, s, runs.run[0], seed, start_dev, init, given);
+    return st == LCN_OK ? run_kmeans(h, sc, s, runs, &T) : st;
 }
 
 // Hierarchical k-means hashing: level 0 is a k-means on all points; level j >= 1 runs, inside every
@@ -349,7 +403,7 @@ lcn_status run_hier_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s,
                            int T, uint64_t seed, int32_t *dst)
 {
     const long long N = h.n + h.m;
-    lcn_status st = run_kmeans(h, sc, km, s, branching[0], T, seed, km.cent, dst);
+    lcn_status st = run_one_kmeans(h, sc, km, s, branching[0], T, seed, km.cent, dst);
     if (st != LCN_OK) return st;
     long long parents = branching[0];
     std::vector<int32_t> ids((size_t)N);
@@ -395,11 +449,15 @@ lcn_status run_hier_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s,
         HIPCHK(launch_gather_rows(h.Z, h.d, km.idx, (int)k, km.cent, s));
         HIPCHK(hipMemsetAsync(km.counts2, 0, 2 * sizeof(int) * (size_t)k, s));
         HIPCHK(hipMemsetAsync(km.cursor2, 0, 2 * sizeof(int) * (size_t)k, s));
+        KmRuns runs{};
+        runs.count = 1;
+        runs.run[0] = kmeans_run(h, km, (int)k, km.cent, dst);
+        runs.run[0].first = nullptr;
+        runs.run[0].keep_counts = 1;
         for (int it = 0; it < T; ++it) {
             HIPCHK(launch_assign_children(h.Z, h.d, km.cent, parents, bl, km.nchild, km.horder, km.hchunks, nchunks,
                                           km.hcent, dst, s));
-            HIPCHK(launch_kmeans_update(h.Z, N, h.d, dst, (int)k, km.counts2, km.cursor2, km.order, km.offs, km.part,
-                                        it, km.cent, CentroidPlanes{}, nullptr, s));
+            HIPCHK(launch_kmeans_update(h.Z, N, h.d, runs, it, s));
         }
         parents = k;
     }
@@ -477,11 +535,12 @@ bool lane_streams(hipStream_t (&out)[KM_LANES])
 // then drains every stream (the caller's inputs and the host vector `starts` are read by work
 // that may still be in flight), then lets the members go.
 //
-// The k-means runs of a build (landmarks, one per hash round) and the factors are independent
-// chains of short launches, and the host needs about as long to enqueue such a launch as the
-// device to execute it.  Each run therefore gets scratch of its own and one of KM_LANES streams of
-// the library's own ("lanes": forked from and joined into the caller's stream by events), and the
-// hash rounds of a lane are enqueued by a host thread of their own while the calling thread
+// The k-means runs of a build (landmarks, one per hash round) are independent chains of short launches, and the host
+// needs about as long to enqueue such a launch as the device to execute it.  Up to KM_MERGE_POINTS points all flat runs
+// therefore advance together, a launch for all of them, on a stream of the library's own, and the factors go on from
+// there beside the bucket sort.  Above that (and for hierarchical runs), where a launch of one run fills the chip,
+// each run has scratch of its own and one of KM_LANES streams ("lanes": forked from and joined into the caller's stream by
+// events), and the hash rounds of a lane are enqueued by a host thread of their own while the calling thread
 // enqueues the landmarks and the factors.
 struct Builder {
     Handle &h;
@@ -529,6 +588,9 @@ struct Builder {
         for (int q = 0; q < KM_LANES; ++q)
             if (threads[q].joinable()) threads[q].join();
     }
+    bool merged() const { return h.merged_runs > 0 && !h.exact_assign_only; }
+    // no hash round left on any lane when the factors are enqueued: the buckets need not wait for those
+    bool buckets_early() const { return merged() && (kmeans_hashing() || h.R == 0); }
     bool kmeans_hashing() const { return uses_lsh(mode) && h.hash == LCN_HASH_KMEANS; }
     // the landmarks and the factors keep lane 0 to themselves
     int lane_of_round(int r) const { return h.l > 0 ? 1 + r % (KM_LANES - 1) : r % KM_LANES; }
@@ -600,7 +662,7 @@ struct Builder {
                     rs = run_hier_kmeans(h, sc, km, ls, lsh->branching, h.hier_levels, lsh->kmeans_iters,
                                          lsh->seed + (uint64_t)r, dst);
                 else
-                    rs = run_kmeans(h, sc, km, ls, h.b, lsh->kmeans_iters, lsh->seed + (uint64_t)r, km.cent, dst,
+                    rs = run_one_kmeans(h, sc, km, ls, h.b, lsh->kmeans_iters, lsh->seed + (uint64_t)r, km.cent, dst,
                                     starts_rounds + (long long)r * h.b);
                 if (rs != LCN_OK) return rs;
             } else if (h.and_width > 1) {
@@ -618,6 +680,38 @@ struct Builder {
         return LCN_OK;
     }
 
+    // All flat k-means runs together on lane 0.
+    lcn_status merged_kmeans()
+    {
+        KmRuns runs{};
+        int T[KM_MAX_RUNS];
+        auto add = [&](int k, float *cent, int32_t *assign) -> KmRun & {
+            runs.run[runs.count] = kmeans_run(h, sc.km[runs.count], k, cent, assign);
+            return runs.run[runs.count++];
+        };
+        if (h.l > 0) {
+            T[0] = lm->kmeans_iters;
+            KmRun &r = add(h.l, h.L, sc.km[0].assign);
+            const lcn_status st = kmeans_init(h, sc.km[0], lane[0], r, lm->seed, starts_landmarks, lm->init, lm->init_centroids);
+            if (st != LCN_OK) return st;
+        }
+        if (kmeans_hashing())
+            for (int r = 0; r < h.R; ++r) {
+                T[runs.count] = lsh->kmeans_iters;
+                KmScratch &km = sc.km[runs.count];
+                add(h.b, km.cent, h.bucket + (long long)r * N).pick = starts_rounds + (long long)r * h.b;
+            }
+        const lcn_status st = run_kmeans(h, sc, lane[0], runs, T);
+        if (st != LCN_OK) return st;
+        lane_used[0] = true;
+        last_nflagged = runs.run[runs.count - 1].nflagged;
+        if (forked && buckets_early()) {   // the caller's stream goes on with the buckets, lane 0 with the factors
+            HIPCHK(hipEventRecord(join[1], lane[0]));
+            HIPCHK(hipStreamWaitEvent(h.stream, join[1], 0));
+        }
+        return LCN_OK;
+    }
+
     // Starts the hash rounds: with lanes and k-means hashing one host thread per lane enqueues them
     // (so that they overlap with what the calling thread enqueues next), otherwise they are enqueued
     // here and now.
@@ -627,7 +721,7 @@ struct Builder {
             HIPCHK(hipMemsetAsync(h.bucket, 0, sizeof(int32_t) * (size_t)N, h.stream));
             return LCN_OK;
         }
-        if (!uses_lsh(mode)) return LCN_OK;
+        if (!uses_lsh(mode) || (merged() && kmeans_hashing())) return LCN_OK;
         for (int r = 0; r < h.R; ++r) lane_used[lane_of_round(r)] = true;
         if (kmeans_hashing() && h.R > 0) last_nflagged = sc.km[lane_of_round(h.R - 1)].nflagged;
         const bool threaded = forked && kmeans_hashing();
@@ -661,8 +755,9 @@ struct Builder {
     // landmarks: centroids of k-means on X u Y, or sampled points (Sec. 4); lane 0
     lcn_status landmarks()
     {
+        if (merged()) return merged_kmeans();
         if (h.l == 0) return LCN_OK;
-        const lcn_status st = run_kmeans(h, sc, sc.km[0], lane[0], h.l, lm->kmeans_iters, lm->seed, h.L, sc.km[0].assign,
+        const lcn_status st = run_one_kmeans(h, sc, sc.km[0], lane[0], h.l, lm->kmeans_iters, lm->seed, h.L, sc.km[0].assign,
                                          starts_landmarks, lm->init, lm->init_centroids);
         if (st != LCN_OK) return st;
         lane_used[0] = true;
@@ -723,7 +818,7 @@ struct Builder {
         join_threads();
         for (int q = 0; q < KM_LANES; ++q)
             if (thread_status[q] != LCN_OK) return thread_status[q];
-        if (forked) {   // the buckets are needed from here on, the factors only by the sparse values
+        if (forked && !buckets_early()) {   // the buckets are needed from here on, the factors only by the sparse values
             for (int q = factors_apart() ? 1 : 0; q < KM_LANES; ++q) {
                 if (!lane_used[q]) continue;
                 HIPCHK(hipEventRecord(join[q], lane[q]));
@@ -772,6 +867,10 @@ struct Builder {
         if (factors_apart()) {
             HIPCHK(hipEventRecord(join[0], lane[0]));
             HIPCHK(hipStreamWaitEvent(h.stream, join[0], 0));
+            if (buckets_early()) {   // U is still out on lane 1
+                HIPCHK(hipEventRecord(join[2], lane[1]));
+                HIPCHK(hipStreamWaitEvent(h.stream, join[2], 0));
+            }
         }
         if (h.R > 0) HIPCHK(launch_correction(h, h.ntiles, h.stream));
         const lcn_status st = init_state(h, true);

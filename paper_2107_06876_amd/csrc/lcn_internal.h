@@ -85,33 +85,43 @@ __device__ inline unsigned bf16_bits(float x)
     const unsigned u = __float_as_uint(x);
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
-// The centroids' two bf16 planes in operand order and their squared norms; first == nullptr: not kept.
-struct CentroidPlanes {
+// One k-means run's own buffers.  `first`, `cn`: the centroids' two bf16 planes in operand order (`plane` entries
+// apart) and their squared norms, null where the filter is not used.
+struct KmRun {
+    int k;
+    const long long *pick;      // the points the centroids start from (null: cent is given)
+    float *cent;
     unsigned short *first;
-    long long plane;   // entries from one plane to the other
-    int steps;         // of 16 dimensions
+    long long plane;
     float *cn;
+    int32_t *assign;
+    int *flagged, *pairs;       // points undecided between more than two centroids; (point, c1, c2) triples
+    int *nflagged;              // how many of either
+    int keep_counts;            // the update leaves nflagged as it is (else zero for the next assignment)
+    unsigned long long *part;   // partial sums, kmeans_partial_elems(N, k, d) words
+    int *order, *offs;          // [N], [k]: members by cluster, or the ranges' member counts
+    int *counts2, *cursor2;     // [2][k] each, zero before the first update (not used where kmeans_by_members())
 };
-CentroidPlanes centroid_planes(void *Ct, int k, int d, float *cn);
-hipError_t launch_kmeans_start(const float *Z, const long long *pick, float *cent, int k, int d, void *Ct, float *cn,
-                               int *nflagged, hipStream_t s);
+// Runs that advance together, a launch for all of them.
+constexpr int KM_MAX_RUNS = 9;
+struct KmRuns {
+    int count;
+    KmRun run[KM_MAX_RUNS];
+};
+void centroid_planes(KmRun &r, void *Ct, float *cn, int d);
+// start of the runs: centroids of the picked points, planes, norms, counters at zero
+hipError_t launch_kmeans_start(const float *Z, int d, const KmRuns &runs, hipStream_t s);
 // MFMA filter: writes the assignment of every point and lists those it could not decide.
-// Zt: planes of the points (zplanes of them); Ct: two planes of k centroids.
-hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, int k, const void *Ct, const double *zn,
-                                const float *cn, int32_t *out, int *flagged, int *pairs, int *nflagged, hipStream_t s);
-// exact rule on what the filter left: list of points (count[0]) over all centroids, pairs = (point, c1, c2) triples
-// (count[1]) over two
-hipError_t launch_assign_undecided(const float *Z, int d, const float *cent, int k, int32_t *out, const int *list,
-                                   const int *pairs, const int *count, hipStream_t s);
+// Zt: planes of the points (zplanes of them).
+hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d, const double *zn, const KmRuns &runs,
+                                hipStream_t s);
+// exact rule on what the filter left
+hipError_t launch_assign_undecided(const float *Z, int d, const KmRuns &runs, hipStream_t s);
 hipError_t launch_assign_crosspolytope(const float *Z, long long N, int d, const float *Rm, int b, int32_t *out,
                                        hipStream_t s);
-// New centroids from the assignment.  counts2 / cursor2: [2][k] ints each, zero before the first update of a k-means
-// run (not used where kmeans_by_members() is true); order: [N], offs: [k] ints; part: kmeans_partial_elems(N, largest
-// k, d) 64-bit words of scratch for the partial sums; `parity` alternates from update to update; planes: the filter's
-// copy of the centroids, kept up to date; reset (nullable): two words cleared for the next assignment step.
-hipError_t launch_kmeans_update(const float *Z, long long N, int d, const int32_t *assign, int k, int *counts2,
-                                int *cursor2, int *order, int *offs, long long *part, int parity, float *cent,
-                                const CentroidPlanes &planes, int *reset, hipStream_t s);
+// New centroids from the assignments, for runs of which kmeans_by_members() holds, or for a single run.  `parity`
+// alternates from update to update.
+hipError_t launch_kmeans_update(const float *Z, long long N, int d, const KmRuns &runs, int parity, hipStream_t s);
 bool kmeans_by_members(long long N, int k, int d);
 size_t kmeans_partial_elems(long long N, int kmax, int d);
 
@@ -194,6 +204,7 @@ struct Handle {
     int mode, cost, hash;
     int in_dtype;              // storage type X and Y were given in
     int hier_levels;           // levels of hierarchical k-means hashing (0 or 1: flat)
+    int merged_runs;           // k-means runs that advance together (0: each on its own)
     int and_width;             // hashes per band of cross-polytope hashing (AND construction)
     int log_domain;            // kernel without signed parts (sparse, dense): values and vectors are logs
     double lambda, ridge;
