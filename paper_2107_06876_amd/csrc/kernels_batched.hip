@@ -16,6 +16,8 @@
 //
 // Compiled with -ffp-contract=off: the bucket rule needs separate multiply and add.
 #include <cmath>
+#include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -48,9 +50,9 @@ struct BatchDev {
     float *landmarks;             // [P][l][d]
     int *buckets;                 // per pair [R][n_p + m_p], pairs back to back at R * (x_off + y_off)
     double *log_u, *log_v;        // per pair at x_off + y_off, length n + m each (n resp. m without BP)
-    double *dist, *resid;         // [P]
+    double *dist, *resid;         // [P], host memory
     unsigned long long *counters; // [0] non-positive sums, [1] / [2] sums of exactly zero without signed terms (rows / columns), per sweep
-    int *fail;
+    int *marks;                   // host memory: [0] a landmark matrix is not positive definite, [1] some counter is not zero
 };
 
 __device__ inline unsigned long long splitmix64_dev(unsigned long long &state)
@@ -691,7 +693,7 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     const int len_u = B.bp ? N : n, len_v = B.bp ? N : m;
     for (int i = tid; i < len_u; i += NT) B.log_u[x0 + y0 + i] = 0.0;
     for (int i = tid; i < len_v; i += NT) B.log_v[x0 + y0 + i] = 0.0;
-    if (tid == 0 && flags[2]) *B.fail = 1;
+    if (tid == 0 && flags[2]) B.marks[0] = 1;
 }
 
 // iters Sinkhorn iterations per pair (iters == 0: only the query part), then the
@@ -899,6 +901,7 @@ __global__ __launch_bounds__(64, 2) void batched_run_kernel(BatchDev B, int iter
         nonpos = (unsigned long long)wave_sum((double)nonpos);
         empty_u = (unsigned long long)wave_sum((double)empty_u);
         empty_v = (unsigned long long)wave_sum((double)empty_v);
+        if (lane == 0 && (nonpos | empty_u | empty_v)) B.marks[1] = 1;
         if (lane == 0 && nonpos) atomicAdd(&B.counters[0], nonpos);
         if (lane == 0 && empty_u) atomicAdd(&B.counters[1], empty_u);
         if (lane == 0 && empty_v) atomicAdd(&B.counters[2], empty_v);
@@ -941,19 +944,133 @@ __global__ __launch_bounds__(64, 2) void batched_run_kernel(BatchDev B, int iter
 }
 
 // c_i = || alpha .* x_i ||_2 (Sec. 6, learnable deletion cost); one thread per
-// point, squares added in fp64 in the order of the dimensions.
-__global__ __launch_bounds__(256) void deletion_cost_kernel(const float *X, long long total, int d, const float *alpha,
-                                                            float *out)
+// point, squares added in fp64 in the order of the dimensions.  The rows come through LDS, 32 dimensions of 256 points
+// at a time in whole lines (a thread that reads its row by itself asks for 64 lines per load).
+__global__ __launch_bounds__(256) void deletion_cost_kernel(const float *__restrict__ X, long long total, int d,
+                                                            const float *__restrict__ alpha, float *__restrict__ out)
+{
+    __shared__ float rows[256][33];
+    const long long i0 = (long long)blockIdx.x * 256;
+    const int dim = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+    double s = 0.0;
+    for (int k0 = 0; k0 < d; k0 += 32) {
+        const int k = k0 + dim < d ? k0 + dim : d - 1;
+        float v[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) {   // past the last point or dimension: the last one again, not used
+            const long long i = i0 + r0 + 8 * u < total ? i0 + r0 + 8 * u : total - 1;
+            v[u] = X[i * d + k];
+        }
+        if (k0 > 0) __syncthreads();   // the dimensions before have been added
+#pragma unroll
+        for (int u = 0; u < 32; ++u) rows[r0 + 8 * u][dim] = v[u];
+        __syncthreads();
+        const int m = d - k0 < 32 ? d - k0 : 32;
+#pragma unroll 8
+        for (int e = 0; e < m; ++e) {
+            const double t = (double)rows[threadIdx.x][e] * (double)alpha[k0 + e];
+            s += t * t;
+        }
+    }
+    if (i0 + threadIdx.x < total) out[i0 + threadIdx.x] = (float)sqrt(s);
+}
+
+// The batch's description into the workspace and the counters at zero, in one launch: from pinned host memory that the
+// device reads itself.  words: multiples of 4 bytes.
+__global__ __launch_bounds__(256) void batch_upload_kernel(const unsigned *__restrict__ src, unsigned *__restrict__ dst,
+                                                           long long words, unsigned *counters, int counter_words)
 {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total) return;
-    const float *x = X + i * d;
-    double s = 0.0;
-    for (int k = 0; k < d; ++k) {
-        const double t = (double)x[k] * (double)alpha[k];
-        s += t * t;
+    if (i < words) dst[i] = src[i];
+    if (i < counter_words) counters[i] = 0u;
+}
+
+// What a batch handle needs of the host: a block of pinned memory that the kernels read the description from and
+// write distances and marks to (a copy by the runtime costs more than these few bytes), and the events around a run.
+// Made once and kept: at most HOST_BLOCKS idle ones and HOST_BYTES in all, the rest is given back at once.
+struct HostBlock {
+    int device;
+    char *ptr;
+    size_t bytes;
+    hipEvent_t ev0, ev1;
+};
+constexpr size_t HOST_BLOCKS = 8, HOST_BYTES = (size_t)16 << 20;
+
+struct HostPool {
+    std::mutex mu;
+    std::vector<HostBlock> idle;
+};
+static HostPool &host_pool()
+{
+    static HostPool *pool = new HostPool;   // never destroyed: the runtime may be gone by then
+    return *pool;
+}
+
+static void free_host_block(HostBlock &b)
+{
+    if (b.ev0) (void)hipEventDestroy(b.ev0);
+    if (b.ev1) (void)hipEventDestroy(b.ev1);
+    if (b.ptr) (void)hipHostFree(b.ptr);
+    b = HostBlock{};
+}
+
+static hipError_t take_host_block(size_t bytes, HostBlock &out)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    {
+        HostPool &pool = host_pool();
+        std::lock_guard<std::mutex> lock(pool.mu);
+        size_t best = pool.idle.size();
+        for (size_t i = 0; i < pool.idle.size(); ++i)
+            if (pool.idle[i].device == dev && pool.idle[i].bytes >= bytes &&
+                (best == pool.idle.size() || pool.idle[i].bytes < pool.idle[best].bytes))
+                best = i;
+        if (best < pool.idle.size()) {
+            out = pool.idle[best];
+            pool.idle[best] = pool.idle.back();
+            pool.idle.pop_back();
+            return hipSuccess;
+        }
     }
-    out[i] = (float)sqrt(s);
+    HostBlock b{};
+    b.device = dev;
+    b.bytes = (size_t)1 << 16;
+    while (b.bytes < bytes) b.bytes *= 2;
+    e = hipHostMalloc((void **)&b.ptr, b.bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipEventCreate(&b.ev0);
+    if (e == hipSuccess) e = hipEventCreate(&b.ev1);
+    if (e != hipSuccess) {
+        free_host_block(b);
+        return e;
+    }
+    out = b;
+    return hipSuccess;
+}
+
+// (nothing on the device uses it any more)
+static void give_host_block(HostBlock &b)
+{
+    if (!b.ptr) return;
+    bool kept = false;
+    {
+        HostPool &pool = host_pool();
+        std::lock_guard<std::mutex> lock(pool.mu);
+        size_t held = b.bytes;
+        for (const HostBlock &i : pool.idle) held += i.bytes;
+        if (pool.idle.size() < HOST_BLOCKS && held <= HOST_BYTES) {
+            try {
+                pool.idle.push_back(b);
+                kept = true;
+            } catch (...) {   // no memory for the list: given back
+            }
+        }
+    }
+    if (kept)
+        b = HostBlock{};
+    else
+        free_host_block(b);
 }
 
 struct BatchHandle {
@@ -962,8 +1079,8 @@ struct BatchHandle {
     hipStream_t stream;
     long long total_x, total_y;
     size_t ws_used;
-    hipEvent_t ev0, ev1;
-    float last_ms;
+    HostBlock host;
+    float last_ms;   // of the last run; < 0: still to be asked from its events
 };
 
 }  // namespace lcn
@@ -987,9 +1104,11 @@ static hipError_t launch_batched_build_as(const BatchHandle &h)
 {
     const BatchDev &D = h.dev;
     const size_t bytes = build_lds(D.l, (D.l > 0 ? 1 : 0) + D.R, D.mt, DT, D.max_points, NT / 64).bytes;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&batched_build_kernel<NT, DT>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e != hipSuccess) return e;
+    if (bytes > 64 * 1024) {   // has to be allowed
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&batched_build_kernel<NT, DT>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((batched_build_kernel<NT, DT>), dim3(D.P), dim3(NT), bytes, h.stream, D);
     return hipGetLastError();
 }
@@ -1021,13 +1140,15 @@ static hipError_t launch_batched_run(const BatchHandle &h, int iters, float *row
 lcn_status batched_run(void *hh, int iters)
 {
     BatchHandle &h = *(BatchHandle *)hh;
-    BHIPCHK(hipEventRecord(h.ev0, h.stream));
+    BHIPCHK(hipEventRecord(h.host.ev0, h.stream));
     BHIPCHK(launch_batched_run(h, iters, nullptr, nullptr));
-    BHIPCHK(hipEventRecord(h.ev1, h.stream));
-    unsigned long long c[3] = {0, 0, 0};
-    BHIPCHK(hipMemcpyAsync(c, h.dev.counters, sizeof(c), hipMemcpyDeviceToHost, h.stream));
+    BHIPCHK(hipEventRecord(h.host.ev1, h.stream));
+    h.last_ms = -1.f;
     BHIPCHK(hipStreamSynchronize(h.stream));
-    BHIPCHK(hipEventElapsedTime(&h.last_ms, h.ev0, h.ev1));
+    if (!*(volatile int *)(h.dev.marks + 1)) return LCN_OK;
+    unsigned long long c[3] = {0, 0, 0};
+    const lcn_status st = batched_counts(hh, c);
+    if (st != LCN_OK) return st;
     if (c[0]) return LCN_ERR_NONPOSITIVE;
     return (c[1] | c[2]) ? LCN_WARN_NO_SUPPORT : LCN_OK;
 }
@@ -1036,11 +1157,9 @@ lcn_status batched_query(void *hh, double *dist_host, double *resid_host, float 
 {
     BatchHandle &h = *(BatchHandle *)hh;
     BHIPCHK(launch_batched_run(h, 0, row_dev, col_dev));
-    if (dist_host)
-        BHIPCHK(hipMemcpyAsync(dist_host, h.dev.dist, sizeof(double) * h.dev.P, hipMemcpyDeviceToHost, h.stream));
-    if (resid_host)
-        BHIPCHK(hipMemcpyAsync(resid_host, h.dev.resid, sizeof(double) * h.dev.P, hipMemcpyDeviceToHost, h.stream));
     BHIPCHK(hipStreamSynchronize(h.stream));
+    if (dist_host) memcpy(dist_host, h.dev.dist, sizeof(double) * h.dev.P);
+    if (resid_host) memcpy(resid_host, h.dev.resid, sizeof(double) * h.dev.P);
     return LCN_OK;
 }
 
@@ -1055,6 +1174,7 @@ lcn_status batched_counts(void *hh, unsigned long long c[3])
 lcn_status batched_timing(void *hh, float *ms, int *launches)
 {
     BatchHandle &h = *(BatchHandle *)hh;
+    if (h.last_ms < 0.f) BHIPCHK(hipEventElapsedTime(&h.last_ms, h.host.ev0, h.host.ev1));
     if (ms) *ms = h.last_ms;
     if (launches) *launches = 1;
     return LCN_OK;
@@ -1064,8 +1184,7 @@ void batched_destroy(void *hh)
 {
     BatchHandle *h = (BatchHandle *)hh;
     (void)hipStreamSynchronize(h->stream);
-    (void)hipEventDestroy(h->ev0);
-    (void)hipEventDestroy(h->ev1);
+    give_host_block(h->host);
     h->magic = 0;
     delete h;
 }
@@ -1116,8 +1235,8 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
         ~Guard()
         {
             if (p) {
-                if (p->ev0) (void)hipEventDestroy(p->ev0);
-                if (p->ev1) (void)hipEventDestroy(p->ev1);
+                if (p->host.ptr) (void)hipStreamSynchronize(p->stream);   // a kernel may still use it
+                give_host_block(p->host);
                 delete p;
             }
         }
@@ -1157,6 +1276,7 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
     long long *xo = (long long *)take(sizeof(long long) * (P + 1));
     long long *yo = (long long *)take(sizeof(long long) * (P + 1));
     float *lam = (float *)take(sizeof(float) * P);
+    const size_t described = used;
     D.Kt = (float *)take(sizeof(float) * (size_t)P * BMAX * BMAX);
     D.kpe = (double *)take(sizeof(double) * (size_t)tx);
     D.keq = (double *)take(sizeof(double) * (size_t)ty);
@@ -1164,10 +1284,7 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
     D.buckets = (int *)take(sizeof(int) * (size_t)(D.R > 0 ? D.R : 1) * (tx + ty));
     D.log_u = (double *)take(sizeof(double) * (size_t)(tx + ty));
     D.log_v = (double *)take(sizeof(double) * (size_t)(tx + ty));
-    D.dist = (double *)take(sizeof(double) * P);
-    D.resid = (double *)take(sizeof(double) * P);
     D.counters = (unsigned long long *)take(64);
-    D.fail = (int *)take(64);
     h.ws_used = used;
     if (bytes_needed) *bytes_needed = used + 256;
     if (used > workspace_bytes) return LCN_ERR_ALLOC;
@@ -1175,18 +1292,27 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
     D.y_off = yo;
     D.lambda = lam;
 
-    BHIPCHK(hipEventCreate(&h.ev0));
-    BHIPCHK(hipEventCreate(&h.ev1));
-    BHIPCHK(hipMemcpyAsync(xo, desc->x_off, sizeof(long long) * (P + 1), hipMemcpyHostToDevice, h.stream));
-    BHIPCHK(hipMemcpyAsync(yo, desc->y_off, sizeof(long long) * (P + 1), hipMemcpyHostToDevice, h.stream));
-    BHIPCHK(hipMemcpyAsync(lam, desc->lambda, sizeof(float) * P, hipMemcpyHostToDevice, h.stream));
-    BHIPCHK(hipMemsetAsync(D.counters, 0, 64, h.stream));
-    BHIPCHK(hipMemsetAsync(D.fail, 0, 64, h.stream));
+    // the host block: the description as it lies in the workspace, then distances, residuals and marks
+    const size_t result_bytes = (sizeof(double) * (size_t)P + 255) & ~(size_t)255;
+    if (take_host_block(described + 2 * result_bytes + 256, h.host) != hipSuccess) {
+        (void)hipGetLastError();
+        return LCN_ERR_DEVICE;
+    }
+    char *host = h.host.ptr;
+    memcpy(host + ((char *)xo - base), desc->x_off, sizeof(long long) * (P + 1));
+    memcpy(host + ((char *)yo - base), desc->y_off, sizeof(long long) * (P + 1));
+    memcpy(host + ((char *)lam - base), desc->lambda, sizeof(float) * P);
+    D.dist = (double *)(host + described);
+    D.resid = (double *)(host + described + result_bytes);
+    D.marks = (int *)(host + described + 2 * result_bytes);
+    D.marks[0] = D.marks[1] = 0;
+    const long long words = (long long)(((char *)(lam + P) - base) / 4);
+    hipLaunchKernelGGL(batch_upload_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, h.stream,
+                       (const unsigned *)host, (unsigned *)base, words, (unsigned *)D.counters, 16);
+    BHIPCHK(hipGetLastError());
     BHIPCHK(launch_batched_build(h));
-    int fail = 0;
-    BHIPCHK(hipMemcpyAsync(&fail, D.fail, sizeof(int), hipMemcpyDeviceToHost, h.stream));
     BHIPCHK(hipStreamSynchronize(h.stream));
-    if (fail) return LCN_ERR_SINGULAR;
+    if (*(volatile int *)D.marks) return LCN_ERR_SINGULAR;
     h.magic = BATCH_MAGIC;
     guard.p = nullptr;
     *out = (lcn_handle)hp;
