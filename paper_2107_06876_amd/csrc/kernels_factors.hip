@@ -621,6 +621,14 @@ hipError_t launch_spd_inverse(double *A, int l, double ridge, double *Lm, double
                               double *Tm, int *fail_flag, hipStream_t s)
 {
     const long long ll = (long long)l * l;
+    if (l <= NB) {   // one diagonal block: A = L L^T, A^{-1} = L^{-T} L^{-1}
+        hipError_t e1 = hipFuncSetAttribute((const void *)chol_diag_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)CHOL_LDS);
+        if (e1 != hipSuccess) return e1;
+        hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(256), CHOL_LDS, s, A, l, 0, l, ridge, Dinv, fail_flag);
+        gemm64(Dinv, NB, true, Dinv, NB, false, Ainv, l, l, l, l, 1.0, 0.0, nullptr, 0, s);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(copy_f64_kernel, dim3((unsigned)((ll + 255) / 256)), dim3(256), 0, s, A, Lm, ll);
     hipError_t e = hipMemsetAsync(Xm, 0, sizeof(double) * (size_t)ll, s);
     if (e != hipSuccess) return e;

@@ -540,8 +540,6 @@ static hipError_t dispatch_pass(const PassSide &S, const Handle &h, int side, in
                                 unsigned long long *cnt = nullptr)
 {
     if (!cnt) cnt = h.counters;
-    if (mode == PASS_INIT)
-        hipLaunchKernelGGL(max_log_kernel, dim3(1), dim3(1024), 0, s, S.log_out, S.rows, S.shift_self);
     hipError_t e = hipErrorInvalidValue;
     if (h.R == 0) {
         e = launch_nystrom_pass(S, h, mode, fuse, fused_in, partial, cnt, s);
@@ -567,6 +565,14 @@ hipError_t launch_pass(const Handle &h, int side, int mode, int acc_in, int acc_
     const PassSide S = make_side(h, side, acc_in, acc_out, marg_out);
     if (h.log_domain) return launch_logpass(S, h, side, mode, s);
     return dispatch_pass(S, h, side, mode, nullptr, false, true, h.partial, s);
+}
+
+hipError_t launch_init_pass(const Handle &h, int side, int acc_out, bool zero_logs, hipStream_t s)
+{
+    const PassSide S = make_side(h, side, -1, acc_out, nullptr);
+    if (!h.log_domain && !zero_logs)   // the exponent to take out
+        hipLaunchKernelGGL(max_log_kernel, dim3(1), dim3(1024), 0, s, S.log_out, S.rows, S.shift_self);
+    return launch_pass(h, side, PASS_INIT, -1, acc_out, nullptr, s);
 }
 
 // `iters` iterations = 2 iters update sweeps (rows of X, then rows of Y).  With

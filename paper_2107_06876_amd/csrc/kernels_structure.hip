@@ -1349,7 +1349,7 @@ hipError_t launch_kmeans_update(const float *Z, long long N, int d, const KmRuns
 
 constexpr int CH = 1024;
 
-__global__ void scan_i64_kernel(long long *data, long long n);
+__global__ void scan_i64_kernel(long long *data, long long n, long long *data2, long long n2);
 
 // Exclusive scan of 1024 per-thread values across a workgroup of 1024 threads: returns the sum
 // of the values of all lower threads; *total receives the sum of all.  wsum: 16 words of LDS.
@@ -1551,8 +1551,7 @@ hipError_t launch_bucket_sort(const SortBuffers &B, hipStream_t s)
     hipLaunchKernelGGL(sort_scatter_kernel, grid, dim3(1024), lds, s, B);
     long long mx = B.n > B.m ? B.n : B.m;
     hipLaunchKernelGGL(seg_kernel, dim3((unsigned)((mx + 255) / 256), 2), dim3(256), 0, s, B);
-    hipLaunchKernelGGL(scan_i64_kernel, dim3(1), dim3(1024), 0, s, B.rowbase_x, B.n);
-    hipLaunchKernelGGL(scan_i64_kernel, dim3(1), dim3(1024), 0, s, B.rowbase_y, B.m);
+    hipLaunchKernelGGL(scan_i64_kernel, dim3(2), dim3(1024), 0, s, B.rowbase_x, B.n, B.rowbase_y, B.m);
     return hipGetLastError();
 }
 
@@ -1803,9 +1802,13 @@ hipError_t launch_csr_values(const Handle &h, const float *rec, const float *rec
 
 // in-place exclusive scan of n int64 values by one block; data[n] receives the total
 // One workgroup; tiles of 4096 elements, four consecutive ones per thread.
-__global__ __launch_bounds__(1024) void scan_i64_kernel(long long *data, long long n)
+__global__ __launch_bounds__(1024) void scan_i64_kernel(long long *data, long long n, long long *data2, long long n2)
 {
     __shared__ long long wsum[16];
+    if (blockIdx.x == 1) {
+        data = data2;
+        n = n2;
+    }
     const int tid = threadIdx.x;
     long long carry = 0;
     for (long long t0 = 0; t0 < n; t0 += 4096) {
@@ -1827,7 +1830,7 @@ __global__ __launch_bounds__(1024) void scan_i64_kernel(long long *data, long lo
 
 hipError_t launch_scan_i64(long long *data, long long n, hipStream_t s)
 {
-    hipLaunchKernelGGL(scan_i64_kernel, dim3(1), dim3(1024), 0, s, data, n);
+    hipLaunchKernelGGL(scan_i64_kernel, dim3(1), dim3(1024), 0, s, data, n, (long long *)nullptr, 0ll);
     return hipGetLastError();
 }
 

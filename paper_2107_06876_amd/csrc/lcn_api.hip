@@ -66,6 +66,8 @@ bool uses_landmarks(int mode) { return mode == LCN_MODE_NYSTROM || mode == LCN_M
 bool uses_lsh(int mode) { return mode == LCN_MODE_SPARSE || mode == LCN_MODE_LCN; }
 constexpr long long KM_MERGE_POINTS = 1ll << 17;
 
+constexpr int REPORT_FAIL = 16, REPORT_TOTALS = 18, REPORT_WORDS = 24;   // 64-bit words behind h.counters
+
 constexpr int KM_LANES = 4;   // k-means runs of a build that may be in flight together on streams of their own
 
 struct KmScratch {  // what one k-means run needs for itself
@@ -102,10 +104,11 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
     h.zn = bump.take<double>((size_t)N);
     h.a = bump.take<float>((size_t)h.n);
     h.b_marg = bump.take<float>((size_t)h.m);
-    h.counters = bump.take<unsigned long long>(16);
+    // counters, a singular landmark matrix, the pattern's totals: what a build reports to the host lies together
+    h.counters = bump.take<unsigned long long>(REPORT_WORDS);
+    sc.fail_flag = (int *)(h.counters + REPORT_FAIL);
+    sc.totals = (long long *)(h.counters + REPORT_TOTALS);
     h.query_out = bump.take<double>(4);
-    sc.fail_flag = bump.take<int>(4);
-    sc.totals = bump.take<long long>(4);
     h.L = bump.take<float>((size_t)(h.l > 0 ? h.l : 1) * h.d);
     sc.starts = bump.take<long long>((size_t)(h.l > 0 ? h.l : 1) + (size_t)(h.R > 0 ? h.R : 1) * (size_t)h.b);
     // bf16 planes for the assignment filter: points (one plane if the input was bf16), centroids
@@ -495,10 +498,11 @@ lcn_status init_state(Handle &h, bool clear_logs = false)
     if (clear_logs) {   // scalings at their start, v = 1 (and u, until the first sweep replaces it)
         cl.add(h.log_u, sizeof(float) * (size_t)h.n);
         cl.add(h.log_v, sizeof(float) * (size_t)h.m);
+        cl.add(h.shift, 4 * sizeof(double));   // their largest log
     }
     HIPCHK(launch_clear_regions(cl, h.stream));
-    HIPCHK(launch_pass(h, 0, PASS_INIT, -1, 1, nullptr, h.stream));
-    HIPCHK(launch_pass(h, 1, PASS_INIT, -1, 0, nullptr, h.stream));
+    HIPCHK(launch_init_pass(h, 0, 1, clear_logs, h.stream));
+    HIPCHK(launch_init_pass(h, 1, 0, clear_logs, h.stream));
     h.fresh = 1;
     return LCN_OK;
 }
@@ -607,9 +611,7 @@ struct Builder {
         HIPCHK(hipEventCreate(&h.ev0));
         HIPCHK(hipEventCreate(&h.ev1));
         ClearRegions cl{};
-        cl.add(h.counters, 16 * sizeof(unsigned long long));
-        cl.add(sc.fail_flag, 4 * sizeof(int));
-        cl.add(sc.totals, 4 * sizeof(long long));
+        cl.add(h.counters, REPORT_WORDS * sizeof(unsigned long long));
         HIPCHK(launch_clear_regions(cl, h.stream));
         HIPCHK(hipMemcpyAsync(h.a, a, sizeof(float) * (size_t)n, hipMemcpyDeviceToDevice, h.stream));
         HIPCHK(hipMemcpyAsync(h.b_marg, b, sizeof(float) * (size_t)m, hipMemcpyDeviceToDevice, h.stream));
@@ -789,11 +791,11 @@ struct Builder {
         }
         // A and its inverse first: a chain of small launches that the two big ones would otherwise
         // keep waiting for compute units; U and V are enqueued behind it and run beside its second half
-        HIPCHK(hipMemsetAsync(h.Wt, 0, sizeof(float) * (size_t)m * h.lp, fs));
+        if (h.lp > h.l) HIPCHK(hipMemsetAsync(h.Wt, 0, sizeof(float) * (size_t)m * h.lp, fs));   // the padding
         HIPCHK(launch_kernel_matrix(h.L, h.l, h.L, h.l, d, cost, h.lambda, sc.ln, sc.ln,
                                     nullptr, sc.A64, h.l, fs));
         HIPCHK(launch_spd_inverse(sc.A64, h.l, h.ridge, sc.Lt, sc.Li, sc.Ainv, sc.Dinv, sc.Tm, sc.fail_flag, fs));
-        HIPCHK(hipMemsetAsync(h.U, 0, sizeof(float) * (size_t)n * h.lp, us));
+        if (h.lp > h.l) HIPCHK(hipMemsetAsync(h.U, 0, sizeof(float) * (size_t)n * h.lp, us));
         HIPCHK(launch_kernel_matrix(Xz, n, h.L, h.l, d, cost, h.lambda, h.zn, sc.ln,
                                     h.U, nullptr, h.lp, us));
         HIPCHK(launch_kernel_matrix(Yz, m, h.L, h.l, d, cost, h.lambda, h.zn + n, sc.ln,
@@ -825,23 +827,16 @@ struct Builder {
                 HIPCHK(hipStreamWaitEvent(h.stream, join[q], 0));
             }
         }
-        long long totals[2] = {0, 0};
-        unsigned long long range_flag = 0;
-        if (h.R > 0) {
-            HIPCHK(launch_bucket_sort(h.sort, h.stream));
-            HIPCHK(hipMemcpyAsync(totals, sc.totals, sizeof(totals), hipMemcpyDeviceToHost, h.stream));
-        }
+        unsigned long long report[REPORT_WORDS];
+        if (h.R > 0) HIPCHK(launch_bucket_sort(h.sort, h.stream));
+        HIPCHK(hipMemcpyAsync(report, h.counters, sizeof(report), hipMemcpyDeviceToHost, h.stream));
         HIPCHK(launch_build_meta(h.sort, h.a, h.b_marg, h.stream));
-        int undecided2[2] = {0, 0};  // points sent to the exact rule over all centroids, and over two
-        if (last_nflagged)
-            HIPCHK(hipMemcpyAsync(undecided2, last_nflagged, 2 * sizeof(int), hipMemcpyDeviceToHost, h.stream));
-        HIPCHK(hipMemcpyAsync(&range_flag, h.counters + 4, sizeof(range_flag), hipMemcpyDeviceToHost, h.stream));
         HIPCHK(hipEventRecord(h.ev0, h.stream));
         HIPCHK(hipEventSynchronize(h.ev0));
-        if (range_flag && (h.l > 0 || h.hash == LCN_HASH_KMEANS)) return LCN_ERR_INVALID_ARG;  // |x| >= 2^10 or not finite
-        h.nnz_stored = totals[0];
-        h.undecided_last = (long long)undecided2[0] + undecided2[1];
-        h.ntiles = (int)totals[1];
+        if (report[4] && (h.l > 0 || h.hash == LCN_HASH_KMEANS)) return LCN_ERR_INVALID_ARG;  // |x| >= 2^10 or not finite
+        h.nnz_stored = h.R > 0 ? (long long)report[REPORT_TOTALS] : 0;
+        h.undecided = last_nflagged;
+        h.ntiles = h.R > 0 ? (int)report[REPORT_TOTALS + 1] : 0;
 
         // slack: a sweep reads whole wavefront-wide chunks, up to four at a time, and masks the excess
         h.vals_x = bump.take<float>((size_t)h.nnz_stored + VALUE_SLACK);
@@ -875,13 +870,11 @@ struct Builder {
         if (h.R > 0) HIPCHK(launch_correction(h, h.ntiles, h.stream));
         const lcn_status st = init_state(h, true);
         if (st != LCN_OK) return st;
-        int fail = 0;
-        unsigned long long uniq = 0;
-        HIPCHK(hipMemcpyAsync(&fail, sc.fail_flag, sizeof(int), hipMemcpyDeviceToHost, h.stream));
-        HIPCHK(hipMemcpyAsync(&uniq, h.counters + 3, sizeof(uniq), hipMemcpyDeviceToHost, h.stream));
+        unsigned long long report[REPORT_WORDS];
+        HIPCHK(hipMemcpyAsync(report, h.counters, sizeof(report), hipMemcpyDeviceToHost, h.stream));
         HIPCHK(hipStreamSynchronize(h.stream));
-        if (fail) return LCN_ERR_SINGULAR;
-        h.nnz_unique = (long long)uniq;
+        if ((int)(report[REPORT_FAIL] & 0xffffffffull)) return LCN_ERR_SINGULAR;
+        h.nnz_unique = (long long)report[3];
         return LCN_OK;
     }
 };
@@ -1250,7 +1243,9 @@ lcn_status lcn_get_info(lcn_handle hh, lcn_info *info)
     if (!info) return LCN_ERR_INVALID_ARG;
     Handle &h = *(Handle *)hh;
     unsigned long long c[6];
+    int undecided[2] = {0, 0};  // points sent to the exact rule over all centroids, and over two
     HIPCHK(hipMemcpyAsync(c, h.counters, sizeof(c), hipMemcpyDeviceToHost, h.stream));
+    if (h.undecided) HIPCHK(hipMemcpyAsync(undecided, h.undecided, sizeof(undecided), hipMemcpyDeviceToHost, h.stream));
     HIPCHK(hipStreamSynchronize(h.stream));
     if (c[5]) return LCN_ERR_DEVICE;  // a sweep gave up waiting for its totals
     info->n = h.n;
@@ -1265,7 +1260,7 @@ lcn_status lcn_get_info(lcn_handle hh, lcn_info *info)
     info->empty_rows = (int64_t)c[1];
     info->empty_cols = (int64_t)c[2];
     info->workspace_used = h.ws_used;
-    info->undecided_last = h.undecided_last;
+    info->undecided_last = (int64_t)undecided[0] + undecided[1];
     return LCN_OK;
 }
 

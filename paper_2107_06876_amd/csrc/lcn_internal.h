@@ -179,6 +179,8 @@ hipError_t launch_csr_values(const Handle &h, const float *rec, const float *rec
 
 // ---- iteration (kernels_iter.hip) ------------------------------------------
 hipError_t launch_pass(const Handle &h, int side, int mode, int acc_in, int acc_out, float *marg_out, hipStream_t s);
+// the working copies and the accumulator from the stored logs; zero_logs: all of them are zero (and the exponents are)
+hipError_t launch_init_pass(const Handle &h, int side, int acc_out, bool zero_logs, hipStream_t s);
 hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s);
 // A whole dense iteration from one read of the kernel matrix (kernels_dense.hip): workgroups whose column sums
 // it leaves, 0 where the two half-iterations by themselves are to be used.
@@ -221,7 +223,7 @@ struct Handle {
     int32_t *bucket;   // [R][n+m]
     SortBuffers sort;
     long long nnz_stored, nnz_unique;
-    long long undecided_last;
+    const int *undecided;      // device: points the last assignment of the last k-means run left to the exact rule (null: none)
     int ntiles;
     // factors
     float *U;          // n x lp
