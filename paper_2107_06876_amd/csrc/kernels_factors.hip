@@ -165,6 +165,46 @@ __device__ inline void tile_mma(TileAcc &acc, const float (*Ps)[LDK], const floa
     }
 }
 
+// The same for a tile of which only the first rows and columns hold points: its 16 x 16 pieces that do are dealt to the
+// wavefronts in equal shares (at most four each), instead of a quarter of the tile to each: a piece of 64 x 20
+// points is then two pieces for every wavefront, not four for two of them.
+struct TilePieces {
+    int rt[4], ct[4], count;   // this wavefront's: row and column of pieces (the same in every lane)
+    __device__ inline TilePieces(int rows, int cols)
+    {
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int nr = (rows + 15) / 16, nc = (cols + 15) / 16, total = nr * nc;
+        count = (total - w + 3) / 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int p = q < count ? w + 4 * q : 0;
+            rt[q] = p / nc;
+            ct[q] = p - rt[q] * nc;
+        }
+    }
+    // place of accumulator e = 4 q + v of this thread
+    __device__ inline int row(int e) const { return 16 * rt[e >> 2] + 4 * (e & 3) + (int)((threadIdx.x & 63) >> 4); }
+    __device__ inline int col(int e) const { return 16 * ct[e >> 2] + (int)(threadIdx.x & 15); }
+};
+
+__device__ inline void pieces_mma(TileAcc &acc, const float (*Ps)[LDK], const float (*Cs)[LDK], const TilePieces &T)
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const int r = threadIdx.x & 15, kq = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (q >= T.count) continue;   // the same in every lane
+        const float *a = &Ps[16 * T.rt[q] + r][8 * kq], *b = &Cs[16 * T.ct[q] + r][8 * kq];
+        const f4 a0 = *(const f4 *)a, a1 = *(const f4 *)(a + 4), b0 = *(const f4 *)b, b1 = *(const f4 *)(b + 4);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            acc.t[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a0[k], (double)b0[k], acc.t[q], 0, 0, 0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            acc.t[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a1[k], (double)b1[k], acc.t[q], 0, 0, 0);
+    }
+}
+
 __device__ inline void tile_zero(TileAcc &acc)
 {
 #pragma unroll
@@ -677,15 +717,27 @@ hipError_t launch_spd_inverse(double *A, int l, double ridge, double *Lm, double
 // fp64 from the gathered rows; a pair that an earlier round already holds is
 // stored as zero so that the union over rounds counts it once.
 
-__global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const float *__restrict__ Z, int d, int cost,
+//
+// What bounds it is the fp64 matrix instruction where the pieces are full, and the chain of chunks in few workgroups where
+// they are small.  Hence the 16 x 16 pieces dealt evenly (TilePieces), and registers for three workgroups per compute
+// unit instead of two: the Nystrom value is subtracted by starting the second product at minus the first one's kernel
+// value, and the tile's values take the chunks' place in LDS.  Before -> now: 185 -> 122 us at 20 000 points of 300
+// dimensions, 256 landmarks, 0.9 M stored pairs; 1620 -> 915 at 200 000, 512 and 3.9 M; 97 -> 82 at 10 000 of 64, 128 and 4.1 M;
+// 822 -> 640 for the dense kernel of 10 000 points of 64.  (Unconditional loads, a piece's last row repeated: 1480
+// instead of 1210 before the pieces were dealt.)
+// DERIV: derivatives instead of values (see below).  VECZ: rows of Z start on 16-byte boundaries (lp is a multiple of 64).
+template <bool DERIV, bool VECZ>
+__global__ __launch_bounds__(256, DERIV ? 2 : 3) void correction_kernel(SortBuffers B, const float *__restrict__ Z, int d, int cost,
                                                          double inv_lambda, const double *__restrict__ zn,
                                                          const float *__restrict__ U, const float *__restrict__ Wt,
                                                          int lp, int log_values, float *vals_x, float *vals_y,
                                                          unsigned long long *unique_counter, BackwardArgs bw)
 {
-    __shared__ __align__(16) float Ps[TILE][LDK];
-    __shared__ __align__(16) float Cs[TILE][LDK];
-    __shared__ float vals[TILE][TILE + 1];
+    // the staged chunks, and in their place, once the last one has been multiplied, the tile's values
+    __shared__ __align__(16) float room[2 * TILE * LDK];
+    static_assert(TILE * (TILE + 1) <= 2 * TILE * LDK, "the values fit the chunks' place");
+    float(*Ps)[LDK] = reinterpret_cast<float(*)[LDK]>(room), (*Cs)[LDK] = Ps + TILE;
+    float(*vals)[TILE + 1] = reinterpret_cast<float(*)[TILE + 1]>(room);
     __shared__ long long xi[TILE], yj[TILE];
     __shared__ double xterm[TILE], yterm[TILE];   // per row / column of the tile: see norm_term
     __shared__ long long xdst[TILE], ydst[TILE];  // where each row's / column's slice of this block starts
@@ -745,13 +797,13 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
     if (tid == 0) cnt_sh = 0;
     const int rows_here = nx - ti * 64 < 64 ? nx - ti * 64 : 64;   // members of the bucket in this piece
     const int cols_here = ny - tj * 64 < 64 ? ny - tj * 64 : 64;
+    const TilePieces pieces(rows_here, cols_here);
 
     // One run of chunks: the features of the points (exact cost), then, in the lcn mode, the
     // Nystrom value on the same pairs, sum_k U[i][k] Wt[j][k].  The loads of a chunk are requested
     // before the chunk ahead of it is multiplied.
     const int nd = (d + KCH - 1) / KCH, nl = U ? (lp + KCH - 1) / KCH : 0;
     constexpr int DEPTH = 2;          // chunks whose loads are in flight (3 measured slower: registers)
-    const bool vecz = (d & 3) == 0;   // rows of Z start on 16-byte boundaries (lp is a multiple of 64)
     struct Chunk {
         float p[8], c[8];
     };
@@ -760,7 +812,7 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
         if (c >= nd) {
             fetch_rows4(C.p, U, lp, xi, 0, (c - nd) * KCH, lp);
             fetch_rows4(C.c, Wt, lp, yj, -(long long)B.n, (c - nd) * KCH, lp);   // yj: rows of Z; Wt has the rows of Y
-        } else if (vecz) {
+        } else if (VECZ) {
             fetch_rows4(C.p, Z, d, xi, 0, c * KCH, d);
             fetch_rows4(C.c, Z, d, yj, 0, c * KCH, d);
         } else {
@@ -770,11 +822,11 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
     };
     TileAcc acc;
     tile_zero(acc);
-    double kv[16];
+    double kv[DERIV ? 16 : 1];
     // chunk c: its registers go to LDS, the loads of chunk c + DEPTH take their place, chunk c is multiplied
     auto step = [&](Chunk &C, int c) {
         __syncthreads();
-        if (c >= nd || vecz) {
+        if (VECZ || c >= nd) {
             store_rows4(Ps, C.p);
             store_rows4(Cs, C.c);
         } else {
@@ -783,20 +835,24 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
         }
         __syncthreads();
         fetch(C, c + DEPTH);
-        tile_mma(acc, Ps, Cs, rows_here, cols_here);
+        pieces_mma(acc, Ps, Cs, pieces);
         if (c == nd - 1) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int li = tile_row(e), lj = tile_col(e);
+                if ((e >> 2) >= pieces.count) continue;   // the same in every lane
+                const int li = pieces.row(e), lj = pieces.col(e);
                 const long long gi = xi[li], gj = yj[lj];
                 double v = 0.0;
                 if (gi >= 0 && gj >= 0) {
                     const double cc = cost_from_dot(acc.get(e), cost, xterm[li], yterm[lj]);
                     v = log_values ? -cc * inv_lambda : exp(-cc * inv_lambda);
                 }
-                kv[e] = v;
+                if constexpr (DERIV)
+                    kv[e] = v;
+                else   // the Nystrom value is added to what is subtracted from
+                    acc.t[e >> 2][e & 3] = -v;
             }
-            tile_zero(acc);
+            if (DERIV) tile_zero(acc);
         }
     };
     Chunk ch[DEPTH] = {};
@@ -808,11 +864,8 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
         for (int j = 0; j < DEPTH; ++j)
             if (c + j < nd + nl) step(ch[j], c + j);
     }
-    if (U && !bw.lin_u) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) kv[e] -= acc.get(e);
-    }
-    if (bw.lin_u) {
+    __syncthreads();   // the last chunk has been multiplied
+    if constexpr (DERIV) {
         // derivatives instead of kernel values (Prop. 1): -lambda u_i K^sp_ij v_j and, from the
         // Nystrom value still in `acc`, +lambda u_i K^sp_Nys,ij v_j, into the records of X only
         const double scale = bw.lambda * exp(bw.acc_y[lp] + bw.acc_z[lp]);  // exponents taken out of v and u
@@ -820,7 +873,8 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int li = tile_row(e), lj = tile_col(e);
+                if ((e >> 2) >= pieces.count) continue;   // the same in every lane
+                const int li = pieces.row(e), lj = pieces.col(e);
                 const long long gi = xi[li], gj = yj[lj];
                 double g = 0.0;
                 if (gi >= 0 && gj >= 0) {
@@ -839,18 +893,19 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
                 }
         }
         return;
-    }
+    } else {
     // drop pairs an earlier round owns, count the rest
     unsigned mine = 0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-        const int li = tile_row(e), lj = tile_col(e);
+        if ((e >> 2) >= pieces.count) continue;   // the same in every lane
+                const int li = pieces.row(e), lj = pieces.col(e);
         bool present = xi[li] >= 0 && yj[lj] >= 0;
         bool dup = false;
         for (int q = 0; q < r; ++q) dup |= bx[q][li] == by[q][lj];
-        if (!present || dup) kv[e] = log_values ? -INFINITY : 0.0;
+        const double value = !present || dup ? (log_values ? -INFINITY : 0.0) : -acc.get(e);
         if (present && !dup) ++mine;
-        vals[li][lj] = (float)kv[e];
+        vals[li][lj] = (float)value;
     }
     atomicAdd(&cnt_sh, mine);
     __syncthreads();
@@ -863,15 +918,22 @@ __global__ __launch_bounds__(256) void correction_kernel(SortBuffers B, const fl
         const int li = ti * 64 + lane;
         if (ydst[rr] >= 0 && li < nx) vals_y[ydst[rr] + li] = vals[lane][rr];
     }
+    }
 }
 
 hipError_t launch_correction(const Handle &h, int ntiles, hipStream_t s)
 {
     if (ntiles <= 0) return hipSuccess;
     const bool lcn_mode = h.mode == LCN_MODE_LCN;
-    hipLaunchKernelGGL(correction_kernel, dim3(ntiles), dim3(256), 0, s, h.sort, h.Z, h.d, h.cost, 1.0 / h.lambda,
-                       h.zn, lcn_mode ? h.U : (const float *)nullptr, lcn_mode ? h.Wt : (const float *)nullptr, h.lp,
-                       h.log_domain, h.vals_x, h.vals_y, h.counters + 3, BackwardArgs{});
+    const float *U = lcn_mode ? h.U : nullptr, *Wt = lcn_mode ? h.Wt : nullptr;
+    if ((h.d & 3) == 0)
+        hipLaunchKernelGGL((correction_kernel<false, true>), dim3(ntiles), dim3(256), 0, s, h.sort, h.Z, h.d, h.cost,
+                           1.0 / h.lambda, h.zn, U, Wt, h.lp, h.log_domain, h.vals_x, h.vals_y, h.counters + 3,
+                           BackwardArgs{});
+    else
+        hipLaunchKernelGGL((correction_kernel<false, false>), dim3(ntiles), dim3(256), 0, s, h.sort, h.Z, h.d, h.cost,
+                           1.0 / h.lambda, h.zn, U, Wt, h.lp, h.log_domain, h.vals_x, h.vals_y, h.counters + 3,
+                           BackwardArgs{});
     return hipGetLastError();
 }
 
@@ -888,9 +950,14 @@ hipError_t launch_backward_pattern(const Handle &h, float *rec_sp, float *rec_ny
     bw.lambda = h.lambda;
     bw.rec_sp = rec_sp;
     bw.rec_nys = rec_nys;
-    hipLaunchKernelGGL(correction_kernel, dim3(h.ntiles), dim3(256), 0, s, h.sort, h.Z, h.d, h.cost, 1.0 / h.lambda,
-                       h.zn, h.U, h.Wt, h.lp, 0,
-                       (float *)nullptr, (float *)nullptr, (unsigned long long *)nullptr, bw);
+    if ((h.d & 3) == 0)
+        hipLaunchKernelGGL((correction_kernel<true, true>), dim3(h.ntiles), dim3(256), 0, s, h.sort, h.Z, h.d, h.cost,
+                           1.0 / h.lambda, h.zn, h.U, h.Wt, h.lp, 0, (float *)nullptr, (float *)nullptr,
+                           (unsigned long long *)nullptr, bw);
+    else
+        hipLaunchKernelGGL((correction_kernel<true, false>), dim3(h.ntiles), dim3(256), 0, s, h.sort, h.Z, h.d, h.cost,
+                           1.0 / h.lambda, h.zn, h.U, h.Wt, h.lp, 0, (float *)nullptr, (float *)nullptr,
+                           (unsigned long long *)nullptr, bw);
     return hipGetLastError();
 }
 
