@@ -1,0 +1,187 @@
+"""Sizes at which a kernel or a rule of a dispatch changes: rows per wavefront of a sweep, lanes per row of a sweep in logs,
+ranges of points and clusters times points in the k-means update, pieces of the sparse values' tiles, pinned blocks
+of batches.  Against the oracle (tolerances of parity.py), or against the exact rule applied to every point."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _cut(n, m, d, landmarks, buckets, rounds, iters, kmeans_iters=2, seed=11):
+    """Unit-free points of two overlapping clouds, smooth enough for every sum to stay positive."""
+    p = workloads.config3(n=64, d=8, landmarks=8, buckets=8, rounds=rounds, iters=iters, name="cut")
+    rng = np.random.default_rng(seed)
+    p.X = rng.standard_normal((n, d)).astype(np.float32)
+    p.Y = (0.9 * rng.standard_normal((m, d)) + 0.1).astype(np.float32)
+    p.a = (rng.random(n) + 0.5).astype(np.float32)
+    p.b = (rng.random(m) + 0.5).astype(np.float32)
+    p.a /= p.a.sum()
+    p.b /= p.b.sum()
+    p.cost, p.lam = workloads.COST_SQEUCLID, 4.0 * d
+    p.num_landmarks, p.num_buckets, p.num_rounds, p.kmeans_iters = landmarks, buckets, rounds, kmeans_iters
+    p.iters, p.ridge = iters, 1e-6
+    return p
+
+
+# a chip of 256 compute units has 4096 wavefronts: one, two, three and five rows per wavefront, then whichever of three and five
+# takes fewer turns; short records (one wavefront of entries requested with a row of five) and long ones (two)
+@pytest.mark.parametrize("n,m,landmarks,buckets,rounds", [
+    (1, 4097, 20, 1, 1),          # a single row against thousands
+    (4096, 4097, 20, 300, 1),     # one row per wavefront / two, up to 64 columns
+    (8192, 8193, 70, 500, 2),     # two / three, up to 128 columns
+    (12288, 12289, 140, 900, 3),  # three / five, up to 192 columns
+    (20480, 20481, 30, 1500, 1),  # five / three, short records
+    (24577, 12300, 20, 400, 2),   # three, unequal sides
+    (13000, 12999, 40, 120, 1),   # five, long records
+    (5000, 5001, 300, 200, 1),    # more than 256 columns
+])
+def test_rows_per_wavefront(n, m, landmarks, buckets, rounds):
+    from parity import compare
+    print("rows", n, m, compare(_cut(n, m, 3, landmarks, buckets, rounds, 6), "lcn"), flush=True)
+
+
+@pytest.mark.parametrize("groups", [63, 64, 65])
+def test_totals_taken_directly_or_handed_over(monkeypatch, groups):
+    """Up to 64 partial sums of 64 columns every workgroup adds up by itself, above that they are handed over; both give
+    the bits of the separate reduction."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    from parity import gpu_build
+    p = _cut(16 * groups, 16 * groups - 3, 4, 24, 40, 1, 8)
+    got = {}
+    for fused in ("1", "0"):
+        monkeypatch.setenv("LCN_FUSED_REDUCE", fused)
+        h = gpu_build(p, "lcn")
+        lcn.sinkhorn_run(h, 5)
+        lcn.sinkhorn_run(h, 3)
+        got[fused] = lcn.lcn_get_scalings(h) + (lcn.transport_cost(h),)
+        lcn.lcn_destroy(h)
+    assert torch.equal(got["1"][0], got["0"][0]) and torch.equal(got["1"][1], got["0"][1])
+    assert got["1"][2] == got["0"][2]
+
+
+# records of a few entries up to hundreds, on both sides of the change from 16 to 32 lanes per row (48 entries on average);
+# 3001 and 9 rows: a last workgroup partly empty; five rounds: unrolled over eight
+@pytest.mark.parametrize("n,m,buckets,rounds", [(3001, 2999, 700, 1), (3001, 2999, 60, 1), (2000, 2001, 150, 2),
+                                               (1500, 1499, 40, 3), (1200, 1201, 60, 4), (1000, 999, 60, 5), (9, 700, 3, 1)])
+def test_lanes_per_row_in_logs(n, m, buckets, rounds):
+    from parity import compare
+    print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 12), "sparse"), flush=True)
+
+
+@pytest.mark.parametrize("n,m,d,landmarks,buckets,rounds", [
+    (4096, 4096, 5, 17, 33, 2),      # exactly one range of points, bucket arrays on multiples of four
+    (4099, 4094, 5, 17, 33, 3),      # one point more, bucket arrays off by one, two and three
+    (8193, 8193, 40, 64, 300, 2),    # three ranges, more than 256 clusters
+    (3, 4, 2, 3, 5, 2),              # fewer points than a group of four has room for
+    (900, 801, 530, 20, 12, 1),      # rows too long for sums in registers
+    (9001, 9002, 3, 40, 3800, 1),    # clusters times points above the limit: counting sort
+    (70000, 70001, 2, 30, 60, 1),    # too many points to advance together: a stream per run
+    (5000, 5003, 512, 70, 9, 1),     # the widest rows summed in registers
+])
+def test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds):
+    """Landmarks and buckets equal those of the exact rule applied to every point, which shares neither the filter nor
+    the list of undecided points."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    from parity import gpu_build
+    p = _cut(n, m, d, landmarks, buckets, rounds, 1, kmeans_iters=4)
+    p.X[: n // 5] = p.X[0]   # coinciding points: ties, and a cluster far larger than the others
+    got = {}
+    for exact in ("0", "1"):
+        monkeypatch.setenv("LCN_EXACT_ASSIGN_ONLY", exact)
+        h = gpu_build(p, "lcn")
+        got[exact] = (lcn.lcn_get_landmarks(h), lcn.lcn_get_buckets(h))
+        lcn.lcn_destroy(h)
+    assert torch.equal(got["0"][0], got["1"][0]) and torch.equal(got["0"][1], got["1"][1])
+
+
+@pytest.mark.parametrize("members", [1, 15, 16, 17, 33, 48, 63, 64, 65, 130])
+def test_pieces_of_a_tile(members):
+    """Sparse values and their derivatives where a bucket holds so many points of one side and 20 of the other: pieces
+    of 16 x 16 dealt to four wavefronts.  A single bucket, so that the sizes are exact."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    from parity import compare, gpu_build
+    p = _cut(members, 20, 5, 4, 1, 1, 10)
+    print("pieces", members, compare(p, "lcn"), flush=True)
+    p.X, p.Y, p.a, p.b = p.Y, p.X, p.b, p.a
+    print("pieces", members, compare(p, "lcn"), flush=True)
+    h = gpu_build(p, "lcn")
+    lcn.sinkhorn_run(h, 10)
+    rowptr, cols, _ = lcn.lcn_get_csr(h)
+    gU, gWt, gsp, gnys = lcn.lcn_backward(h, nnz=len(cols))
+    # one bucket: the pattern is everything, and with a_i b_j mass the derivative of every K^sp entry is -lambda u_i v_j
+    log_u, log_v = (t.double() for t in lcn.lcn_get_scalings(h))
+    K = torch.exp(-((torch.from_numpy(p.X).double()[:, None] - torch.from_numpy(p.Y).double()[None]) ** 2).sum(2) / p.lam)
+    want = -p.lam * torch.exp(log_u.cpu()[:, None] + log_v.cpu()[None]) * K
+    got = gsp.cpu().double().reshape(want.shape)
+    # scalings in single precision (their logs to 6e-8 of up to about 10) and one rounding of the product
+    assert float((got - want).abs().max()) <= 4e-6 * float(want.abs().max())
+    lcn.lcn_destroy(h)
+
+
+@pytest.mark.parametrize("total,d", [(1, 1), (255, 31), (256, 32), (257, 33), (1000, 100)])
+def test_deletion_costs_sizes(total, d):
+    import torch
+    import paper_2107_06876_amd as lcn
+    rng = np.random.default_rng(total + d)
+    X, alpha = rng.standard_normal((total, d)).astype(np.float32), rng.random(d).astype(np.float32)
+    got = lcn.lcn_deletion_costs(torch.from_numpy(X).cuda(), torch.from_numpy(alpha).cuda()).cpu().numpy()
+    np.testing.assert_array_equal(got, oracle.deletion_costs(X, alpha))
+
+
+def test_many_batches_at_once():
+    """More batch handles alive than pinned blocks are kept, given back in another order, from several threads and
+    streams: each keeps its own results."""
+    import threading
+    import torch
+    import paper_2107_06876_amd as lcn
+    rng = np.random.default_rng(3)
+
+    def batch(pairs, seed):
+        r = np.random.default_rng(seed)
+        x_off = np.concatenate([[0], np.cumsum(r.integers(5, 40, pairs))]).astype(np.int64)
+        y_off = np.concatenate([[0], np.cumsum(r.integers(5, 40, pairs))]).astype(np.int64)
+        X = torch.from_numpy(r.standard_normal((x_off[-1], 8)).astype(np.float32)).cuda()
+        Y = torch.from_numpy(r.standard_normal((y_off[-1], 8)).astype(np.float32)).cuda()
+        return X, Y, x_off, y_off, np.full(pairs, 2.0, dtype=np.float32)
+
+    def solve(args, stream=None):
+        h = lcn.lcn_build_batched(*args, lcn.COST_SQEUCLID, lcn.MODE_DENSE, stream=stream)
+        lcn.sinkhorn_run(h, 20)
+        return h
+
+    problems = [batch(int(rng.integers(1, 50)) if i else 9000, 100 + i) for i in range(12)]
+    want = []
+    for args in problems:
+        h = solve(args)
+        want.append(lcn.lcn_batched_results(h))
+        lcn.lcn_destroy(h)
+    handles = [solve(args) for args in problems]
+    for i in rng.permutation(len(problems)):
+        got = lcn.lcn_batched_results(handles[i])
+        np.testing.assert_array_equal(got[0], want[i][0])
+        np.testing.assert_array_equal(got[1], want[i][1])
+        lcn.lcn_destroy(handles[i])
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(mine):
+        s = torch.cuda.Stream()
+        for i in mine:
+            h = solve(problems[i], stream=s.cuda_stream)
+            got = lcn.lcn_batched_results(h)
+            if not (np.array_equal(got[0], want[i][0]) and np.array_equal(got[1], want[i][1])):
+                wrong.append(i)
+            lcn.lcn_destroy(h)
+
+    threads = [threading.Thread(target=work, args=([i for i in range(12) if i % 4 == t],)) for t in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
