@@ -1230,7 +1230,7 @@ lcn_status lcn_plan_rows(lcn_handle hh, int64_t i0, int64_t nrows, float *out_de
     if (nrows == 0) return LCN_OK;
     if (h.l > 0)
         HIPCHK(launch_plan_nystrom(h, i0, nrows, out_dev, h.stream));
-    else
+    else if (h.mode != LCN_MODE_DENSE)   // (a dense plan's entries are all written below)
         HIPCHK(hipMemsetAsync(out_dev, 0, sizeof(float) * (size_t)nrows * (size_t)h.m, h.stream));
     if (h.R > 0) HIPCHK(launch_plan_sparse(h, i0, nrows, out_dev, h.stream));
     HIPCHK(hipStreamSynchronize(h.stream));

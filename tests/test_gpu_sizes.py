@@ -185,3 +185,31 @@ def test_many_batches_at_once():
     for t in threads:
         t.join()
     assert not wrong
+
+
+@pytest.mark.parametrize("n,m,blocks", [
+    (7, 1, [(0, 7)]), (5, 63, [(4, 1), (0, 3)]), (9, 1023, [(0, 9), (1, 5)]), (17, 1024, [(0, 16), (13, 4)]),
+    (18, 1025, [(0, 18), (16, 2)]), (33, 2049, [(0, 33), (3, 17)]), (1, 5000, [(0, 1)]),
+])
+def test_dense_plan_blocks(n, m, blocks):
+    """Four rows and 1024 columns per wavefront: every entry of a block is written, none beside it.  Against the stored
+    kernel: the logs of the scalings come rounded to single precision, and so do the kernel's and the plan's values."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    from parity import gpu_build
+    p = _cut(n, m, 3, 0, 0, 0, 4)
+    p.a[0] = 0.0    # a row without mass
+    h = gpu_build(p, "dense")
+    lcn.sinkhorn_run(h, 4)
+    lu, lv = (x.double() for x in lcn.lcn_get_scalings(h))
+    K = lcn.lcn_get_csr(h)[2].double().reshape(n, m)
+    t = lu[:, None] + lv[None, :]
+    want = K * torch.exp(t)
+    bound = want * 2.0 ** -24 * (2 + 1.01 * torch.nan_to_num(lu[:, None].abs() + lv[None, :].abs(), posinf=0.0)) + 1e-37
+    for i0, rows in blocks:
+        room = torch.full((rows * m + 64,), -7.0, device=h.device)
+        lcn.lcn_plan_rows(h, i0, rows, out=room[:rows * m].view(rows, m))
+        got = room[:rows * m].view(rows, m).double()
+        assert bool((room[rows * m:] == -7.0).all())
+        assert bool(((got - want[i0:i0 + rows]).abs() <= bound[i0:i0 + rows]).all()), (i0, rows)
+    lcn.lcn_destroy(h)
