@@ -4,10 +4,13 @@
 namespace lcn {
 
 // Factor rows of more than 256 entries: a row per wavefront at a time, the next row's factor entries and first record
-// entries requested before the current row is reduced.  Two rows at a time leave no registers for that: 200 000 rows of
-// 512 entries 109 us per sweep instead of 106 (four rows spill), and the record walked flat 111.
+// entries requested before the current row is reduced.  The loop's body stands there twice, the two sets of registers in
+// exchanged roles: where the requested set is copied to the current one at a row's end, the compiler waits for it there.
+// 200 000 rows of 512 entries, 19 stored values: 101.4 us per sweep, 111 with the copy, 105 with the copy and a round's
+// segment after the other instead of the record walked flat; two rows at a time leave no registers for the next ones
+// (109, four rows spill).  What bounds it is memory: the factor rows alone, 410 MB, take 82 us at 5 TB/s.
 // The copies of the scalings, the masked lanes and the zero slot are as in pass_kernel.
-template <int T, int RR, int MODE, bool FUSED>
+template <int T, int RR, int V, int MODE, bool FUSED>
 __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int R, int lp, double *partial,
                                                                  unsigned long long *counters, FuseArgs Fz)
 {
@@ -50,7 +53,7 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
     // those loads are in flight.
     struct RowData {
         FRow<T> f;
-        float tv, vv;
+        float tv[V], vv[V];
     };
     const float *__restrict__ perm_in = reinterpret_cast<const float *>(S.perm_in);
     float *__restrict__ perm_out = reinterpret_cast<float *>(S.perm_out);
@@ -59,8 +62,11 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
         D.f.load(S.F, r, lp, lane);
         if (MODE != PASS_INIT) {
             const float *__restrict__ vals = S.vals + M.base;
-            D.tv = vals[lane];
-            D.vv = perm_in[gather_place<RR>(M.walk, lane, zero_slot)];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                D.tv[v] = vals[64 * v + lane];
+                D.vv[v] = perm_in[gather_place<RR>(M.walk, 64 * v + lane, zero_slot)];
+            }
         }
     };
     RowData cur{}, nxt{};
@@ -100,8 +106,10 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
         } else {
             double acc = 0.0;
             const int total = mc.walk.end[RR - 1];
-            acc = fma((double)(lane < total ? C.tv : 0.f), (double)C.vv, acc);
-            for (int e0 = 64; e0 < total; e0 += 256) {   // all eight loads of a trip before the first use
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                acc = fma((double)(64 * v + lane < total ? C.tv[v] : 0.f), (double)C.vv[v], acc);
+            for (int e0 = 64 * V; e0 < total; e0 += 256) {   // all eight loads of a trip before the first use
                 const float *__restrict__ vals = S.vals + mc.base;
                 float tt[4], pp[4];
 #pragma unroll
@@ -168,20 +176,34 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
     }
 }
 
-template <int T, int RR>
-static void launch_long_rounds(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
+template <int T, int RR, int V>
+static void launch_long_mode(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
                                double *partial, unsigned long long *cnt, hipStream_t s)
 {
     const dim3 grid(groups), block(PASS_THREADS);
     const size_t lds = pass_lds_bytes(h.lp, fused_in);
     if (mode == PASS_UPDATE && fused_in)
-        hipLaunchKernelGGL((long_pass_kernel<T, RR, PASS_UPDATE, true>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
+        hipLaunchKernelGGL((long_pass_kernel<T, RR, V, PASS_UPDATE, true>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else if (mode == PASS_UPDATE)
-        hipLaunchKernelGGL((long_pass_kernel<T, RR, PASS_UPDATE, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
+        hipLaunchKernelGGL((long_pass_kernel<T, RR, V, PASS_UPDATE, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else if (mode == PASS_QUERY)
-        hipLaunchKernelGGL((long_pass_kernel<T, RR, PASS_QUERY, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
+        hipLaunchKernelGGL((long_pass_kernel<T, RR, 1, PASS_QUERY, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else
-        hipLaunchKernelGGL((long_pass_kernel<T, 1, PASS_INIT, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
+        hipLaunchKernelGGL((long_pass_kernel<T, 1, 1, PASS_INIT, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
+}
+
+// Entries of a record requested with its row: a wavefront of them where records are short (200 000 rows of 512 factor
+// entries and 19 stored values on average: 101.8 us per sweep, 103.2 with two, 104.9 with three; 100 000 rows of 36:
+// 58.3, 59.1, 59.8), else three (200 000 rows of 120: 133.3 with one, 129.5 with two, 129.0 with three).  The bits are the
+// same, as in sweep.h.
+template <int T, int RR>
+static void launch_long_rounds(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
+                               double *partial, unsigned long long *cnt, hipStream_t s)
+{
+    if (h.nnz_stored <= 64 * S.rows)
+        launch_long_mode<T, RR, 1>(S, h, mode, F, fused_in, groups, partial, cnt, s);
+    else
+        launch_long_mode<T, RR, 3>(S, h, mode, F, fused_in, groups, partial, cnt, s);
 }
 
 template <int T>

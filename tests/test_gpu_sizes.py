@@ -37,6 +37,7 @@ def _cut(n, m, d, landmarks, buckets, rounds, iters, kmeans_iters=2, seed=11):
     (24577, 12300, 20, 400, 2),   # three, unequal sides
     (13000, 12999, 40, 120, 1),   # five, long records
     (5000, 5001, 300, 200, 1),    # more than 256 columns
+    (5000, 5001, 300, 20, 2),     # the same with long records: three wavefronts of entries requested with a row
 ])
 def test_rows_per_wavefront(n, m, landmarks, buckets, rounds):
     from parity import compare
