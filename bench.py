@@ -69,7 +69,7 @@ def counter_traffic(config: int):
     for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "lcn_sinkhorn_c%d_*.md" % config))):
         for line in open(path):
             cells = [c.strip() for c in line.split("|")]
-            if len(cells) > 6 and re.match(r"`pass_kernel<.*true>`", cells[1]):
+            if len(cells) > 6 and re.match(r"`(long_)?pass_kernel<.*true>`", cells[1]):
                 try:
                     return (float(cells[5]) + float(cells[6])) * 1e6
                 except ValueError:

@@ -711,7 +711,7 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
 // What bounds it is one wavefront's instruction stream: about 170 vector instructions per
 // half-iteration, 64 of them the product itself (the version before it, a row and a column per lane with
 // the vector passed round by lane reads, needed 330).  50 iterations of 4096 pairs with deletion rows:
-// 188 us for the call instead of 481; of 16 pairs: 79 instead of 134.
+// 157 us, of 16 pairs 47.
 //
 // The entries of u = [u^ (n); u~ (m)] and v = [v^ (m); v~ (n)] (point part; deletion part, Sec. 6) live
 // where the products leave them: u^_i and v~_i in the lane of row i, v^_j and u~_j in the lane of column j.
@@ -1114,10 +1114,9 @@ static hipError_t launch_batched_build_as(const BatchHandle &h)
 }
 
 // Eight wavefronts instead of four per pair: where a compute unit has at most two pairs and the pairs more
-// than the four tiles of points that four wavefronts hold (call with its copies, d = 32, 16 to 64 points per
-// side: 64 pairs 96 against 109 us, 512 pairs 118 against 127, 768 pairs 150 against 149, 1024 pairs 167
-// against 153; 10 to 30 points: 512 pairs 84 against 83), and for more than 32 dimensions, where four
-// wavefronts have too few registers for their points (1024 pairs, d = 64: 238 against 280).
+// than the four tiles of points that four wavefronts hold (what a call takes less, d = 32, 16 to 64 points per
+// side: 64 pairs 13 us, 512 pairs 9, 768 pairs -1, 1024 pairs -14; 10 to 30 points: 512 pairs -1), and for more
+// than 32 dimensions, where four wavefronts have too few registers for their points (1024 pairs, d = 64: 42 us).
 static hipError_t launch_batched_build(const BatchHandle &h)
 {
     const BatchDev &D = h.dev;

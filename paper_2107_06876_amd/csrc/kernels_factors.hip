@@ -134,16 +134,11 @@ __device__ inline void store_rows4(float (*dst)[LDK], const float (&v)[8])
 }
 
 // acc += P_chunk Q_chunk^T for the KCH staged features (dot products; the staged values are fp32,
-// products and sums fp64).  Only the first `rows` rows and `cols` columns of the tile hold points:
-// an instruction tile of 16 x 16 that lies wholly outside is skipped (its accumulators stay zero).
-__device__ inline void tile_mma(TileAcc &acc, const float (*Ps)[LDK], const float (*Cs)[LDK], int rows = TILE,
-                                int cols = TILE)
+// products and sums fp64).
+__device__ inline void tile_mma(TileAcc &acc, const float (*Ps)[LDK], const float (*Cs)[LDK])
 {
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int rw = 32 * (w >> 1), cw = 32 * (w & 1);
-    const int r0 = rw + (l & 15), c0 = cw + (l & 15), kq = l >> 4;
-    const bool ra = rw < rows, rb = rw + 16 < rows, ca = cw < cols, cb = cw + 16 < cols;   // wave-uniform
-    if (!ra || !ca) return;
+    const int r0 = 32 * (w >> 1) + (l & 15), c0 = 32 * (w & 1) + (l & 15), kq = l >> 4;
     // Lane quarter kq feeds features 8 kq .. 8 kq + 7 of the chunk, one per instruction (the order
     // in which a dot product's terms are added is free): eight consecutive floats per operand row.
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -151,17 +146,17 @@ __device__ inline void tile_mma(TileAcc &acc, const float (*Ps)[LDK], const floa
         const f4 lo = *(const f4 *)&M[r][8 * kq], hi = *(const f4 *)&M[r][8 * kq + 4];
         o[0] = lo.x, o[1] = lo.y, o[2] = lo.z, o[3] = lo.w, o[4] = hi.x, o[5] = hi.y, o[6] = hi.z, o[7] = hi.w;
     };
-    float a0[8], b0[8], a1[8] = {}, b1[8] = {};
+    float a0[8], b0[8], a1[8], b1[8];
     row8(Ps, r0, a0);
     row8(Cs, c0, b0);
-    if (rb) row8(Ps, r0 + 16, a1);
-    if (cb) row8(Cs, c0 + 16, b1);
+    row8(Ps, r0 + 16, a1);
+    row8(Cs, c0 + 16, b1);
 #pragma unroll
     for (int ks = 0; ks < KCH / 4; ++ks) {
         acc.t[0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a0[ks], (double)b0[ks], acc.t[0], 0, 0, 0);
-        if (cb) acc.t[1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a0[ks], (double)b1[ks], acc.t[1], 0, 0, 0);
-        if (rb) acc.t[2] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a1[ks], (double)b0[ks], acc.t[2], 0, 0, 0);
-        if (rb && cb) acc.t[3] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a1[ks], (double)b1[ks], acc.t[3], 0, 0, 0);
+        acc.t[1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a0[ks], (double)b1[ks], acc.t[1], 0, 0, 0);
+        acc.t[2] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a1[ks], (double)b0[ks], acc.t[2], 0, 0, 0);
+        acc.t[3] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a1[ks], (double)b1[ks], acc.t[3], 0, 0, 0);
     }
 }
 

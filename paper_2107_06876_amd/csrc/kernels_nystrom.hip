@@ -2,7 +2,7 @@
 //     s_i = F_i . acc_in,   out_i = marg_i / s_i,   acc_out = F^T out
 // with F = U, acc_in = y = W v, acc_out = z = U^T u for the rows of X and F = W^T, acc_in = z, acc_out = y
 // for the rows of Y.  State, exponents and hand-over of the totals as in the sweep with a sparse part
-// (kernels_iter.hip); what differs is how rows are dealt out.
+// (sweep.h); what differs is how rows are dealt out.
 //
 // One wavefront owns RG consecutive rows at a time: their factor rows are one contiguous piece of memory and are
 // requested together, the RG partial sums go through the cross-lane reduction together (recursive halving:
@@ -10,7 +10,7 @@
 // logarithm, stores -- is done for the RG rows at once, a row per group of lanes.  With a row at a time a short
 // factor row (64 entries: one load) costs over a hundred instructions and a trip to memory of its own;
 // what bounds the sweep now is the launch, the hand-over and one trip to memory.  50 000 rows of 64
-// entries: 22.9 -> 9.2 us per sweep.  (For rows with a sparse part the same dealing is slower, 28 against
+// entries: 22.9 -> 8.4 us per sweep.  (For rows with a sparse part the same dealing is slower, 28 against
 // 23 us at 470 stored values per row: there the wavefronts are needed to hide the walk over the records.)
 #include "iter_common.h"
 
