@@ -87,10 +87,9 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             };
             auto sum_lanes = [&](double v) { return G == 32 ? half_sum(v) : row_sum(v); };
             // The row's log-sum-exp.  First with the row's previous value as the shift (near the answer, so the
-            // terms are of order one): one subtraction, one single-precision exp and one addition per entry.  Four
-            // terms of a long row are added in single precision, all else in double: a lane has up to four times the
-            // entries it would have if a wavefront shared the row (from trip to trip in single precision, 510 entries
-            // per row, 200 iterations: the scalings' logs were off by 6.9e-6 against 3.4e-6, root mean square).  If that
+            // terms are of order one): one subtraction, one single-precision exp and one addition in double per entry (a
+            // lane has up to four times the entries it would have if a wavefront shared the row: added in single precision,
+            // 510 entries per row, 200 iterations, the scalings' logs were off by 6.9e-6, root mean square).  If that
             // shift is unusable (no previous value, or the sum leaves single precision's range) the row is walked again
             // with a running maximum per lane, which cannot over- or underflow.
             const double shift = log_marg - prev;
@@ -99,15 +98,9 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             if (shift > -INFINITY && shift < INFINITY) {   // the same in every lane of the row
                 double acc = 0.0;
                 walk([&](const float (&k)[U], const double (&p)[U], const bool (&in)[U]) {
-                    float t[U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) t[u] = in[u] ? __expf(k[u] + (float)(p[u] - shift)) : 0.f;
-                    if constexpr (U == 4) {
-                        acc += (double)((t[0] + t[1]) + (t[2] + t[3]));
-                    } else {
-#pragma unroll
-                        for (int u = 0; u < U; ++u) acc += (double)t[u];
-                    }
+                    for (int u = 0; u < U; ++u)
+                        acc += in[u] ? (double)__expf(k[u] + (float)(p[u] - shift)) : 0.0;
                 });
                 const double tot = sum_lanes(acc);
                 if (tot > 1e-30 && tot < 1e30) {
@@ -500,7 +493,7 @@ static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int
 
 // Lanes per row by the length of the records: 10 000 rows of 20 stored values 3.6 us per sweep with sixteen lanes
 // and two entries each at a time (a wavefront with four: 6.1; a wavefront per row and a 1024-thread workgroup working
-// through its rows, loads unrolled over four rounds: 6.4); 20 000 rows of 510 values in three rounds 14.8 us with 32
+// through its rows, loads unrolled over four rounds: 6.4); 20 000 rows of 510 values in three rounds 15.2 us with 32
 // lanes and four entries each, 16.3 with sixteen and two, 15.5 with 64 and four (19.6 before).
 template <int RR>
 static int launch_logpass_length(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
