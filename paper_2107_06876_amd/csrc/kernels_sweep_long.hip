@@ -14,6 +14,8 @@ template <int T, int RR, int V, int MODE, bool FUSED>
 __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int R, int lp, double *partial,
                                                                  unsigned long long *counters, FuseArgs Fz)
 {
+    constexpr int TRIP = LONG_TRIP;
+    static_assert(64 * TRIP <= VALUE_SLACK && 64 * V <= VALUE_SLACK, "read past the last record");
     extern __shared__ double zsh[];  // [PASS_WAVES / 2][lp + 3], then [lp + 2] and [16][64] if FUSED
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -109,18 +111,18 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
 #pragma unroll
             for (int v = 0; v < V; ++v)
                 acc = fma((double)(64 * v + lane < total ? C.tv[v] : 0.f), (double)C.vv[v], acc);
-            for (int e0 = 64 * V; e0 < total; e0 += 256) {   // all eight loads of a trip before the first use
+            for (int e0 = 64 * V; e0 < total; e0 += 64 * TRIP) {   // all loads of a trip before the first use
                 const float *__restrict__ vals = S.vals + mc.base;
-                float tt[4], pp[4];
+                float tt[TRIP], pp[TRIP];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
+                for (int k = 0; k < TRIP; ++k) {
                     const int e = e0 + 64 * k + lane;
                     tt[k] = vals[(unsigned)e];
                     pp[k] = perm_in[gather_place<RR>(mc.walk, e, zero_slot)];
                     if (e >= total) tt[k] = 0.f;
                 }
 #pragma unroll
-                for (int k = 0; k < 4; ++k) acc = fma((double)tt[k], (double)pp[k], acc);
+                for (int k = 0; k < TRIP; ++k) acc = fma((double)tt[k], (double)pp[k], acc);
             }
             acc *= PERM_UNSCALE;
 #pragma unroll

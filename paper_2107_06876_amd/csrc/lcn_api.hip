@@ -838,7 +838,7 @@ struct Builder {
         h.undecided = last_nflagged;
         h.ntiles = h.R > 0 ? (int)report[REPORT_TOTALS + 1] : 0;
 
-        // slack: a sweep reads whole wavefront-wide chunks, up to four at a time, and masks the excess
+        // slack: a sweep reads whole wavefront-wide chunks, several at a time, and masks the excess (record_reach.h)
         h.vals_x = bump.take<float>((size_t)h.nnz_stored + VALUE_SLACK);
         h.vals_y = bump.take<float>((size_t)h.nnz_stored + VALUE_SLACK);
         h.ws_used = bump.used;

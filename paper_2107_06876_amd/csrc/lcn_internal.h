@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "lcn.h"
+#include "record_reach.h"
 
 namespace lcn {
 
@@ -46,8 +47,6 @@ struct BackwardArgs {
     double lambda = 0.0;
     float *rec_sp = nullptr, *rec_nys = nullptr;      // outputs, layout of the row records of X
 };
-
-constexpr int VALUE_SLACK = 256;   // floats behind the stored values that a sweep may read
 
 struct Handle;
 

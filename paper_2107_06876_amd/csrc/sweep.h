@@ -37,14 +37,15 @@ namespace lcn {
 // A row's record is walked flat: its values of all rounds lie back to back, so 64 consecutive entries are one
 // load whatever the rounds' lengths, and the entry's place in the gathered vector is its number plus an offset
 // that changes where a round's segment ends (uniform comparisons).  V: entries of a row requested with it, in
-// wavefronts; the rest of a longer record follows in trips of 4 V.
+// wavefronts; the rest of a longer record follows in trips of SWEEP_TRIP wavefronts.
 template <int T, int RR, int RG, int V, int MODE, bool FUSED>
 __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, int lp, double *partial,
                                                             unsigned long long *counters, FuseArgs Fz)
 {
     constexpr int NV = RG <= 4 ? 4 : 8;
     constexpr int GL = 64 / NV;      // lanes per row once the sums are taken (at least 8: one per hash round)
-    constexpr int TRIP = T <= 4 ? 6 : 4;   // chunks of a long record per trip
+    constexpr int TRIP = SWEEP_TRIP;
+    static_assert(64 * TRIP <= VALUE_SLACK && 64 * V <= VALUE_SLACK, "read past the last record");
     extern __shared__ double zsh[];  // [PASS_WAVES / 2][lp + 3], then [lp + 2] and the reduction's scratch if FUSED
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, i
     float *__restrict__ perm_out = reinterpret_cast<float *>(S.perm_out);
     // Loads are issued for whole wavefront-wide chunks without predication: lanes
     // beyond a record's length read the next stored values (masked when used; the
-    // arrays end with VALUE_SLACK entries) and the zero slot behind the gathered vector.
+    // arrays end with VALUE_SLACK entries, see record_reach.h) and the zero slot behind the gathered vector.
     const unsigned zero_slot = (unsigned)(R * S.rows_in);
     RecordWalk<RR> walk[RG];   // of the group at hand (scalars)
     long long base = 0;        // where the records of the group begin: they lie back to back
