@@ -762,7 +762,7 @@ hipError_t launch_combine_hash(int32_t *acc, const int32_t *h, int b, int first,
 // Member sums in 2^-32 fixed point: integer addition is associative, so the
 // sums are the same in any order.  Two ways to them:
 //
-// kmeans_by_members (few clusters times points): a workgroup takes ONE cluster and a range of at most 8192 points, reads
+// By members (few clusters times points): a workgroup takes ONE cluster and a range of at most 8192 points, reads
 // that range's assignments, keeps the indices of its members in LDS and adds up their rows.  One range: the new
 // centroid follows in the same launch; several: a second launch adds up the ranges' sums.  Every workgroup of a range
 // reads the same assignments (from the cache, 4 k N bytes in all).
@@ -947,24 +947,29 @@ __global__ __launch_bounds__(64 * WPB) void kmeans_sum_kernel(const float *__res
 // does) whose low mantissa bits are that integer in two's complement, so the bit patterns are added
 // as they are and the constants' share is taken off per member (all modulo 2^64).
 constexpr int KM_RANGE = 8192;   // points a workgroup looks through for its cluster's members
-// Clusters times points up to which every cluster's workgroups look through the assignments themselves: 268 MB of reads
-// from the cache, about what counting and scattering take.
+// Clusters times points up to which every cluster's workgroups look through the assignments themselves.  The clusters are
+// those of all runs of a build: its runs look through their assignments at the same time, from the same caches.
+// Build times, by members / counting and scattering (us), by millions of clusters times points: 24 (40 000 points, a run of 510
+// clusters and one of 200) 1870 / 1940, 46 (40 000, two of 512 and 128) 2120 / 2200, 44 (60 000, two of 270 and 200) 2050 / 2110,
+// 49 (60 000, 760 and 64) 1490 / 1530; 101 (60 000, two of 780 and 128) 3140 / 2930, 107 (100 000, three of 270 and 256)
+// 5000 / 4800, 128 (80 000, four of 400) 3930 / 3520.
 constexpr long long KM_MEMBERS_WORK = 1ll << 26;
 
 static int kmeans_ranges(long long N) { return (int)((N + KM_RANGE - 1) / KM_RANGE); }
 
-bool kmeans_by_members(long long N, int k, int d) { return d <= 512 && (long long)k * N <= KM_MEMBERS_WORK; }
+bool kmeans_by_members(long long N, long long clusters, int d) { return d <= 512 && clusters * N <= KM_MEMBERS_WORK; }
 
 int kmeans_sum_chunk(long long N) { return N <= 65536 ? 16 : N <= 131072 ? 32 : N <= 262144 ? 64 : 128; }
 
-size_t kmeans_partial_elems(long long N, int kmax, int d)
+size_t kmeans_partial_elems(long long N, int kmax, int d, bool by_members)
 {
     if (d > 512) return 1;   // wider rows take the sliced kernel, which needs none
+    if (by_members) {   // (kmax may be the buckets of a hash that is not k-means)
+        const long long k = KM_MEMBERS_WORK / N < kmax ? KM_MEMBERS_WORK / N : kmax;
+        return (size_t)k * (size_t)kmeans_ranges(N) * (size_t)d;
+    }
     const int M = kmeans_sum_chunk(N);
-    // (any number of clusters up to kmax, by whichever way that number takes)
-    const long long k = KM_MEMBERS_WORK / N < kmax ? KM_MEMBERS_WORK / N : kmax;
-    const size_t sorted = (size_t)((N + M - 1) / M + kmax), members = (size_t)k * (size_t)kmeans_ranges(N);
-    return (members > sorted ? members : sorted) * (size_t)d;
+    return (size_t)((N + M - 1) / M + kmax) * (size_t)d;
 }
 
 constexpr unsigned long long FIX_MAGIC_BITS = 0x4338000000000000ull;   // 1.5 * 2^52
@@ -1281,7 +1286,7 @@ hipError_t launch_kmeans_update(const float *Z, long long N, int d, const KmRuns
     const int ns = (d + 63) / 64;
     int k = 0;
     for (int q = 0; q < runs.count; ++q) k = runs.run[q].k > k ? runs.run[q].k : k;
-    if (kmeans_by_members(N, k, d)) {
+    if (runs.by_members) {
         switch (ns) {
             case 1: launch_members<1>(Z, N, d, runs, k, s); break;
             case 2: launch_members<2>(Z, N, d, runs, k, s); break;

@@ -64,7 +64,6 @@ std::vector<long long> seeded_indices(uint64_t seed, long long N, int k)
 
 bool uses_landmarks(int mode) { return mode == LCN_MODE_NYSTROM || mode == LCN_MODE_LCN; }
 bool uses_lsh(int mode) { return mode == LCN_MODE_SPARSE || mode == LCN_MODE_LCN; }
-constexpr long long KM_MERGE_POINTS = 1ll << 17;
 
 constexpr int REPORT_FAIL = 16, REPORT_TOTALS = 18, REPORT_WORDS = 24;   // 64-bit words behind h.counters
 
@@ -125,7 +124,7 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
         km.nflagged = bump.take<int>(4);
         km.order = bump.take<int>((size_t)N);
         km.offs = bump.take<int>((size_t)kmax);
-        km.part = bump.take<long long>(kmeans_partial_elems(N, kmax, h.d));
+        km.part = bump.take<long long>(kmeans_partial_elems(N, kmax, h.d, h.by_members));
         km.assign = bump.take<int32_t>((size_t)N);
         km.cn = bump.take<float>((size_t)kmax);
         km.ct = bump.take<char>(2 * split_plane_bytes(kmax, h.d));
@@ -250,6 +249,32 @@ lcn_status check_params(long long n, long long m, int d, int dtype, float lambda
     return LCN_OK;
 }
 
+// Flat k-means runs (landmarks, one per hash round) that advance together, a launch for all of them: how many, or 0 where
+// each goes on a lane of its own (see Builder).  Together means a third of the launches, which is what bounds the
+// smallest builds; on their own the runs fill the chip beside each other and the factors start when the landmarks are there,
+// not when the last hash round is.  So together up to 2^14 points, where a launch of one run leaves half of the compute units
+// without a workgroup, and only where the factors are short: up to 64 landmarks the inverse is a single block.  How far that
+// holds depends on the scores of an iteration (points x padded dimensions x clusters of all runs); with more points it
+// pays only for two runs of very few scores.  Build times in us, together / on their own (points, dimensions, landmarks +
+// rounds x buckets):
+//   2048, 16, 64 + 16: 400 / 470                10 000, 100, 2 x 100: 512 / 598       16 200, 24, 2 x 350: 618 / 649
+//   10 000, 300, 64 + 2 x 130: 894 / 941        13 000, 300, 2 x 300: 1010 / 1075     16 000, 200, 3 x 300: 1048 / 1055
+//   13 000, 300, 64 + 2 x 200: 1002 / 975       16 000, 300, 4 x 400: 1650 / 1625     16 000, 200, 64 + 2 x 230: 890 / 855
+//   30 000, 32, 64 + 100: 600 / 631             60 000, 16, 50 + 100: 785 / 812       60 000, 64, 64 + 100: 898 / 856
+//   20 000, 16, 2 x 430: 718 / 680              40 000, 16, 64 + 2 x 100: 784 / 763   60 000, 50, 64 + 2 x 100: 1128 / 1040
+//   6000, 16, 128 + 32: 574 / 527               40 000, 300, 128 + 2 x 512: 2400 / 2110
+constexpr long long KM_MERGE_POINTS = 1ll << 14;
+int merged_runs(const Handle &h, long long clusters)
+{
+    const bool kmeans_hash = h.hash == LCN_HASH_KMEANS;
+    const int runs = (h.l > 0 ? 1 : 0) + (kmeans_hash ? h.R : 0);
+    if (runs == 0 || (kmeans_hash && h.hier_levels > 1)) return 0;
+    if (runs == 1) return 1;   // nothing goes beside it: no thread and no lane but the first
+    const long long N = h.n + h.m, scores = N * ((h.d + 15) / 16 * 16) * clusters;
+    const long long most = N <= KM_MERGE_POINTS ? (h.l > 0 ? 1ll << 30 : 3ll << 30) : runs == 2 && h.l > 0 ? 1ll << 28 : 0;
+    return h.by_members && h.l <= 64 && scores <= most ? runs : 0;
+}
+
 void fill_shape(Handle &h, long long n, long long m, int d, int mode, const lcn_landmark_params *lm,
                 const lcn_lsh_params *lsh)
 {
@@ -281,13 +306,9 @@ void fill_shape(Handle &h, long long n, long long m, int d, int mode, const lcn_
         h.b = 1;
         h.hash = -1;
     }
-    // Flat k-means runs (landmarks, one per hash round) advance together, a launch for all of them, where the points
-    // are few enough for that to be the faster way; see Builder.
-    const int hashing = h.hash == LCN_HASH_KMEANS && h.hier_levels <= 1 ? h.R : 0;
-    const int most = h.l > h.b ? h.l : h.b;
-    const bool merge = n + m <= KM_MERGE_POINTS && kmeans_by_members(n + m, most, d) && (h.l > 0 || hashing > 0) &&
-                       (h.hash != LCN_HASH_KMEANS || h.hier_levels <= 1);
-    h.merged_runs = merge ? (h.l > 0 ? 1 : 0) + hashing : 0;
+    const long long clusters = h.l + (h.hash == LCN_HASH_KMEANS ? (long long)h.R * h.b : 0);
+    h.by_members = kmeans_by_members(n + m, clusters, d);
+    h.merged_runs = merged_runs(h, clusters);
 }
 
 #define HIPCHK(expr)                         \
@@ -346,11 +367,12 @@ lcn_status kmeans_init(Handle &h, KmScratch &km, hipStream_t s, KmRun &r, uint64
     return LCN_OK;
 }
 
-// T[q] Lloyd iterations of every run, all of them together (more than one: kmeans_by_members() holds for each):
+// T[q] Lloyd iterations of every run, all of them together (more than one: the update is by members):
 // centroids into cent, the last iteration's assignment into assign (untouched if T[q] == 0).
 lcn_status run_kmeans(Handle &h, Scratch &sc, hipStream_t s, const KmRuns &all, const int *T)
 {
     const long long N = h.n + h.m;
+    const bool sorted = !all.by_members;
     KmRuns start{};
     int most = 0;
     for (int q = 0; q < all.count; ++q) {
@@ -362,12 +384,13 @@ lcn_status run_kmeans(Handle &h, Scratch &sc, hipStream_t s, const KmRuns &all, 
             if (r.pick) HIPCHK(launch_gather_rows(h.Z, h.d, r.pick, r.k, r.cent, s));
             HIPCHK(hipMemsetAsync(r.nflagged, 0, 2 * sizeof(int), s));
         }
-        if (T[q] > 0 && !kmeans_by_members(N, r.k, h.d))   // member counts and cursors lie side by side
+        if (T[q] > 0 && sorted)   // member counts and cursors lie side by side
             HIPCHK(hipMemsetAsync(r.counts2, 0, (size_t)((char *)r.nflagged - (char *)r.counts2), s));
     }
     if (start.count > 0) HIPCHK(launch_kmeans_start(h.Z, h.d, start, s));
     for (int it = 0; it < most; ++it) {
         KmRuns now{};   // those that are not done yet
+        now.by_members = all.by_members;
         for (int q = 0; q < all.count; ++q)
             if (it < T[q]) {
                 now.run[now.count] = all.run[q];
@@ -392,6 +415,7 @@ lcn_status run_one_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s, 
 {
     KmRuns runs{};
     runs.count = 1;
+    runs.by_members = h.by_members;
     runs.run[0] = kmeans_run(h, km, k, cent, assign);
     const lcn_status st = kmeans_init(h, km, s, runs.run[0], seed, start_dev, init, given);
     return st == LCN_OK ? run_kmeans(h, sc, s, runs, &T) : st;
@@ -454,6 +478,7 @@ lcn_status run_hier_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s,
         HIPCHK(hipMemsetAsync(km.cursor2, 0, 2 * sizeof(int) * (size_t)k, s));
         KmRuns runs{};
         runs.count = 1;
+        runs.by_members = h.by_members;
         runs.run[0] = kmeans_run(h, km, (int)k, km.cent, dst);
         runs.run[0].first = nullptr;
         runs.run[0].keep_counts = 1;
@@ -540,12 +565,11 @@ bool lane_streams(hipStream_t (&out)[KM_LANES])
 // that may still be in flight), then lets the members go.
 //
 // The k-means runs of a build (landmarks, one per hash round) are independent chains of short launches, and the host
-// needs about as long to enqueue such a launch as the device to execute it.  Up to KM_MERGE_POINTS points all flat runs
-// therefore advance together, a launch for all of them, on a stream of the library's own, and the factors go on from
-// there beside the bucket sort.  Above that (and for hierarchical runs), where a launch of one run fills the chip,
-// each run has scratch of its own and one of KM_LANES streams ("lanes": forked from and joined into the caller's stream by
-// events), and the hash rounds of a lane are enqueued by a host thread of their own while the calling thread
-// enqueues the landmarks and the factors.
+// needs about as long to enqueue such a launch as the device to execute it.  In the smallest builds all flat runs
+// therefore advance together (merged_runs()), a launch for all of them, on a stream of the library's own, and the factors
+// go on from there beside the bucket sort.  Otherwise each run has scratch of its own and one of KM_LANES
+// streams ("lanes": forked from and joined into the caller's stream by events), and the hash rounds of a lane are enqueued by
+// a host thread of their own while the calling thread enqueues the landmarks and the factors.
 struct Builder {
     Handle &h;
     Bump bump;
@@ -686,6 +710,7 @@ struct Builder {
     lcn_status merged_kmeans()
     {
         KmRuns runs{};
+        runs.by_members = h.by_members;
         int T[KM_MAX_RUNS];
         auto add = [&](int k, float *cent, int32_t *assign) -> KmRun & {
             runs.run[runs.count] = kmeans_run(h, sc.km[runs.count], k, cent, assign);

@@ -97,14 +97,15 @@ struct KmRun {
     int *flagged, *pairs;       // points undecided between more than two centroids; (point, c1, c2) triples
     int *nflagged;              // how many of either
     int keep_counts;            // the update leaves nflagged as it is (else zero for the next assignment)
-    unsigned long long *part;   // partial sums, kmeans_partial_elems(N, k, d) words
+    unsigned long long *part;   // partial sums, kmeans_partial_elems() words
     int *order, *offs;          // [N], [k]: members by cluster, or the ranges' member counts
-    int *counts2, *cursor2;     // [2][k] each, zero before the first update (not used where kmeans_by_members())
+    int *counts2, *cursor2;     // [2][k] each, zero before the first update (not used where the update is by members)
 };
 // Runs that advance together, a launch for all of them.
 constexpr int KM_MAX_RUNS = 9;
 struct KmRuns {
     int count;
+    int by_members;   // how the centroids are updated: kmeans_by_members() of the build
     KmRun run[KM_MAX_RUNS];
 };
 void centroid_planes(KmRun &r, void *Ct, float *cn, int d);
@@ -118,11 +119,12 @@ hipError_t launch_assign_filter(const void *Zt, int zplanes, long long N, int d,
 hipError_t launch_assign_undecided(const float *Z, int d, const KmRuns &runs, hipStream_t s);
 hipError_t launch_assign_crosspolytope(const float *Z, long long N, int d, const float *Rm, int b, int32_t *out,
                                        hipStream_t s);
-// New centroids from the assignments, for runs of which kmeans_by_members() holds, or for a single run.  `parity`
+// New centroids from the assignments; several runs only where the update is by members.  `parity`
 // alternates from update to update.
 hipError_t launch_kmeans_update(const float *Z, long long N, int d, const KmRuns &runs, int parity, hipStream_t s);
-bool kmeans_by_members(long long N, int k, int d);
-size_t kmeans_partial_elems(long long N, int kmax, int d);
+// clusters: of all k-means runs of the build together
+bool kmeans_by_members(long long N, long long clusters, int d);
+size_t kmeans_partial_elems(long long N, int kmax, int d, bool by_members);
 
 struct SortBuffers {
     int R, b;
@@ -206,6 +208,7 @@ struct Handle {
     int in_dtype;              // storage type X and Y were given in
     int hier_levels;           // levels of hierarchical k-means hashing (0 or 1: flat)
     int merged_runs;           // k-means runs that advance together (0: each on its own)
+    int by_members;            // how k-means updates its centroids (kmeans_by_members)
     int and_width;             // hashes per band of cross-polytope hashing (AND construction)
     int log_domain;            // kernel without signed parts (sparse, dense): values and vectors are logs
     double lambda, ridge;

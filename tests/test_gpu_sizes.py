@@ -100,6 +100,21 @@ def test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds
     assert torch.equal(got["0"][0], got["1"][0]) and torch.equal(got["0"][1], got["1"][1])
 
 
+# up to 2^14 points and 64 landmarks together, above either each run on its own, but for two runs of few scores; by
+# members up to 2^26 clusters times points of all runs
+@pytest.mark.parametrize("n,m,d,landmarks,buckets,rounds", [
+    (8192, 8192, 5, 64, 33, 2),      # the most points that advance together
+    (8192, 8192, 5, 65, 33, 2),      # one landmark more
+    (8192, 8193, 5, 64, 33, 2),      # one point more
+    (8192, 8193, 5, 64, 33, 1),      # the same, two runs
+    (8000, 7999, 130, 64, 300, 2),   # few points, many scores
+    (10000, 10000, 3, 1, 1118, 3),   # just below 2^26
+    (10000, 10000, 3, 2, 1118, 3),   # just above: sorted
+])
+def test_runs_together_or_apart(monkeypatch, n, m, d, landmarks, buckets, rounds):
+    test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds)
+
+
 @pytest.mark.parametrize("members", [1, 15, 16, 17, 33, 48, 63, 64, 65, 130])
 def test_pieces_of_a_tile(members):
     """Sparse values and their derivatives where a bucket holds so many points of one side and 20 of the other: pieces
