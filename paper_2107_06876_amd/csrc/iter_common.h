@@ -227,12 +227,32 @@ struct FRow {
     }
 };
 
+// Up to so many hash rounds RR is the number of rounds; ANY_ROUNDS stands for more of them.
+constexpr int EXACT_ROUNDS = 4, ANY_ROUNDS = 8;
+
 // The rounds' segments of a row's record, read from the packed metadata (wave-uniform: scalar registers).
 template <int RR>
 struct RecordWalk {
     unsigned shift[RR];  // entry e of round r stands at place e + shift[r] of the gathered vector
     int end[RR];         // ... and is below end[r]; rounds that do not exist are empty
 };
+
+// More rounds: the words shift and end of every round, a word per lane.  Held in scalars and compared one after the other,
+// eight rounds cost more instructions per entry than everything else, and five rows of them more scalar registers
+// than there are.
+template <>
+struct RecordWalk<ANY_ROUNDS> {
+    int words;   // lane 2 r: shift[r], lane 2 r + 1: end[r]
+};
+
+template <int RR>
+__device__ inline int record_total(const RecordWalk<RR> &W, int R)
+{
+    if constexpr (RR == ANY_ROUNDS)
+        return __builtin_amdgcn_readlane(W.words, 2 * R - 1);
+    else
+        return W.end[RR - 1];
+}
 
 // Where entry e of the record gathers from; `zero_slot` past its end.
 template <int RR, class Walk>
@@ -249,9 +269,40 @@ __device__ inline unsigned gather_place(const Walk &M, int e, unsigned zero_slot
     return e < M.end[RR - 1] ? (unsigned)e + sh : zero_slot;
 }
 
-// Up to so many hash rounds RR is the number of rounds; above it rounds RR > R are read as far as they go (a record
-// of R rounds holds at least 6 + 2 R + 6 words) and taken as empty.
-constexpr int EXACT_ROUNDS = 4;
+// Walks a record a chunk of 64 entries after the other, in ascending order: where entry e = c + lane of the chunk that
+// starts at c gathers from, `other` past the record's end.
+template <int RR>
+struct RecordCursor {
+    const RecordWalk<RR> &W;
+    __device__ inline RecordCursor(const RecordWalk<RR> &walk, int) : W(walk) {}
+    __device__ inline unsigned place(int, int e, unsigned other) { return gather_place<RR>(W, e, other); }
+};
+
+// The round that the chunk begins in is at hand, the next ones are taken up where they begin: a comparison per round that
+// ends in the chunk, not one per round there is.
+template <>
+struct RecordCursor<ANY_ROUNDS> {
+    const int words, R, total;
+    int r, end;
+    unsigned shift;
+    __device__ inline RecordCursor(const RecordWalk<ANY_ROUNDS> &walk, int rounds)
+        : words(walk.words), R(rounds), total(record_total<ANY_ROUNDS>(walk, rounds)), r(0),
+          end(__builtin_amdgcn_readlane(walk.words, 1)), shift((unsigned)__builtin_amdgcn_readlane(walk.words, 0))
+    {
+    }
+    __device__ inline unsigned place(int c, int e, unsigned other)
+    {
+        unsigned sh = shift;
+        while (end < c + 64 && r + 1 < R) {   // uniform
+            const int before = end;
+            ++r;
+            shift = (unsigned)__builtin_amdgcn_readlane(words, 2 * r);
+            end = __builtin_amdgcn_readlane(words, 2 * r + 1);
+            sh = e >= before ? shift : sh;
+        }
+        return e < total ? (unsigned)e + sh : other;
+    }
+};
 
 // the records are written once at build time: reading them through the constant
 // address space lets the compiler use scalar loads although the kernel also stores
@@ -268,12 +319,18 @@ template <int RR>
 __device__ inline void load_walk(RecordWalk<RR> &W, const PassSide &S, int R, long long row)
 {
     const bool exists = row < S.rows;
-    const_int_ptr rec = (const_int_ptr)(S.meta + (exists ? row : S.rows - 1) * S.meta_stride);
+    const int *at = S.meta + (exists ? row : S.rows - 1) * S.meta_stride;
+    if constexpr (RR == ANY_ROUNDS) {
+        const int lane = threadIdx.x & 63, word = at[6 + (lane < 2 * R ? lane : 0)];
+        W.words = exists ? word : 0;
+    } else {
+        const_int_ptr rec = (const_int_ptr)at;
 #pragma unroll
-    for (int r = 0; r < RR; ++r) {
-        W.shift[r] = (unsigned)rec[6 + 2 * r];
-        const int end = rec[7 + 2 * r];
-        W.end[r] = !exists ? 0 : RR <= EXACT_ROUNDS || r < R ? end : W.end[r > 0 ? r - 1 : 0];
+        for (int r = 0; r < RR; ++r) {
+            W.shift[r] = (unsigned)rec[6 + 2 * r];
+            const int end = rec[7 + 2 * r];
+            W.end[r] = !exists ? 0 : end;
+        }
     }
 }
 

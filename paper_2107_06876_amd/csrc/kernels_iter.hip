@@ -13,7 +13,7 @@ namespace lcn {
 // lane, so that scalings may drift arbitrarily far (a sparse kernel need not
 // have support, App. "Limitations") without over- or underflow.
 //
-// G lanes work on a row (16 or 32), a workgroup on 256 / G rows, and an update has a workgroup for
+// G lanes work on a row (16, 32 or 64), a workgroup on 256 / G rows, and an update has a workgroup for
 // every 256 / G rows there are: nothing is carried from row to row, so it is the chip that refills its compute units.
 // The record is walked flat (see pass_kernel), G U entries at a time, all loads of a trip requested together.
 // What bounds it: rows of some twenty entries, the launch and three trips to memory one after the other (record,
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
     }
     // (an update and the initial copies run through this once)
     for (long long r0 = (long long)blockIdx.x * RPB; r0 < S.rows; r0 += (long long)gridDim.x * RPB) {
-        long long row = r0 + threadIdx.x / G;
+        long long row = r0 + (G == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / G) : threadIdx.x / G);
         const bool exists = row < S.rows;
         if (!exists) row = S.rows - 1;   // worked on again, not written
         double lg;
@@ -47,14 +47,16 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             double log_marg;
             int end[RR];
             unsigned place[RR];
+            RecordWalk<ANY_ROUNDS> words{};   // of a wavefront's one row instead
             {
                 const int *rec = S.meta + row * S.meta_stride;
                 base = ((long long)rec[1] << 32) | (unsigned)rec[0];
                 marg = __int_as_float(rec[2]);
                 log_marg = __hiloint2double(rec[5], rec[4]);
+                if (G == 64) load_walk<ANY_ROUNDS>(words, S, R, row);
                 unsigned before = 0u;
 #pragma unroll
-                for (int r = 0; r < RR; ++r) {
+                for (int r = 0; r < (G == 64 ? 0 : RR); ++r) {
                     const unsigned shift = (unsigned)rec[6 + 2 * r];
                     place[r] = shift - before;
                     before = shift;
@@ -64,9 +66,10 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             }
             const double prev = S.lin_out[row];   // what the row's current scaling was computed from
             const float *__restrict__ vals = S.vals + base;
-            const int total = end[RR - 1];
+            const int total = G == 64 ? record_total<ANY_ROUNDS>(words, R) : end[RR - 1];
             // f(log kernel values, log scalings, which of them are entries) for each trip
             auto walk = [&](auto &&f) {
+                RecordCursor<ANY_ROUNDS> cursor(words, R);
                 for (int e0 = 0; e0 < total; e0 += G * U) {
                     float k[U];
                     double p[U];
@@ -75,17 +78,21 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
                     for (int u = 0; u < U; ++u) {
                         int e = e0 + G * u + sub;
                         in[u] = e < total;
+                        unsigned at;
+                        if constexpr (G == 64) at = cursor.place(e0 + G * u, e, 0u);
                         e = e < total ? e : total - 1;   // past the end: the last entry again, not counted
-                        unsigned at = (unsigned)e + place[0];
+                        if constexpr (G != 64) {
+                            at = (unsigned)e + place[0];
 #pragma unroll
-                        for (int r = 1; r < RR; ++r) at += e >= end[r - 1] ? place[r] : 0u;
+                            for (int r = 1; r < RR; ++r) at += e >= end[r - 1] ? place[r] : 0u;
+                        }
                         k[u] = vals[(unsigned)e];
                         p[u] = S.perm_in[at];
                     }
                     f(k, p, in);
                 }
             };
-            auto sum_lanes = [&](double v) { return G == 32 ? half_sum(v) : row_sum(v); };
+            auto sum_lanes = [&](double v) { return G == 64 ? wave_sum(v) : G == 32 ? half_sum(v) : row_sum(v); };
             // The row's log-sum-exp.  First with the row's previous value as the shift (near the answer, so the
             // terms are of order one): one subtraction, one single-precision exp and one addition in double per entry (a
             // lane has up to four times the entries it would have if a wavefront shared the row: added in single precision,
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
 #pragma unroll
                     for (int u = 0; u < U; ++u) lse_step(in[u] ? (double)k[u] + p[u] : -INFINITY, mx, sm);
                 });
-                const double M = G == 32 ? half_max(mx) : row_max(mx);
+                const double M = G == 64 ? wave_max(mx) : G == 32 ? half_max(mx) : row_max(mx);
                 const double part = mx > -INFINITY ? sm * exp(mx - M) : 0.0;
                 const double ssum = sum_lanes(part);
                 lse = ssum > 0.0 ? M + log(ssum) : -INFINITY;
@@ -479,13 +486,13 @@ template <int RR, int G, int U>
 static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
 {
     // a query leaves 3 partial sums per workgroup and there is room for h.grid of them
-    const int lanes = mode == PASS_UPDATE ? G : mode == PASS_QUERY ? 32 : 16;
+    const int lanes = mode == PASS_INIT ? 16 : G;
     const long long all = (S.rows + 256 / lanes - 1) / (256 / lanes);
     const int grid = (int)(mode == PASS_QUERY && all > h.grid ? h.grid : all);
     if (mode == PASS_UPDATE)
         hipLaunchKernelGGL((logpass_kernel<RR, G, U, PASS_UPDATE>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
     else if (mode == PASS_QUERY)
-        hipLaunchKernelGGL((logpass_kernel<RR, 32, 4, PASS_QUERY>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
+        hipLaunchKernelGGL((logpass_kernel<RR, G, U, PASS_QUERY>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
     else
         hipLaunchKernelGGL((logpass_kernel<1, 16, 1, PASS_INIT>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
     return grid;
@@ -495,22 +502,33 @@ static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int
 // and two entries each at a time (a wavefront with four: 6.1; a wavefront per row and a 1024-thread workgroup working
 // through its rows, loads unrolled over four rounds: 6.4); 20 000 rows of 510 values in three rounds 15.2 us with 32
 // lanes and four entries each, 16.3 with sixteen and two, 15.5 with 64 and four (19.6 before).
+// A whole wavefront (four entries per lane) where looking up an entry's round weighs more than lanes without an entry at the
+// record's end: 5000 rows of 420 values in five rounds 5.9 us against 7.5, of 670 in eight 7.3 against 10.3, 20 000 of 250
+// in five 13.6 against 17.0, of 1600 in eight 37 against 57, but 5000 of 65 in eight 5.4 against 5.1; in four rounds 5000 of 1000 7.9 against 9.6, 40 000 of 1600 84
+// against 86, but 10 000 of 670 11.4 against 10.8.
+static int log_lanes(const Handle &h, long long rows)
+{
+    if (h.R > EXACT_ROUNDS ? h.nnz_stored > 80 * rows : h.R == 4 && h.nnz_stored > 1000 * rows) return 64;
+    return h.nnz_stored <= 48 * rows ? 16 : 32;
+}
+
 template <int RR>
 static int launch_logpass_length(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
 {
-    return h.nnz_stored <= 48 * S.rows ? launch_logpass_rows<RR, 16, 2>(S, h, mode, empty_slot, s)
-                                       : launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);
+    return log_lanes(h, S.rows) == 16 ? launch_logpass_rows<RR, 16, 2>(S, h, mode, empty_slot, s)
+                                 : launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);
 }
 
 // returns the workgroups launched
 static int launch_logpass_rounds(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
 {
+    if (log_lanes(h, S.rows) == 64) return launch_logpass_rows<ANY_ROUNDS, 64, 4>(S, h, mode, empty_slot, s);
     switch (h.R) {
         case 1: return launch_logpass_length<1>(S, h, mode, empty_slot, s);
         case 2: return launch_logpass_length<2>(S, h, mode, empty_slot, s);
         case 3: return launch_logpass_length<3>(S, h, mode, empty_slot, s);
         case 4: return launch_logpass_length<4>(S, h, mode, empty_slot, s);
-        default: return launch_logpass_length<8>(S, h, mode, empty_slot, s);
+        default: return launch_logpass_length<ANY_ROUNDS>(S, h, mode, empty_slot, s);
     }
 }
 

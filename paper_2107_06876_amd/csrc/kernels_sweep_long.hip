@@ -64,10 +64,11 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
         D.f.load(S.F, r, lp, lane);
         if (MODE != PASS_INIT) {
             const float *__restrict__ vals = S.vals + M.base;
+            RecordCursor<RR> cursor(M.walk, R);
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 D.tv[v] = vals[64 * v + lane];
-                D.vv[v] = perm_in[gather_place<RR>(M.walk, 64 * v + lane, zero_slot)];
+                D.vv[v] = perm_in[cursor.place(64 * v, 64 * v + lane, zero_slot)];
             }
         }
     };
@@ -95,11 +96,17 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
     }
     // one row: `C` holds the row's data, `N` receives the next row's
     auto step = [&](RowData &C, RowData &N) {
+        auto look_ahead = [&]() {
+            if (next2 < S.rows) {
+                load_meta<RR, MODE>(mn2, S, Rm, next2, lane);
+                if (MODE == PASS_INIT && lane < R) mn2.pos = S.meta[next2 * S.meta_stride + 6 + 2 * R + lane];
+            }
+        };
+        // (the words of more than EXACT_ROUNDS rounds come as a vector load, which is there no sooner than what was
+        // requested before it)
+        if (RR == ANY_ROUNDS) look_ahead();
         if (next < S.rows) issue(N, mn, next);
-        if (next2 < S.rows) {
-            load_meta<RR, MODE>(mn2, S, Rm, next2, lane);
-            if (MODE == PASS_INIT && lane < R) mn2.pos = S.meta[next2 * S.meta_stride + 6 + 2 * R + lane];
-        }
+        if (RR != ANY_ROUNDS) look_ahead();
         double out;
         if (MODE == PASS_INIT) {
             const double lo = (double)S.log_out[row];
@@ -107,18 +114,19 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
             if (lo > maxlog && lo < INFINITY) maxlog = lo;
         } else {
             double acc = 0.0;
-            const int total = mc.walk.end[RR - 1];
+            const int total = record_total<RR>(mc.walk, R);
 #pragma unroll
             for (int v = 0; v < V; ++v)
                 acc = fma((double)(64 * v + lane < total ? C.tv[v] : 0.f), (double)C.vv[v], acc);
+            RecordCursor<RR> cursor(mc.walk, R);
             for (int e0 = 64 * V; e0 < total; e0 += 64 * TRIP) {   // all loads of a trip before the first use
                 const float *__restrict__ vals = S.vals + mc.base;
                 float tt[TRIP], pp[TRIP];
 #pragma unroll
                 for (int k = 0; k < TRIP; ++k) {
-                    const int e = e0 + 64 * k + lane;
+                    const int c = e0 + 64 * k, e = c + lane;
                     tt[k] = vals[(unsigned)e];
-                    pp[k] = perm_in[gather_place<RR>(mc.walk, e, zero_slot)];
+                    pp[k] = perm_in[cursor.place(c, e, zero_slot)];
                     if (e >= total) tt[k] = 0.f;
                 }
 #pragma unroll
@@ -217,7 +225,7 @@ static void launch_long_columns(const PassSide &S, const Handle &h, int mode, co
         case 2: launch_long_rounds<T, 2>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
         case 3: launch_long_rounds<T, 3>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
         case 4: launch_long_rounds<T, 4>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
-        default: launch_long_rounds<T, 8>(S, h, mode, F, fused_in, groups, partial, cnt, s);
+        default: launch_long_rounds<T, ANY_ROUNDS>(S, h, mode, F, fused_in, groups, partial, cnt, s);
     }
 }
 

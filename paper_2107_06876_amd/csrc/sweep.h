@@ -110,12 +110,13 @@ __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, i
             const float *__restrict__ vals = S.vals + base;
 #pragma unroll
             for (int t = 0; t < RG; ++t) {
+                RecordCursor<RR> cursor(walk[t], R);
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
                     tv[t][v] = vals[(unsigned)(lane + 64 * v)];
-                    pv[t][v] = perm_in[gather_place<RR>(walk[t], lane + 64 * v, zero_slot)];
+                    pv[t][v] = perm_in[cursor.place(64 * v, lane + 64 * v, zero_slot)];
                 }
-                vals += walk[t].end[RR - 1];
+                vals += record_total<RR>(walk[t], R);
             }
         }
         const long long mine = row0 + my < S.rows ? row0 + my : S.rows - 1;
@@ -153,17 +154,18 @@ __global__ __launch_bounds__(PASS_THREADS) void pass_kernel(PassSide S, int R, i
             const float *__restrict__ vals = S.vals + base;
 #pragma unroll
             for (int t = 0; t < RG; ++t) {
-                const int total = walk[t].end[RR - 1];
+                const int total = record_total<RR>(walk[t], R);
 #pragma unroll
                 for (int v = 0; v < V; ++v)
                     acc[t] = fma((double)(lane + 64 * v < total ? tv[t][v] : 0.f), (double)pv[t][v], acc[t]);
+                RecordCursor<RR> cursor(walk[t], R);
                 for (int e0 = 64 * V; e0 < total; e0 += 64 * TRIP) {   // all loads of a trip before the first use
                     float tt[TRIP], pp[TRIP];
 #pragma unroll
                     for (int k = 0; k < TRIP; ++k) {
-                        const int e = e0 + 64 * k + lane;
+                        const int c = e0 + 64 * k, e = c + lane;
                         tt[k] = vals[(unsigned)e];
-                        pp[k] = perm_in[gather_place<RR>(walk[t], e, zero_slot)];
+                        pp[k] = perm_in[cursor.place(c, e, zero_slot)];
                         if (e >= total) tt[k] = 0.f;
                     }
 #pragma unroll
@@ -283,7 +285,7 @@ static void launch_sweep_rounds(const PassSide &S, const Handle &h, int mode, co
     }
 }
 
-// The loads are unrolled over exactly the hash rounds there are, up to four.
+// The loads are unrolled over exactly the hash rounds there are, up to EXACT_ROUNDS.
 template <int T>
 static void launch_sweep_columns(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
                                  double *partial, unsigned long long *cnt, hipStream_t s)
@@ -293,7 +295,7 @@ static void launch_sweep_columns(const PassSide &S, const Handle &h, int mode, c
         case 2: launch_sweep_rounds<T, 2>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
         case 3: launch_sweep_rounds<T, 3>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
         case 4: launch_sweep_rounds<T, 4>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
-        default: launch_sweep_rounds<T, 8>(S, h, mode, F, fused_in, groups, partial, cnt, s);
+        default: launch_sweep_rounds<T, ANY_ROUNDS>(S, h, mode, F, fused_in, groups, partial, cnt, s);
     }
 }
 

@@ -73,6 +73,26 @@ def test_lanes_per_row_in_logs(n, m, buckets, rounds):
     print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 12), "sparse"), flush=True)
 
 
+# more than four rounds: their words are looked up as the walk reaches them; several rounds ending in one piece of 64
+# entries, empty ones, ones longer than a trip; every width of the sweeps and rows per wavefront
+@pytest.mark.parametrize("n,m,landmarks,buckets,rounds", [
+    (300, 301, 20, 40, 5), (40, 41, 8, 80, 8), (2500, 2501, 20, 4, 6), (4100, 4099, 70, 60, 7), (9000, 8999, 140, 100, 5),
+    (17000, 17001, 130, 2600, 8), (17000, 16999, 250, 300, 6), (2000, 1999, 300, 30, 5), (1500, 1501, 512, 700, 8),
+    (600, 601, 400, 3, 7),
+])
+def test_many_rounds(n, m, landmarks, buckets, rounds):
+    from parity import compare
+    print("rounds", n, m, rounds, compare(_cut(n, m, 3, landmarks, buckets, rounds, 6), "lcn"), flush=True)
+
+
+# a wavefront per row: more than four rounds of more than 80 entries together, or four of more than 1000
+@pytest.mark.parametrize("n,m,buckets,rounds", [(900, 901, 30, 5), (899, 900, 53, 5), (901, 900, 60, 5), (70, 2100, 300, 8),
+                                               (2100, 70, 3, 8), (700, 650, 5, 7), (1100, 1099, 4, 4), (9, 5000, 2, 4)])
+def test_a_wavefront_per_row_in_logs(n, m, buckets, rounds):
+    from parity import compare
+    print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 12), "sparse"), flush=True)
+
+
 @pytest.mark.parametrize("n,m,d,landmarks,buckets,rounds", [
     (4096, 4096, 5, 17, 33, 2),      # exactly one range of points, bucket arrays on multiples of four
     (4099, 4094, 5, 17, 33, 3),      # one point more, bucket arrays off by one, two and three
