@@ -191,6 +191,7 @@ inline size_t dense_iteration_floats(int groups, long long m) { return groups ? 
 hipError_t launch_dense_iteration(const PassSide &X, const PassSide &Y, const Handle &h, hipStream_t s);
 int device_compute_units();
 int pass_grid(const Handle &h);
+constexpr int MOST_GROUPS = 2048;   // what pass_grid() gives at most by itself
 
 // ---- batched small problems (kernels_batched.hip) ---------------------------
 bool is_batched_handle(const void *h);

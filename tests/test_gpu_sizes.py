@@ -93,6 +93,22 @@ def test_a_wavefront_per_row_in_logs(n, m, buckets, rounds):
     print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 12), "sparse"), flush=True)
 
 
+# a query in logs: up to 2^22 entries by 512 workgroups, above that by up to 2048, fewer where rows run out
+@pytest.mark.parametrize("n,m,buckets", [(8300, 8301, 8), (8300, 8301, 40), (1800, 1801, 1), (20000, 300, 1)])
+def test_queries_over_many_rows(n, m, buckets):
+    import torch
+    import paper_2107_06876_amd as lcn
+    from parity import compare, gpu_build
+    p = _cut(n, m, 3, 8, buckets, 1, 4)
+    print("query", n, m, buckets, compare(p, "sparse"), flush=True)
+    # what the library asks for beforehand, told how many pairs there are, is enough
+    h = gpu_build(p, "sparse")
+    info = lcn.lcn_get_info(h)
+    lsh = dict(num_buckets=buckets, num_rounds=1, kmeans_iters=p.kmeans_iters, seed=1)
+    assert lcn.lcn_workspace_bytes(n, m, 3, lcn.MODE_SPARSE, None, lsh, nnz_guess=info.nnz_stored) >= info.workspace_used
+    lcn.lcn_destroy(h)
+
+
 @pytest.mark.parametrize("n,m,d,landmarks,buckets,rounds", [
     (4096, 4096, 5, 17, 33, 2),      # exactly one range of points, bucket arrays on multiples of four
     (4099, 4094, 5, 17, 33, 3),      # one point more, bucket arrays off by one, two and three
