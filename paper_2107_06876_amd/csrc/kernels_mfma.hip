@@ -140,15 +140,17 @@ hipError_t launch_kmeans_start(const float *Z, int d, const KmRuns &runs, hipStr
     return hipGetLastError();
 }
 
-// The largest squared norm of a centroid (rounded up), by a workgroup of 256 threads; sh: four words of LDS.
-__device__ inline float largest_norm(const float *__restrict__ cn, int k, float *sh)
+// The largest squared norm of a centroid (rounded up), by a workgroup of 256 threads; sh: four words of LDS.  Bit patterns
+// of floats without a sign order like unsigned integers, with what is not a number above infinity: one such centroid (of
+// those the caller gives) makes the bound not a number either, and then no point counts as decided.
+__device__ inline float largest_norm(const float *__restrict__ cn, int k, unsigned *sh)
 {
-    float m = 0.f;
-    for (int c = threadIdx.x; c < k; c += 256) m = fmaxf(m, cn[c]);
-    for (int o = 1; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    unsigned m = 0u;
+    for (int c = threadIdx.x; c < k; c += 256) m = max(m, __float_as_uint(cn[c]) & 0x7FFFFFFFu);
+    for (int o = 1; o < 64; o <<= 1) m = max(m, (unsigned)__shfl_xor((int)m, o, 64));
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
     __syncthreads();
-    return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])) * 1.0000002f;
+    return __uint_as_float(max(max(sh[0], sh[1]), max(sh[2], sh[3]))) * 1.0000002f;
 }
 
 // What the filter makes of a point's three smallest scores.
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void a
     // [buffer][step of the stage][centroid group][plane][lane]: 32 KB
     __shared__ bf16x8 Cs[2][2][4][2][64];
     __shared__ float cn_s[FC];  // squared norms of the pass's centroids (+inf beyond the last one)
-    __shared__ float cmax_s[4];
+    __shared__ unsigned cmax_s[4];
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(256, 2) void assign_filter_resident_kernel(const bf
     const long long cplane = run.plane / 8;
     const int k = run.k;
     const float *__restrict__ cn = run.cn;
-    __shared__ float cmax_s[4];
+    __shared__ unsigned cmax_s[4];
     extern __shared__ __align__(16) unsigned char fr_lds[];
     bf16x8 *Zs = reinterpret_cast<bf16x8 *>(fr_lds);   // [4 point groups][S][64]
     const int tid = threadIdx.x;

@@ -265,3 +265,28 @@ def test_dense_plan_blocks(n, m, blocks):
         assert bool((room[rows * m:] == -7.0).all())
         assert bool(((got - want[i0:i0 + rows]).abs() <= bound[i0:i0 + rows]).all()), (i0, rows)
     lcn.lcn_destroy(h)
+
+
+@pytest.mark.parametrize("landmarks", [5, 40, 300])
+def test_a_given_centroid_that_is_not_a_number(monkeypatch, landmarks):
+    """The exact rule keeps the first of the centroids that no other beats, and nothing beats a distance that is not a
+    number: with such a centroid in front every point is its member.  The filter decides nothing then."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    rng = np.random.default_rng(5)
+    X = torch.from_numpy(rng.standard_normal((400, 6)).astype(np.float32)).cuda()
+    Y = torch.from_numpy(rng.standard_normal((300, 6)).astype(np.float32)).cuda()
+    a, b = torch.full((400,), 1 / 400, device="cuda"), torch.full((300,), 1 / 300, device="cuda")
+    start = torch.cat([X, Y])[:landmarks].clone()
+    start[0] = float("nan")
+    got = {}
+    for exact in ("0", "1"):
+        monkeypatch.setenv("LCN_EXACT_ASSIGN_ONLY", exact)
+        lm = dict(num_landmarks=landmarks, kmeans_iters=1, seed=1, init=lcn.INIT_GIVEN, init_centroids=start, ridge=1e-3)
+        h = lcn.lcn_build(X, Y, a, b, 4.0, lcn.COST_SQEUCLID, lcn.MODE_NYSTROM, landmarks=lm)
+        got[exact] = lcn.lcn_get_landmarks(h)
+        lcn.lcn_destroy(h)
+    assert torch.equal(got["0"], got["1"])
+    assert torch.equal(got["0"][1:], start[1:])
+    # one rounding of the mean to single precision, and sums in units of 2^-32
+    assert float((got["0"][0].double() - torch.cat([X, Y]).double().mean(0)).abs().max()) < 1e-7
