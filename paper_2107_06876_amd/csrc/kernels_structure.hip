@@ -463,8 +463,8 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ Z
 // Exact rule on what the filter left undecided, in one launch.
 //
 // Points with more than two candidates (the list): one workgroup per point, one thread per centroid (strided), each
-// adding the dimensions left to right.  The centroids come through LDS, 32 dimensions of 256 of them at a time in
-// whole lines, the next 32 already requested (a thread that reads its centroid's row by itself asks for 64 lines per
+// adding the dimensions left to right.  The centroids come through LDS, 32 dimensions of 256 of them (or 128 of 64) at a time in
+// whole lines, the next ones already requested (a thread that reads its centroid's row by itself asks for 64 lines per
 // load: 17 us for a few hundred points of 300 dimensions).
 //
 // Points with two candidates: sixteen per workgroup at a time.  The order of the additions is the rule, but the squares
@@ -472,8 +472,70 @@ __global__ __launch_bounds__(256) void assign_kernel(const float *__restrict__ Z
 // lines of the two rows, and a lane per pair adds them up from LDS, the next 64 dimensions already requested.  (A thread
 // that reads both rows by itself waits ten times for memory: 17 us at 38 768 points of 300 dimensions.)
 constexpr int UP = 32, UD = 64;   // pairs of a point and a centroid, dimensions
-constexpr int UL = 32, UC = 256;  // dimensions and centroids at a time for a listed point
+constexpr int UV = 8192;          // values of the centroids at a time for a listed point
 
+union UndecidedRoom {
+    float cent[UV + 128];   // [UL][UC + 1]
+    double sq[UP][UD + 1];
+};
+
+// One listed point: UL dimensions of UC = UV / UL centroids at a time.
+template <int UL>
+__device__ inline void undecided_point(const float *__restrict__ z, int d, const float *__restrict__ C, int k, UndecidedRoom &room,
+                                       float (*zs)[128], double &bv, int &bi)
+{
+    constexpr int UC = UV / UL, STEP = 256 / UL;
+    float(*cent)[UC + 1] = reinterpret_cast<float(*)[UC + 1]>(room.cent);
+    const int dim = threadIdx.x & (UL - 1), r0 = threadIdx.x / UL;
+    for (int c0 = 0; c0 < k; c0 += UC) {
+        const int c = c0 + (int)threadIdx.x;
+        const bool mine = (int)threadIdx.x < UC;
+        double s = 0.0;
+        float cv[32], zv;
+        auto fetch = [&](int j0) {   // past the last dimension or centroid: the last one again, not added
+            const int j = j0 + dim < d ? j0 + dim : d - 1;
+#pragma unroll
+            for (int u = 0; u < 32; ++u) {
+                const int r = c0 + r0 + STEP * u < k ? c0 + r0 + STEP * u : k - 1;
+                cv[u] = C[(long long)r * d + j];
+            }
+            zv = z[j];
+        };
+        fetch(0);
+        for (int j0 = 0; j0 < d; j0 += UL) {
+            const int buf = (j0 / UL) & 1;
+            __syncthreads();   // the dimensions before have been added
+#pragma unroll
+            for (int u = 0; u < 32; ++u) cent[dim][r0 + STEP * u] = cv[u];
+            if (threadIdx.x < UL) zs[buf][dim] = zv;
+            __syncthreads();
+            fetch(j0 + UL);
+            const int m = d - j0 < UL ? d - j0 : UL;
+            if (mine) {
+                if (m == UL) {
+#pragma unroll 32
+                    for (int e = 0; e < UL; ++e) {
+                        const double t = (double)zs[buf][e] - (double)cent[e][threadIdx.x];
+                        const double t2 = t * t;
+                        s = s + t2;
+                    }
+                } else {
+                    for (int e = 0; e < m; ++e) {
+                        const double t = (double)zs[buf][e] - (double)cent[e][threadIdx.x];
+                        const double t2 = t * t;
+                        s = s + t2;
+                    }
+                }
+            }
+        }
+        if (mine && c < k && (bi < 0 || s < bv)) {  // ascending c: strict < keeps the lowest index
+            bv = s;
+            bi = c;
+        }
+    }
+}
+
+template <int UL>
 __global__ __launch_bounds__(256) void assign_undecided_kernel(const float *__restrict__ Z, int d, KmRuns R)
 {
     const KmRun &run = R.run[blockIdx.y];
@@ -483,62 +545,16 @@ __global__ __launch_bounds__(256) void assign_undecided_kernel(const float *__re
     const int *__restrict__ list = run.flagged, *__restrict__ pairs = run.pairs, *__restrict__ count = run.nflagged;
     __shared__ double bv_sh[256];
     __shared__ int bi_sh[256];
-    __shared__ float zs[2][UL];
-    __shared__ union {
-        float cent[UL][UC + 1];
-        double sq[UP][UD + 1];
-    } sh;
-    auto &sq = sh.sq;
+    __shared__ float zs[2][128];
+    __shared__ UndecidedRoom room;
+    auto &sq = room.sq;
     const int cnt = count[0];
     const long long npairs = count[1];
     for (int it = blockIdx.x; it < cnt; it += gridDim.x) {
         const long long p = list[it];
         double bv = 0.0;
         int bi = -1;
-        const int dim = threadIdx.x & (UL - 1), r0 = threadIdx.x / UL;
-        for (int c0 = 0; c0 < k; c0 += UC) {
-            const int c = c0 + (int)threadIdx.x;
-            double s = 0.0;
-            float cv[UL], zv;
-            auto fetch = [&](int j0) {   // past the last dimension or centroid: the last one again, not added
-                const int j = j0 + dim < d ? j0 + dim : d - 1;
-#pragma unroll
-                for (int u = 0; u < UL; ++u) {
-                    const int r = c0 + r0 + 8 * u < k ? c0 + r0 + 8 * u : k - 1;
-                    cv[u] = C[(long long)r * d + j];
-                }
-                zv = Z[p * d + j];
-            };
-            fetch(0);
-            for (int j0 = 0; j0 < d; j0 += UL) {
-                const int buf = (j0 / UL) & 1;
-                __syncthreads();   // the dimensions before have been added
-#pragma unroll
-                for (int u = 0; u < UL; ++u) sh.cent[dim][r0 + 8 * u] = cv[u];
-                if (threadIdx.x < UL) zs[buf][dim] = zv;
-                __syncthreads();
-                fetch(j0 + UL);
-                const int m = d - j0 < UL ? d - j0 : UL;
-                if (m == UL) {
-#pragma unroll
-                    for (int e = 0; e < UL; ++e) {
-                        const double t = (double)zs[buf][e] - (double)sh.cent[e][threadIdx.x];
-                        const double t2 = t * t;
-                        s = s + t2;
-                    }
-                } else {
-                    for (int e = 0; e < m; ++e) {
-                        const double t = (double)zs[buf][e] - (double)sh.cent[e][threadIdx.x];
-                        const double t2 = t * t;
-                        s = s + t2;
-                    }
-                }
-            }
-            if (c < k && (bi < 0 || s < bv)) {  // ascending c: strict < keeps the lowest index
-                bv = s;
-                bi = c;
-            }
-        }
+        undecided_point<UL>(Z + p * d, d, C, k, room, zs, bv, bi);
         bv_sh[threadIdx.x] = bv;
         bi_sh[threadIdx.x] = bi;
         __syncthreads();
@@ -614,7 +630,14 @@ __global__ __launch_bounds__(256) void assign_undecided_kernel(const float *__re
 
 hipError_t launch_assign_undecided(const float *Z, int d, const KmRuns &runs, hipStream_t s)
 {
-    hipLaunchKernelGGL(assign_undecided_kernel, dim3(1024, (unsigned)runs.count), dim3(256), 0, s, Z, d, runs);
+    const dim3 grid(1024, (unsigned)runs.count);
+    // What bounds a listed point is a trip to memory per UL dimensions: wide rows are taken 128 dimensions at a time if the
+    // centroids are few enough (6000 points of 1000 dimensions, 40 centroids: 31 us instead of 38; up to 512 dimensions the
+    // shorter trips are as good).  Such runs come one at a time.
+    if (d > 512 && runs.run[0].k <= UV / 128)
+        hipLaunchKernelGGL(assign_undecided_kernel<128>, grid, dim3(256), 0, s, Z, d, runs);
+    else
+        hipLaunchKernelGGL(assign_undecided_kernel<32>, grid, dim3(256), 0, s, Z, d, runs);
     return hipGetLastError();
 }
 

@@ -146,6 +146,8 @@ def test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds
     (8000, 7999, 130, 64, 300, 2),   # few points, many scores
     (10000, 10000, 3, 1, 1118, 3),   # just below 2^26
     (10000, 10000, 3, 2, 1118, 3),   # just above: sorted
+    (400, 390, 640, 64, 65, 2),      # rows of more than 512 dimensions: 64 centroids at a time, 256
+    (400, 390, 515, 3, 64, 1),       # ... and a last piece of three dimensions
 ])
 def test_runs_together_or_apart(monkeypatch, n, m, d, landmarks, buckets, rounds):
     test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds)
