@@ -975,24 +975,28 @@ constexpr int KM_RANGE = 8192;   // points a workgroup looks through for its clu
 // Build times, by members / counting and scattering (us), by millions of clusters times points: 24 (40 000 points, a run of 510
 // clusters and one of 200) 1870 / 1940, 46 (40 000, two of 512 and 128) 2120 / 2200, 44 (60 000, two of 270 and 200) 2050 / 2110,
 // 49 (60 000, 760 and 64) 1490 / 1530; 101 (60 000, two of 780 and 128) 3140 / 2930, 107 (100 000, three of 270 and 256)
-// 5000 / 4800, 128 (80 000, four of 400) 3930 / 3520.
-constexpr long long KM_MEMBERS_WORK = 1ll << 26;
+// 5000 / 4800, 128 (80 000, four of 400) 3930 / 3520.  Up to 2^14 points, two ranges, whatever the clusters (at most 4096 of
+// a run): 8000 points, five of 2000 2180 / 3070, 16 000, three of 2000 2530 / 2560.  And twice as much for more rounds than
+// lanes, which only then can advance together: 72 (60 000, six of 200) 4050 / 4260, 74 (40 000, eight of 200 and 256) 4670 / 5100.
+constexpr long long KM_MEMBERS_WORK = 1ll << 26, KM_MEMBERS_POINTS = 1ll << 14;
 
 static int kmeans_ranges(long long N) { return (int)((N + KM_RANGE - 1) / KM_RANGE); }
 
-bool kmeans_by_members(long long N, long long clusters, int d) { return d <= 512 && clusters * N <= KM_MEMBERS_WORK; }
+bool kmeans_by_members(long long N, long long clusters, int d, bool more_than_lanes)
+{
+    return d <= 512 && (N <= KM_MEMBERS_POINTS || clusters * N <= (more_than_lanes ? 2 : 1) * KM_MEMBERS_WORK);
+}
 
 int kmeans_sum_chunk(long long N) { return N <= 65536 ? 16 : N <= 131072 ? 32 : N <= 262144 ? 64 : 128; }
 
-size_t kmeans_partial_elems(long long N, int kmax, int d, bool by_members)
+size_t kmeans_partial_elems(long long N, int kmax, int d, bool members, bool sorted)
 {
     if (d > 512) return 1;   // wider rows take the sliced kernel, which needs none
-    if (by_members) {   // (kmax may be the buckets of a hash that is not k-means)
-        const long long k = KM_MEMBERS_WORK / N < kmax ? KM_MEMBERS_WORK / N : kmax;
-        return (size_t)k * (size_t)kmeans_ranges(N) * (size_t)d;
-    }
+    // (4096 clusters of 2^14 points are 2^26 as well; kmax may be the buckets of a hash that is not k-means)
+    const long long k = KM_MEMBERS_WORK / N < kmax ? KM_MEMBERS_WORK / N : kmax;
     const int M = kmeans_sum_chunk(N);
-    return (size_t)((N + M - 1) / M + kmax) * (size_t)d;
+    const size_t by_members = members ? (size_t)k * (size_t)kmeans_ranges(N) : 0, by_sort = sorted ? (size_t)((N + M - 1) / M + kmax) : 0;
+    return (by_members > by_sort ? by_members : by_sort) * (size_t)d;
 }
 
 constexpr unsigned long long FIX_MAGIC_BITS = 0x4338000000000000ull;   // 1.5 * 2^52

@@ -69,6 +69,9 @@ constexpr int REPORT_FAIL = 16, REPORT_TOTALS = 18, REPORT_WORDS = 24;   // 64-b
 
 constexpr int KM_LANES = 4;   // k-means runs of a build that may be in flight together on streams of their own
 
+// lanes for the hash rounds: the landmarks and the factors keep lane 0 to themselves
+int round_lanes(const Handle &h) { return h.l > 0 ? KM_LANES - 1 : KM_LANES; }
+
 struct KmScratch {  // what one k-means run needs for itself
     long long *idx;
     float *cent;
@@ -124,7 +127,7 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
         km.nflagged = bump.take<int>(4);
         km.order = bump.take<int>((size_t)N);
         km.offs = bump.take<int>((size_t)kmax);
-        km.part = bump.take<long long>(kmeans_partial_elems(N, kmax, h.d, h.by_members));
+        km.part = bump.take<long long>(kmeans_partial_elems(N, kmax, h.d, h.by_members || h.hier_levels > 1, !h.by_members || h.hier_levels > 1));
         km.assign = bump.take<int32_t>((size_t)N);
         km.cn = bump.take<float>((size_t)kmax);
         km.ct = bump.take<char>(2 * split_plane_bytes(kmax, h.d));
@@ -252,27 +255,35 @@ lcn_status check_params(long long n, long long m, int d, int dtype, float lambda
 // Flat k-means runs (landmarks, one per hash round) that advance together, a launch for all of them: how many, or 0 where
 // each goes on a lane of its own (see Builder).  Together means a third of the launches, which is what bounds the
 // smallest builds; on their own the runs fill the chip beside each other and the factors start when the landmarks are there,
-// not when the last hash round is.  So together up to 2^14 points, where a launch of one run leaves half of the compute units
-// without a workgroup, and only where the factors are short: up to 64 landmarks the inverse is a single block.  How far that
-// holds depends on the scores of an iteration (points x padded dimensions x clusters of all runs); with more points it
-// pays only for two runs of very few scores.  Build times in us, together / on their own (points, dimensions, landmarks +
-// rounds x buckets):
-//   2048, 16, 64 + 16: 400 / 470                10 000, 100, 2 x 100: 512 / 598       16 200, 24, 2 x 350: 618 / 649
-//   10 000, 300, 64 + 2 x 130: 894 / 941        13 000, 300, 2 x 300: 1010 / 1075     16 000, 200, 3 x 300: 1048 / 1055
-//   13 000, 300, 64 + 2 x 200: 1002 / 975       16 000, 300, 4 x 400: 1650 / 1625     16 000, 200, 64 + 2 x 230: 890 / 855
-//   30 000, 32, 64 + 100: 600 / 631             60 000, 16, 50 + 100: 785 / 812       60 000, 64, 64 + 100: 898 / 856
-//   20 000, 16, 2 x 430: 718 / 680              40 000, 16, 64 + 2 x 100: 784 / 763   60 000, 50, 64 + 2 x 100: 1128 / 1040
-//   6000, 16, 128 + 32: 574 / 527               40 000, 300, 128 + 2 x 512: 2400 / 2110
+// not when the last hash round is.  Build times in us, together / on their own (points, dimensions, landmarks + rounds x
+// buckets):
+//   more rounds than lanes, so that some lane has to take two of them one after the other
+//     8000, 200, 5 x 2000: 3440 / 4900            18 000, 100, 64 + 4 x 200: 1000 / 1270     40 000, 300, 256 + 8 x 200: 4670 / 5100
+//     60 000, 64, 5 x 100: 1390 / 1520            100 000, 64, 64 + 4 x 100: 2500 / 2630     120 000, 32, 32 + 8 x 64: 6120 / 6400
+//   up to 2^14 points, where a launch of one run leaves half of the compute units without a workgroup, and up to 64
+//   landmarks, whose factors are short (the inverse is a single block); with landmarks only while an iteration has few scores
+//   (points x padded dimensions x clusters of all runs)
+//     2048, 16, 64 + 16: 400 / 470                10 000, 100, 2 x 100: 512 / 598            16 200, 24, 2 x 350: 618 / 649
+//     10 000, 300, 64 + 2 x 130: 894 / 941        13 000, 300, 2 x 300: 1010 / 1075          16 000, 300, 4 x 400: 1650 / 1625
+//     13 000, 300, 64 + 2 x 200: 1002 / 975       16 000, 200, 64 + 2 x 230: 890 / 855       12 000, 300, 64 + 3 x 600: 2050 / 1920
+//     6000, 16, 128 + 32: 574 / 527               40 000, 300, 128 + 2 x 512: 2400 / 2110
+//   up to 2^15 points, or two runs, and very few scores
+//     20 000, 8, 64 + 2 x 64: 539 / 576           24 000, 16, 2 x 100: 502 / 553             32 000, 8, 3 x 100: 606 / 660
+//     30 000, 32, 64 + 100: 600 / 631             60 000, 16, 50 + 100: 785 / 812            60 000, 64, 64 + 100: 898 / 856
+//     20 000, 16, 2 x 430: 718 / 680              40 000, 16, 64 + 2 x 100: 784 / 763        60 000, 50, 64 + 2 x 100: 1128 / 1040
 constexpr long long KM_MERGE_POINTS = 1ll << 14;
-int merged_runs(const Handle &h, long long clusters)
+int merged_runs(const Handle &h, long long scores, bool more_than_lanes)
 {
     const bool kmeans_hash = h.hash == LCN_HASH_KMEANS;
     const int runs = (h.l > 0 ? 1 : 0) + (kmeans_hash ? h.R : 0);
     if (runs == 0 || (kmeans_hash && h.hier_levels > 1)) return 0;
     if (runs == 1) return 1;   // nothing goes beside it: no thread and no lane but the first
-    const long long N = h.n + h.m, scores = N * ((h.d + 15) / 16 * 16) * clusters;
-    const long long most = N <= KM_MERGE_POINTS ? (h.l > 0 ? 1ll << 30 : 3ll << 30) : runs == 2 && h.l > 0 ? 1ll << 28 : 0;
-    return h.by_members && h.l <= 64 && scores <= most ? runs : 0;
+    if (!h.by_members) return 0;
+    if (more_than_lanes) return runs;
+    if (h.l > 64) return 0;
+    const long long N = h.n + h.m;
+    if (N <= KM_MERGE_POINTS && (h.l == 0 || scores <= 1ll << 30)) return runs;
+    return scores <= 1ll << 28 && (N <= 2 * KM_MERGE_POINTS || (runs == 2 && h.l > 0)) ? runs : 0;
 }
 
 void fill_shape(Handle &h, long long n, long long m, int d, int mode, const lcn_landmark_params *lm,
@@ -306,9 +317,13 @@ void fill_shape(Handle &h, long long n, long long m, int d, int mode, const lcn_
         h.b = 1;
         h.hash = -1;
     }
-    const long long clusters = h.l + (h.hash == LCN_HASH_KMEANS ? (long long)h.R * h.b : 0);
-    h.by_members = kmeans_by_members(n + m, clusters, d);
-    h.merged_runs = merged_runs(h, clusters);
+    const long long N = n + m;
+    const bool hashing = h.hash == LCN_HASH_KMEANS;
+    // (of a hierarchical hash: the clusters of its first level)
+    const long long clusters = h.l + (long long)h.R * (!hashing ? 0 : h.hier_levels > 1 ? lsh->branching[0] : h.b);
+    const bool more_than_lanes = hashing && h.hier_levels <= 1 && N <= 1ll << 17 && h.R > round_lanes(h);
+    h.by_members = kmeans_by_members(N, clusters, d, more_than_lanes);
+    h.merged_runs = merged_runs(h, N * ((d + 15) / 16 * 16) * clusters, more_than_lanes);
 }
 
 #define HIPCHK(expr)                         \
@@ -478,7 +493,7 @@ lcn_status run_hier_kmeans(Handle &h, Scratch &sc, KmScratch &km, hipStream_t s,
         HIPCHK(hipMemsetAsync(km.cursor2, 0, 2 * sizeof(int) * (size_t)k, s));
         KmRuns runs{};
         runs.count = 1;
-        runs.by_members = h.by_members;
+        runs.by_members = kmeans_by_members(N, h.l + (long long)h.R * k, h.d, false);
         runs.run[0] = kmeans_run(h, km, (int)k, km.cent, dst);
         runs.run[0].first = nullptr;
         runs.run[0].keep_counts = 1;
@@ -620,8 +635,7 @@ struct Builder {
     // no hash round left on any lane when the factors are enqueued: the buckets need not wait for those
     bool buckets_early() const { return merged() && (kmeans_hashing() || h.R == 0); }
     bool kmeans_hashing() const { return uses_lsh(mode) && h.hash == LCN_HASH_KMEANS; }
-    // the landmarks and the factors keep lane 0 to themselves
-    int lane_of_round(int r) const { return h.l > 0 ? 1 + r % (KM_LANES - 1) : r % KM_LANES; }
+    int lane_of_round(int r) const { return KM_LANES - round_lanes(h) + r % round_lanes(h); }
 
     // Inputs into the workspace (fp32 points, norms, bf16 planes, marginals), seeded starts to the
     // device in one copy, lanes forked.

@@ -122,9 +122,10 @@ hipError_t launch_assign_crosspolytope(const float *Z, long long N, int d, const
 // New centroids from the assignments; several runs only where the update is by members.  `parity`
 // alternates from update to update.
 hipError_t launch_kmeans_update(const float *Z, long long N, int d, const KmRuns &runs, int parity, hipStream_t s);
-// clusters: of all k-means runs of the build together
-bool kmeans_by_members(long long N, long long clusters, int d);
-size_t kmeans_partial_elems(long long N, int kmax, int d, bool by_members);
+// clusters: of all k-means runs that are under way together
+bool kmeans_by_members(long long N, long long clusters, int d, bool more_than_lanes);
+// room for the partial sums of an update by members, of a sorted one, or of either
+size_t kmeans_partial_elems(long long N, int kmax, int d, bool members, bool sorted);
 
 struct SortBuffers {
     int R, b;
@@ -209,7 +210,7 @@ struct Handle {
     int in_dtype;              // storage type X and Y were given in
     int hier_levels;           // levels of hierarchical k-means hashing (0 or 1: flat)
     int merged_runs;           // k-means runs that advance together (0: each on its own)
-    int by_members;            // how k-means updates its centroids (kmeans_by_members)
+    int by_members;            // how flat k-means runs update their centroids (kmeans_by_members)
     int and_width;             // hashes per band of cross-polytope hashing (AND construction)
     int log_domain;            // kernel without signed parts (sparse, dense): values and vectors are logs
     double lambda, ridge;

@@ -136,21 +136,36 @@ def test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds
     assert torch.equal(got["0"][0], got["1"][0]) and torch.equal(got["0"][1], got["1"][1])
 
 
-# up to 2^14 points and 64 landmarks together, above either each run on its own, but for two runs of few scores; by
-# members up to 2^26 clusters times points of all runs
+# runs together up to 2^14 points and 64 landmarks (few scores), up to 2^15 or as two runs (very few), as more rounds than
+# lanes; otherwise each on its own.  Centroids by members up to 2^26 clusters times points of all runs, twice that with
+# more rounds than lanes, always up to 2^14 points
 @pytest.mark.parametrize("n,m,d,landmarks,buckets,rounds", [
-    (8192, 8192, 5, 64, 33, 2),      # the most points that advance together
+    (8192, 8192, 130, 64, 100, 2),   # the most points that advance together
+    (8192, 8193, 130, 64, 100, 2),   # one point more
     (8192, 8192, 5, 65, 33, 2),      # one landmark more
-    (8192, 8193, 5, 64, 33, 2),      # one point more
-    (8192, 8193, 5, 64, 33, 1),      # the same, two runs
     (8000, 7999, 130, 64, 300, 2),   # few points, many scores
+    (16384, 16384, 5, 64, 33, 2),    # very few scores
+    (16384, 16385, 5, 64, 33, 2),    # ... and one point more
+    (16384, 16385, 5, 64, 33, 1),    # the same, two runs
+    (3000, 3001, 40, 70, 50, 4),     # more rounds than lanes
+    (20000, 20001, 3, 20, 300, 5),
+    (20000, 20000, 3, 20, 700, 5),   # ... above 2^27: sorted
     (10000, 10000, 3, 1, 1118, 3),   # just below 2^26
     (10000, 10000, 3, 2, 1118, 3),   # just above: sorted
+    (8000, 8000, 3, 5, 1500, 3),     # few points: by members all the same
     (400, 390, 640, 64, 65, 2),      # rows of more than 512 dimensions: 64 centroids at a time, 256
     (400, 390, 515, 3, 64, 1),       # ... and a last piece of three dimensions
 ])
 def test_runs_together_or_apart(monkeypatch, n, m, d, landmarks, buckets, rounds):
     test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds)
+
+
+def test_hierarchical_levels_by_members_and_sorted():
+    """Three levels of 15, 225 and 3600 clusters: the last has too many for 20 001 points to be updated by members."""
+    from parity import compare
+    p = _cut(10000, 10001, 3, 8, 3600, 1, 4)
+    p.branching = (15, 15, 16)
+    print("hierarchical", compare(p, "sparse"), flush=True)
 
 
 @pytest.mark.parametrize("members", [1, 15, 16, 17, 33, 48, 63, 64, 65, 130])
