@@ -65,7 +65,7 @@ std::vector<long long> seeded_indices(uint64_t seed, long long N, int k)
 bool uses_landmarks(int mode) { return mode == LCN_MODE_NYSTROM || mode == LCN_MODE_LCN; }
 bool uses_lsh(int mode) { return mode == LCN_MODE_SPARSE || mode == LCN_MODE_LCN; }
 
-constexpr int REPORT_FAIL = 16, REPORT_TOTALS = 18, REPORT_WORDS = 24;   // 64-bit words behind h.counters
+constexpr int REPORT_FAIL = 16, REPORT_TOTALS = 18, REPORT_UNDECIDED = 22, REPORT_WORDS = 24;   // 64-bit words behind h.counters
 
 constexpr int KM_LANES = 4;   // k-means runs of a build that may be in flight together on streams of their own
 
@@ -106,7 +106,8 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
     h.zn = bump.take<double>((size_t)N);
     h.a = bump.take<float>((size_t)h.n);
     h.b_marg = bump.take<float>((size_t)h.m);
-    // counters, a singular landmark matrix, the pattern's totals: what a build reports to the host lies together
+    // counters, a singular landmark matrix, the pattern's totals, the undecided points of the last k-means run: what a build
+    // reports to the host lies together
     h.counters = bump.take<unsigned long long>(REPORT_WORDS);
     sc.fail_flag = (int *)(h.counters + REPORT_FAIL);
     sc.totals = (long long *)(h.counters + REPORT_TOTALS);
@@ -400,7 +401,7 @@ lcn_status run_kmeans(Handle &h, Scratch &sc, hipStream_t s, const KmRuns &all, 
             HIPCHK(hipMemsetAsync(r.nflagged, 0, 2 * sizeof(int), s));
         }
         if (T[q] > 0 && sorted)   // member counts and cursors lie side by side
-            HIPCHK(hipMemsetAsync(r.counts2, 0, (size_t)((char *)r.nflagged - (char *)r.counts2), s));
+            HIPCHK(hipMemsetAsync(r.counts2, 0, (size_t)((char *)(r.cursor2 + 2 * r.k) - (char *)r.counts2), s));
     }
     if (start.count > 0) HIPCHK(launch_kmeans_start(h.Z, h.d, start, s));
     for (int it = 0; it < most; ++it) {
@@ -601,7 +602,6 @@ struct Builder {
     hipEvent_t join[KM_LANES] = {}, extra[2] = {};
     std::thread threads[KM_LANES];
     lcn_status thread_status[KM_LANES];
-    const int *last_nflagged = nullptr;   // the undecided counts of the build's last k-means run
     int device_id = 0;
 
     Builder(Handle &handle, const lcn_landmark_params *lm_, const lcn_lsh_params *lsh_, int cost_, int mode_)
@@ -677,6 +677,10 @@ struct Builder {
             if (lm_sample) starts_landmarks = sc.starts;
             if (flat_rounds) starts_rounds = sc.starts + rounds_at;
         }
+        if (h.l > 0 || kmeans_hashing()) {   // the last run's undecided counts go straight into the report
+            const int last = merged() ? h.merged_runs - 1 : kmeans_hashing() ? lane_of_round(h.R - 1) : 0;
+            sc.km[last].nflagged = (int *)(h.counters + REPORT_UNDECIDED);
+        }
         if (forked) {
             HIPCHK(hipEventRecord(h.ev1, h.stream));
             for (int q = 0; q < KM_LANES; ++q) {
@@ -745,7 +749,6 @@ struct Builder {
         const lcn_status st = run_kmeans(h, sc, lane[0], runs, T);
         if (st != LCN_OK) return st;
         lane_used[0] = true;
-        last_nflagged = runs.run[runs.count - 1].nflagged;
         if (forked && buckets_early()) {   // the caller's stream goes on with the buckets, lane 0 with the factors
             HIPCHK(hipEventRecord(join[1], lane[0]));
             HIPCHK(hipStreamWaitEvent(h.stream, join[1], 0));
@@ -764,7 +767,6 @@ struct Builder {
         }
         if (!uses_lsh(mode) || (merged() && kmeans_hashing())) return LCN_OK;
         for (int r = 0; r < h.R; ++r) lane_used[lane_of_round(r)] = true;
-        if (kmeans_hashing() && h.R > 0) last_nflagged = sc.km[lane_of_round(h.R - 1)].nflagged;
         const bool threaded = forked && kmeans_hashing();
         for (int q = 0; q < KM_LANES; ++q) {
             bool has_round = false;
@@ -802,7 +804,6 @@ struct Builder {
                                          starts_landmarks, lm->init, lm->init_centroids);
         if (st != LCN_OK) return st;
         lane_used[0] = true;
-        if (!last_nflagged) last_nflagged = sc.km[0].nflagged;
         return LCN_OK;
     }
 
@@ -851,9 +852,8 @@ struct Builder {
     // lane 0 holds the landmarks and the factors only
     bool factors_apart() const { return forked && h.l > 0; }
 
-    // Buckets -> blocks (bucket sort, per-row metadata); the host learns the pair count, the
-    // undecided-point count and the input-range flag (the build's one wait for the device) and lays
-    // out the sparse values.
+    // Buckets -> blocks (bucket sort, per-row metadata); the host learns the pair count and the
+    // input-range flag (the build's one wait for the device) and lays out the sparse values.
     lcn_status structure(size_t *bytes_needed)
     {
         join_threads();
@@ -874,7 +874,6 @@ struct Builder {
         HIPCHK(hipEventSynchronize(h.ev0));
         if (report[4] && (h.l > 0 || h.hash == LCN_HASH_KMEANS)) return LCN_ERR_INVALID_ARG;  // |x| >= 2^10 or not finite
         h.nnz_stored = h.R > 0 ? (long long)report[REPORT_TOTALS] : 0;
-        h.undecided = last_nflagged;
         h.ntiles = h.R > 0 ? (int)report[REPORT_TOTALS + 1] : 0;
 
         // slack: a sweep reads whole wavefront-wide chunks, several at a time, and masks the excess (record_reach.h)
@@ -914,6 +913,7 @@ struct Builder {
         HIPCHK(hipStreamSynchronize(h.stream));
         if ((int)(report[REPORT_FAIL] & 0xffffffffull)) return LCN_ERR_SINGULAR;
         h.nnz_unique = (long long)report[3];
+        h.undecided_last = (long long)(report[REPORT_UNDECIDED] & 0xffffffffull) + (long long)(report[REPORT_UNDECIDED] >> 32);
         return LCN_OK;
     }
 };
@@ -1282,9 +1282,7 @@ lcn_status lcn_get_info(lcn_handle hh, lcn_info *info)
     if (!info) return LCN_ERR_INVALID_ARG;
     Handle &h = *(Handle *)hh;
     unsigned long long c[6];
-    int undecided[2] = {0, 0};  // points sent to the exact rule over all centroids, and over two
     HIPCHK(hipMemcpyAsync(c, h.counters, sizeof(c), hipMemcpyDeviceToHost, h.stream));
-    if (h.undecided) HIPCHK(hipMemcpyAsync(undecided, h.undecided, sizeof(undecided), hipMemcpyDeviceToHost, h.stream));
     HIPCHK(hipStreamSynchronize(h.stream));
     if (c[5]) return LCN_ERR_DEVICE;  // a sweep gave up waiting for its totals
     info->n = h.n;
@@ -1299,7 +1297,7 @@ lcn_status lcn_get_info(lcn_handle hh, lcn_info *info)
     info->empty_rows = (int64_t)c[1];
     info->empty_cols = (int64_t)c[2];
     info->workspace_used = h.ws_used;
-    info->undecided_last = (int64_t)undecided[0] + undecided[1];
+    info->undecided_last = h.undecided_last;
     return LCN_OK;
 }
 

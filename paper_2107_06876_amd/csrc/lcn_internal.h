@@ -227,7 +227,7 @@ struct Handle {
     int32_t *bucket;   // [R][n+m]
     SortBuffers sort;
     long long nnz_stored, nnz_unique;
-    const int *undecided;      // device: points the last assignment of the last k-means run left to the exact rule (null: none)
+    long long undecided_last;  // points the last assignment of the last k-means run left to the exact rule
     int ntiles;
     // factors
     float *U;          // n x lp

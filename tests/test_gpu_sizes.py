@@ -160,6 +160,22 @@ def test_runs_together_or_apart(monkeypatch, n, m, d, landmarks, buckets, rounds
     test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds)
 
 
+def test_undecided_points_are_those_of_the_last_run():
+    """What lcn_get_info reports belongs to the last hash round, however the runs advance: together, each on its own, with
+    and without landmarks beside them."""
+    import paper_2107_06876_amd as lcn
+    from parity import gpu_build
+    p = _cut(3000, 3001, 7, 64, 40, 3, 1, kmeans_iters=3)
+    p.X, p.Y = np.round(2 * p.X).astype(np.float32), np.round(2 * p.Y).astype(np.float32)   # ties
+    got = []
+    for mode, landmarks, rounds in (("lcn", 64, 3), ("lcn", 65, 3), ("sparse", 64, 3), ("lcn", 64, 2), ("sparse", 64, 2)):
+        p.num_landmarks, p.num_rounds = landmarks, rounds
+        h = gpu_build(p, mode)
+        got.append(lcn.lcn_get_info(h).undecided_last)
+        lcn.lcn_destroy(h)
+    assert got[0] == got[1] == got[2] > 0 and got[3] == got[4] > 0
+
+
 def test_hierarchical_levels_by_members_and_sorted():
     """Three levels of 15, 225 and 3600 clusters: the last has too many for 20 001 points to be updated by members."""
     from parity import compare
