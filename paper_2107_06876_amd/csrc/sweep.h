@@ -260,7 +260,7 @@ static void launch_sweep_rows(const PassSide &S, const Handle &h, int mode, cons
     else if (mode == PASS_UPDATE)
         hipLaunchKernelGGL((pass_kernel<T, RR, RG, 1, PASS_UPDATE, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else if (mode == PASS_QUERY)
-        hipLaunchKernelGGL((pass_kernel<T, RR, 3, 1, PASS_QUERY, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
+        hipLaunchKernelGGL((pass_kernel<T, RR, RG == 1 ? 1 : 3, 1, PASS_QUERY, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
     else
         hipLaunchKernelGGL((pass_kernel<T, 1, 3, 1, PASS_INIT, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
 }
