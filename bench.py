@@ -61,8 +61,12 @@ def _omp_threads(n=None):
         return int(os.environ.get("OMP_NUM_THREADS", "0")) or os.cpu_count()
 
 
+def half_iteration(landmarks: int):
+    return ("long_pass_kernel" if landmarks > 256 else "pass_kernel") + " (one half-iteration)"
+
+
 def counter_traffic(config: int):
-    """HBM bytes per pass_kernel launch from the counter table of the profile summary of this
+    """HBM bytes per launch of the half-iteration from the counter table of the profile summary of this
     configuration (scaled read MB + scaled write MB of the fused update sweep), or None."""
     import glob
     import re
@@ -170,7 +174,7 @@ def timed_run(config: int, mode_name: str, steps: int, warmup: int):
     return {"workload": wl, "steps": steps, "warmup": warmup, "value": p.iters / (run_mean * 1e-3),
             "unit": "iterations/s", "ms_per_step": ms_per_step, "build_ms": float(np.mean(build_ms)),
             "sinkhorn_ms": run_mean, "distance": dist, "nnz_unique": info.nnz_unique,
-            "roofline": {"bound": "hbm", "kernel": "pass_kernel (one half-iteration)", "achieved": achieved,
+            "roofline": {"bound": "hbm", "kernel": half_iteration(info.l), "achieved": achieved,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                          "traffic": counter_traffic(config), "bytes_per_launch": bytes_launch,
                          "launch_us": launch_us}}
@@ -413,7 +417,7 @@ def main():
     bytes_launch = bytes_iter / 2.0
     launch_us = run_mean * 1e3 / max(n_launch, 1)
     achieved = bytes_launch / (launch_us * 1e-6) / 1e9
-    # HBM bytes per pass_kernel launch from the rocprofv3 counter runs (FETCH_SIZE scaled by 2.000 plus
+    # HBM bytes per launch from the rocprofv3 counter runs (FETCH_SIZE scaled by 2.000 plus
     # WRITE_SIZE scaled by 1.000 against a 256 MiB device copy); see profiles/lcn_sinkhorn_c*.md
     traffic = counter_traffic(args.config) if args.mode == "lcn" else None
     out = {
@@ -424,7 +428,7 @@ def main():
         "config": {"workload": wl, "mode": args.mode, "iters": p.iters, "nnz_unique": nnz_unique,
                    "nnz_stored": nnz_stored},
         "build_ms": float(np.mean(build_ms)), "sinkhorn_ms": run_mean, "distance": dist,
-        "roofline": {"bound": "hbm", "kernel": "pass_kernel (one half-iteration)", "achieved": achieved,
+        "roofline": {"bound": "hbm", "kernel": half_iteration(l), "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "bytes_per_launch": bytes_launch, "launch_us": launch_us},
     }

@@ -462,7 +462,7 @@ __device__ inline void reduce_publish(const FuseArgs &Fz, int lp, double *red)
 
 // Up to 64 factor columns and 64 partial sums: every workgroup takes the totals for itself (at most 34 KB from the
 // cache) and nothing has to be handed over: a store, a trip through memory and the wait for it less per sweep (1024
-// rows: 5.8 us instead of 6.5).  With 256 partial sums, 137 KB, it is the slower way (50 000 rows: 8.9 against 8.5).
+// rows: 5.5 us instead of 6.2).  With 256 partial sums, 137 KB, it is the slower way (50 000 rows: 8.9 against 8.5).
 // Wavefront w has the rows g % 16 == w, a lane a column; all loads are requested at once, before the workgroup's own
 // rows are.  The exponents exist twice (shift_other is read by every workgroup, shift_next written by one).
 constexpr int DIRECT_GROUPS = 64;

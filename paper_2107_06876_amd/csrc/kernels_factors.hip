@@ -889,30 +889,30 @@ __global__ __launch_bounds__(256, DERIV ? 2 : 3) void correction_kernel(SortBuff
         }
         return;
     } else {
-    // drop pairs an earlier round owns, count the rest
-    unsigned mine = 0;
+        // drop pairs an earlier round owns, count the rest
+        unsigned mine = 0;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        if ((e >> 2) >= pieces.count) continue;   // the same in every lane
-                const int li = pieces.row(e), lj = pieces.col(e);
-        bool present = xi[li] >= 0 && yj[lj] >= 0;
-        bool dup = false;
-        for (int q = 0; q < r; ++q) dup |= bx[q][li] == by[q][lj];
-        const double value = !present || dup ? (log_values ? -INFINITY : 0.0) : -acc.get(e);
-        if (present && !dup) ++mine;
-        vals[li][lj] = (float)value;
-    }
-    atomicAdd(&cnt_sh, mine);
-    __syncthreads();
-    if (tid == 0) atomicAdd(unique_counter, (unsigned long long)cnt_sh);
-    // write the piece into the row records of X and of Y, coalesced along each record
-    const int lane = tid & 63, w = tid >> 6;
-    for (int rr = w; rr < TILE; rr += 4) {
-        const int lj = tj * 64 + lane;
-        if (xdst[rr] >= 0 && lj < ny) vals_x[xdst[rr] + lj] = vals[rr][lane];
-        const int li = ti * 64 + lane;
-        if (ydst[rr] >= 0 && li < nx) vals_y[ydst[rr] + li] = vals[lane][rr];
-    }
+        for (int e = 0; e < 16; ++e) {
+            if ((e >> 2) >= pieces.count) continue;   // the same in every lane
+            const int li = pieces.row(e), lj = pieces.col(e);
+            bool present = xi[li] >= 0 && yj[lj] >= 0;
+            bool dup = false;
+            for (int q = 0; q < r; ++q) dup |= bx[q][li] == by[q][lj];
+            const double value = !present || dup ? (log_values ? -INFINITY : 0.0) : -acc.get(e);
+            if (present && !dup) ++mine;
+            vals[li][lj] = (float)value;
+        }
+        atomicAdd(&cnt_sh, mine);
+        __syncthreads();
+        if (tid == 0) atomicAdd(unique_counter, (unsigned long long)cnt_sh);
+        // write the piece into the row records of X and of Y, coalesced along each record
+        const int lane = tid & 63, w = tid >> 6;
+        for (int rr = w; rr < TILE; rr += 4) {
+            const int lj = tj * 64 + lane;
+            if (xdst[rr] >= 0 && lj < ny) vals_x[xdst[rr] + lj] = vals[rr][lane];
+            const int li = ti * 64 + lane;
+            if (ydst[rr] >= 0 && li < nx) vals_y[ydst[rr] + li] = vals[lane][rr];
+        }
     }
 }
 

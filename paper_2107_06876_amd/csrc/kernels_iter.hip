@@ -425,8 +425,8 @@ int pass_grid(const Handle &h)
 }
 
 // Rows a wavefront takes at a time in a sweep with a sparse part: as many as give every wavefront of the chip one
-// group (up to five), else three or five, whichever comes to fewer rows per wavefront.  1024 rows: one 5.6 us, two
-// 5.9, three 6.2; 10 000 rows of 128 entries: two 13.6, three 11.6, five 13.6; 20 000 rows of 256: two 15.1, three
+// group (up to five), else three or five, whichever comes to fewer rows per wavefront.  1024 rows: one 5.5 us, two
+// 5.8, three 6.1; 10 000 rows of 128 entries: two 13.6, three 11.6, five 13.6; 20 000 rows of 256: two 15.1, three
 // 13.8, five 13.3 (eight spill).
 int rows_at_a_time(const Handle &h, long long rows)
 {

