@@ -96,6 +96,20 @@ struct Scratch {  // build-only buffers
     KmScratch km[KM_MAX_RUNS];   // one per lane, or one per run where all runs advance together
 };
 
+// Flat k-means runs of a build: the landmarks', one per hash round (0: there are others).
+int flat_runs(const Handle &h)
+{
+    const bool kmeans_hash = h.hash == LCN_HASH_KMEANS;
+    return kmeans_hash && h.hier_levels > 1 ? 0 : (h.l > 0 ? 1 : 0) + (kmeans_hash ? h.R : 0);
+}
+
+// Whether each of them alone would be updated by members.
+bool one_by_members(const Handle &h)
+{
+    const int b = h.hash == LCN_HASH_KMEANS ? h.b : 0;
+    return flat_runs(h) > 0 && kmeans_by_members(h.n + h.m, h.l > b ? h.l : b, h.d, false);
+}
+
 // Lays out everything except the sparse values.  With bump.dry only sizes are
 // computed.
 void layout(Handle &h, Bump &bump, Scratch &sc)
@@ -128,7 +142,7 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
         km.nflagged = bump.take<int>(4);
         km.order = bump.take<int>((size_t)N);
         km.offs = bump.take<int>((size_t)kmax);
-        km.part = bump.take<long long>(kmeans_partial_elems(N, kmax, h.d, h.by_members || h.hier_levels > 1, !h.by_members || h.hier_levels > 1));
+        km.part = bump.take<long long>(kmeans_partial_elems(N, kmax, h.d, h.by_members || one_by_members(h) || h.hier_levels > 1, !h.by_members || h.hier_levels > 1));
         km.assign = bump.take<int32_t>((size_t)N);
         km.cn = bump.take<float>((size_t)kmax);
         km.ct = bump.take<char>(2 * split_plane_bytes(kmax, h.d));
@@ -253,7 +267,7 @@ lcn_status check_params(long long n, long long m, int d, int dtype, float lambda
     return LCN_OK;
 }
 
-// Flat k-means runs (landmarks, one per hash round) that advance together, a launch for all of them: how many, or 0 where
+// Flat k-means runs that advance together, a launch for all of them: how many, or 0 where
 // each goes on a lane of its own (see Builder).  Together means a third of the launches, which is what bounds the
 // smallest builds; on their own the runs fill the chip beside each other and the factors start when the landmarks are there,
 // not when the last hash round is.  Build times in us, together / on their own (points, dimensions, landmarks + rounds x
@@ -275,10 +289,8 @@ lcn_status check_params(long long n, long long m, int d, int dtype, float lambda
 constexpr long long KM_MERGE_POINTS = 1ll << 14;
 int merged_runs(const Handle &h, long long scores, bool more_than_lanes)
 {
-    const bool kmeans_hash = h.hash == LCN_HASH_KMEANS;
-    const int runs = (h.l > 0 ? 1 : 0) + (kmeans_hash ? h.R : 0);
-    if (runs == 0 || (kmeans_hash && h.hier_levels > 1)) return 0;
-    if (runs == 1) return 1;   // nothing goes beside it: no thread and no lane but the first
+    const int runs = flat_runs(h);
+    if (runs <= 1) return runs;   // nothing goes beside it: no thread and no lane but the first
     if (!h.by_members) return 0;
     if (more_than_lanes) return runs;
     if (h.l > 64) return 0;
@@ -631,7 +643,8 @@ struct Builder {
         for (int q = 0; q < KM_LANES; ++q)
             if (threads[q].joinable()) threads[q].join();
     }
-    bool merged() const { return h.merged_runs > 0 && !h.exact_assign_only; }
+    int together = 0;   // k-means runs that advance together
+    bool merged() const { return together > 0; }
     // no hash round left on any lane when the factors are enqueued: the buckets need not wait for those
     bool buckets_early() const { return merged() && (kmeans_hashing() || h.R == 0); }
     bool kmeans_hashing() const { return uses_lsh(mode) && h.hash == LCN_HASH_KMEANS; }
@@ -646,6 +659,13 @@ struct Builder {
         lane[KM_LANES - 1] = h.stream;
         if (!forked)
             for (int q = 0; q < KM_LANES; ++q) lane[q] = h.stream;
+        together = h.merged_runs;
+        if (!forked && together == 0 && one_by_members(h) && flat_runs(h) <= KM_LANES) {
+            // without lanes no run goes beside another: together if they may (there is scratch for KM_LANES of them)
+            together = flat_runs(h);
+            h.by_members = 1;
+        }
+        if (h.exact_assign_only) together = 0;
         HIPCHK(hipEventCreate(&h.ev0));
         HIPCHK(hipEventCreate(&h.ev1));
         ClearRegions cl{};
@@ -678,7 +698,7 @@ struct Builder {
             if (flat_rounds) starts_rounds = sc.starts + rounds_at;
         }
         if (h.l > 0 || kmeans_hashing()) {   // the last run's undecided counts go straight into the report
-            const int last = merged() ? h.merged_runs - 1 : kmeans_hashing() ? lane_of_round(h.R - 1) : 0;
+            const int last = merged() ? together - 1 : kmeans_hashing() ? lane_of_round(h.R - 1) : 0;
             sc.km[last].nflagged = (int *)(h.counters + REPORT_UNDECIDED);
         }
         if (forked) {

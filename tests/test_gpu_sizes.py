@@ -160,6 +160,15 @@ def test_runs_together_or_apart(monkeypatch, n, m, d, landmarks, buckets, rounds
     test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds)
 
 
+@pytest.mark.parametrize("n,m,d,landmarks,buckets,rounds", [
+    (8192, 8193, 130, 64, 100, 2), (3000, 3001, 40, 70, 50, 3), (3000, 3001, 40, 70, 50, 5), (70000, 70001, 2, 30, 60, 1),
+    (10000, 10000, 3, 2, 1118, 3),
+])
+def test_runs_without_streams_of_their_own(monkeypatch, n, m, d, landmarks, buckets, rounds):
+    monkeypatch.setenv("LCN_BUILD_OVERLAP", "0")
+    test_kmeans_ranges_and_runs(monkeypatch, n, m, d, landmarks, buckets, rounds)
+
+
 def test_undecided_points_are_those_of_the_last_run():
     """What lcn_get_info reports belongs to the last hash round, however the runs advance: together, each on its own, with
     and without landmarks beside them."""
