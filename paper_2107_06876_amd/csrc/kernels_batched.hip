@@ -19,7 +19,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <vector>
+#include <type_traits>
 
 #include "iter_common.h"   // cross-lane sums and maxima through the DPP data path
 #include "lcn_internal.h"
@@ -996,15 +996,15 @@ struct HostBlock {
 };
 constexpr size_t HOST_BLOCKS = 8, HOST_BYTES = (size_t)16 << 20;
 
+// Room for them all from the start, so that nothing here allocates on the host, and nothing to do when the process ends: the
+// runtime may be gone by then.
 struct HostPool {
     std::mutex mu;
-    std::vector<HostBlock> idle;
+    size_t count;
+    HostBlock idle[HOST_BLOCKS];
 };
-static HostPool &host_pool()
-{
-    static HostPool *pool = new HostPool;   // never destroyed: the runtime may be gone by then
-    return *pool;
-}
+static_assert(std::is_trivially_destructible<HostPool>::value, "blocks are not given back at the end of the process");
+static HostPool host_pool;
 
 static void free_host_block(HostBlock &b)
 {
@@ -1020,17 +1020,16 @@ static hipError_t take_host_block(size_t bytes, HostBlock &out)
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     {
-        HostPool &pool = host_pool();
+        HostPool &pool = host_pool;
         std::lock_guard<std::mutex> lock(pool.mu);
-        size_t best = pool.idle.size();
-        for (size_t i = 0; i < pool.idle.size(); ++i)
+        size_t best = pool.count;
+        for (size_t i = 0; i < pool.count; ++i)
             if (pool.idle[i].device == dev && pool.idle[i].bytes >= bytes &&
-                (best == pool.idle.size() || pool.idle[i].bytes < pool.idle[best].bytes))
+                (best == pool.count || pool.idle[i].bytes < pool.idle[best].bytes))
                 best = i;
-        if (best < pool.idle.size()) {
+        if (best < pool.count) {
             out = pool.idle[best];
-            pool.idle[best] = pool.idle.back();
-            pool.idle.pop_back();
+            pool.idle[best] = pool.idle[--pool.count];
             return hipSuccess;
         }
     }
@@ -1055,16 +1054,13 @@ static void give_host_block(HostBlock &b)
     if (!b.ptr) return;
     bool kept = false;
     {
-        HostPool &pool = host_pool();
+        HostPool &pool = host_pool;
         std::lock_guard<std::mutex> lock(pool.mu);
         size_t held = b.bytes;
-        for (const HostBlock &i : pool.idle) held += i.bytes;
-        if (pool.idle.size() < HOST_BLOCKS && held <= HOST_BYTES) {
-            try {
-                pool.idle.push_back(b);
-                kept = true;
-            } catch (...) {   // no memory for the list: given back
-            }
+        for (size_t i = 0; i < pool.count; ++i) held += pool.idle[i].bytes;
+        if (pool.count < HOST_BLOCKS && held <= HOST_BYTES) {
+            pool.idle[pool.count++] = b;
+            kept = true;
         }
     }
     if (kept)

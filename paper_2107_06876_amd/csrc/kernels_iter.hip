@@ -507,6 +507,8 @@ static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int
 // and two entries each at a time (a wavefront with four: 6.1; a wavefront per row and a 1024-thread workgroup working
 // through its rows, loads unrolled over four rounds: 6.4); 20 000 rows of 510 values in three rounds 15.2 us with 32
 // lanes and four entries each, 16.3 with sixteen and two, 15.5 with 64 and four (19.6 before).
+// Sixteen lanes / 32: 20 000 rows of 20 values in three rounds 5.5 / 7.7 us, of 27 in four 6.3 / 8.3, of 33 in five 7.7 / 11.0; few rows turn
+// earlier (5000 of 40 in five 5.2 / 4.6).
 // A whole wavefront (four entries per lane) where looking up an entry's round weighs more than lanes without an entry at the
 // record's end: 5000 rows of 420 values in five rounds 5.9 us against 7.5, of 670 in eight 7.3 against 10.3, 20 000 of 250
 // in five 13.6 against 17.0, of 1600 in eight 37 against 57, but 5000 of 65 in eight 5.4 against 5.1; in four rounds 5000 of 1000 7.9 against 9.6, 40 000 of 1600 84
