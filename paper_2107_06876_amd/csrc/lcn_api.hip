@@ -557,6 +557,7 @@ lcn_status init_state(Handle &h, bool clear_logs = false)
     HIPCHK(launch_init_pass(h, 0, 1, clear_logs, h.stream));
     HIPCHK(launch_init_pass(h, 1, 0, clear_logs, h.stream));
     h.fresh = 1;
+    h.dense_backward = 0;
     return LCN_OK;
 }
 

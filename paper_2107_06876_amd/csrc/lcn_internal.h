@@ -189,7 +189,7 @@ hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s);
 constexpr long long DENSE_ITERATION_MIN_PAIRS = 3000000, DENSE_ITERATION_MAX_COLUMNS = 18 * 1024;
 int dense_iteration_groups(long long n, long long m, int cus);
 inline size_t dense_iteration_floats(int groups, long long m) { return groups ? (size_t)(groups + 1) * (size_t)(m + 1) : 0; }
-hipError_t launch_dense_iteration(const PassSide &X, const PassSide &Y, const Handle &h, hipStream_t s);
+hipError_t launch_dense_iteration(const PassSide &X, const PassSide &Y, Handle &h, hipStream_t s);
 int device_compute_units();
 int pass_grid(const Handle &h);
 constexpr int MOST_GROUPS = 2048;   // what pass_grid() gives at most by itself
@@ -245,6 +245,7 @@ struct Handle {
     double *partial2;          // second buffer: consecutive sweeps alternate when the reduction is fused
     float *column_part;        // column sums of a dense iteration and their corrections, (column_groups + 1)(m + 1) floats (null: not used)
     int column_groups;
+    int dense_backward;        // the next dense iteration goes through the rows from the last to the first
     int fused_reduce;          // sweeps add up their predecessor's partial sums themselves
     int fresh;                 // the scalings have not been iterated since they were set: their exponents are stale
     unsigned long long wait_ticks;  // bound of a sweep's wait for its totals, in ticks of the 100 MHz clock (default 0.2 s)
