@@ -22,6 +22,7 @@ SOURCES = {
     "kernels_iter.hip": [],
     "kernels_nystrom.hip": [],
     "kernels_dense.hip": [],
+    "kernels_buckets.hip": [],
     "kernels_batched.hip": ["-ffp-contract=off"],  # bucket rule again
     "lcn_api.hip": [],
     "calibrate.hip": [],

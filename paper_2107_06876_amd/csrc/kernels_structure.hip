@@ -1456,6 +1456,7 @@ __global__ void sort_chunk_prefix_kernel(SortBuffers B)
 __global__ __launch_bounds__(1024) void sort_offsets_kernel(SortBuffers B)
 {
     __shared__ long long wsum[16];
+    __shared__ unsigned long long most[2];
     const int tid = threadIdx.x;
     // per (side, round): exclusive scan of totals over buckets; 2R <= 16 sequences
     for (int sr = 0; sr < 2 * B.R; ++sr) {
@@ -1478,9 +1479,13 @@ __global__ __launch_bounds__(1024) void sort_offsets_kernel(SortBuffers B)
     const int seg = (nb + 1023) / 1024;
     const int lo = tid * seg, hi = lo + seg < nb ? lo + seg : nb;
     long long sum = 0, sum2 = 0;
+    if (tid < 2) most[tid] = 0;
+    __syncthreads();
     for (int i = lo; i < hi; ++i) {
         const long long nx = B.totals[i];
         const long long ny = B.totals[B.R * B.b + i];
+        atomicMax(&most[0], (unsigned long long)bucket_block_bytes((int)nx, (int)ny));
+        atomicMax(&most[1], (unsigned long long)(nx > ny ? nx : ny));
         sum += nx * ny;
         sum2 += ((nx + 63) / 64) * ((ny + 63) / 64);
     }
@@ -1491,6 +1496,8 @@ __global__ __launch_bounds__(1024) void sort_offsets_kernel(SortBuffers B)
         B.tile_off[nb] = (int)all2;
         B.totals_out[0] = all;
         B.totals_out[1] = all2;
+        B.totals_out[2] = (long long)most[0];
+        B.totals_out[3] = (long long)most[1];
     }
     for (int i = lo; i < hi; ++i) {
         const long long nx = B.totals[i];

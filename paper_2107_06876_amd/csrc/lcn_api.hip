@@ -896,6 +896,8 @@ struct Builder {
         if (report[4] && (h.l > 0 || h.hash == LCN_HASH_KMEANS)) return LCN_ERR_INVALID_ARG;  // |x| >= 2^10 or not finite
         h.nnz_stored = h.R > 0 ? (long long)report[REPORT_TOTALS] : 0;
         h.ntiles = h.R > 0 ? (int)report[REPORT_TOTALS + 1] : 0;
+        h.block_bytes = (long long)report[REPORT_TOTALS + 2];
+        h.block_side = (long long)report[REPORT_TOTALS + 3];
 
         // slack: a sweep reads whole wavefront-wide chunks, several at a time, and masks the excess (record_reach.h)
         h.vals_x = bump.take<float>((size_t)h.nnz_stored + VALUE_SLACK);

@@ -93,6 +93,37 @@ def test_a_wavefront_per_row_in_logs(n, m, buckets, rounds):
     print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 12), "sparse"), flush=True)
 
 
+# one round: a workgroup per bucket through the whole run, with 256 threads up to 6 KB a block (32 x 32), 512 up to 24 (72 x 72)
+# or with more than 512 buckets, else 1024, up to 320 rows or columns a block and 160 KB (beyond either a launch per sweep);
+# fewer points on a side than buckets, a single row
+@pytest.mark.parametrize("mode,n,m,buckets,iters", [
+    ("sparse", 32, 33, 1, 9), ("dense", 72, 72, 1, 9), ("sparse", 73, 73, 1, 9), ("sparse", 320, 100, 1, 9),
+    ("dense", 100, 321, 1, 9), ("dense", 9, 320, 1, 9), ("sparse", 192, 192, 1, 9), ("sparse", 193, 193, 1, 9),
+    ("dense", 1, 300, 1, 9), ("sparse", 300, 7, 40, 9), ("sparse", 2500, 2400, 90, 9), ("sparse", 4000, 4100, 33, 9),
+    ("sparse", 9000, 9100, 600, 3), ("sparse", 9000, 9100, 2100, 3)])
+def test_runs_bucket_by_bucket(mode, n, m, buckets, iters):
+    from parity import compare
+    p = _cut(n, m, 4, 8, buckets, 1, iters)
+    p.b[m // 3] = 0    # a point without mass
+    print("buckets", mode, n, m, buckets, compare(p, mode), flush=True)
+
+
+def test_a_run_bucket_by_bucket_in_parts():
+    """The state passes through memory between the launches of a run (4096 iterations each) and between runs without a loss."""
+    import torch
+    import paper_2107_06876_amd as lcn
+    from parity import gpu_build
+    got = []
+    for runs in ([4100], [4, 4096], [1000, 3100]):
+        h = gpu_build(_cut(40, 41, 4, 8, 3, 1, 1), "sparse")
+        for iters in runs:
+            lcn.sinkhorn_run(h, iters)
+        got.append(lcn.lcn_get_scalings(h) + (lcn.transport_cost(h),))
+        lcn.lcn_destroy(h)
+    for other in got[1:]:
+        assert torch.equal(got[0][0], other[0]) and torch.equal(got[0][1], other[1]) and got[0][2] == other[2]
+
+
 # a query in logs: up to 2^22 entries by 512 workgroups, above that by up to 2048, fewer where rows run out
 @pytest.mark.parametrize("n,m,buckets", [(8300, 8301, 8), (8300, 8301, 40), (1800, 1801, 1), (20000, 300, 1)])
 def test_queries_over_many_rows(n, m, buckets):
