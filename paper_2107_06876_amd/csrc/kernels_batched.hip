@@ -64,6 +64,8 @@ __device__ inline unsigned long long splitmix64_dev(unsigned long long &state)
 }
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef int int4_t __attribute__((ext_vector_type(4)));
 
 // The centroids of all k-means runs of a pair (run 0: the landmarks if there are any, then the hash rounds)
 // share tiles of 16 rows; a run starts on a multiple of four and does not straddle tiles.
@@ -86,11 +88,11 @@ __host__ inline void build_rows(BatchDev &D)
 // upper limits: doubles first, then floats, then integers.
 struct BuildLds {
     int zs, ls, rows;   // row length of points / centroids and of the factors; points of the largest pair
-    size_t f, am, sums, pn, rn, z, cent, assign, cnts, start, flags, bytes;
+    size_t f, am, sums, pn, rn, z, cent, mid, assign, cnts, start, flags, bytes;
 };
 
-// dt: tiles of 16 dimensions, waves: wavefronts of the workgroup
-__host__ __device__ inline BuildLds build_lds(int l, int runs, int mt, int dt, int max_points, int waves)
+// dt: tiles of 16 dimensions
+__host__ __device__ inline BuildLds build_lds(int l, int runs, int mt, int dt, int max_points)
 {
     BuildLds L;
     // rows of 16-byte pieces, an odd number of them: the operand reads of a wavefront then spread over the banks
@@ -103,16 +105,16 @@ __host__ __device__ inline BuildLds build_lds(int l, int runs, int mt, int dt, i
         at += (bytes + 15) & ~(size_t)15;
         return here;
     };
-    const int tiles = mt * dt, parts = tiles > 0 && waves > tiles ? waves / tiles : 1;
     // the member sums are done with when the factors are formed: they share their place
-    const size_t f_bytes = l > 0 ? sizeof(double) * L.rows * L.ls : 0, sum_bytes = sizeof(double) * parts * tiles * 256;
+    const size_t f_bytes = l > 0 ? sizeof(double) * L.rows * L.ls : 0, sum_bytes = sizeof(double) * mt * dt * 256;
     L.f = L.sums = take(f_bytes > sum_bytes ? f_bytes : sum_bytes);
     L.am = take(sizeof(double) * l * (l + 1));
     L.pn = take(sizeof(double) * L.rows);
     L.rn = take(sizeof(double) * BL);
     L.z = take(sizeof(float) * L.rows * L.zs);
     L.cent = take(sizeof(float) * 16 * mt * L.zs);
-    L.assign = take(sizeof(int) * runs * L.rows);
+    L.mid = take(sizeof(float) * 16 * dt);
+    L.assign = take(runs * L.rows + 112);   // bytes; 128 of a run are read whatever the number of points
     L.cnts = take(sizeof(int) * 2 * 16 * mt);
     L.start = take(2 * sizeof(int) * 16 * mt);
     L.flags = take(sizeof(int) * 8);
@@ -139,23 +141,29 @@ __device__ inline double cost_of_dot(double dot, double a2, double b2, const flo
     return cost == LCN_COST_EUCLID ? sqrt(sq) : sq;
 }
 
-// the smaller of two numbers in one instruction (fmin first quiets both arguments)
-__device__ inline double min64(double a, double b)
+// the smaller of two numbers in one instruction (fminf first quiets both arguments)
+__device__ inline float min32(float a, float b)
 {
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
 
 // over the four lanes that share l % 16
-__device__ inline double quarter_min(double v)
+__device__ inline float quarter_min(float v)
 {
-    double w = v;
-    lane_swap<32>(v, w);
-    v = min64(v, w);
-    w = v;
-    lane_swap<16>(v, w);
-    return min64(v, w);
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = min32(__int_as_float(a[0]), __int_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    return min32(__int_as_float(b[0]), __int_as_float(b[1]));
+}
+
+__device__ inline float quarter_sum(float v)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = __int_as_float(a[0]) + __int_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    return __int_as_float(b[0]) + __int_as_float(b[1]);
 }
 
 __device__ inline double quarter_sum(double v)
@@ -215,22 +223,22 @@ __device__ inline void landmark_cholesky(double *A, int l, int *not_positive)
 //  * all k-means runs of the pair (landmarks and every hash round) advance together, a Lloyd iteration
 //    costing three barriers however many runs there are, and stop as soon as no assignment changed
 //    (from then on an iteration reproduces its own centroids bit for bit);
-//  * an assignment is a product on the fp64 matrix instruction, |c|^2 - 2 z.c for 16 points (columns; their
-//    operands stay in registers for all iterations) against 16 centroid rows, exact to rounding: centroids
-//    within 2 delta of a point's smallest score are its candidates, and only a point with several of them
-//    (near ties) is decided by the bucket rule itself;
-//  * the member sums are a product as well, of the 0/1 membership matrix with the fixed-point values: whole
-//    numbers below 2^53, so exact in any order;
+//  * an assignment is a product on the fp32 matrix instruction, |c|^2 - 2 z.c for 16 points (columns; their
+//    operands stay in registers for all iterations) against 16 centroid rows: centroids within 2 delta of a
+//    point's smallest score are its candidates, and only a point with several of them (near ties) is decided
+//    by the bucket rule itself;
+//  * the member sums are products as well, of the 0/1 membership matrix with the digits of the fixed-point values
+//    on the 8-bit matrix instruction: whole numbers, so exact in any order;
 //  * the start indices of a run are drawn by a lane each and the shuffle is resolved by ballots;
 //  * the Nystrom values are products of L^{-1} u and L^{-1} v (A = L L^T): a Cholesky by one wavefront in
 //    registers and one forward substitution per point, no inverse;
 //  * the costs of the pairs that share a bucket come from dot products on the matrix instruction (see
 //    cost_of_dot), and so do the Nystrom values; tiles of the kernel without such a pair skip the costs.
-// Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 44 us for 16 pairs
-// (243 with one k-means run after the other, the rule on vector instructions and 64-bit LDS atomics), 117 us
-// for 1024 (336) and 364 us for 4096 (1145).
+// Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 42 us for 16 pairs, 92 us for 1024
+// and 300 us for 4096 (52, 118 and 377 with scores and member sums on v_mfma_f64_16x16x4, whose instruction takes four
+// times the matrix cores' time for an eighth of the dimensions of scores, or a sixteenth of the points of sums).
 // Layout of v_mfma_f64_16x16x4_f64: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16] and receives
-// D[4 v + l / 16][l % 16], v = 0..3; which dimension a step of a dot product takes is free, so a lane reads
+// D[4 v + l / 16][l % 16], v = 0..3 (of the 32-bit instructions D[4 (l / 16) + v][l % 16]); which dimension a step of a dot product takes is free, so a lane reads
 // four consecutive ones (16 t + 4 (l / 16) ..) for four steps.
 template <int NT, int DT>
 __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
@@ -238,12 +246,13 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     constexpr int NW = NT / 64, TPW = 8 / NW;   // wavefronts; tiles of 16 points each of them holds (at most 128 points)
     extern __shared__ __align__(16) unsigned char lds[];
     const int l = B.l, d = B.d, runs = (l > 0 ? 1 : 0) + B.R;
-    const BuildLds L = build_lds(l, runs, B.mt, DT, B.max_points, NW);
+    const BuildLds L = build_lds(l, runs, B.mt, DT, B.max_points);
     constexpr int zs = 16 * DT + 4;
     double *F = (double *)(lds + L.f), *Am = (double *)(lds + L.am), *sums = (double *)(lds + L.sums);
     double *pn = (double *)(lds + L.pn), *rn = (double *)(lds + L.rn);   // squared norms of the points, of the landmarks
-    float *Z = (float *)(lds + L.z), *cent = (float *)(lds + L.cent);
-    int *assign = (int *)(lds + L.assign), *cnts = (int *)(lds + L.cnts), *start = (int *)(lds + L.start);
+    float *Z = (float *)(lds + L.z), *cent = (float *)(lds + L.cent), *mid = (float *)(lds + L.mid);
+    unsigned char *assign = lds + L.assign;
+    int *cnts = (int *)(lds + L.cnts), *start = (int *)(lds + L.start);
     int *owner = start + 16 * B.mt;   // of every centroid row: 256 run + index in the run, -1 if none
     // [0], [1]: some assignment changed (by parity); [2]: not positive definite; [3]: a large coordinate;
     // [4:5]: bits of the largest squared norm of a point; [6]: a coordinate the rule alone decides on
@@ -319,14 +328,32 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
         const int c = e / (16 * DT), j = e % (16 * DT), s = start[c];
         cent[c * zs + j] = s >= 0 ? Z[s * zs + j] : 0.f;
     }
-    // this wavefront's points as matrix operands, and their squared norms
-    double zop[TPW][4 * DT];
+    // the scores are formed about the middle of eight points, wherever the pair lies
+    if (tid < 16 * DT) {
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += Z[(e * N >> 3) * zs + tid];
+        mid[tid] = 0.125f * s;
+    }
+    __syncthreads();
+    for (int e = tid; e < 256 * B.mt * DT; e += NT) sums[e] = 0.0;
+    // this wavefront's points less the middle as matrix operands; squared norms of the points
+    float zop[TPW][4 * DT], mid_sq = 0.f;
     {
+        float about[4 * DT];
+#pragma unroll
+        for (int t = 0; t < DT; ++t) {
+            const float4 v = *(const float4 *)(mid + 16 * t + 4 * quarter);
+            about[4 * t] = v.x, about[4 * t + 1] = v.y, about[4 * t + 2] = v.z, about[4 * t + 3] = v.w;
+        }
+#pragma unroll
+        for (int e = 0; e < 4 * DT; ++e) mid_sq = fmaf(about[e], about[e], mid_sq);
+        mid_sq = quarter_sum(mid_sq);
         double largest = 0.0;
 #pragma unroll
         for (int u = 0; u < TPW; ++u) {
             const int pt = 16 * (wave + NW * u) + col;
-            double sq = 0.0;
+            double sq = 0.0, sq_about = 0.0;
 #pragma unroll
             for (int t = 0; t < DT; ++t) {
                 float4 v = {0.f, 0.f, 0.f, 0.f};
@@ -334,29 +361,72 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
                 const float f[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    zop[u][4 * t + e] = (double)f[e];
+                    const float z = f[e] - about[4 * t + e];
+                    zop[u][4 * t + e] = z;
                     sq = fma((double)f[e], (double)f[e], sq);
+                    sq_about = fma((double)z, (double)z, sq_about);
                 }
             }
             sq = quarter_sum(sq);
+            sq_about = quarter_sum(sq_about);
             if (quarter == 0 && pt < 16 * PT) pn[pt] = sq;
-            largest = fmax(largest, sq);
+            largest = fmax(largest, pt < N ? sq_about : 0.0);
         }
         largest = wave_max(largest);
         if (lane == 0) atomicMax((unsigned long long *)(flags + 4), (unsigned long long)__double_as_longlong(largest));
     }
+    // The operands of the member sums below: this wavefront has 16 dimensions of 64 points, and their six digits or a share of
+    // them.
+    constexpr int GROUPS = NW / (2 * DT), DIGITS = (6 + GROUPS - 1) / GROUPS;   // wavefronts that share out the digits; of each
+    const int sum_dt = wave % DT, sum_half = wave / DT % 2, sum_group = wave / (2 * DT);
+    const bool sums_here = B.mt > 0 && 64 * sum_half < N && sum_group * DIGITS < 6;
+    int4_t digits[DIGITS];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {   // four points each
+        if (!sums_here) break;   // the same in every lane
+        unsigned lo[4], hi[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int pt = 64 * sum_half + 16 * quarter + 4 * w + e;
+            const float z = pt < 16 * PT ? Z[pt * zs + 16 * sum_dt + col] : 0.f;
+            // 2^-32 fixed point plus 128 in every byte (coordinates beyond 2^13 take the other way below)
+            const long long x = __double2ll_rn((double)z * 4294967296.0) + 0x808080808080ll;
+            lo[e] = (unsigned)x, hi[e] = (unsigned)((unsigned long long)x >> 32);
+        }
+        // four words of four bytes -> the words of their lowest, second, ... bytes
+        const unsigned a01 = __builtin_amdgcn_perm(lo[1], lo[0], 0x05010400u), a23 = __builtin_amdgcn_perm(lo[3], lo[2], 0x05010400u),
+                       b01 = __builtin_amdgcn_perm(lo[1], lo[0], 0x07030602u), b23 = __builtin_amdgcn_perm(lo[3], lo[2], 0x07030602u),
+                       c01 = __builtin_amdgcn_perm(hi[1], hi[0], 0x05010400u), c23 = __builtin_amdgcn_perm(hi[3], hi[2], 0x05010400u);
+        const unsigned all[6] = {__builtin_amdgcn_perm(a23, a01, 0x05040100u), __builtin_amdgcn_perm(a23, a01, 0x07060302u),
+                                 __builtin_amdgcn_perm(b23, b01, 0x05040100u), __builtin_amdgcn_perm(b23, b01, 0x07060302u),
+                                 __builtin_amdgcn_perm(c23, c01, 0x05040100u), __builtin_amdgcn_perm(c23, c01, 0x07060302u)};
+#pragma unroll
+        for (int i = 0; i < DIGITS; ++i) {
+            unsigned v = all[i];
+#pragma unroll
+            for (int g = 1; g < GROUPS; ++g)
+                if (g * DIGITS + i < 6) v = sum_group == g ? all[g * DIGITS + i] : v;
+            digits[i][w] = (int)(v ^ 0x80808080u);   // the byte less 128
+        }
+    }
     __syncthreads();
-    // Bound on |score - what the bucket rule computes| for any centroid: means do not leave the hull of the
-    // points, so |c|^2 and |z|^2 are at most M = the largest squared norm (plus the centroid's rounding to
-    // single precision); the score's d + 2 products and sums and the rule's 3 d operations are each off by
-    // 2^-53 of at most 4 M.  16 (d + 8) 2^-53 M covers both sides of a comparison.
+    // Bound on |score - exact score|, the score of a point z and a centroid c being |c - s|^2 - 2 (z - s).(c - s) about the middle
+    // s: means do not leave the hull of the points, so |z - s|^2 and |c - s|^2 are at most M = the largest of the points'
+    // (plus the centroid's rounding to single precision, small against M unless s is 2^15 sqrt(M) away).  The
+    // differences' rounding makes 7 u M (u = 2^-24); |c - s|^2 takes 4 DT + 2 roundings of at most M, each of the two chains
+    // of products 8 DT + 2 sums and their sum one more, of at most 3 M, the products 2 M together: (28 DT + 20) u M; the
+    // rule's own error is far below.  What is closer than that goes to the rule, one decision in some thousand.
+    // (Double precision would be half the instructions' rate and twice the registers; without the middle, pairs far from the
+    // origin would have all their points decided by the rule.)
     // With a coordinate that is not finite, or so large (2^24) that the 64-bit sum of 128 of them may wrap and leave
-    // the hull, there is no such bound: every centroid is a candidate and the rule decides by itself.
-    const double two_delta = flags[6] ? INFINITY
-                                      : 2.0 * 1.01 * 16.0 * (double)(d + 8) * 0x1p-53 *
-                                            __longlong_as_double(*(const long long *)(flags + 4));
+    // the hull, a middle that far away, or squares near single precision's smallest numbers there is no such bound: every
+    // centroid is a candidate and the rule decides by itself.
+    const double most_sq = __longlong_as_double(*(const long long *)(flags + 4));
+    const float two_delta = flags[6] || !(most_sq > 0x1p-80) || !((double)mid_sq < 0x1p30 * most_sq)
+                                ? INFINITY
+                                : (float)(2.0 * 1.01 * (double)(28 * DT + 20) * 0x1p-24 * most_sq);
     const bool large = flags[3] != 0;
-    const int tiles = B.mt * DT, parts = tiles > 0 && NW > tiles ? NW / tiles : 1;
+    const int tiles = B.mt * DT;
     const int iters = T_l > T_b ? T_l : T_b;   // 0 for what does not run
     // The bucket rule (fp64, dimensions in order, multiply and add separately, lowest index among equals) on
     // the candidates of the points that have several: `mine` has bit v set if centroid 4 v + quarter of run q
@@ -385,8 +455,11 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
         }
         return (c & 3) == quarter ? 1u << (c >> 2) : 0u;
     };
-    unsigned valid = 0;   // bit t: row col of centroid tile t holds a centroid
-    for (int t = 0; t < B.mt; ++t) valid |= (start[16 * t + col] >= 0 ? 1u : 0u) << t;
+    // Row i of a tile's operand holds centroid 4 (i % 4) + i / 4, so that lane l receives the scores of centroids
+    // 4 v + l / 16: a run's are the same v in every lane.
+    const int crow = 4 * (col & 3) + (col >> 2);
+    unsigned valid = 0;   // bit t: row crow of centroid tile t holds a centroid
+    for (int t = 0; t < B.mt; ++t) valid |= (start[16 * t + crow] >= 0 ? 1u : 0u) << t;
     unsigned held[TPW];   // by run, four bits: which of this lane's centroids had the point in the last iteration
 #pragma unroll
     for (int u = 0; u < TPW; ++u) held[u] = 0u;
@@ -396,42 +469,42 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
         for (int mt = 0; mt < B.mt; ++mt) {
             // this tile's centroids as operands: -2 c, and one step more that adds |c|^2 (rows without a
             // centroid: a score no minimum picks)
-            double aop[4 * DT], cn = 0.0;
+            float aop[4 * DT], cn = 0.f;
 #pragma unroll
             for (int t = 0; t < DT; ++t) {
-                const float4 v = *(const float4 *)(cent + (16 * mt + col) * zs + 16 * t + 4 * quarter);
-                const float f[4] = {v.x, v.y, v.z, v.w};
+                const float4 v = *(const float4 *)(cent + (16 * mt + crow) * zs + 16 * t + 4 * quarter);
+                const float4 s = *(const float4 *)(mid + 16 * t + 4 * quarter);
+                const float f[4] = {v.x - s.x, v.y - s.y, v.z - s.z, v.w - s.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const double c = (double)f[e];
-                    aop[4 * t + e] = -2.0 * c;
-                    cn = fma(c, c, cn);
+                    aop[4 * t + e] = -2.f * f[e];
+                    cn = fmaf(f[e], f[e], cn);
                 }
             }
             cn = quarter_sum(cn);
-            const double an = quarter == 0 ? (valid >> mt & 1u ? cn : 1e300) : 0.0;
-            const double bn = quarter == 0 ? 1.0 : 0.0;
+            const float an = quarter == 0 ? (valid >> mt & 1u ? cn : 1e38f) : 0.f;
+            const float bn = quarter == 0 ? 1.f : 0.f;
 #pragma unroll
             for (int u = 0; u < TPW; ++u) {
                 const int tile = wave + NW * u;
                 if (tile >= PT) continue;   // the same in every lane
-                double4_t acc = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};   // two chains
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(an, bn, acc, 0, 0, 0);
+                float4_t acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};   // two chains
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(an, bn, acc, 0, 0, 0);
 #pragma unroll
                 for (int e = 0; e < 4 * DT; e += 2) {
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(aop[e], zop[u][e], acc, 0, 0, 0);
-                    acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(aop[e + 1], zop[u][e + 1], acc2, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[e], zop[u][e], acc, 0, 0, 0);
+                    acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[e + 1], zop[u][e + 1], acc2, 0, 0, 0);
                 }
                 acc += acc2;
                 const int pt = 16 * tile + col;
                 for (int q = 0; q < runs; ++q) {
                     if (row_of(q) >> 4 != mt || it >= iters_of(q)) continue;   // the same in every lane
                     const int k = k_of(q), va = (row_of(q) & 15) >> 2, vb = va + ((k + 3) >> 2);
-                    double best = INFINITY;
+                    float best = INFINITY;
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        best = v >= va && v < vb ? min64(best, acc[v]) : best;
-                    const double most = quarter_min(best) + two_delta;
+                        best = v >= va && v < vb ? min32(best, acc[v]) : best;
+                    const float most = quarter_min(best) + two_delta;
                     // the lanes that hold a candidate; a column (point) in which two do is undecided
                     unsigned mine = 0;
                     unsigned long long seen = 0, twice = 0;
@@ -455,7 +528,7 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
                     held[u] ^= differs;
                     if (mine && pt < N) {   // one lane per point
                         const int c = 4 * __builtin_ctz(mine) + quarter;
-                        assign[q * L.rows + pt] = c;
+                        assign[q * L.rows + pt] = (unsigned char)c;
                         atomicAdd(&cnt[row_of(q) + c], 1);
                     }
                 }
@@ -465,33 +538,34 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
         __syncthreads();
         if (!flags[it & 1]) break;   // the same in every thread
         if (!large) {
-            // Member sums in 2^-32 fixed point as a matrix product: rows = centroids, columns = dimensions, one
-            // step = four points.  |z| < 2^13 makes every value a whole number below 2^45 and every sum one
-            // below 2^52: exact.  With fewer output tiles than wavefronts the points are split into parts.
-            const int steps = (N + 7) / 8 * 2, per_part = ((steps + parts - 1) / parts + 1) & ~1;   // even: two steps at a time
-            for (int u = wave; u < parts * tiles; u += NW) {
-                const int tile = u % tiles, part = u / tiles, mt = tile / DT, dt = tile % DT;
-                // the run and index of this lane's centroid row
-                const int own = owner[16 * mt + col];
-                const int *as = assign + (own >= 0 ? own >> 8 : 0) * L.rows;
-                const int mine = own >= 0 ? own & 255 : -1;
-                const float *zc = Z + 16 * dt + col;
-                double4_t acc = {0.0, 0.0, 0.0, 0.0};
-                const int s1 = per_part * (part + 1) < steps ? per_part * (part + 1) : steps;
-                for (int s = per_part * part; s < s1; s += 2) {   // points past the last one are zero rows
-                    double a[2], b[2];
+            // Member sums in 2^-32 fixed point as products on the 8-bit matrix instruction, rows = centroids,
+            // columns = dimensions, 64 points per instruction: of the 0/1 membership matrix with each of the six signed
+            // digits to the base 256 (kept in registers) that a coordinate below 2^13 has, put together in double
+            // precision: whole numbers below 2^52, exact in any order.
+            if (sums_here)
+                for (int mt = 0; mt < B.mt; ++mt) {
+                    // the run and index of this lane's centroid row
+                    const int own = owner[16 * mt + col];
+                    const unsigned mine = own >= 0 ? (unsigned)(own & 255) * 0x01010101u : 0u;
+                    const uint4 as = *(const uint4 *)(assign + (own >= 0 ? own >> 8 : 0) * L.rows + 64 * sum_half + 16 * quarter);
+                    const unsigned a[4] = {as.x, as.y, as.z, as.w};
+                    int4_t member;   // (both bytes are below 16, so nothing is borrowed from the next one)
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const int pt = 4 * (s + e) + quarter;
-                        a[e] = as[pt] == mine ? 1.0 : 0.0;
-                        b[e] = rint((double)zc[pt * zs] * 4294967296.0);
+                    for (int w = 0; w < 4; ++w)
+                        member[w] = (int)((0x10101010u - ((a[w] ^ mine) & 0x0F0F0F0Fu)) >> 4 & 0x01010101u);
+                    int4_t acc[DIGITS];
+#pragma unroll
+                    for (int i = 0; i < DIGITS; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(member, digits[i], int4_t{0, 0, 0, 0}, 0, 0, 0);
+                    const double unit = ldexp(1.0, 8 * DIGITS * sum_group);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {   // lane l has rows 4 (l / 16) + v
+                        double t = (double)acc[DIGITS - 1][v];
+#pragma unroll
+                        for (int i = DIGITS - 2; i >= 0; --i) t = fma(t, 256.0, (double)acc[i][v]);
+                        unsafeAtomicAdd(&sums[256 * (mt * DT + sum_dt) + 16 * (4 * quarter + v) + col], t * unit);
                     }
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b[0], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], b[1], acc, 0, 0, 0);
                 }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) sums[256 * u + 16 * (4 * v + quarter) + col] = acc[v];
-            }
         } else {
             // coordinates up to 2^31: 64-bit integers
             unsigned long long *isum = (unsigned long long *)sums;
@@ -510,18 +584,12 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
         __syncthreads();
         for (int e = tid; e < 16 * DT * rows16; e += NT) {
             const int row = e / (16 * DT), j = e % (16 * DT);
-            const int k = cnt[row];
+            const int k = cnt[row], at = 256 * ((row >> 4) * DT + (j >> 4)) + 16 * (row & 15) + (j & 15);
             if (it < (row < landmark_rows ? T_l : T_b) && k > 0) {   // an empty cluster keeps its centroid
-                const int at = 256 * ((row >> 4) * DT + (j >> 4)) + 16 * (row & 15) + (j & 15);
-                double sum;
-                if (large) {
-                    sum = (double)(long long)((const unsigned long long *)sums)[at];
-                } else {
-                    sum = sums[at];
-                    for (int part = 1; part < parts; ++part) sum += sums[256 * tiles * part + at];
-                }
+                const double sum = large ? (double)(long long)((const unsigned long long *)sums)[at] : sums[at];
                 cent[row * zs + j] = (float)((sum * (1.0 / 4294967296.0)) / (double)k);
             }
+            sums[at] = 0.0;   // for the next iteration
         }
         for (int e = tid; e < rows16; e += NT) cnts[((it + 1) & 1) * rows16 + e] = 0;
         if (tid == 0) flags[(it + 1) & 1] = 0;
@@ -659,7 +727,7 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
 #pragma unroll
             for (int r = 0; r < BR; ++r)
                 if (r < B.R) {
-                    const int *as = assign + (first_hash + r) * L.rows;
+                    const unsigned char *as = assign + (first_hash + r) * L.rows;
                     near[v] = near[v] || (in && as[i < n ? i : n - 1] == as[br]);
                 }
             any_near = any_near || near[v];
@@ -1099,7 +1167,7 @@ template <int NT, int DT>
 static hipError_t launch_batched_build_as(const BatchHandle &h)
 {
     const BatchDev &D = h.dev;
-    const size_t bytes = build_lds(D.l, (D.l > 0 ? 1 : 0) + D.R, D.mt, DT, D.max_points, NT / 64).bytes;
+    const size_t bytes = build_lds(D.l, (D.l > 0 ? 1 : 0) + D.R, D.mt, DT, D.max_points).bytes;
     if (bytes > 64 * 1024) {   // has to be allowed
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&batched_build_kernel<NT, DT>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);

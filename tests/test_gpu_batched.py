@@ -451,3 +451,29 @@ def test_batched_build_by_four_wavefronts(d, l, b, rounds, kind, many):
         for r in range(rounds):
             np.testing.assert_array_equal(st["buckets"][z0 + r * (n + m):z0 + (r + 1) * (n + m)],
                                           oracle.kmeans(Z, b, 9, 41 + p * rounds + r)[1])
+
+
+@pytest.mark.parametrize("many", [False, True])
+@pytest.mark.parametrize("d,scale,offset", [(32, 1.0, 300.0), (16, 1.0, 1e6), (64, 2.0, -8000.0), (20, 3e-13, 0.0),
+                                            (32, 1e-11, 0.0), (9, 0.0, 7.0), (31, 4000.0, 0.0)])
+def test_batched_build_decides_like_the_rule_anywhere(d, scale, offset, many):
+    """Scores in single precision about the middle of the points, member sums digit by digit: pairs far from the origin, squares
+    near single precision's smallest numbers, points that all coincide, coordinates just below 2^13; the buckets
+    are the rule's, bit for bit."""
+    import paper_2107_06876_amd as lcn
+    base = [(16, 16), (17, 20), (64, 64), (33, 31), (40, 9), (5, 4)]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    sizes = base * ((2 * cus) // len(base) + 1) if many else base
+    B = _edge_batch(sizes, d, 6, 5, seed=11)
+    for Z in (B.X, B.Y):
+        Z[:] = np.clip(Z * np.float32(scale), -8191.5, 8191.5) + np.float32(offset)
+    B.lam[:] = 1.0
+    h = _build_only(B, "sparse", None, dict(num_buckets=5, num_rounds=2, kmeans_iters=9, seed=41))
+    st = {k: v.cpu().numpy() for k, v in lcn.lcn_batched_get(h).items()}
+    for p in range(len(base)):
+        n, m = sizes[p]
+        Z = np.concatenate([B.X[B.x_off[p]:B.x_off[p + 1]], B.Y[B.y_off[p]:B.y_off[p + 1]]])
+        z0 = int(B.x_off[p] + B.y_off[p]) * 2
+        for r in range(2):
+            np.testing.assert_array_equal(st["buckets"][z0 + r * (n + m):z0 + (r + 1) * (n + m)],
+                                          oracle.kmeans(Z, 5, 9, 41 + p * 2 + r)[1])
