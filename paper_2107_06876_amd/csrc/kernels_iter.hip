@@ -15,9 +15,13 @@ namespace lcn {
 //
 // G lanes work on a row (16, 32 or 64), a workgroup on 256 / G rows, and an update has a workgroup for
 // every 256 / G rows there are: nothing is carried from row to row, so it is the chip that refills its compute units.
-// The record is walked flat (see pass_kernel), G U entries at a time, all loads of a trip requested together.
+// The record is walked round by round, G U entries at a time, all loads of a trip requested together at fixed distances from
+// the lane's first: nothing has to be looked up per entry, which walked flat (see pass_kernel) cost 34 vector instructions per
+// 64 entries of three rounds, twice as many as now.  Lanes past the round's end read on (the next values, the
+// next places or what lies behind them in the workspace) and count as log K = -infinity.  With more than EXACT_ROUNDS rounds,
+// or a wavefront per row, it is walked flat.
 // What bounds it: rows of some twenty entries, the launch and three trips to memory one after the other (record,
-// values and scalings, stores); rows of some hundred entries, the values and the gathered scalings (8 bytes each).
+// values and scalings, stores); rows of some hundred entries, the trips of the rounds and the values.
 template <int RR, int G, int U, int MODE>
 __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double *partial, unsigned long long *counters,
                                                       int empty_slot)
@@ -31,8 +35,10 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
         if (threadIdx.x == 0) empty_rows = 0;
         __syncthreads();
     }
-    // (an update and the initial copies run through this once)
-    for (long long r0 = (long long)blockIdx.x * RPB; r0 < S.rows; r0 += (long long)gridDim.x * RPB) {
+    // (Once in an update and for the initial copies, and written so: of a loop the compiler takes the constants of exp and log in
+    // double out, 36 registers of every lane for what hardly any row needs.)
+    long long r0 = (long long)blockIdx.x * RPB;
+    do {
         long long row = r0 + (G == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / G) : threadIdx.x / G);
         const bool exists = row < S.rows;
         if (!exists) row = S.rows - 1;   // worked on again, not written
@@ -40,8 +46,9 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
         if (MODE == PASS_INIT) {
             lg = (double)S.log_out[row];
         } else {
-            // what takes an entry's number to its place in the gathered vector: place[0], and from the end of
-            // every round on place[r] more
+            // what takes an entry's number to its place in the gathered vector: place[r] in round r, or, where the record is
+            // walked flat, place[0], and from the end of every round on place[r] more
+            constexpr bool BY_ROUNDS = G != 64 && RR <= EXACT_ROUNDS;
             long long base;
             float marg;
             double log_marg;
@@ -58,7 +65,7 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
 #pragma unroll
                 for (int r = 0; r < (G == 64 ? 0 : RR); ++r) {
                     const unsigned shift = (unsigned)rec[6 + 2 * r];
-                    place[r] = shift - before;
+                    place[r] = BY_ROUNDS ? shift : shift - before;
                     before = shift;
                     const int e = rec[7 + 2 * r];
                     end[r] = RR <= EXACT_ROUNDS || r < R ? e : end[r > 0 ? r - 1 : 0];
@@ -67,29 +74,47 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             const double prev = S.lin_out[row];   // what the row's current scaling was computed from
             const float *__restrict__ vals = S.vals + base;
             const int total = G == 64 ? record_total<ANY_ROUNDS>(words, R) : end[RR - 1];
-            // f(log kernel values, log scalings, which of them are entries) for each trip
+            // f(log kernel values, log scalings, entries that are left from this lane's first on) for pieces of G entries
             auto walk = [&](auto &&f) {
-                RecordCursor<ANY_ROUNDS> cursor(words, R);
-                for (int e0 = 0; e0 < total; e0 += G * U) {
-                    float k[U];
-                    double p[U];
-                    bool in[U];
+                if constexpr (BY_ROUNDS) {
+                    static_assert(G * U <= VALUE_SLACK && 2 * G * U <= 2 * VALUE_SLACK, "read past the last record or place");
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        int e = e0 + G * u + sub;
-                        in[u] = e < total;
-                        unsigned at;
-                        if constexpr (G == 64) at = cursor.place(e0 + G * u, e, 0u);
-                        e = e < total ? e : total - 1;   // past the end: the last entry again, not counted
-                        if constexpr (G != 64) {
-                            at = (unsigned)e + place[0];
+                    for (int r = 0; r < RR; ++r)
+#pragma unroll 1
+                        for (int e0 = r > 0 ? end[r > 0 ? r - 1 : 0] : 0; e0 < end[r]; e0 += G * U) {
+                            const unsigned e = (unsigned)(e0 + sub);
+                            const float *__restrict__ v = vals + e;
+                            const double *__restrict__ q = S.perm_in + (e + place[r]);
+                            float k[U];
+                            double p[U];
 #pragma unroll
-                            for (int r = 1; r < RR; ++r) at += e >= end[r - 1] ? place[r] : 0u;
+                            for (int u = 0; u < U; ++u) {
+                                k[u] = v[G * u];
+                                p[u] = q[G * u];
+                            }
+                            f(k, p, end[r] - e0 - sub);
                         }
-                        k[u] = vals[(unsigned)e];
-                        p[u] = S.perm_in[at];
+                } else {
+                    RecordCursor<ANY_ROUNDS> cursor(words, R);
+                    for (int e0 = 0; e0 < total; e0 += G * U) {
+                        float k[U];
+                        double p[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            int e = e0 + G * u + sub;
+                            unsigned at;
+                            if constexpr (G == 64) at = cursor.place(e0 + G * u, e, 0u);
+                            e = e < total ? e : total - 1;   // past the end: the last entry again, not counted
+                            if constexpr (G != 64) {
+                                at = (unsigned)e + place[0];
+#pragma unroll
+                                for (int r = 1; r < RR; ++r) at += e >= end[r - 1] ? place[r] : 0u;
+                            }
+                            k[u] = vals[(unsigned)e];
+                            p[u] = S.perm_in[at];
+                        }
+                        f(k, p, total - e0 - sub);
                     }
-                    f(k, p, in);
                 }
             };
             auto sum_lanes = [&](double v) { return G == 64 ? wave_sum(v) : G == 32 ? half_sum(v) : row_sum(v); };
@@ -104,10 +129,12 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             bool done = false;
             if (shift > -INFINITY && shift < INFINITY) {   // the same in every lane of the row
                 double acc = 0.0;
-                walk([&](const float (&k)[U], const double (&p)[U], const bool (&in)[U]) {
+                walk([&](const auto &k, const auto &p, int left) {
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        acc += in[u] ? (double)__expf(k[u] + (float)(p[u] - shift)) : 0.0;
+                    for (int u = 0; u < U; ++u) {
+                        const float x = k[u] + (float)(p[u] - shift);
+                        acc += (double)__expf(G * u < left ? x : -INFINITY);
+                    }
                 });
                 const double tot = sum_lanes(acc);
                 if (tot > 1e-30 && tot < 1e30) {
@@ -117,10 +144,20 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             }
             if (!done) {
                 double mx = -INFINITY, sm = 0.0;
-                walk([&](const float (&k)[U], const double (&p)[U], const bool (&in)[U]) {
+                if constexpr (BY_ROUNDS) {
+#pragma unroll 1
+                    for (int e = sub; e < total; e += G) {
+                        unsigned at = (unsigned)e + place[0];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) lse_step(in[u] ? (double)k[u] + p[u] : -INFINITY, mx, sm);
-                });
+                        for (int r = 1; r < RR; ++r) at = e >= end[r - 1] ? (unsigned)e + place[r] : at;
+                        lse_step((double)vals[(unsigned)e] + S.perm_in[at], mx, sm);
+                    }
+                } else {
+                    walk([&](const auto &k, const auto &p, int left) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) lse_step(G * u < left ? (double)k[u] + p[u] : -INFINITY, mx, sm);
+                    });
+                }
                 const double M = G == 64 ? wave_max(mx) : G == 32 ? half_max(mx) : row_max(mx);
                 const double part = mx > -INFINITY ? sm * exp(mx - M) : 0.0;
                 const double ssum = sum_lanes(part);
@@ -148,7 +185,8 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
             if (sub == 0) S.lin_out[row] = lg;
             if (sub < R) S.perm_out[(long long)sub * S.rows + S.meta[row * S.meta_stride + 6 + 2 * R + sub]] = lg;
         }
-    }
+        r0 += (long long)gridDim.x * RPB;
+    } while (MODE == PASS_QUERY && r0 < S.rows);
     if (MODE == PASS_QUERY) {
         q0 = wave_sum(q0);
         q1 = wave_sum(q1);
@@ -503,39 +541,50 @@ static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int
     return grid;
 }
 
-// Lanes per row by the length of the records: 10 000 rows of 20 stored values 3.6 us per sweep with sixteen lanes
-// and two entries each at a time (a wavefront with four: 6.1; a wavefront per row and a 1024-thread workgroup working
-// through its rows, loads unrolled over four rounds: 6.4); 20 000 rows of 510 values in three rounds 15.2 us with 32
-// lanes and four entries each, 16.3 with sixteen and two, 15.5 with 64 and four (19.6 before).
-// Sixteen lanes / 32: 20 000 rows of 20 values in three rounds 5.5 / 7.7 us, of 27 in four 6.3 / 8.3, of 33 in five 7.7 / 11.0; few rows turn
-// earlier (5000 of 40 in five 5.2 / 4.6).
 // A whole wavefront (four entries per lane) where looking up an entry's round weighs more than lanes without an entry at the
 // record's end: 5000 rows of 420 values in five rounds 5.9 us against 7.5, of 670 in eight 7.3 against 10.3, 20 000 of 250
 // in five 13.6 against 17.0, of 1600 in eight 37 against 57, but 5000 of 65 in eight 5.4 against 5.1; in four rounds 5000 of 1000 7.9 against 9.6, 40 000 of 1600 84
 // against 86, but 10 000 of 670 11.4 against 10.8.
-static int log_lanes(const Handle &h, long long rows)
+static bool log_whole_wave(const Handle &h, long long rows)
 {
-    if (h.R > EXACT_ROUNDS ? h.nnz_stored > 80 * rows : h.R == 4 && h.nnz_stored > 1000 * rows) return 64;
-    return h.nnz_stored <= 48 * rows ? 16 : 32;
+    return h.R > EXACT_ROUNDS ? h.nnz_stored > 80 * rows : h.R == 4 && h.nnz_stored > 1000 * rows;
 }
 
+// Otherwise lanes per row and entries of a lane at a time, by the mean length L of a row's piece of a round (us per sweep, the record
+// walked flat / so):
+//  * L up to 28, at most two rounds, 16 lanes x 2: 30 000 rows of 25 + 25 values 9.9 / 6.5, 12 000 6.0 / 4.4;
+//  * fewer than 12 000 rows, too few for the chip with 16 lanes, 32 x 2: 9000 of 90 + 90 5.8 / 5.3, of 3 x 32 5.4 / 5.1; x 4 where they
+//    are few and long: 6000 of 3 x 97 5.4 / 5.1 (x 2 5.6), of 502 6.2 / 5.3;
+//  * L below 140, 16 x 4: 16 000 of 3 x 42 7.9 / 6.4, 28 000 of 4 x 125 20.0 / 18.7 (32 x 4 21.0);
+//  * longer ones 32 x 4: 40 000 of 369 20.5 / 17.0, of 141 + 141 21.6 / 19.0 (16 x 4 20.5), of 470 + 470 57.9 / 55.0 (67);
+//    three and more rounds of up to 24 000 rows 16 x 6: 20 000 of 3 x 163 14.7 / 14.1 (32 x 4 14.9), of 3 x 169 15.2 / 15.2 (15.5).
 template <int RR>
 static int launch_logpass_length(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
 {
-    return log_lanes(h, S.rows) == 16 ? launch_logpass_rows<RR, 16, 2>(S, h, mode, empty_slot, s)
-                                 : launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);
+    const long long pieces = (long long)h.R * S.rows, nnz = h.nnz_stored;
+    if (nnz <= 28 * pieces && h.R <= 2) return launch_logpass_rows<RR, 16, 2>(S, h, mode, empty_slot, s);
+    if (S.rows < 12000 && nnz >= 90 * pieces && (S.rows < 8000 || mode == PASS_QUERY))
+        return launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);   // (a query of 9000 of 3 x 106: 45 us, x 2 51)
+    if (S.rows < 12000) return launch_logpass_rows<RR, 32, 2>(S, h, mode, empty_slot, s);
+    if (nnz < 140 * pieces) return launch_logpass_rows<RR, 16, 4>(S, h, mode, empty_slot, s);
+    if constexpr (RR >= 3)
+        if (S.rows < 24000) return launch_logpass_rows<RR, 16, 6>(S, h, mode, empty_slot, s);
+    return launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);
 }
 
 // returns the workgroups launched
 static int launch_logpass_rounds(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
 {
-    if (log_lanes(h, S.rows) == 64) return launch_logpass_rows<ANY_ROUNDS, 64, 4>(S, h, mode, empty_slot, s);
+    if (log_whole_wave(h, S.rows)) return launch_logpass_rows<ANY_ROUNDS, 64, 4>(S, h, mode, empty_slot, s);
     switch (h.R) {
         case 1: return launch_logpass_length<1>(S, h, mode, empty_slot, s);
         case 2: return launch_logpass_length<2>(S, h, mode, empty_slot, s);
         case 3: return launch_logpass_length<3>(S, h, mode, empty_slot, s);
         case 4: return launch_logpass_length<4>(S, h, mode, empty_slot, s);
-        default: return launch_logpass_length<ANY_ROUNDS>(S, h, mode, empty_slot, s);
+        // sixteen lanes / 32, walked flat: 20 000 rows of 33 in five 7.7 / 11.0, but 5000 of 40 in five 5.2 / 4.6
+        default:
+            return h.nnz_stored <= 48 * S.rows ? launch_logpass_rows<ANY_ROUNDS, 16, 2>(S, h, mode, empty_slot, s)
+                                               : launch_logpass_rows<ANY_ROUNDS, 32, 4>(S, h, mode, empty_slot, s);
     }
 }
 

@@ -199,7 +199,8 @@ void layout(Handle &h, Bump &bump, Scratch &sc)
     h.log_v = bump.take<float>((size_t)h.m);
     h.lin_u = bump.take<double>((size_t)h.n);
     h.lin_v = bump.take<double>((size_t)h.m);
-    // each is followed by a slot that stays zero (what masked-out lanes of a sweep read)
+    // each is followed by a slot that stays zero (what masked-out lanes of a sweep read); a sweep in logs reads up to 128 places
+    // past the end, which lie in what is taken behind them here: the stored values' slack alone, twice, is longer
     h.perm_u = bump.take<double>((size_t)(h.R > 0 ? h.R : 1) * h.n + 8);
     h.perm_v = bump.take<double>((size_t)(h.R > 0 ? h.R : 1) * h.m + 8);
     for (int i = 0; i < 2; ++i) h.acc[i] = bump.take<double>(lp1 + 2);

@@ -73,6 +73,15 @@ def test_lanes_per_row_in_logs(n, m, buckets, rounds):
     print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 12), "sparse"), flush=True)
 
 
+# records walked round by round, by every choice of lanes and entries at a time: short pieces (up to 28 entries on average), fewer
+# than 8000 and 12 000 rows, pieces up to 140 and longer ones, up to 24 000 rows of three rounds; empty rounds of a row
+@pytest.mark.parametrize("n,m,buckets,rounds", [(12100, 11900, 560, 2), (7000, 6900, 70, 2), (7999, 8001, 100, 3), (12001, 11999, 300, 4),
+                                               (12500, 12100, 80, 3), (12500, 12100, 80, 2), (6100, 6000, 13, 1), (3000, 40, 30, 3)])
+def test_rounds_of_a_record_in_logs(n, m, buckets, rounds):
+    from parity import compare
+    print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 3), "sparse"), flush=True)
+
+
 # more than four rounds: their words are looked up as the walk reaches them; several rounds ending in one piece of 64
 # entries, empty ones, ones longer than a trip; every width of the sweeps and rows per wavefront
 @pytest.mark.parametrize("n,m,landmarks,buckets,rounds", [
