@@ -15,6 +15,7 @@
 // Without deletion costs it is plain Sinkhorn on K~.
 //
 // Compiled with -ffp-contract=off: the bucket rule needs separate multiply and add.
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -50,6 +51,7 @@ struct BatchDev {
     float *landmarks;             // [P][l][d]
     int *buckets;                 // per pair [R][n_p + m_p], pairs back to back at R * (x_off + y_off)
     double *log_u, *log_v;        // per pair at x_off + y_off, length n + m each (n resp. m without BP)
+    float *row_marg, *col_marg;   // marginals of the last run's plan, laid out like log_u and log_v (null: no room)
     double *dist, *resid;         // [P], host memory
     unsigned long long *counters; // [0] non-positive sums, [1] / [2] sums of exactly zero without signed terms (rows / columns), per sweep
     int *marks;                   // host memory: [0] a landmark matrix is not positive definite, [1] some counter is not zero
@@ -764,6 +766,8 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     if (tid == 0 && flags[2]) B.marks[0] = 1;
 }
 
+constexpr int RUN_PAIRS = 4;   // of a workgroup of the run kernel, one per SIMD of a compute unit
+
 // iters Sinkhorn iterations per pair (iters == 0: only the query part), then the
 // pair's distance and marginal residual.
 //
@@ -790,10 +794,11 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
 //   (K_BP v)_i     = sum_j K_ij v^_j + k_{i,eps} v~_i          (K_BP v)_{n+j}     = k_{eps,j} v^_j + sum v~
 //   (K_BP^T u)_j   = sum_i K_ij u^_i + k_{eps,j} u~_j          (K_BP^T u)_{m+i}   = k_{i,eps} u^_i + sum u~
 template <bool BP>
-__global__ __launch_bounds__(64, 2) void batched_run_kernel(BatchDev B, int iters, float *row_marg, float *col_marg)
+__global__ __launch_bounds__(64 * RUN_PAIRS, 2) void batched_run_kernel(BatchDev B, int iters, float *row_marg, float *col_marg)
 {
     const double LN2 = 0.69314718055994530942;
-    const int p = blockIdx.x, lane = threadIdx.x;
+    const int p = (int)blockIdx.x * RUN_PAIRS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (p >= B.P) return;
     const long long x0 = B.x_off[p], y0 = B.y_off[p];
     const int n = (int)(B.x_off[p + 1] - x0), m = (int)(B.y_off[p + 1] - y0);
     const int len_u = BP ? n + m : n, len_v = BP ? n + m : m;
@@ -1053,6 +1058,17 @@ __global__ __launch_bounds__(256) void batch_upload_kernel(const unsigned *__res
     if (i < counter_words) counters[i] = 0u;
 }
 
+// The marginals of the last run to where the caller wants them (either may be null); a workgroup per pair, since the
+// entries between the pairs are not the library's to write where there are no deletion entries.
+__global__ __launch_bounds__(128) void batch_marginals_kernel(BatchDev B, float *__restrict__ rows, float *__restrict__ cols)
+{
+    const long long x0 = B.x_off[blockIdx.x], y0 = B.y_off[blockIdx.x];
+    const int n = (int)(B.x_off[blockIdx.x + 1] - x0), m = (int)(B.y_off[blockIdx.x + 1] - y0);
+    const int i = threadIdx.x;   // at most BMAX + BMAX entries
+    if (rows && i < (B.bp ? n + m : n)) rows[x0 + y0 + i] = B.row_marg[x0 + y0 + i];
+    if (cols && i < (B.bp ? n + m : m)) cols[x0 + y0 + i] = B.col_marg[x0 + y0 + i];
+}
+
 // What a batch handle needs of the host: a block of pinned memory that the kernels read the description from and
 // write distances and marks to (a copy by the runtime costs more than these few bytes), and the events around a run.
 // Made once and kept: at most HOST_BLOCKS idle ones and HOST_BYTES in all, the rest is given back at once.
@@ -1145,6 +1161,7 @@ struct BatchHandle {
     size_t ws_used;
     HostBlock host;
     float last_ms;   // of the last run; < 0: still to be asked from its events
+    bool run_done;   // dist, resid and the marginals are those of the present state
 };
 
 }  // namespace lcn
@@ -1191,23 +1208,50 @@ static hipError_t launch_batched_build(const BatchHandle &h)
     return launch_batched_build_as<512, 4>(h);
 }
 
+// Up to four pairs per compute unit every wavefront can have a SIMD to itself, and then each workgroup is given more than half
+// a compute unit's LDS, which it does not use, so that no two of them share one: left to the dispatcher, which compute units get
+// one pair more depends on what ran before (1024 pairs, 50 iterations: 62 or 88 us a call).
+constexpr size_t RUN_ALONE_LDS = 96 * 1024;
+
+template <bool BP>
+static hipError_t launch_batched_run_as(const BatchHandle &h, int iters, float *row_dev, float *col_dev)
+{
+    const int groups = (h.dev.P + RUN_PAIRS - 1) / RUN_PAIRS;
+    const bool alone = groups <= device_compute_units();
+    if (alone) {   // has to be allowed, once per device
+        static std::atomic<bool> allowed[64];
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        const bool known = dev >= 0 && dev < 64;
+        if (!known || !allowed[dev].load(std::memory_order_acquire)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&batched_run_kernel<BP>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)RUN_ALONE_LDS);
+            if (e != hipSuccess) return e;
+            if (known) allowed[dev].store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL(batched_run_kernel<BP>, dim3(groups), dim3(64 * RUN_PAIRS), alone ? RUN_ALONE_LDS : 0, h.stream, h.dev,
+                       iters, row_dev, col_dev);
+    return hipGetLastError();
+}
+
 static hipError_t launch_batched_run(const BatchHandle &h, int iters, float *row_dev, float *col_dev)
 {
-    if (h.dev.bp)
-        hipLaunchKernelGGL(batched_run_kernel<true>, dim3(h.dev.P), dim3(64), 0, h.stream, h.dev, iters, row_dev, col_dev);
-    else
-        hipLaunchKernelGGL(batched_run_kernel<false>, dim3(h.dev.P), dim3(64), 0, h.stream, h.dev, iters, row_dev, col_dev);
-    return hipGetLastError();
+    return h.dev.bp ? launch_batched_run_as<true>(h, iters, row_dev, col_dev)
+                    : launch_batched_run_as<false>(h, iters, row_dev, col_dev);
 }
 
 lcn_status batched_run(void *hh, int iters)
 {
     BatchHandle &h = *(BatchHandle *)hh;
     BHIPCHK(hipEventRecord(h.host.ev0, h.stream));
-    BHIPCHK(launch_batched_run(h, iters, nullptr, nullptr));
+    h.run_done = false;
+    BHIPCHK(launch_batched_run(h, iters, h.dev.row_marg, h.dev.col_marg));
     BHIPCHK(hipEventRecord(h.host.ev1, h.stream));
     h.last_ms = -1.f;
     BHIPCHK(hipStreamSynchronize(h.stream));
+    h.run_done = true;
     if (!*(volatile int *)(h.dev.marks + 1)) return LCN_OK;
     unsigned long long c[3] = {0, 0, 0};
     const lcn_status st = batched_counts(hh, c);
@@ -1219,7 +1263,15 @@ lcn_status batched_run(void *hh, int iters)
 lcn_status batched_query(void *hh, double *dist_host, double *resid_host, float *row_dev, float *col_dev)
 {
     BatchHandle &h = *(BatchHandle *)hh;
-    BHIPCHK(launch_batched_run(h, 0, row_dev, col_dev));
+    // A run leaves all of this; forming the marginals again means reading every kernel again (4096 pairs: 26 us against 6).
+    if (h.run_done && h.dev.row_marg) {
+        if (row_dev || col_dev) {
+            hipLaunchKernelGGL(batch_marginals_kernel, dim3(h.dev.P), dim3(2 * BMAX), 0, h.stream, h.dev, row_dev, col_dev);
+            BHIPCHK(hipGetLastError());
+        }
+    } else {
+        BHIPCHK(launch_batched_run(h, 0, row_dev, col_dev));
+    }
     BHIPCHK(hipStreamSynchronize(h.stream));
     if (dist_host) memcpy(dist_host, h.dev.dist, sizeof(double) * h.dev.P);
     if (resid_host) memcpy(resid_host, h.dev.resid, sizeof(double) * h.dev.P);
@@ -1349,8 +1401,18 @@ lcn_status lcn_build_batched(const float *X, const float *Y, int32_t d, const lc
     D.log_v = (double *)take(sizeof(double) * (size_t)(tx + ty));
     D.counters = (unsigned long long *)take(64);
     h.ws_used = used;
+    const size_t least = used;
+    // Last, room for the marginals of a run.  It belongs to what a batch needs; a workspace that ends before it is still
+    // taken, and the marginals are then formed when they are asked for.
+    float *row_marg = (float *)take(sizeof(float) * (size_t)(tx + ty));
+    float *col_marg = (float *)take(sizeof(float) * (size_t)(tx + ty));
+    if (used <= workspace_bytes) {
+        D.row_marg = row_marg;
+        D.col_marg = col_marg;
+        h.ws_used = used;
+    }
     if (bytes_needed) *bytes_needed = used + 256;
-    if (used > workspace_bytes) return LCN_ERR_ALLOC;
+    if (least > workspace_bytes) return LCN_ERR_ALLOC;
     D.x_off = xo;
     D.y_off = yo;
     D.lambda = lam;

@@ -477,3 +477,47 @@ def test_batched_build_decides_like_the_rule_anywhere(d, scale, offset, many):
         for r in range(2):
             np.testing.assert_array_equal(st["buckets"][z0 + r * (n + m):z0 + (r + 1) * (n + m)],
                                           oracle.kmeans(Z, 5, 9, 41 + p * 2 + r)[1])
+
+
+@pytest.mark.parametrize("pairs", [5, 1023, 1025])
+@pytest.mark.parametrize("bp", [True, False])
+def test_marginals_left_by_a_run_or_formed_when_asked_for(pairs, bp):
+    """A run leaves the marginals where the workspace has room for them; without it they are formed from the state, and so they are before
+    any run.  Both are roundings of the same double precision sums (relative difference some 1e-15 before it).  Entries
+    between the pairs are not written without deletion entries.  Up to four pairs per compute unit and more, the last
+    workgroup of the run with one to three pairs."""
+    import ctypes
+    import paper_2107_06876_amd as lcn
+    B = _edge_batch([(16 + (7 * p) % 49, 16 + (11 * p) % 49) for p in range(pairs)], 8, 3, 4)
+    lsh = dict(num_buckets=4, num_rounds=1, kmeans_iters=3, seed=41)
+    X, Y = torch.from_numpy(B.X).cuda(), torch.from_numpy(B.Y).cuda()
+    dx = torch.from_numpy(B.del_x).cuda() if bp else None
+    dy = torch.from_numpy(B.del_y).cuda() if bp else None
+    total = len(B.X) + len(B.Y)
+
+    def build(workspace):
+        return lcn.lcn_build_batched(X, Y, B.x_off, B.y_off, B.lam, B.cost, lcn.MODE_DENSE, dx, dy, lsh=lsh, workspace=workspace)
+
+    def results(h):
+        dist, resid = np.empty(pairs), np.empty(pairs)
+        rows, cols = torch.full((total,), -7.0, device="cuda"), torch.full((total,), -7.0, device="cuda")
+        st = lcn.load_library().lcn_batched_results(h.raw, dist.ctypes.data, resid.ctypes.data, ctypes.c_void_p(rows.data_ptr()),
+                                                    ctypes.c_void_p(cols.data_ptr()))
+        assert st == 0
+        return dist, resid, rows.cpu().numpy(), cols.cpu().numpy()
+
+    need = build(None).workspace.numel()
+    room = build(torch.empty(need + (1 << 16), dtype=torch.uint8, device="cuda"))
+    none = build(torch.empty(need - 256 - 8 * total, dtype=torch.uint8, device="cuda"))
+    if need > 1 << 20:   # what a batch without a workspace gets at least
+        assert none.workspace.numel() == need - 256 - 8 * total
+    for iters in (0, 3, 2):
+        if iters:
+            lcn.sinkhorn_run(room, iters)
+            lcn.sinkhorn_run(none, iters)
+        got, want = results(room), results(none)
+        np.testing.assert_allclose(got[0], want[0], rtol=1e-12, atol=1e-13)
+        np.testing.assert_allclose(got[1], want[1], rtol=0, atol=1e-13)
+        for g, w in zip(got[2:], want[2:]):
+            np.testing.assert_array_equal(g == -7.0, w == -7.0)
+            np.testing.assert_allclose(g, w, rtol=1.2e-7, atol=0)   # a rounding to single precision
