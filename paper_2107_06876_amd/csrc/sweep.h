@@ -265,22 +265,35 @@ static void launch_sweep_rows(const PassSide &S, const Handle &h, int mode, cons
         hipLaunchKernelGGL((pass_kernel<T, 1, 3, 1, PASS_INIT, false>), grid, block, lds, s, S, h.R, h.lp, partial, cnt, F);
 }
 
-// Entries of a record requested with its row: two wavefronts of them, except for short records five rows at a time
+// Entries of a record requested with its row, in wavefronts of them: two, but one for short records five rows at a time
 // (20 000 rows of 256 factor entries, 45 stored values on average: 13.3 us per sweep against 13.6 with two; 18 757 rows
-// of 128, 98 stored values: 12.8 against 11.1).
+// of 128, 98 stored values: 12.8 against 11.1), and three for longer ones of up to 128 factor entries, whose rows leave the
+// registers for it (two / three: 10 000 rows of 451 values 11.95 / 11.78 us, 745 14.14 / 13.85, 28 000 of 637 25.4 / 23.5, 20 011 of 90
+// 11.02 / 10.79; one row at a time 4000 of 334 8.25 / 8.03, but 3000 of 248 7.29 / 7.40; four are no faster, six spill).
 // (An entry's order in its lane's sum does not depend on that: both give the same bits.)
 template <int T, int RR>
 static void launch_sweep_rounds(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
                                 double *partial, unsigned long long *cnt, hipStream_t s)
 {
-    switch (rows_at_a_time(h, S.rows)) {
+    const int rows = rows_at_a_time(h, S.rows);
+    if constexpr (T <= 2)
+        if (h.nnz_stored > (rows == 1 ? 256 : 64) * S.rows) {
+            switch (rows) {
+                case 1: launch_sweep_rows<T, RR, 1, 3>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
+                case 2: launch_sweep_rows<T, RR, 2, 3>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
+                case 3: launch_sweep_rows<T, RR, 3, 3>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
+                default: launch_sweep_rows<T, RR, 5, 3>(S, h, mode, F, fused_in, groups, partial, cnt, s);
+            }
+            return;
+        }
+    switch (rows) {
         case 1: launch_sweep_rows<T, RR, 1, 2>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
         case 2: launch_sweep_rows<T, RR, 2, 2>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
         case 3: launch_sweep_rows<T, RR, 3, 2>(S, h, mode, F, fused_in, groups, partial, cnt, s); break;
         default:
             if (h.nnz_stored <= 64 * S.rows)
                 launch_sweep_rows<T, RR, 5, 1>(S, h, mode, F, fused_in, groups, partial, cnt, s);
-            else
+            else if constexpr (T > 2)
                 launch_sweep_rows<T, RR, 5, 2>(S, h, mode, F, fused_in, groups, partial, cnt, s);
     }
 }

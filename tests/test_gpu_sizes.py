@@ -82,6 +82,15 @@ def test_rounds_of_a_record_in_logs(n, m, buckets, rounds):
     print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 3), "sparse"), flush=True)
 
 
+# the bucket sort: buckets on both sides of 256 (a wavefront's share of a scan) and of a power of two (bits of a key), blocks on both
+# sides of 1024 (a workgroup's), points on both sides of 1024 (a chunk), eight chunks and more, of 4096 (rows of a scan's tile)
+@pytest.mark.parametrize("n,m,buckets,rounds", [(1024, 1025, 256, 1), (8193, 7, 257, 2), (3000, 4097, 342, 3), (4096, 2000, 1025, 1),
+                                               (9000, 8191, 512, 2), (600, 601, 130, 8)])
+def test_bucket_sort_edges(n, m, buckets, rounds):
+    from parity import compare
+    print("sort", n, m, buckets, rounds, compare(_cut(n, m, 3, 8, buckets, rounds, 2), "sparse"), flush=True)
+
+
 # more than four rounds: their words are looked up as the walk reaches them; several rounds ending in one piece of 64
 # entries, empty ones, ones longer than a trip; every width of the sweeps and rows per wavefront
 @pytest.mark.parametrize("n,m,landmarks,buckets,rounds", [

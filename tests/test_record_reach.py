@@ -15,7 +15,7 @@ PROGRAM = r"""
 int main()
 {
     // chunks requested with a row, chunks per trip: rows of up to 256 factor entries, longer ones
-    const int sweeps[][2] = {{1, lcn::SWEEP_TRIP}, {2, lcn::SWEEP_TRIP}, {1, lcn::LONG_TRIP}, {3, lcn::LONG_TRIP}};
+    const int sweeps[][2] = {{1, lcn::SWEEP_TRIP}, {2, lcn::SWEEP_TRIP}, {3, lcn::SWEEP_TRIP}, {1, lcn::LONG_TRIP}, {3, lcn::LONG_TRIP}};
     int furthest = 0;
     for (const auto &s : sweeps)
         for (int total = 0; total <= 2000; ++total) {
