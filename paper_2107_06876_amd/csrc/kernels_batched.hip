@@ -244,8 +244,8 @@ __device__ inline void landmark_cholesky(double *A, int l, int *not_positive)
 //    registers and one forward substitution per point, no inverse;
 //  * the costs of the pairs that share a bucket come from dot products on the matrix instruction (see
 //    cost_of_dot), and so do the Nystrom values; tiles of the kernel without such a pair skip the costs.
-// Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 42 us for 16 pairs, 92 us for 1024
-// and 300 us for 4096 (52, 118 and 377 with scores and member sums on v_mfma_f64_16x16x4, whose instruction takes four
+// Pairs of 16 to 64 points (d = 32, l = 8, b = 4, ten Lloyd iterations): the kernel takes 37 us for 16 pairs, 86 us for 1024
+// and 276 us for 4096 (43, 115 and 363 with scores and member sums on v_mfma_f64_16x16x4, whose instruction takes four
 // times the matrix cores' time for an eighth of the dimensions of scores, or a sixteenth of the points of sums).
 // Layout of v_mfma_f64_16x16x4_f64: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16] and receives
 // D[4 v + l / 16][l % 16], v = 0..3 (of the 32-bit instructions D[4 (l / 16) + v][l % 16]); which dimension a step of a dot product takes is free, so a lane reads
