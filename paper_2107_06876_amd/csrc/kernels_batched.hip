@@ -421,20 +421,23 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     }
     __syncthreads();
     // Bound on |score - exact score|, the score of a point z and a centroid c being |c - s|^2 - 2 (z - s).(c - s) about the middle
-    // s: means do not leave the hull of the points, so |z - s|^2 and |c - s|^2 are at most M = the largest of the points'
-    // (plus the centroid's rounding to single precision, small against M unless s is 2^15 sqrt(M) away).  The
-    // differences' rounding makes 7 u M (u = 2^-24); |c - s|^2 takes 4 DT + 2 roundings of at most M, each of the two chains
-    // of products 8 DT + 2 sums and their sum one more, of at most 3 M, the products 2 M together: (28 DT + 20) u M; the
-    // rule's own error is far below.  What is closer than that goes to the rule, one decision in some thousand.
+    // s.  With M = the largest |z - s|^2: a mean is formed from coordinates rounded to 2^-32, so it may lie up to 2^-33 per
+    // coordinate outside the points' hull, and |c - s| is at most r = sqrt(M) + sqrt(d) 2^-33, r^2 at most 1.01 M + 101 d 2^-66
+    // (plus its rounding to single precision, small against M unless s is 2^15 sqrt(M) away).  The differences' rounding makes
+    // 7 u r^2 (u = 2^-24); |c - s|^2 takes 4 DT + 2 roundings of at most r^2, each of the two chains of products 8 DT + 2 sums
+    // and their sum one more, of at most 3 r^2, the products 2 r^2 together; adding 2 delta to the smallest score below is one
+    // more of 3 r^2: (28 DT + 23) u r^2, and one to spare; the rule's own error is far below.  What is closer than that goes to
+    // the rule, one decision in some thousand, or all where the points lie closer together than the 2^-32.
     // (Double precision would be half the instructions' rate and twice the registers; without the middle, pairs far from the
     // origin would have all their points decided by the rule.)
     // With a coordinate that is not finite, or so large (2^24) that the 64-bit sum of 128 of them may wrap and leave
     // the hull, a middle that far away, or squares near single precision's smallest numbers there is no such bound: every
     // centroid is a candidate and the rule decides by itself.
     const double most_sq = __longlong_as_double(*(const long long *)(flags + 4));
+    const double reach_sq = 1.01 * most_sq + 101.0 * (16 * DT) * 0x1p-66;
     const float two_delta = flags[6] || !(most_sq > 0x1p-80) || !((double)mid_sq < 0x1p30 * most_sq)
                                 ? INFINITY
-                                : (float)(2.0 * 1.01 * (double)(28 * DT + 20) * 0x1p-24 * most_sq);
+                                : (float)(2.0 * 1.01 * (double)(28 * DT + 24) * 0x1p-24 * reach_sq);
     const bool large = flags[3] != 0;
     const int tiles = B.mt * DT;
     const int iters = T_l > T_b ? T_l : T_b;   // 0 for what does not run

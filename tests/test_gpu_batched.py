@@ -479,6 +479,32 @@ def test_batched_build_decides_like_the_rule_anywhere(d, scale, offset, many):
                                           oracle.kmeans(Z, 5, 9, 41 + p * 2 + r)[1])
 
 
+@pytest.mark.parametrize("d,values,base,spread", [(8, 2, 2.0 ** -33, 0.7 * 2.0 ** -41), (32, 2, 2.0 ** -33, 0.7 * 2.0 ** -37),
+                                                  (8, 3, 2.0 ** -33, 0.7 * 2.0 ** -37), (16, 3, 1.5 * 2.0 ** -32, 0.7 * 2.0 ** -40),
+                                                  (48, 3, 2.0 ** -33, 0.7 * 2.0 ** -41)])
+def test_batched_build_of_points_closer_than_a_means_rounding(d, values, base, spread):
+    """Coordinates on either side of a tie of the 2^-32 fixed point that means are formed in, far closer together than
+    that: the centroids leave the points' hull by many times its width.  600 pairs (a share of
+    the first four cases' decided wrongly where the scores' bound took the centroids to be inside)."""
+    import paper_2107_06876_amd as lcn
+    sizes = [(16, 16), (9, 11), (20, 12), (13, 31), (10, 9), (8, 8), (64, 64), (40, 41)] * 75
+    B = _edge_batch(sizes, d, 6, 16, seed=11)
+    rng = np.random.default_rng(5)
+    for Z in (B.X, B.Y):
+        s = rng.integers(0, 2, Z.shape) * 2 - 1 if values == 2 else rng.integers(-1, 2, Z.shape)
+        Z[:] = (base + spread * s).astype(np.float32)
+    B.lam[:] = 1.0
+    h = _build_only(B, "sparse", None, dict(num_buckets=16, num_rounds=1, kmeans_iters=9, seed=41))
+    st = {k: v.cpu().numpy() for k, v in lcn.lcn_batched_get(h).items()}
+    wrong = []
+    for p, (n, m) in enumerate(sizes):
+        Z = np.concatenate([B.X[B.x_off[p]:B.x_off[p + 1]], B.Y[B.y_off[p]:B.y_off[p + 1]]])
+        z0 = int(B.x_off[p] + B.y_off[p])
+        if not np.array_equal(st["buckets"][z0:z0 + n + m], oracle.kmeans(Z, 16, 9, 41 + p)[1]):
+            wrong.append(p)
+    assert wrong == []
+
+
 @pytest.mark.parametrize("pairs", [5, 1023, 1025])
 @pytest.mark.parametrize("bp", [True, False])
 def test_marginals_left_by_a_run_or_formed_when_asked_for(pairs, bp):
