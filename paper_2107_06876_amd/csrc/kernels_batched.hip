@@ -15,7 +15,6 @@
 // Without deletion costs it is plain Sinkhorn on K~.
 //
 // Compiled with -ffp-contract=off: the bucket rule needs separate multiply and add.
-#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -1243,38 +1242,16 @@ static hipError_t launch_batched_build(const BatchHandle &h)
     return launch_batched_build_as<512, 4>(h);
 }
 
-// Up to four pairs per compute unit every wavefront can have a SIMD to itself, and then each workgroup is given more than half
-// a compute unit's LDS, which it does not use, so that no two of them share one: left to the dispatcher, which compute units get
-// one pair more depends on what ran before (1024 pairs, 50 iterations: 62 or 88 us a call).
-constexpr size_t RUN_ALONE_LDS = 96 * 1024;
-
-template <bool BP>
-static hipError_t launch_batched_run_as(const BatchHandle &h, int iters, float *row_dev, float *col_dev)
-{
-    const int groups = (h.dev.P + RUN_PAIRS - 1) / RUN_PAIRS;
-    const bool alone = groups <= device_compute_units();
-    if (alone) {   // has to be allowed, once per device
-        static std::atomic<bool> allowed[64];
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        const bool known = dev >= 0 && dev < 64;
-        if (!known || !allowed[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&batched_run_kernel<BP>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)RUN_ALONE_LDS);
-            if (e != hipSuccess) return e;
-            if (known) allowed[dev].store(true, std::memory_order_release);
-        }
-    }
-    hipLaunchKernelGGL(batched_run_kernel<BP>, dim3(groups), dim3(64 * RUN_PAIRS), alone ? RUN_ALONE_LDS : 0, h.stream, h.dev,
-                       iters, row_dev, col_dev);
-    return hipGetLastError();
-}
-
+// Nothing keeps two workgroups of a run apart: with half a compute unit's LDS reserved per workgroup for that, a run by itself took
+// the same (1024 pairs, 50 iterations: 63 us), two on two streams one after the other (400 iterations: 671 us instead of 500).
 static hipError_t launch_batched_run(const BatchHandle &h, int iters, float *row_dev, float *col_dev)
 {
-    return h.dev.bp ? launch_batched_run_as<true>(h, iters, row_dev, col_dev)
-                    : launch_batched_run_as<false>(h, iters, row_dev, col_dev);
+    const dim3 grid((h.dev.P + RUN_PAIRS - 1) / RUN_PAIRS), block(64 * RUN_PAIRS);
+    if (h.dev.bp)
+        hipLaunchKernelGGL(batched_run_kernel<true>, grid, block, 0, h.stream, h.dev, iters, row_dev, col_dev);
+    else
+        hipLaunchKernelGGL(batched_run_kernel<false>, grid, block, 0, h.stream, h.dev, iters, row_dev, col_dev);
+    return hipGetLastError();
 }
 
 lcn_status batched_run(void *hh, int iters)

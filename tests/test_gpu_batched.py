@@ -505,6 +505,39 @@ def test_batched_build_of_points_closer_than_a_means_rounding(d, values, base, s
     assert wrong == []
 
 
+def test_runs_of_two_batches_share_the_chip():
+    """Four pairs per compute unit leave room for a second run on another stream.  Some 3 ms each: both together take 1.6
+    times one (2.0 where the second has to wait for the first, also for want of a hardware queue of its own: the best of
+    the pairs that four streams make counts)."""
+    import itertools
+    import threading
+    import time
+    import paper_2107_06876_amd as lcn
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    B = _edge_batch([(40, 41)] * (4 * cus), 8, 3, 4)
+    X, Y, dx, dy = (torch.from_numpy(v).cuda() for v in (B.X, B.Y, B.del_x, B.del_y))
+    torch.cuda.synchronize()
+    handles = []
+    for stream in [torch.cuda.Stream() for _ in range(4)]:
+        with torch.cuda.stream(stream):
+            handles.append(lcn.lcn_build_batched(X, Y, B.x_off, B.y_off, B.lam, B.cost, lcn.MODE_DENSE, dx, dy))
+
+    def seconds(used):
+        threads = [threading.Thread(target=lcn.sinkhorn_run, args=(h, 4000)) for h in used]
+        start = time.perf_counter()
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        return time.perf_counter() - start
+
+    seconds(handles)
+    one = min(seconds(handles[:1]) for _ in range(5))
+    two = min(seconds(pair) for pair in itertools.combinations(handles, 2) for _ in range(3))
+    print("one run %.2f ms, two runs %.2f ms" % (1e3 * one, 1e3 * two), flush=True)
+    assert two < 1.8 * one
+
+
 @pytest.mark.parametrize("pairs", [5, 1023, 1025])
 @pytest.mark.parametrize("bp", [True, False])
 def test_marginals_left_by_a_run_or_formed_when_asked_for(pairs, bp):
