@@ -3,6 +3,7 @@
 #include <atomic>
 
 #include "iter_common.h"
+#include "log_walk.h"
 
 namespace lcn {
 
@@ -15,14 +16,14 @@ namespace lcn {
 //
 // G lanes work on a row (16, 32 or 64), a workgroup on 256 / G rows, and an update has a workgroup for
 // every 256 / G rows there are: nothing is carried from row to row, so it is the chip that refills its compute units.
-// The record is walked round by round, G U entries at a time, all loads of a trip requested together at fixed distances from
-// the lane's first: nothing has to be looked up per entry, which walked flat (see pass_kernel) cost 34 vector instructions per
-// 64 entries of three rounds, twice as many as now.  Lanes past the round's end read on (the next values, the
-// next places or what lies behind them in the workspace) and count as log K = -infinity.  With more than EXACT_ROUNDS rounds,
-// or a wavefront per row, it is walked flat.
+// The record is walked G U entries at a time, all loads of a trip requested together.  Flat (see pass_kernel), every entry's
+// round is looked up: 34 vector instructions per 64 entries of three rounds.  Round by round that falls away, half of the
+// instructions, the loads at fixed distances from the lane's first; but every round is a trip, or several, of its own.  Lanes past the
+// round's end read on (the next values, the next places or what lies behind them in the workspace) and count as
+// log K = -infinity.  log_walk.h says which is taken where.
 // What bounds it: rows of some twenty entries, the launch and three trips to memory one after the other (record,
-// values and scalings, stores); rows of some hundred entries, the trips of the rounds and the values.
-template <int RR, int G, int U, int MODE>
+// values and scalings, stores); rows of some hundred entries, the trips and the values.
+template <int RR, int G, int U, int MODE, bool BY_ROUNDS>
 __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double *partial, unsigned long long *counters,
                                                       int empty_slot)
 {
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(256) void logpass_kernel(PassSide S, int R, double 
         } else {
             // what takes an entry's number to its place in the gathered vector: place[r] in round r, or, where the record is
             // walked flat, place[0], and from the end of every round on place[r] more
-            constexpr bool BY_ROUNDS = G != 64 && RR <= EXACT_ROUNDS;
+            static_assert(!BY_ROUNDS || (G != 64 && RR <= EXACT_ROUNDS), "the ends of all rounds are in registers");
             long long base;
             float marg;
             double log_marg;
@@ -518,73 +519,77 @@ static PassSide make_side(const Handle &h, int side, int acc_in, int acc_out, fl
     return S;
 }
 
-template <int RR, int G, int U>
-static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
+template <int RR, int G, int U, bool BY_ROUNDS>
+static int launch_log_update(const PassSide &S, const Handle &h, int empty_slot, hipStream_t s)
+{
+    const int grid = (int)((S.rows + 256 / G - 1) / (256 / G));
+    hipLaunchKernelGGL((logpass_kernel<RR, G, U, PASS_UPDATE, BY_ROUNDS>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters,
+                       empty_slot);
+    return grid;
+}
+
+template <int RR, int G, int U, bool BY_ROUNDS>
+static int launch_log_query(const PassSide &S, const Handle &h, int empty_slot, hipStream_t s)
 {
     // A query leaves 3 partial sums per workgroup and there is room for h.grid of them.  Few entries are read faster than
     // many partial sums are added up (a query of both sides, 512 workgroups / as many as there is room for: 10 000 rows
     // of 167 values 38 / 43 us, 20 000 of 200 52 / 55, 20 000 of 250 72 / 65, 40 000 of 1200 212 / 178, with a wavefront per
     // row 30 000 of 2000 312 / 216).
-    const int lanes = mode == PASS_INIT ? 16 : G;
-    const long long all = (S.rows + 256 / lanes - 1) / (256 / lanes);
+    const long long all = (S.rows + 256 / G - 1) / (256 / G);
     const long long most = h.nnz_stored <= (1ll << 22) && h.grid > 512 ? 512 : h.grid;
+    const int grid = (int)(all > most ? most : all);
     constexpr int LONG_U = G == 64 ? 8 : U;   // long rows, a wavefront each (40 000 of 1600 values 233 -> 197 us; of 140 82 -> 93)
-    const int grid = (int)(mode == PASS_QUERY && all > most ? most : all);
-    if (mode == PASS_UPDATE)
-        hipLaunchKernelGGL((logpass_kernel<RR, G, U, PASS_UPDATE>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
-    else if (mode == PASS_QUERY && h.nnz_stored > 500 * S.rows)
-        hipLaunchKernelGGL((logpass_kernel<RR, G, LONG_U, PASS_QUERY>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
-    else if (mode == PASS_QUERY)
-        hipLaunchKernelGGL((logpass_kernel<RR, G, U, PASS_QUERY>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
+    if (LONG_U != U && h.nnz_stored > 500 * S.rows)
+        hipLaunchKernelGGL((logpass_kernel<RR, G, LONG_U, PASS_QUERY, BY_ROUNDS>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial,
+                           h.counters, empty_slot);
     else
-        hipLaunchKernelGGL((logpass_kernel<1, 16, 1, PASS_INIT>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters, empty_slot);
+        hipLaunchKernelGGL((logpass_kernel<RR, G, U, PASS_QUERY, BY_ROUNDS>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial,
+                           h.counters, empty_slot);
     return grid;
 }
 
-// A whole wavefront (four entries per lane) where looking up an entry's round weighs more than lanes without an entry at the
-// record's end: 5000 rows of 420 values in five rounds 5.9 us against 7.5, of 670 in eight 7.3 against 10.3, 20 000 of 250
-// in five 13.6 against 17.0, of 1600 in eight 37 against 57, but 5000 of 65 in eight 5.4 against 5.1; in four rounds 5000 of 1000 7.9 against 9.6, 40 000 of 1600 84
-// against 86, but 10 000 of 670 11.4 against 10.8.
-static bool log_whole_wave(const Handle &h, long long rows)
-{
-    return h.R > EXACT_ROUNDS ? h.nnz_stored > 80 * rows : h.R == 4 && h.nnz_stored > 1000 * rows;
-}
-
-// Otherwise lanes per row and entries of a lane at a time, by the mean length L of a row's piece of a round (us per sweep, the record
-// walked flat / so):
-//  * L up to 28, at most two rounds, 16 lanes x 2: 30 000 rows of 25 + 25 values 9.9 / 6.5, 12 000 6.0 / 4.4;
-//  * fewer than 12 000 rows, too few for the chip with 16 lanes, 32 x 2: 9000 of 90 + 90 5.8 / 5.3, of 3 x 32 5.4 / 5.1; x 4 where they
-//    are few and long: 6000 of 3 x 97 5.4 / 5.1 (x 2 5.6), of 502 6.2 / 5.3;
-//  * L below 140, 16 x 4: 16 000 of 3 x 42 7.9 / 6.4, 28 000 of 4 x 125 20.0 / 18.7 (32 x 4 21.0);
-//  * longer ones 32 x 4: 40 000 of 369 20.5 / 17.0, of 141 + 141 21.6 / 19.0 (16 x 4 20.5), of 470 + 470 57.9 / 55.0 (67);
-//    three and more rounds of up to 24 000 rows 16 x 6: 20 000 of 3 x 163 14.7 / 14.1 (32 x 4 14.9), of 3 x 169 15.2 / 15.2 (15.5).
+// RR rounds, the walk as log_walk() gives it for them; only what it gives is compiled.  Returns the workgroups launched.
 template <int RR>
-static int launch_logpass_length(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
+static int launch_log_walk(const PassSide &S, const Handle &h, LogWalk walk, bool query, int empty_slot, hipStream_t s)
 {
-    const long long pieces = (long long)h.R * S.rows, nnz = h.nnz_stored;
-    if (nnz <= 28 * pieces && h.R <= 2) return launch_logpass_rows<RR, 16, 2>(S, h, mode, empty_slot, s);
-    if (S.rows < 12000 && nnz >= 90 * pieces && (S.rows < 8000 || mode == PASS_QUERY))
-        return launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);   // (a query of 9000 of 3 x 106: 45 us, x 2 51)
-    if (S.rows < 12000) return launch_logpass_rows<RR, 32, 2>(S, h, mode, empty_slot, s);
-    if (nnz < 140 * pieces) return launch_logpass_rows<RR, 16, 4>(S, h, mode, empty_slot, s);
-    if constexpr (RR >= 3)
-        if (S.rows < 24000) return launch_logpass_rows<RR, 16, 6>(S, h, mode, empty_slot, s);
-    return launch_logpass_rows<RR, 32, 4>(S, h, mode, empty_slot, s);
+#define LCN_LOG_WALK(G, U, BY_ROUNDS)                                             \
+    (query ? launch_log_query<RR, G, U, BY_ROUNDS>(S, h, empty_slot, s) : launch_log_update<RR, G, U, BY_ROUNDS>(S, h, empty_slot, s))
+    if constexpr (RR == ANY_ROUNDS) {
+        if (walk == FLAT_16x2) return LCN_LOG_WALK(16, 2, false);
+        if (walk == FLAT_64x4) return LCN_LOG_WALK(64, 4, false);
+        return LCN_LOG_WALK(32, 4, false);
+    } else if constexpr (RR == 1) {
+        if (walk == ROUNDS_16x2) return LCN_LOG_WALK(16, 2, true);
+        if (walk == ROUNDS_16x4) return LCN_LOG_WALK(16, 4, true);
+        if (walk == ROUNDS_32x2) return LCN_LOG_WALK(32, 2, true);
+        return LCN_LOG_WALK(32, 4, true);
+    } else {
+        if (walk == FLAT_16x2) return LCN_LOG_WALK(16, 2, false);
+        if (walk == ROUNDS_32x4) return LCN_LOG_WALK(32, 4, true);
+        if (walk == ROUNDS_32x2 && !query) return launch_log_update<RR, 32, 2, true>(S, h, empty_slot, s);
+        if (walk == ROUNDS_16x4 && query) return launch_log_query<RR, 16, 4, true>(S, h, empty_slot, s);
+        return LCN_LOG_WALK(32, 4, false);
+    }
+#undef LCN_LOG_WALK
 }
 
-// returns the workgroups launched
-static int launch_logpass_rounds(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
+static int launch_logpass_rows(const PassSide &S, const Handle &h, int mode, int empty_slot, hipStream_t s)
 {
-    if (log_whole_wave(h, S.rows)) return launch_logpass_rows<ANY_ROUNDS, 64, 4>(S, h, mode, empty_slot, s);
+    if (mode == PASS_INIT) {
+        const int grid = (int)((S.rows + 15) / 16);
+        hipLaunchKernelGGL((logpass_kernel<1, 16, 1, PASS_INIT, false>), dim3(grid), dim3(256), 0, s, S, h.R, h.partial, h.counters,
+                           empty_slot);
+        return grid;
+    }
+    const bool query = mode == PASS_QUERY;
+    const LogWalk walk = log_walk(h.R, S.rows, h.nnz_stored, query);
+    if (walk == FLAT_64x4) return launch_log_walk<ANY_ROUNDS>(S, h, walk, query, empty_slot, s);
     switch (h.R) {
-        case 1: return launch_logpass_length<1>(S, h, mode, empty_slot, s);
-        case 2: return launch_logpass_length<2>(S, h, mode, empty_slot, s);
-        case 3: return launch_logpass_length<3>(S, h, mode, empty_slot, s);
-        case 4: return launch_logpass_length<4>(S, h, mode, empty_slot, s);
-        // sixteen lanes / 32, walked flat: 20 000 rows of 33 in five 7.7 / 11.0, but 5000 of 40 in five 5.2 / 4.6
-        default:
-            return h.nnz_stored <= 48 * S.rows ? launch_logpass_rows<ANY_ROUNDS, 16, 2>(S, h, mode, empty_slot, s)
-                                               : launch_logpass_rows<ANY_ROUNDS, 32, 4>(S, h, mode, empty_slot, s);
+        case 1: return launch_log_walk<1>(S, h, walk, query, empty_slot, s);
+        case 2: return launch_log_walk<2>(S, h, walk, query, empty_slot, s);
+        case 3: return launch_log_walk<3>(S, h, walk, query, empty_slot, s);
+        case 4: return launch_log_walk<4>(S, h, walk, query, empty_slot, s);
+        default: return launch_log_walk<ANY_ROUNDS>(S, h, walk, query, empty_slot, s);
     }
 }
 
@@ -608,7 +613,7 @@ static hipError_t launch_logpass(const PassSide &S, const Handle &h, int side, i
                                h.query_out + 2 * side, S.shift_self, mode);
         return hipGetLastError();
     }
-    const int grid = launch_logpass_rounds(S, h, mode, empty_slot, s);
+    const int grid = launch_logpass_rows(S, h, mode, empty_slot, s);
     if (mode == PASS_QUERY)
         hipLaunchKernelGGL(reduce_partials_kernel, dim3(1), dim3(1024), 0, s, h.partial, grid, 3, 0, S.acc_out,
                            h.query_out + 2 * side, S.shift_self, mode);

@@ -82,6 +82,14 @@ def test_rounds_of_a_record_in_logs(n, m, buckets, rounds):
     print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 3), "sparse"), flush=True)
 
 
+# each choice of log_walk.h for two to four rounds, the lines between them lying between the two sides' numbers of rows
+@pytest.mark.parametrize("n,m,buckets,rounds", [(10003, 9997, 190, 3), (5003, 4997, 300, 3), (5001, 4996, 240, 2), (7999, 8001, 40, 2),
+                                               (12001, 11999, 40, 2), (18001, 17999, 70, 3), (3000, 12001, 14, 3), (12003, 11997, 1000, 4)])
+def test_walks_of_a_record_in_logs(n, m, buckets, rounds):
+    from parity import compare
+    print("walks", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 3), "sparse"), flush=True)
+
+
 # the bucket sort: buckets on both sides of 256 (a wavefront's share of a scan) and of a power of two (bits of a key), blocks on both
 # sides of 1024 (a workgroup's), points on both sides of 1024 (a chunk), eight chunks and more, of 4096 (rows of a scan's tile)
 @pytest.mark.parametrize("n,m,buckets,rounds", [(1024, 1025, 256, 1), (8193, 7, 257, 2), (3000, 4097, 342, 3), (4096, 2000, 1025, 1),
