@@ -10,9 +10,9 @@
 // logarithm, a barrier.  Eight lanes share a row, so that a block of 32 x 32 is one step of 256 threads.  Rows of the
 // tile are an odd multiple of eight floats apart: eight rows times eight columns then lie in 64 different banks, whichever of the
 // two runs along the lanes.
-// us per half-iteration, a launch per sweep / so: 10 000 x 10 000 in 500 buckets 3.9 / 1.07, 30 000 x 30 000 in 1200 6.1 / 1.4,
-// 3000 x 3000 in 32 4.4 / 1.6, a block of 32 x 32 5.2 / 0.53, of 100 x 100 5.2 / 1.4; the largest ones that fit, 192 x 192 and
-// 320 x 110, 5.2 / 2.9 and 5.4 / 3.2.  (With entries past a row's end masked instead of padded: 1.97 instead of 1.4 at 30 000.)
+// us per half-iteration, a launch per sweep / so: 10 000 x 10 000 in 500 buckets 3.6 / 0.64, 30 000 x 30 000 in 1200 5.1 / 1.2,
+// 3000 x 3000 in 32 3.6 / 1.5, a block of 32 x 32 3.3 / 0.52, of 100 x 100 3.2 / 1.4; the largest ones that fit, 192 x 192 and
+// 320 x 110, 3.5 / 2.9 and 3.5 / 3.2. (With entries past a row's end masked instead of padded: 1.97 instead of 1.4 at 30 000.)
 #include <mutex>
 #include <type_traits>
 
@@ -169,27 +169,30 @@ static hipError_t allow_bucket_lds()
     return e;
 }
 
-// A block has to fit the LDS of a compute unit.  The longest side: beyond it eight lanes per row are too few (4 x 2000
-// would be 250 entries per lane, two thirds of the threads without a row).
-bool bucket_run_fits(const Handle &h)
+static BucketRun bucket_run_of(const Handle &h)
 {
-    return h.log_domain && h.R == 1 && h.block_side <= BUCKET_MAX_SIDE && h.block_bytes <= BUCKET_LDS_BYTES;
+    BucketRun r{};
+    r.block_bytes = h.block_bytes;
+    r.block_side = h.block_side;
+    r.b = h.b;
+    r.nnz = h.nnz_stored;
+    r.rows = h.n > h.m ? h.n : h.m;
+    r.cus = h.cus > 0 ? h.cus : 256;
+    return r;
 }
 
-// Threads by the largest block: as many as its rows fill in a step or two, fewer where many buckets share a compute unit,
-// most of them smaller ones.  us per half-iteration with 256 / 512 / 1024 threads: a block of 40 x 40 0.99 / 0.69 / 0.69, 64 x 64
-// 1.19 / 0.78 / 0.78, 192 x 192 - / 3.8 / 2.9; 1200 buckets of 25 x 25 on average 1.39 / 1.35 / 2.76, 4000 of them 3.0 / 3.6 / 8.5, 600 of
-// 70 x 70 - / 2.7 / 3.2.
+bool bucket_run_taken(const Handle &h) { return h.log_domain && h.R == 1 && bucket_run_pays(bucket_run_of(h)); }
+
 template <int THREADS>
-static hipError_t launch_bucket_threads(const PassSide &X, const PassSide &Y, const Handle &h, int iters, hipStream_t s)
+static hipError_t launch_bucket_threads(const PassSide &X, const PassSide &Y, const Handle &h, const BucketRun &r, int iters, hipStream_t s)
 {
-    if (h.block_bytes > 64 * 1024) {
+    if (r.block_bytes > 64 * 1024) {
         const hipError_t e = allow_bucket_lds<THREADS>();
         if (e != hipSuccess) return e;
     }
     for (; iters > 0; iters -= BUCKET_MOST_ITERATIONS) {   // (the state passes through memory without a loss)
         const int some = iters < BUCKET_MOST_ITERATIONS ? iters : BUCKET_MOST_ITERATIONS;
-        hipLaunchKernelGGL(bucket_run_kernel<THREADS>, dim3(h.b), dim3(THREADS), (size_t)h.block_bytes, s, X, Y, h.sort, some,
+        hipLaunchKernelGGL(bucket_run_kernel<THREADS>, dim3(h.b), dim3(THREADS), (size_t)r.block_bytes, s, X, Y, h.sort, some,
                            h.counters);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -199,11 +202,12 @@ static hipError_t launch_bucket_threads(const PassSide &X, const PassSide &Y, co
 
 hipError_t launch_bucket_run(const PassSide &X, const PassSide &Y, const Handle &h, int iters, hipStream_t s)
 {
-    const int cus = h.cus > 0 ? h.cus : 256;
-    if (h.block_bytes <= 6 * 1024 || (h.block_bytes <= 24 * 1024 && h.b > 8 * cus))
-        return launch_bucket_threads<256>(X, Y, h, iters, s);
-    if (h.block_bytes <= 24 * 1024 || h.b > 2 * cus) return launch_bucket_threads<512>(X, Y, h, iters, s);
-    return launch_bucket_threads<1024>(X, Y, h, iters, s);
+    const BucketRun r = bucket_run_of(h);
+    switch (bucket_threads(r)) {
+        case 256: return launch_bucket_threads<256>(X, Y, h, r, iters, s);
+        case 512: return launch_bucket_threads<512>(X, Y, h, r, iters, s);
+        default: return launch_bucket_threads<1024>(X, Y, h, r, iters, s);
+    }
 }
 
 }  // namespace lcn

@@ -692,7 +692,7 @@ hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s)
     h.last_launches = 2 * iters + (first ? 2 : 0);   // half-iteration launches of this run, the repeated ones included
     const bool fresh = h.fresh != 0;
     if (iters > 0) h.fresh = 0;
-    if (bucket_run_fits(h)) return launch_bucket_run(make_side(h, 0, -1, -1, nullptr), make_side(h, 1, -1, -1, nullptr), h, iters, s);
+    if (bucket_run_taken(h)) return launch_bucket_run(make_side(h, 0, -1, -1, nullptr), make_side(h, 1, -1, -1, nullptr), h, iters, s);
     for (int t = first; t < 2 * iters; ++t) {
         const int side = t & 1;
         const PassSide S = make_side(h, side, side == 0 ? 0 : 1, side == 0 ? 1 : 0, nullptr);

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bucket_rule.h"
 #include "lcn.h"
 #include "record_reach.h"
 
@@ -190,18 +191,8 @@ constexpr long long DENSE_ITERATION_MIN_PAIRS = 3000000, DENSE_ITERATION_MAX_COL
 int dense_iteration_groups(long long n, long long m, int cus);
 inline size_t dense_iteration_floats(int groups, long long m) { return groups ? (size_t)(groups + 1) * (size_t)(m + 1) : 0; }
 hipError_t launch_dense_iteration(const PassSide &X, const PassSide &Y, Handle &h, hipStream_t s);
-// A whole run of a sparse kernel with one hash round, a workgroup per bucket (kernels_buckets.hip).
-// LDS of a block: two doubles per row and column, then its values, rows an odd multiple of eight floats apart; rows and columns
-// up to a multiple of eight.
-constexpr long long BUCKET_LDS_BYTES = 160 * 1024;
-constexpr int BUCKET_MAX_SIDE = 320;
-__host__ __device__ inline int bucket_padded(int n) { return (n + 7) / 8 * 8; }
-__host__ __device__ inline int bucket_tile_step(int ny) { return ((ny + 7) / 8 | 1) * 8; }
-__host__ __device__ inline long long bucket_block_bytes(int nx, int ny)
-{
-    return 16ll * (bucket_padded(nx) + bucket_padded(ny)) + 4ll * bucket_padded(nx) * bucket_tile_step(ny);
-}
-bool bucket_run_fits(const Handle &h);
+// A whole run of a sparse kernel with one hash round, a workgroup per bucket (kernels_buckets.hip, bucket_rule.h).
+bool bucket_run_taken(const Handle &h);
 hipError_t launch_bucket_run(const PassSide &X, const PassSide &Y, const Handle &h, int iters, hipStream_t s);
 int device_compute_units();
 int pass_grid(const Handle &h);

@@ -134,6 +134,42 @@ def test_runs_bucket_by_bucket(mode, n, m, buckets, iters):
     print("buckets", mode, n, m, buckets, compare(p, mode), flush=True)
 
 
+def _in_buckets(nx, ny, iters, d=24, seed=5):
+    """A problem whose cross-polytope hash puts nx[k] of X's points and ny[k] of Y's into bucket k: every point lies in
+    the direction of a projection or opposite to it, whatever its length."""
+    b = len(nx)
+    rng = np.random.default_rng(seed)
+    p = workloads.config3(n=64, d=8, landmarks=8, buckets=8, rounds=1, iters=iters, name="buckets")
+    R = rng.standard_normal((d, b // 2))
+    R /= np.linalg.norm(R, axis=0)
+
+    def points(counts):
+        k = rng.permutation(np.repeat(np.arange(b), counts))
+        Z = R[:, k % (b // 2)].T * np.where(k < b // 2, 1.0, -1.0)[:, None] * rng.uniform(0.5, 2.0, (len(k), 1))
+        return (Z + 0.002 * rng.standard_normal(Z.shape)).astype(np.float32)
+    p.X, p.Y = points(nx), points(ny)
+    p.a = rng.uniform(0.5, 1.5, len(p.X)).astype(np.float32)
+    p.b = rng.uniform(0.5, 1.5, len(p.Y)).astype(np.float32)
+    p.a /= p.a.sum()
+    p.b /= p.b.sum()
+    p.cost, p.lam = workloads.COST_SQEUCLID, 1.0
+    p.num_buckets, p.num_rounds, p.projections = b, 1, R[None].astype(np.float32)
+    for Z, counts in ((p.X, nx), (p.Y, ny)):
+        assert sorted(np.bincount(oracle.crosspolytope(Z, p.projections[0], b), minlength=b)) == sorted(counts)
+    return p
+
+
+# blocks of unlike size: bucket by bucket with the LDS of the largest, a launch per sweep (bucket_rule.h), and with a
+# block that does not fit by every choice of log_walk.h for one round; sizes that are no multiples of eight
+@pytest.mark.parametrize("buckets,many,nx,ny,sx,sy", [
+    (1000, 1, 190, 189, 3, 5), (2000, 7, 109, 141, 6, 3), (4096, 1, 190, 150, 1, 2), (4096, 10, 139, 141, 3, 3),
+    (2000, 1, 401, 403, 6, 7), (400, 1, 499, 501, 31, 29), (200, 1, 333, 402, 21, 19), (60, 1, 401, 403, 21, 20), (2, 1, 401, 30, 30, 401)])
+def test_blocks_of_unlike_size(buckets, many, nx, ny, sx, sy):
+    from parity import compare
+    p = _in_buckets([nx] * many + [sx] * (buckets - many), [ny] * many + [sy] * (buckets - many), 5)
+    print("unlike", buckets, nx, ny, sx, sy, compare(p, "sparse", workloads.HASH_CROSSPOLYTOPE), flush=True)
+
+
 def test_a_run_bucket_by_bucket_in_parts():
     """The state passes through memory between the launches of a run (4096 iterations each) and between runs without a loss."""
     import torch
