@@ -42,6 +42,15 @@ constexpr long long bucket_resident(const BucketRun &r)
 // Workgroups that follow one another on a compute unit, as blocks beyond bucket_resident() do.
 constexpr long long bucket_turns(const BucketRun &r) { return (r.b + bucket_resident(r) - 1) / bucket_resident(r); }
 
+// A half-iteration in ns, no less than it takes: 400 for each turn, however small its block, and the chain of as many
+// blocks of the largest size as there are values for (us, so / measured: a block of 40 x 40 1.0 / 0.7, of 192 x 192 4.9 / 2.9; 4000
+// buckets, one of 180 x 180, the others of 5 x 5, 10.4 / 6.2, with 200 of 180 x 180 13 / 9.1).
+constexpr long long bucket_half_ns(const BucketRun &r)
+{
+    const long long chain = 400 + r.block_bytes / 40, blocks = 4 * r.nnz / r.block_bytes;
+    return 400 * bucket_turns(r) + chain * (1 + blocks / bucket_resident(r));
+}
+
 // A block has to fit the LDS of a compute unit.  The longest side: beyond it eight lanes per row are too few (4 x 2000
 // would be 250 entries per lane, two thirds of the threads without a row).
 //
@@ -55,6 +64,14 @@ constexpr bool bucket_run_pays(const BucketRun &r)
 {
     if (r.block_bytes <= 0 || r.block_bytes > BUCKET_LDS_BYTES || r.block_side > BUCKET_MAX_SIDE) return false;
     return 400 * bucket_turns(r) <= 3600 + r.rows / 20 + r.nnz / 1250;
+}
+
+// Iterations of a launch: 4 ms of them at most, so that no launch keeps others waiting for long.  (The state passes through
+// memory between launches without a loss.)
+constexpr int bucket_launch_iterations(const BucketRun &r)
+{
+    const long long some = 4000000 / (2 * bucket_half_ns(r));
+    return some > 1 ? (int)some : 1;
 }
 
 }  // namespace lcn

@@ -22,7 +22,6 @@ namespace lcn {
 
 constexpr int BK_LANES = 8;      // lanes per row
 constexpr int BK_AHEAD = 4;      // entries of a row that a lane requests together
-constexpr int BUCKET_MOST_ITERATIONS = 4096;   // of a launch: a few milliseconds, so that no launch keeps others waiting for long
 
 __device__ inline double eight_sum(double v)   // every lane of the eight gets the result
 {
@@ -190,12 +189,14 @@ static hipError_t launch_bucket_threads(const PassSide &X, const PassSide &Y, co
         const hipError_t e = allow_bucket_lds<THREADS>();
         if (e != hipSuccess) return e;
     }
-    for (; iters > 0; iters -= BUCKET_MOST_ITERATIONS) {   // (the state passes through memory without a loss)
-        const int some = iters < BUCKET_MOST_ITERATIONS ? iters : BUCKET_MOST_ITERATIONS;
+    const int most = bucket_launch_iterations(r);
+    while (iters > 0) {
+        const int some = iters < most ? iters : most;
         hipLaunchKernelGGL(bucket_run_kernel<THREADS>, dim3(h.b), dim3(THREADS), (size_t)r.block_bytes, s, X, Y, h.sort, some,
                            h.counters);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        iters -= some;
     }
     return hipSuccess;
 }

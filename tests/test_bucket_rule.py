@@ -1,5 +1,5 @@
 """When a sparse run of one hash round goes bucket by bucket, without a GPU: bucket_rule.h is plain C++, so a small host
-program asks it for blocks on both sides of its lines."""
+program asks it for blocks on both sides of its lines and compares its estimate of a half-iteration with measured ones."""
 import os
 import shutil
 import subprocess
@@ -28,26 +28,27 @@ int main(int argc, char **argv)   // buckets, of which so many have X points x Y
         r.rows = n > m ? n : m;
         r.cus = atoi(argv[i + 6]);
         const bool run = lcn::bucket_run_pays(r);
-        printf("%d %d\n", run, run ? lcn::bucket_threads(r) : 0);
+        printf("%d %d %lld %d\n", run, run ? lcn::bucket_threads(r) : 0, run ? lcn::bucket_half_ns(r) : 0,
+               run ? lcn::bucket_launch_iterations(r) : 0);
     }
     return 0;
 }
 """
 
-# buckets, so many of them nx x ny, the others sx x sy; threads (0: a launch per sweep)
+# buckets, so many of them nx x ny, the others sx x sy; threads (0: a launch per sweep); measured ns of a half-iteration (0: not)
 BLOCKS = [
     # the largest blocks that fit
-    (1, 1, 192, 192, 0, 0, 1024), (1, 1, 193, 193, 0, 0, 0), (1, 1, 320, 100, 0, 0, 1024), (1, 1, 321, 9, 0, 0, 0),
+    (1, 1, 192, 192, 0, 0, 1024, 2900), (1, 1, 193, 193, 0, 0, 0, 0), (1, 1, 320, 100, 0, 0, 1024, 0), (1, 1, 321, 9, 0, 0, 0, 0),
     # threads
-    (1, 1, 32, 32, 0, 0, 256), (1, 1, 40, 40, 0, 0, 512), (1, 1, 72, 72, 0, 0, 512), (1, 1, 73, 73, 0, 0, 1024),
-    (513, 1, 73, 73, 5, 5, 512), (2049, 1, 72, 72, 5, 5, 256),
+    (1, 1, 32, 32, 0, 0, 256, 0), (1, 1, 40, 40, 0, 0, 512, 690), (1, 1, 72, 72, 0, 0, 512, 0), (1, 1, 73, 73, 0, 0, 1024, 0),
+    (513, 1, 73, 73, 5, 5, 512, 0), (2049, 1, 72, 72, 5, 5, 256, 0),
     # a full bucket among many small ones
-    (2000, 1, 140, 140, 3, 3, 512), (2000, 1, 190, 190, 3, 3, 512), (3000, 1, 140, 140, 3, 3, 0),
-    (3000, 1, 140, 140, 10, 10, 512), (3500, 1, 140, 140, 6, 6, 0), (3500, 40, 190, 190, 6, 6, 512),
-    (4096, 10, 190, 190, 1, 1, 0), (4096, 1, 140, 140, 3, 3, 0), (4096, 1, 140, 140, 10, 10, 0),
-    (4096, 1, 110, 110, 3, 3, 512), (4000, 200, 180, 180, 5, 5, 512),
+    (2000, 1, 140, 140, 3, 3, 512, 3426), (2000, 1, 190, 190, 3, 3, 512, 3839), (3000, 1, 140, 140, 3, 3, 0, 0),
+    (3000, 1, 140, 140, 10, 10, 512, 5353), (3500, 1, 140, 140, 6, 6, 0, 0), (3500, 40, 190, 190, 6, 6, 512, 6041),
+    (4096, 10, 190, 190, 1, 1, 0, 0), (4096, 1, 140, 140, 3, 3, 0, 0), (4096, 1, 140, 140, 10, 10, 0, 0),
+    (4096, 1, 110, 110, 3, 3, 512, 3431), (4000, 200, 180, 180, 5, 5, 512, 9109),
     # balanced ones
-    (600, 600, 20, 20, 0, 0, 256), (4096, 4096, 20, 20, 0, 0, 256), (1000, 1000, 190, 190, 0, 0, 512),
+    (600, 600, 20, 20, 0, 0, 256, 0), (4096, 4096, 20, 20, 0, 0, 256, 0), (1000, 1000, 190, 190, 0, 0, 512, 0),
 ]
 
 
@@ -60,5 +61,8 @@ def test_runs_bucket_by_bucket_by_block_and_number(tmp_path):
     args = [str(a) for block in BLOCKS for a in block[:6] + (256,)]
     got = [tuple(int(v) for v in line.split()) for line in subprocess.check_output([str(exe)] + args, text=True).splitlines()]
     assert len(got) == len(BLOCKS)
-    for block, (run, threads) in zip(BLOCKS, got):
+    for block, (run, threads, ns, iterations) in zip(BLOCKS, got):
         assert (run, threads) == (block[6] > 0, block[6]), block
+        if run:   # the estimate is not below what was measured, and a launch takes 4 ms or a single iteration
+            assert ns >= block[7], block
+            assert iterations >= 1 and (iterations == 1 or 2 * iterations * ns <= 4_000_000), block
