@@ -338,17 +338,33 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
         cent[c * zs + j] = s >= 0 ? Z[s * zs + j] : 0.f;
     }
     // the scores are formed about the middle of eight points, wherever the pair lies
-    if (tid < 16 * DT) {
+    if (B.mt > 0 && tid < 16 * DT) {
         float s = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) s += Z[(e * N >> 3) * zs + tid];
         mid[tid] = 0.125f * s;
     }
-    __syncthreads();
+    if (B.mt > 0) __syncthreads();
     for (int e = tid; e < 256 * B.mt * DT; e += NT) sums[e] = 0.0;
     // this wavefront's points less the middle as matrix operands; squared norms of the points
     float zop[TPW][4 * DT], mid_sq = 0.f;
-    {
+    if (B.mt == 0) {   // no k-means run: the norms are all
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+            const int pt = 16 * (wave + NW * u) + col;
+            if (pt >= 16 * PT) continue;   // the same in every lane
+            double sq = 0.0;
+#pragma unroll
+            for (int t = 0; t < DT; ++t) {
+                const float4 v = *(const float4 *)(Z + pt * zs + 16 * t + 4 * quarter);
+                const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sq = fma((double)f[e], (double)f[e], sq);
+            }
+            sq = quarter_sum(sq);
+            if (quarter == 0) pn[pt] = sq;
+        }
+    } else {
         float about[4 * DT];
 #pragma unroll
         for (int t = 0; t < DT; ++t) {
