@@ -816,7 +816,7 @@ __global__ __launch_bounds__(NT, 4) void batched_build_kernel(BatchDev B)
     if (tid == 0 && flags[2]) B.marks[0] = 1;
 }
 
-constexpr int RUN_PAIRS = 4;   // of a workgroup of the run kernel, one per SIMD of a compute unit
+constexpr int RUN_PAIRS = 4;   // of a workgroup of the run kernel at most, one per SIMD of a compute unit
 
 // iters Sinkhorn iterations per pair (iters == 0: only the query part), then the
 // pair's distance and marginal residual.
@@ -847,7 +847,7 @@ template <bool BP>
 __global__ __launch_bounds__(64 * RUN_PAIRS, 2) void batched_run_kernel(BatchDev B, int iters, float *row_marg, float *col_marg)
 {
     const double LN2 = 0.69314718055994530942;
-    const int p = (int)blockIdx.x * RUN_PAIRS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int p = (int)(blockIdx.x * (blockDim.x >> 6)) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (p >= B.P) return;
     const long long x0 = B.x_off[p], y0 = B.y_off[p];
     const int n = (int)(B.x_off[p + 1] - x0), m = (int)(B.y_off[p + 1] - y0);
@@ -1258,11 +1258,15 @@ static hipError_t launch_batched_build(const BatchHandle &h)
     return launch_batched_build_as<512, 4>(h);
 }
 
+// Four pairs per workgroup are one per SIMD; left to the dispatcher one by one, which SIMDs get two of them depends on what ran
+// before (1024 pairs, 50 iterations, after their build: 63 us, one by one 89).  Where every pair can have a compute unit, one by one
+// (50 iterations without deletion entries 48.5 us instead of 50.7, with them 59.2 / 60.5).
 // Nothing keeps two workgroups of a run apart: with half a compute unit's LDS reserved per workgroup for that, a run by itself took
-// the same (1024 pairs, 50 iterations: 63 us), two on two streams one after the other (400 iterations: 671 us instead of 500).
+// the same (1024 pairs: 63 us), two on two streams one after the other (400 iterations: 671 us instead of 500).
 static hipError_t launch_batched_run(const BatchHandle &h, int iters, float *row_dev, float *col_dev)
 {
-    const dim3 grid((h.dev.P + RUN_PAIRS - 1) / RUN_PAIRS), block(64 * RUN_PAIRS);
+    const int each = h.dev.P <= device_compute_units() ? 1 : RUN_PAIRS;
+    const dim3 grid((h.dev.P + each - 1) / each), block(64 * each);
     if (h.dev.bp)
         hipLaunchKernelGGL(batched_run_kernel<true>, grid, block, 0, h.stream, h.dev, iters, row_dev, col_dev);
     else
