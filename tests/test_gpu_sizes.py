@@ -170,6 +170,71 @@ def test_blocks_of_unlike_size(buckets, many, nx, ny, sx, sy):
     print("unlike", buckets, nx, ny, sx, sy, compare(p, "sparse", workloads.HASH_CROSSPOLYTOPE), flush=True)
 
 
+def _rounds_apart(n, m, seed=5):
+    """Two rounds of two buckets each: halves of both sides, then half of X's points with all of Y's (those rows' second round
+    is long) and half with none (it is empty)."""
+    rng = np.random.default_rng(seed)
+    p = _in_buckets([n // 2, n - n // 2], [m // 2, m - m // 2], 1, d=2, seed=seed)
+    p.X, p.Y = (rng.uniform(0.5, 1.5, (k, 2)) * rng.choice([-1, 1], (k, 2)) for k in (n, m))
+    p.Y[:, 1] = np.abs(p.Y[:, 1])
+    p.X, p.Y = p.X.astype(np.float32), p.Y.astype(np.float32)
+    p.num_rounds, p.projections = 2, np.eye(2, dtype=np.float32).reshape(2, 2, 1)
+    return p
+
+
+# Sums out of single precision's range: the walk with running maxima, by every kernel that has one of its own.  The scalings
+# before the iteration are up to e^150 off, so most rows and columns take it, and all of them have a weighty result.
+@pytest.mark.parametrize("what", [
+    ([41, 30, 9, 1], [37, 43, 8, 2]), ([190, 3], [189, 5]),              # bucket by bucket, no multiples of eight
+    ([401, 20], [333, 45]), ([50] * 290 + [330] * 2, [49] * 292),        # one round, a launch per sweep
+    (3000, 2999, 700, 2), (1500, 1499, 40, 3), (1200, 1201, 60, 4),      # two to four, flat
+    (700, 661, "apart"), (8101, 407, "apart"),                           # two, round by round; an empty round
+    (1000, 999, 60, 5), (700, 650, 5, 7)])                               # more, flat, a wavefront per row
+def test_sums_out_of_range(what):
+    import torch
+    import paper_2107_06876_amd as lcn
+    from parity import gpu_build
+    hash_kind = workloads.HASH_CROSSPOLYTOPE
+    if isinstance(what[0], list):
+        p = _in_buckets(what[0], what[1], 1)
+    elif what[-1] == "apart":
+        p = _rounds_apart(what[0], what[1])
+    else:
+        p, hash_kind = _cut(what[0], what[1], 4, 8, what[2], what[3], 1), workloads.HASH_KMEANS
+        p.lam = 40.0
+    B = oracle.build_problem(p.X, p.Y, p.cost, p.lam, "sparse", p.num_landmarks, p.landmark_seed, p.kmeans_iters, p.ridge, hash_kind,
+                             p.num_buckets, p.num_rounds, p.lsh_seed, p.projections, branching=p.branching, and_width=p.and_width)
+    rng = np.random.default_rng(3)
+    log_u, log_v = (rng.uniform(-150.0, 150.0, k).astype(np.float32) for k in (len(p.X), len(p.Y)))
+    h = gpu_build(p, "sparse", hash_kind)
+    lcn.lcn_set_scalings(h, torch.from_numpy(log_u).cuda(), torch.from_numpy(log_v).cuda())
+    lcn.sinkhorn_run(h, 1, check=False)
+    got = [v.cpu().numpy().astype(np.float64) for v in lcn.lcn_get_scalings(h)]
+    lcn.lcn_destroy(h)
+    rows, cols, logs = np.repeat(np.arange(len(p.X)), np.diff(B.op.rowptr)), B.op.colidx, np.log(B.op.val)
+
+    def logsumexp(at, terms, size):
+        top = np.full(size, -np.inf)
+        np.maximum.at(top, at, terms)
+        total = np.zeros(size)
+        np.add.at(total, at, np.exp(terms - top[at]))
+        with np.errstate(divide="ignore"):
+            return top + np.log(total)
+    with np.errstate(divide="ignore", invalid="ignore"):
+        want_u = np.log(p.a.astype(np.float64)) - logsumexp(rows, logs + log_v.astype(np.float64)[cols], len(p.X))
+        want_v = np.log(p.b.astype(np.float64)) - logsumexp(cols, logs + want_u[rows], len(p.Y))
+    beyond, least = 0, min(len(p.X), len(p.Y)) // 4
+    for g, w, before in ((got[0], want_u, log_u), (got[1], want_v, log_v)):
+        some = np.isfinite(w)
+        assert (g[~some] == -np.inf).all()
+        # What is returned is rounded to single precision, 2^-17 below 256.  Where the first walk does, its terms are
+        # exp(k + (p - shift)) of numbers below 70: the difference, the sum and the product with log2(e) are rounded to 2^-18
+        # each, k and exp to 2^-21; log v takes log u's error on top of its own.
+        assert np.abs(w[some]).max() < 256 and np.abs(g[some] - w[some]).max() <= 2.0 ** -17 + 2 * (3 * 2.0 ** -18 + 2.0 ** -20)
+        beyond += int((np.abs(before[some] - w[some]) > 70).sum())   # sum over shift: exp of that, and 1e30 is e^69
+    assert beyond >= least
+
+
 def test_a_run_bucket_by_bucket_in_parts():
     """The state passes through memory between the launches of a run (4 ms each, some 2000 iterations) and between runs without a loss."""
     import torch
