@@ -36,7 +36,10 @@
  *   - Same inputs and seeds give bit-identical landmarks, buckets, block
  *     structure, factors and scalings.  (A dense build whose workspace has
  *     fewer bytes than its *bytes_needed, but enough to succeed, sums in
- *     another order: its scalings agree to single precision only.)
+ *     another order: its scalings agree to single precision only.  A batch
+ *     with such a workspace forms its marginals when they are asked for
+ *     instead of in the run: they agree to a rounding to single precision,
+ *     distances and residuals to 1e-12.)
  *   - A handle must not be used from two threads at once.
  */
 #ifndef LCN_H
@@ -327,9 +330,12 @@ lcn_status lcn_last_error_counts(lcn_handle h, int64_t *nonpositive, int64_t *em
 
 /* Elapsed GPU time in milliseconds of the kernels of the last sinkhorn_run on
  * this handle, measured with HIP events on the handle's stream, and the
- * number of half-iteration launches it covered (2 per iteration, plus 2 for the
- * first run after a build or lcn_set_scalings, whose first sweep over each side
- * runs twice: once to learn the exponent of its result). */
+ * number of half-iterations it covered (2 per iteration, plus 2 for the first
+ * run after a build or lcn_set_scalings, whose first sweep over each side runs
+ * twice: once to learn the exponent of its result).  A half-iteration is a
+ * launch of its own, except for sparse and small dense kernels whose run of many
+ * iterations is a single launch, where the number says how many it covered; the
+ * run of a batch, one launch, counts as 1. */
 lcn_status lcn_last_run_timing(lcn_handle h, float *ms_host, int32_t *launches_host);
 
 /* What this part reaches, measured in place (the roofline's practical ceilings;

@@ -1246,7 +1246,7 @@ static hipError_t launch_batched_build_as(const BatchHandle &h)
 
 // Eight wavefronts instead of four per pair: where a compute unit has at most two pairs and the pairs more
 // than the four tiles of points that four wavefronts hold (what a call takes less, d = 32, 16 to 64 points per
-// side: 64 pairs 13 us, 512 pairs 9, 768 pairs -1, 1024 pairs -14; 10 to 30 points: 512 pairs -1), and for more
+// side: 64 pairs 11 us, 512 pairs 9, 768 pairs -18, 1024 pairs -18; 10 to 30 points: 64 pairs 3, 512 pairs 2, 768 pairs -13), and for more
 // than 32 dimensions, where four wavefronts have too few registers for their points (1024 pairs, d = 64: 42 us).
 static hipError_t launch_batched_build(const BatchHandle &h)
 {

@@ -689,7 +689,7 @@ hipError_t launch_update_sweeps(Handle &h, int iters, hipStream_t s)
         if (e != hipSuccess) return e;
         first = 1;   // the loop below starts with the sweep over Y, now with its exponent known
     }
-    h.last_launches = 2 * iters + (first ? 2 : 0);   // half-iteration launches of this run, the repeated ones included
+    h.last_launches = 2 * iters + (first ? 2 : 0);   // half-iterations of this run, the repeated ones included
     const bool fresh = h.fresh != 0;
     if (iters > 0) h.fresh = 0;
     if (bucket_run_taken(h)) return launch_bucket_run(make_side(h, 0, -1, -1, nullptr), make_side(h, 1, -1, -1, nullptr), h, iters, s);

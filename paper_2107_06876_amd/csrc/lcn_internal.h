@@ -268,7 +268,7 @@ struct Handle {
 
     hipEvent_t ev0, ev1;
     float last_ms;
-    int last_launches;
+    int last_launches;         // half-iterations of the last run
 };
 
 constexpr uint32_t HANDLE_MAGIC = 0x4C434E31u;  // "LCN1"

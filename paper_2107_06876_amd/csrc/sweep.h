@@ -268,8 +268,10 @@ static void launch_sweep_rows(const PassSide &S, const Handle &h, int mode, cons
 // Entries of a record requested with its row, in wavefronts of them: two, but one for short records five rows at a time
 // (20 000 rows of 256 factor entries, 45 stored values on average: 13.3 us per sweep against 13.6 with two; 18 757 rows
 // of 128, 98 stored values: 12.8 against 11.1), and three for longer ones of up to 128 factor entries, whose rows leave the
-// registers for it (two / three: 10 000 rows of 451 values 11.95 / 11.78 us, 745 14.14 / 13.85, 28 000 of 637 25.4 / 23.5, 20 011 of 90
-// 11.02 / 10.79; one row at a time 4000 of 334 8.25 / 8.03, but 3000 of 248 7.29 / 7.40; four are no faster, six spill).
+// registers for it.  That is most where the third holds the rest of a record (two / three, as shares: 40 000 rows of 129 values in
+// three rounds 0.82, 16 000 of 148 0.87, 60 000 of 180 in two 0.87, 28 000 of 118 in one 0.92), little for longer ones (10 000 of 451 11.95 / 11.78 us, 745
+// 14.14 / 13.85) and up to 3 % slower for some of 300 to 400 (21 000 of 385 in one round 15.3 / 15.8); one row at a time 4000 of 334 8.25 / 8.03,
+// but 3000 of 248 7.29 / 7.40; four are no faster, six spill.
 // (An entry's order in its lane's sum does not depend on that: both give the same bits.)
 template <int T, int RR>
 static void launch_sweep_rounds(const PassSide &S, const Handle &h, int mode, const FuseArgs &F, bool fused_in, int groups,
