@@ -64,8 +64,8 @@ def test_totals_taken_directly_or_handed_over(monkeypatch, groups):
     assert got["1"][2] == got["0"][2]
 
 
-# records of a few entries up to hundreds, on both sides of the change from 16 to 32 lanes per row (48 entries on average);
-# 3001 and 9 rows: a last workgroup partly empty; five rounds: unrolled over eight
+# records of a few entries up to hundreds, on both sides of the change from 16 to 32 lanes per row (40 entries of two to four
+# rounds, 48 of more); 3001 and 9 rows: a last workgroup partly empty; five rounds: unrolled over eight
 @pytest.mark.parametrize("n,m,buckets,rounds", [(3001, 2999, 700, 1), (3001, 2999, 60, 1), (2000, 2001, 150, 2),
                                                (1500, 1499, 40, 3), (1200, 1201, 60, 4), (1000, 999, 60, 5), (9, 700, 3, 1)])
 def test_lanes_per_row_in_logs(n, m, buckets, rounds):
@@ -73,8 +73,8 @@ def test_lanes_per_row_in_logs(n, m, buckets, rounds):
     print("logs", n, m, buckets, rounds, compare(_cut(n, m, 4, 8, buckets, rounds, 12), "sparse"), flush=True)
 
 
-# records walked round by round, by every choice of lanes and entries at a time: short pieces (up to 28 entries on average), fewer
-# than 8000 and 12 000 rows, pieces up to 140 and longer ones, up to 24 000 rows of three rounds; empty rounds of a row
+# records of several rounds: short pieces (up to 28 entries on average) and longer ones, fewer than 8000 and 12 000 rows and more,
+# one round of long pieces; empty rounds of a row
 @pytest.mark.parametrize("n,m,buckets,rounds", [(12100, 11900, 560, 2), (7000, 6900, 70, 2), (7999, 8001, 100, 3), (12001, 11999, 300, 4),
                                                (12500, 12100, 80, 3), (12500, 12100, 80, 2), (6100, 6000, 13, 1), (3000, 40, 30, 3)])
 def test_rounds_of_a_record_in_logs(n, m, buckets, rounds):
